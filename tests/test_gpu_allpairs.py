@@ -97,3 +97,28 @@ def test_fp64_pair_field_to_rounding_over_distances():
         rel = np.abs(H[:, 2, k] - exact) / exact
         assert rel.max() <= 2e-15, (k, rel.max())  # a few roundings; a 2^-46 or worse 1/sqrt fails
         assert np.abs(H[:, :2, k]).max() == 0.0
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("n,batch", [(1, 1), (15, 2), (17, 1), (64, 3), (65, 1), (255, 2), (257, 1), (1025, 1),
+                                     (8191, 1), (8193, 1), (1000, 40), (1000, 70)])
+def test_source_split_at_the_edges_of_units_and_target_groups(oracle_mod, n, batch, precision):
+    """Sizes around the source units (16 to 256), the target groups (16, 32 or 64) and the sizes where the
+    split changes; field and gradient of the first and last system against the oracle (bars: FP64 sums of up
+    to 8193 terms, 1e-12; FP32 pairs, 1e-5)."""
+    rng = np.random.default_rng(1000 * n + batch)
+    side = 1.5 * n ** (1.0 / 3.0)
+    pos = rng.random((batch, 3, n)) * side
+    mom = workloads.unit_vectors(rng, n * batch).reshape(3, batch, n).transpose(1, 0, 2).copy()
+    H, G, E = allpairs(torch.from_numpy(pos).cuda(), torch.from_numpy(mom).cuda(), precision=precision,
+                       want_dEdr=True, want_E=True)
+    H, G, E = H.cpu().numpy(), G.cpu().numpy(), E.cpu().numpy()
+    tol = 1e-12 if precision == "fp64" else 1e-5
+    for b in {0, batch - 1}:
+        Href, Gref = oracle_mod.allpairs_field(pos[b], mom[b]), oracle_mod.allpairs_grad_r(pos[b], mom[b])
+        if n == 1:
+            assert (H[b] == 0).all() and (G[b] == 0).all() and E[b] == 0
+            continue
+        assert np.linalg.norm(H[b] - Href) <= tol * np.linalg.norm(Href)
+        assert np.linalg.norm(G[b] - Gref) <= tol * np.linalg.norm(Gref)
+        assert abs(E[b] - oracle_mod.energy(mom[b], Href)) <= tol * 0.5 * np.abs(mom[b] * Href).sum()

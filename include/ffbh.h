@@ -98,8 +98,9 @@ bh_status bh_workspace_bytes(const bh_params *p, size_t *out_bytes);
  * buffer of 384 bytes per particle in the workspace (bh_workspace_bytes depends on tuning_id).  Others
  * order the adjoint walk's wave items by the cost each had in the previous call on the handle (the first
  * call after bh_create runs them in index order), in one persistent launch or one wave per item.  The
- * forward walk of bh_field takes its items in the order of its previous call's costs in every shape, from
- * 16384 particles up (ordered by bh_build). */
+ * forward walk of bh_field takes its items in the order of its previous call's costs in every shape above 1600
+ * groups of 64 targets over the batch (ordered by bh_build); in smaller calls several waves share the walk of a
+ * group, their number a function of the groups. */
 int32_t bh_num_tunings(void);
 
 /* Create a handle (host memory, owned by the caller until bh_destroy) bound to the current HIP device

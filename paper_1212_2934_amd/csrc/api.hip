@@ -400,17 +400,18 @@ bh_status bh_build(bh_handle *hh, const double *d_pos, void *stream)
     const hipStream_t s = (hipStream_t)stream;
     // the forward walk's wave items are ordered from the costs of the previous walk, and the next bh_field
     // takes them in that order: beside the octree on the side stream, or after the build on the caller's
-    // stream for a handle without one (the ordering costs less than the walk's tail it removes from 16384
-    // particles up)
+    // stream for a handle without one (the ordering costs less than the walk's tail it removes); walks that a
+    // workgroup's waves share need no order, all of them run at once
+    const bool ordered = uses_field_order(h.L);
     SortedWork order_field;
-    if (side) order_field = [&h](hipStream_t q) {
+    if (side && ordered) order_field = [&h](hipStream_t q) {
         launch_order_field(h, q);
         return hipGetLastError();
     };
-    const bool order_here = !side && h.L.ntot >= kForkMinParticles;
+    const bool order_here = !side && ordered;
     if (launch_build(h, d_pos, s, nullptr, side, true, true, order_field) != hipSuccess) return BH_EDEVICE;
     if (order_here) launch_order_field(h, s);
-    h.field_sched = side || order_here ? 1 : 0;
+    h.field_sched = ordered ? 1 : 0;
     hipLaunchKernelGGL(k_leave, dim3(1), dim3(64), 0, s, h.w.status);
     if (hipGetLastError() != hipSuccess) return BH_EDEVICE;
     hh->h.built = 1;

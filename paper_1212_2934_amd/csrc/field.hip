@@ -3,7 +3,8 @@
 // wavefront).
 //
 // One wavefront owns 64 consecutive targets of its system's target order (Hilbert order above 2048
-// particles, sorted Morton order below).  The wave walks the union of
+// particles, sorted Morton order below); in small systems the waves of a workgroup share 64 targets and
+// divide the tree (see SPLIT).  The wave walks the union of
 // its lanes' traversals depth first, children in octant order: the node on top of the stack is
 // fetched once for the whole wave with a scalar load, every lane in the node's lane mask applies its
 // own acceptance test (FP64, exactly as the definition states), accepting lanes add the
@@ -14,21 +15,30 @@
 
 namespace ffbh {
 
-// Per-wave LDS of the forward traversal (dynamic shared memory, one record per wave of the block).
+// Per-wave LDS of the forward traversal (dynamic shared memory, one record per wave of the block, after one
+// list of the wave's targets per wave, or one for the block where its waves share their targets).
 template <typename T>
 struct FieldLds {
-    LdsTarget tgt[kWave];  // the wave's targets
-    T acc[kWave][4];       // direct-sum field of the current leaf, by owner lane
-    int cnt[kWave];        // direct interactions of the current leaf (counting launches)
-    int list[kWave];       // lanes that opened the current leaf
+    T acc[kWave][4];  // direct-sum field of the current leaf, by owner lane
+    int cnt[kWave];   // direct interactions of the current leaf (counting launches)
+    int list[kWave];  // lanes that opened the current leaf
 };
+
+// Bytes of one wave's record in a split walk, which at its end holds the wave's sums: three FP64 field
+// components and two counts per target.
+template <typename T>
+constexpr size_t split_record()
+{
+    constexpr size_t sums = kWave * (3 * sizeof(double) + 2 * sizeof(int));
+    return sizeof(FieldLds<T>) > sums ? sizeof(FieldLds<T>) : sums;
+}
 
 // Direct sums of one leaf (first, count) for the c listed lanes, in groups of G lanes (see the compacted
 // direct sums in traverse.h): lane b of group g pairs member b with listed target t0 + g; the group's
 // field total is added to the target's LDS slot.  Pairs are skipped for the target itself and flagged when
 // coincident, as in the definition of the direct sum.
 template <bool COUNT, int G, typename T, typename Src>
-__device__ inline void field_leaf(FieldLds<T> &W, int lane, const Src *__restrict__ sr, int first, int count, int c,
+__device__ inline void field_leaf(FieldLds<T> &W, const LdsTarget *tgt, int lane, const Src *__restrict__ sr, int first, int count, int c,
                                   uint32_t &coincident)
 {
     const int grp = lane / G, b = lane % G;
@@ -44,7 +54,7 @@ __device__ inline void field_leaf(FieldLds<T> &W, int lane, const Src *__restric
             const int a = t0 + grp;
             const bool tok = a < c;
             const int tl = W.list[tok ? a : 0];
-            const LdsTarget tg = W.tgt[tl];
+            const LdsTarget tg = tgt[tl];
             const T x = (T)(tg.rx - sk.x), y = (T)(tg.ry - sk.y), z = (T)(tg.rz - sk.z);
             const T r2 = norm2<T>(x, y, z);
             const bool other = tok && sok && k != tg.si;
@@ -70,23 +80,32 @@ __device__ inline void field_leaf(FieldLds<T> &W, int lane, const Src *__restric
 // scalar instructions.
 // Eight waves per SIMD (64 VGPRs): the FP64 walk spills a few bytes there and runs as fast as at seven;
 // the FP32-mixed walk fits without spilling and runs 2-3 % faster than with the hint at seven.
-template <bool MIXED, bool COUNT, bool QUAD, int MAC>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k_field(
+// SPLIT: the W waves of the block (a power of two) walk the same 64 targets and share out the tree by the
+// sorted positions of its cells.  Positions fall in intervals of 2^split_shift, interval q belongs to wave
+// q mod W, and a wave skips every cell that holds none of its positions.  In FP64 a wave sums the cells that
+// start in its intervals.  The FP32-mixed walk sums far cells in FP32 between two leaf visits, and those
+// sums must not be cut: there a wave sums from each leaf visit in its intervals up to and including the next
+// leaf visit, wherever that is (wave 0 also up to the first), and only opens cells in between.  Either way
+// each FP32 sum is the undivided walk's, and the waves' FP64 sums are added in wave order.
+template <bool MIXED, bool COUNT, bool QUAD, int MAC, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(SPLIT ? 4 : 8))) void k_field(
     const NodeRec *__restrict__ nodes, const double *__restrict__ node_m64, const double *__restrict__ spos,
     const double *__restrict__ smom, const void *__restrict__ src, const uint32_t *__restrict__ perm,
     const double *__restrict__ hext, double *__restrict__ H, double *__restrict__ Hs,
     double *__restrict__ e_part, int32_t *__restrict__ cnt_far, int32_t *__restrict__ cnt_near,
     uint32_t *__restrict__ status, int64_t n, int64_t ntot, int waves_per_seg, int num_waves,
     double theta2, int max_nodes, const void *__restrict__ node_q, const uint32_t *__restrict__ tgt_order,
-    const uint32_t *__restrict__ order, uint32_t *__restrict__ wave_cost)
+    const uint32_t *__restrict__ order, uint32_t *__restrict__ wave_cost, int split_shift)
 {
     using T = typename std::conditional<MIXED, float, double>::type;
     using Src = typename std::conditional<MIXED, Src32, Src64>::type;
     const Src *__restrict__ sr = (const Src *)src;
     const int lane = threadIdx.x & (kWave - 1);
     const int wpb = blockDim.x / kWave;
-    const int lin = xcd_block(blockIdx.x, gridDim.x) * wpb + (int)(threadIdx.x / kWave);
-    if (lin >= num_waves) return;  // whole waves only
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int lin = SPLIT ? xcd_block(blockIdx.x, gridDim.x)
+                          : xcd_block(blockIdx.x, gridDim.x) * wpb + (int)(threadIdx.x / kWave);
+    if (lin >= num_waves) return;  // whole waves only (whole blocks of a split walk)
     // with an order, the wave takes the item at its place in it (heavy items of the previous walk first
     // within each XCD's range, light ones last); an order outside the items is ignored
     int gw = lin;
@@ -106,8 +125,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
     // a lane value, not a bool: a divergent bool carried around the walk loop costs scalar mask merges at
     // every iteration
     uint32_t coincident = 0u;
-    FieldLds<T> &W = ((FieldLds<T> *)ffbh_dyn_lds)[threadIdx.x / kWave];
-    W.tgt[lane] = LdsTarget{rx, ry, rz, si, 0};
+    constexpr size_t kTgt = kWave * sizeof(LdsTarget);
+    unsigned char *rec = ffbh_dyn_lds + (SPLIT ? kTgt + (threadIdx.x / kWave) * split_record<T>()
+                                               : (threadIdx.x / kWave) * (kTgt + sizeof(FieldLds<T>)) + kTgt);
+    FieldLds<T> &W = *(FieldLds<T> *)rec;
+    // the waves of a split walk write the same targets to one list (each reads what it has written itself)
+    LdsTarget *tgt = (LdsTarget *)(SPLIT ? ffbh_dyn_lds : rec - kTgt);
+    tgt[lane] = LdsTarget{rx, ry, rz, si, 0};
     W.acc[lane][0] = W.acc[lane][1] = W.acc[lane][2] = (T)0;
     W.cnt[lane] = 0;
 
@@ -118,10 +142,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
     // at most once, so at most max_nodes pushes keep the walk finite whatever the tree holds.
     int guard = max_nodes;
     uint32_t rounds = 0;  // leaf pair rounds (wave-uniform)
+    const int seg0 = (int)(seg * n);
+    bool live = !SPLIT || (MIXED && wave == 0);  // whether what is visited now is this wave's to sum
     while (st.more()) {
         uint64_t mask;
         const int cur = st.pop_settled(mask);
         const NodeRec nd = nodes[cur];
+        bool own = true;
+        if constexpr (SPLIT) {
+            const int q0 = (nd.first - seg0) >> split_shift, q1 = (nd.first - seg0 + nd.count - 1) >> split_shift;
+            own = ((q0 ^ wave) & (wpb - 1)) == 0;
+            if constexpr (!MIXED) live = own;
+            // none of this wave's positions in the cell
+            if (!live && ((wave - q0) & (wpb - 1)) > q1 - q0) {
+                st.settle();
+                continue;
+            }
+        }
         // masks of the lanes that take part, of the targets inside the node (opened whatever the test
         // says; below kSelfRejectTheta2 the test rejects them itself) and of the acceptance test
         uint64_t insm = 0ull;
@@ -131,7 +168,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
         const double d2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
         const uint64_t accm = mask & ~insm & ballot(MAC == kMacScaled ? nd.s2 < d2 : nd.s2 < theta2 * d2);
         const bool acc = lane_in(accm);
-        if (accm != 0ull) {
+        if (accm != 0ull && live) {
             // the whole wave computes (lanes that do not accept add exact zeros)
             if (MIXED) {
                 dip_acc_r2<T>(acc, (T)d2, (T)dx, (T)dy, (T)dz, (T)nd.mx, (T)nd.my, (T)nd.mz, px, py, pz);
@@ -164,14 +201,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
                 // the member range is checked here, where it is first used to index memory
                 if (lane == 0) set_flag(status, BH_FLAG_TREE);
                 st.clear();
+            } else if (!live) {
+                live = own;
             } else {
                 // leaf: direct sums over its members, packed over the lanes that opened it
+                if constexpr (SPLIT) live = own;
                 if (lane_in(open)) W.list[lanes_below(open)] = lane;
                 const int c = __builtin_popcountll(open);
                 wave_lds_sync();
-                if (nd.count <= 4) field_leaf<COUNT, 4>(W, lane, sr, nd.first, nd.count, c, coincident);
-                else if (nd.count <= 8) field_leaf<COUNT, 8>(W, lane, sr, nd.first, nd.count, c, coincident);
-                else field_leaf<COUNT, 16>(W, lane, sr, nd.first, nd.count, c, coincident);
+                if (nd.count <= 4) field_leaf<COUNT, 4>(W, tgt, lane, sr, nd.first, nd.count, c, coincident);
+                else if (nd.count <= 8) field_leaf<COUNT, 8>(W, tgt, lane, sr, nd.first, nd.count, c, coincident);
+                else field_leaf<COUNT, 16>(W, tgt, lane, sr, nd.first, nd.count, c, coincident);
                 {
                     const int G = nd.count <= 4 ? 4 : nd.count <= 8 ? 8 : 16;
                     rounds += (uint32_t)(((nd.count + G - 1) / G) * ((c * G + kWave - 1) / kWave + 1));
@@ -197,6 +237,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
         hx += (double)px; hy += (double)py; hz += (double)pz;
     }
     if (ballot(coincident != 0u) != 0ull && lane == 0) set_flag(status, BH_FLAG_COINCIDENT);
+    if constexpr (SPLIT) {
+        // the waves' sums meet in their records and wave 0 adds them in wave order
+        wave_lds_sync();
+        double *hs = (double *)rec;
+        int *cs = (int *)(rec + 3 * kWave * sizeof(double));
+        hs[lane] = hx; hs[kWave + lane] = hy; hs[2 * kWave + lane] = hz;
+        if (COUNT) {
+            cs[lane] = nfar;
+            cs[kWave + lane] = nnear;
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        for (int w = 1; w < wpb; ++w) {
+            const unsigned char *other = rec + w * split_record<T>();
+            const double *ho = (const double *)other;
+            const int *co = (const int *)(other + 3 * kWave * sizeof(double));
+            hx += ho[lane]; hy += ho[kWave + lane]; hz += ho[2 * kWave + lane];
+            if (COUNT) {
+                nfar += co[lane];
+                nnear += co[kWave + lane];
+            }
+        }
+    }
     // the item's work (internal nodes opened, times eight, plus leaf pair rounds) orders the next walk
     if (wave_cost && lane == 0) wave_cost[gw] = 8u * (uint32_t)(max_nodes - guard) + rounds;
 
@@ -247,30 +310,58 @@ __global__ __launch_bounds__(256) void k_energy_final(const double *__restrict__
     if (threadIdx.x == 0) E[b] = red[0];
 }
 
-template <bool MIXED, bool COUNT, bool QUAD>
-static void launch_k_field(Handle &h, const double *d_hext, double *d_H, hipStream_t s)
+// Waves that share the walk of 64 targets.  A walk is one chain of dependent instructions (about 1000 cycles a
+// node with one wave on a SIMD), so systems whose waves do not fill the 1024 SIMDs are bound by the longest
+// walk.  Cells that hold positions of several waves are tested by each of them, so the split costs more than
+// it gives once the chip is full.  Measured (FP64 / FP32-mixed, undivided -> divided): 300 particles 77 / 68
+// -> 23 / 22 us, 4096 273 / 236 -> 66 / 72 us, 20000 475 / 402 -> 155 / 184 us, 100003 739 / 596 -> 480 / 437
+// us; at 131072 particles four waves take 681 / 643 us against 684 / 564.  The rule counts the target groups of
+// the whole batch: a batch of 1000 x 1000 takes 0.5 ms undivided and 2.2 ms with sixteen waves.
+int field_split(const Layout &L)
+{
+    return L.num_waves <= 192 ? 16 : L.num_waves <= 768 ? 8 : L.num_waves <= 1600 ? 4 : 1;
+}
+
+template <bool MIXED, bool COUNT, bool QUAD, bool SPLIT>
+static void launch_k_field(Handle &h, const double *d_hext, double *d_H, int W, int shift, hipStream_t s)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
-    const int wpb = h.waves_per_block;
-    const unsigned blocks = (unsigned)((L.num_waves + wpb - 1) / wpb);
+    const int wpb = SPLIT ? W : h.waves_per_block;
+    const unsigned blocks = SPLIT ? (unsigned)L.num_waves : (unsigned)((L.num_waves + wpb - 1) / wpb);
     const int waves_per_seg = (int)((L.n + kWave - 1) / kWave);
     const double theta2 = h.p.theta * h.p.theta;
     const void *src = MIXED ? (const void *)w.src32 : (const void *)w.src64;
     using T = typename std::conditional<MIXED, float, double>::type;
-    const size_t lds = (size_t)wpb * sizeof(FieldLds<T>);
+    const size_t tgt_bytes = kWave * sizeof(LdsTarget);
+    const size_t lds = SPLIT ? tgt_bytes + wpb * split_record<T>() : wpb * (tgt_bytes + sizeof(FieldLds<T>));
     const void *q = MIXED ? (const void *)w.node_q32 : (const void *)w.node_q64;
     const uint32_t *tgt = uses_target_order(L) ? w.tgt_order : nullptr;
 #define FFBH_FIELD(MAC)                                                                                          \
-    hipLaunchKernelGGL((k_field<MIXED, COUNT, QUAD, MAC>), dim3(blocks), dim3(wpb * kWave), lds, s, w.nodes,         \
+    hipLaunchKernelGGL((k_field<MIXED, COUNT, QUAD, MAC, SPLIT>), dim3(blocks), dim3(wpb * kWave), lds, s, w.nodes,  \
                        w.node_m64, w.spos, w.smom, src, w.perm, d_hext, d_H, w.Hs, w.e_part, h.cnt_far,          \
                        h.cnt_near, w.status, L.n, L.ntot, waves_per_seg, (int)L.num_waves, theta2,               \
-                       (int)L.max_nodes, q, tgt, h.field_sched ? w.field_order : nullptr, w.field_cost)
+                       (int)L.max_nodes, q, tgt, h.field_sched ? w.field_order : nullptr,   \
+                       SPLIT ? nullptr : w.field_cost, shift)
     const int mac = mac_form(theta2);
     if (mac == kMacInside) FFBH_FIELD(kMacInside);
     else if (mac == kMacScaled) FFBH_FIELD(kMacScaled);
     else FFBH_FIELD(kMacPlain);
 #undef FFBH_FIELD
+}
+
+template <bool MIXED, bool COUNT, bool QUAD>
+static void launch_k_field(Handle &h, const double *d_hext, double *d_H, hipStream_t s)
+{
+    const int W = field_split(h.L);
+    // intervals: two per wave with sixteen waves, sixteen per wave otherwise (4096 particles, sixteen waves: 70,
+    // 66, 75 us with 2, 4, 8; 20000, eight waves: 210, 184 us with 8, 16; 100003, four: 540, 491, 439, 524 us
+    // with 4, 8, 16, 32)
+    const int64_t per = W == 16 ? 2 : 16;
+    int shift = 0;
+    while ((W * per << (shift + 1)) <= h.L.n) ++shift;
+    if (W > 1) launch_k_field<MIXED, COUNT, QUAD, true>(h, d_hext, d_H, W, shift, s);
+    else launch_k_field<MIXED, COUNT, QUAD, false>(h, d_hext, d_H, 1, 0, s);
 }
 
 hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, double *d_H, double *d_E,

@@ -159,3 +159,32 @@ def test_field_with_and_without_the_side_stream(oracle_mod, precision):
     assert all((a == b).all() for a, b in zip(outs[0], outs[1]))
     out = dict(H=outs[0][0], E=outs[0][1], flags=0, n_far=outs[0][2].reshape(-1), n_near=outs[0][3].reshape(-1))
     _check(out, H, E, nf, nr, w.mom, precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("n,leaf,theta,expansion", [
+    (3, 16, 0.5, 1), (70, 1, 0.5, 1), (3001, 64, 0.5, 1), (3001, 33, 0.3, 2), (64 * 192, 16, 0.5, 1),
+    (64 * 192 + 1, 16, 0.9, 1), (64 * 768 + 1, 16, 0.7, 1), (64 * 1600 + 1, 16, 0.5, 1)])
+def test_divided_walks_at_the_edges_of_their_range(oracle_mod, precision, n, leaf, theta, expansion):
+    """16, 8, 4 or 1 waves walk the tree for 64 targets, by the number of target groups.  Field and interaction
+    counts against the oracle on either side of each change, with leaves of more than one chunk of sixteen
+    members and with order-2 cells."""
+    w = workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n + leaf)
+    t = oracle_mod.Tree(w.pos, w.mom, leaf)
+    H, nf, nr = t.field(theta, expansion)
+    out = run_field(w.pos, w.mom, theta=theta, leaf=leaf, precision=precision, expansion=expansion)
+    _check(out, H, oracle_mod.energy(w.mom, H), nf, nr, w.mom, precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
+def test_divided_walk_keeps_the_sums_of_the_undivided_walk(precision):
+    """101 copies of a system of 1000 particles are 1616 target groups and walk undivided, one copy is walked
+    by sixteen waves per group.  The division regroups FP64 sums only, also in the FP32-mixed walk, so the
+    fields agree to FP64 rounding (about 300 terms of either sign: 1e-14)."""
+    w = workloads.config3(seed=99, n=1000)
+    one = run_field(w.pos, w.mom, precision=precision, counters=False)
+    many = run_field(np.repeat(w.pos[None], 101, 0), np.repeat(w.mom[None], 101, 0), precision=precision,
+                     counters=False)
+    assert one["flags"] == 0 and many["flags"] == 0
+    for b in (0, 57, 100):
+        assert np.linalg.norm(many["H"][b] - one["H"]) <= 1e-14 * np.linalg.norm(one["H"])

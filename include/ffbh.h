@@ -100,7 +100,7 @@ bh_status bh_workspace_bytes(const bh_params *p, size_t *out_bytes);
  * call after bh_create runs them in index order), in one persistent launch or one wave per item.  The
  * forward walk of bh_field takes its items in the order of its previous call's costs in every shape above 1600
  * groups of 64 targets over the batch (ordered by bh_build); in smaller calls several waves share the walk of a
- * group, their number a function of the groups. */
+ * group, their number a function of the groups (also the adjoint walk of the default shape and shapes 1-3). */
 int32_t bh_num_tunings(void);
 
 /* Create a handle (host memory, owned by the caller until bh_destroy) bound to the current HIP device

@@ -54,7 +54,7 @@ __device__ inline void fused_pair(bool use, T r2, T x, T y, T z, T ax, T ay, T a
 // reduced units) in opposite directions, and its net force can be a thousand times smaller, so the FP32
 // rounding of those two pairs (offset and arithmetic, about 1e-6 each) would dominate its error.  Direct
 // pairs closer than 1.25 d (measured on the FP32 offset) are therefore listed per target during the walk
-// and evaluated in FP64 after it, at most kCloseMax per target (any further ones stay FP32).
+// and evaluated in FP64 after it, at most kCloseMax per target and wave (any further ones stay FP32).
 constexpr int kCloseMax = 6;
 constexpr float kClose2 = 1.5625f;  // (1.25 d)^2
 template <bool ON>
@@ -66,23 +66,40 @@ struct CloseList<true> {
     int32_t k[kWave][kCloseMax];   // their sorted indices
 };
 
-// Per-wave LDS of the fused traversal (dynamic shared memory, one record per wave of the block).
+// LDS of the fused traversal (dynamic shared memory).  The targets: one record per wave of the block, or one
+// for the block where its waves share their targets (split walks).
 template <typename T>
-struct AdjLds {
+struct AdjTargets {
     LdsTarget tgt[kWave];  // the wave's targets
     T hb[kWave][4];        // their upstream field gradients
-    T acc[kWave][6];       // direct-sum g (0..2) and field (3..5) of the current leaf, by owner lane
-    T sbuf[16][6];         // member totals of the current chunk: sum g (0..2), sum T(x) a (3..5)
-    int list[kWave];       // lanes that opened the current leaf
+};
+// The rest: one record per wave.  A split walk lists lanes in bytes, so that sixteen records fit beside the
+// targets in 64 KB.
+template <typename T, bool SPLIT>
+struct AdjLds {
+    T acc[kWave][6];  // direct-sum g (0..2) and field (3..5) of the current leaf, by owner lane
+    T sbuf[16][6];    // member totals of the current chunk: sum g (0..2), sum T(x) a (3..5)
+    typename std::conditional<SPLIT, uint8_t, int>::type list[kWave];  // lanes that opened the current leaf
     CloseList<std::is_same<T, float>::value> cl;  // contact pairs deferred to FP64 (FP32-mixed walk)
 };
+constexpr int kSplitMaxWaves = 16;
+// A split walk's record also holds the wave's six FP64 sums per target at the end.
+static_assert(sizeof(AdjLds<float, true>) >= 6 * kWave * sizeof(double) &&
+                  sizeof(AdjLds<double, true>) >= 6 * kWave * sizeof(double),
+              "the sums fit the record");
+template <typename T, bool SPLIT>
+constexpr size_t adj_lds_bytes(int waves)
+{
+    return (SPLIT ? 1 : waves) * sizeof(AdjTargets<T>) + waves * sizeof(AdjLds<T, SPLIT>);
+}
+static_assert(adj_lds_bytes<float, true>(kSplitMaxWaves) <= 65536, "LDS of the FP32-mixed split walk");
 
 // Direct sums of one leaf (first, count) for the c listed lanes, in groups of G lanes (see the compacted
 // direct sums in traverse.h).  Lane b of group g pairs member b with listed target t0 + g: the group's
 // totals of g and of the field go to the target's LDS slot; the member's totals over all listed targets
 // are summed across the groups and added to its record with one atomic per component.
-template <int G, typename T, typename Src>
-__device__ inline void adj_leaf(AdjLds<T> &W, int lane, const Src *__restrict__ sr, double *__restrict__ g_rm,
+template <int G, typename T, bool SPLIT, typename Src>
+__device__ inline void adj_leaf(AdjLds<T, SPLIT> &W, const AdjTargets<T> &A, int lane, const Src *__restrict__ sr, double *__restrict__ g_rm,
                                 int first, int count, int c, bool &coincident)
 {
     const int grp = lane / G, b = lane % G;
@@ -97,8 +114,8 @@ __device__ inline void adj_leaf(AdjLds<T> &W, int lane, const Src *__restrict__ 
             const int a = t0 + grp;
             const bool tok = a < c;
             const int tl = W.list[tok ? a : 0];
-            const LdsTarget tg = W.tgt[tl];
-            const T ax = W.hb[tl][0], ay = W.hb[tl][1], az = W.hb[tl][2];
+            const LdsTarget tg = A.tgt[tl];
+            const T ax = A.hb[tl][0], ay = A.hb[tl][1], az = A.hb[tl][2];
             const T x = (T)(tg.rx - sk.x), y = (T)(tg.ry - sk.y), z = (T)(tg.rz - sk.z);
             const T r2 = norm2<T>(x, y, z);
             const bool other = tok && sok && k != tg.si;
@@ -159,7 +176,8 @@ __device__ inline void adj_leaf(AdjLds<T> &W, int lane, const Src *__restrict__ 
 // The deferred contact pairs of one target lane, in FP64: offset from the FP64 positions, pair arithmetic
 // with the FP64 upstream gradient and source moment; g and the field go to the lane's FP64 sums, the
 // member's share (g and T(x) a) to its record with FP64 atomics.  Lanes walk their own lists together.
-__device__ inline void close_pairs(AdjLds<float> &W, int lane, bool valid, int si, double rx, double ry, double rz,
+template <bool SPLIT>
+__device__ inline void close_pairs(AdjLds<float, SPLIT> &W, int lane, bool valid, int si, double rx, double ry, double rz,
                                    const double *__restrict__ spos, const double *__restrict__ smom,
                                    const double *__restrict__ hbar, int64_t ntot, double *__restrict__ g_rm,
                                    double &grx, double &gry, double &grz, double &hx, double &hy, double &hz)
@@ -205,9 +223,13 @@ __device__ inline void close_pairs(AdjLds<float> &W, int lane, bool valid, int s
 // the item's work (node visits plus leaf pair rounds), which orders the next launch.  QUAD: order-2 cells
 // (node_q holds each node's first moment D, stride 16); an accepted cell adds its first-moment field, its
 // gradient to the target and (negated) to the cell centre, and d/dD to node_adjq (six values, stride 8).
-// SCALED: the node records hold s^2 / theta^2 and the acceptance test is s2 < d^2 (kMacScaled).
-template <bool MIXED, bool QUAD, bool SCALED>
-__device__ __forceinline__ void adjoint_wave(int gw, FFBH_ADJ_PARAMS)
+// SCALED: the node records hold s^2 / theta^2 and the acceptance test is s2 < d^2 (kMacScaled).  SPLIT: the
+// block's waves (a power of two) share the item's targets and divide the tree by sorted positions, as in the
+// forward walk (k_field): interval q of 2^split_shift positions belongs to wave q mod W.  Every far cell and
+// every leaf is summed and scattered by one wave, an FP32-mixed wave sums whole segments between two leaf
+// visits, and the FP64 sums of the targets meet in LDS, in wave order.
+template <bool MIXED, bool QUAD, bool SCALED, bool SPLIT>
+__device__ __forceinline__ void adjoint_wave(int gw, int split_shift, FFBH_ADJ_PARAMS)
 {
     using T = typename std::conditional<MIXED, float, double>::type;
     using Src = typename std::conditional<MIXED, Src32, Src64>::type;
@@ -230,15 +252,21 @@ __device__ __forceinline__ void adjoint_wave(int gw, FFBH_ADJ_PARAMS)
     double hx = 0.0, hy = 0.0, hz = 0.0;     // forward field of the target (FP64)
     T pgx = 0, pgy = 0, pgz = 0, phx = 0, phy = 0, phz = 0;  // partial sums since the last flush
     bool coincident = false;
-    AdjLds<T> &W = ((AdjLds<T> *)ffbh_dyn_lds)[threadIdx.x / kWave];
-    W.tgt[lane] = LdsTarget{rx, ry, rz, si, 0};
-    W.hb[lane][0] = ax; W.hb[lane][1] = ay; W.hb[lane][2] = az;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), waves = (int)(blockDim.x / kWave);
+    // the waves of a split walk write the same targets to one record (each reads what it has written itself)
+    unsigned char *rec = SPLIT ? ffbh_dyn_lds + sizeof(AdjTargets<T>) + (threadIdx.x / kWave) * sizeof(AdjLds<T, SPLIT>)
+                               : ffbh_dyn_lds + (threadIdx.x / kWave) * adj_lds_bytes<T, SPLIT>(1) +
+                                     sizeof(AdjTargets<T>);
+    AdjTargets<T> &A = *(AdjTargets<T> *)(SPLIT ? ffbh_dyn_lds : rec - sizeof(AdjTargets<T>));
+    AdjLds<T, SPLIT> &W = *(AdjLds<T, SPLIT> *)rec;
+    A.tgt[lane] = LdsTarget{rx, ry, rz, si, 0};
+    A.hb[lane][0] = ax; A.hb[lane][1] = ay; A.hb[lane][2] = az;
 #pragma unroll
     for (int j = 0; j < 6; ++j) W.acc[lane][j] = (T)0;
     if constexpr (MIXED) W.cl.n[lane] = 0u;
 
     LaneStack st;
-    if (parts == 1) {
+    if (SPLIT || parts == 1) {
         st.init(seg, 1, ballot(valid));
     } else {
         // the root holds every target of the system, so it is always opened: start at child `part` (a leaf
@@ -258,11 +286,21 @@ __device__ __forceinline__ void adjoint_wave(int gw, FFBH_ADJ_PARAMS)
     // so at most max_nodes pushes keep the walk finite whatever the tree holds.
     int guard = max_nodes;
     uint32_t work = 0;      // node visits plus leaf pair rounds (wave-uniform)
+    const int seg0 = (int)(seg * n);
+    bool live = !SPLIT || (MIXED && wave == 0);  // whether what is visited now is this wave's to sum
     while (st.more_any()) {
         uint64_t mask;
         const int cur = st.pop(mask);
         const NodeRec nd = nodes[cur];
         ++work;
+        bool own = true;
+        if constexpr (SPLIT) {
+            const int q0 = (nd.first - seg0) >> split_shift, q1 = (nd.first - seg0 + nd.count - 1) >> split_shift;
+            own = ((q0 ^ wave) & (waves - 1)) == 0;
+            if constexpr (!MIXED) live = own;
+            // none of this wave's positions in the cell
+            if (!live && ((wave - q0) & (waves - 1)) > q1 - q0) continue;
+        }
         // masks of the lanes that take part, of the targets inside the node (opened whatever the test
         // says; below kSelfRejectTheta2 the test rejects them itself) and of the acceptance test
         uint64_t insm = 0ull;
@@ -271,7 +309,7 @@ __device__ __forceinline__ void adjoint_wave(int gw, FFBH_ADJ_PARAMS)
         const double d2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
         const uint64_t accm = mask & ~insm & ballot(SCALED ? nd.s2 < d2 : nd.s2 < theta2 * d2);
         const bool acc = lane_in(accm);
-        if (accm != 0ull) {
+        if (accm != 0ull && live) {
             // the whole wave evaluates the pair (lanes that do not accept add zeros)
             T bx, by, bz;
             if (MIXED) {
@@ -320,14 +358,17 @@ __device__ __forceinline__ void adjoint_wave(int gw, FFBH_ADJ_PARAMS)
                 // the member range is checked here, where it is first used to index memory
                 if (lane == 0) set_flag(status, BH_FLAG_TREE);
                 st.clear();
+            } else if (!live) {
+                live = own;
             } else {
                 // leaf: direct sums over its members, packed over the lanes that opened it
+                if constexpr (SPLIT) live = own;
                 if (lane_in(open)) W.list[lanes_below(open)] = lane;
                 const int c = __builtin_popcountll(open);
                 wave_lds_sync();
-                if (nd.count <= 4) adj_leaf<4>(W, lane, sr, g_rm, nd.first, nd.count, c, coincident);
-                else if (nd.count <= 8) adj_leaf<8>(W, lane, sr, g_rm, nd.first, nd.count, c, coincident);
-                else adj_leaf<16>(W, lane, sr, g_rm, nd.first, nd.count, c, coincident);
+                if (nd.count <= 4) adj_leaf<4>(W, A, lane, sr, g_rm, nd.first, nd.count, c, coincident);
+                else if (nd.count <= 8) adj_leaf<8>(W, A, lane, sr, g_rm, nd.first, nd.count, c, coincident);
+                else adj_leaf<16>(W, A, lane, sr, g_rm, nd.first, nd.count, c, coincident);
                 {
                     const int G = nd.count <= 4 ? 4 : nd.count <= 8 ? 8 : 16;
                     work += (uint32_t)(((nd.count + G - 1) / G) * ((c * G + kWave - 1) / kWave + 1));
@@ -355,8 +396,22 @@ __device__ __forceinline__ void adjoint_wave(int gw, FFBH_ADJ_PARAMS)
         close_pairs(W, lane, valid, si, rx, ry, rz, spos, smom, hbar, ntot, g_rm, grx, gry, grz, hx, hy, hz);
     }
     if (ballot(coincident) != 0ull && lane == 0) set_flag(status, BH_FLAG_COINCIDENT);
+    if constexpr (SPLIT) {
+        wave_lds_sync();
+        double *sums = (double *)rec;
+        const double mine[6] = {grx, gry, grz, hx, hy, hz};
+#pragma unroll
+        for (int c = 0; c < 6; ++c) sums[c * kWave + lane] = mine[c];
+        __syncthreads();
+        if (wave != 0) return;
+        for (int w = 1; w < waves; ++w) {
+            const double *o = (const double *)(rec + w * sizeof(AdjLds<T, SPLIT>)) + lane;
+            grx += o[0]; gry += o[kWave]; grz += o[2 * kWave];
+            hx += o[3 * kWave]; hy += o[4 * kWave]; hz += o[5 * kWave];
+        }
+    }
     if (wave_cost && lane == 0) wave_cost[gw] = work;
-    if (parts > 1) {
+    if (!SPLIT && parts > 1) {
         if (valid) {
             double *q = part_buf + (int64_t)part * 6 * ntot;
             q[si] = grx; q[ntot + si] = gry; q[2 * ntot + si] = grz;
@@ -421,7 +476,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MIXED && !Q
             const uint32_t o = order[lin];
             if (o < (uint32_t)num_waves) gw = (int)o;
         }
-        adjoint_wave<MIXED, QUAD, SCALED>(gw, FFBH_ADJ_ARGS);
+        adjoint_wave<MIXED, QUAD, SCALED, false>(gw, 0, FFBH_ADJ_ARGS);
         return;
     }
     // The items are split into kXcds contiguous segments (neighbouring items share tree data).  Workgroups
@@ -443,9 +498,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MIXED && !Q
                 if (lane == 0) set_flag(status, BH_FLAG_TREE);
                 return;
             }
-            adjoint_wave<MIXED, QUAD, SCALED>((int)gw, FFBH_ADJ_ARGS);
+            adjoint_wave<MIXED, QUAD, SCALED, false>((int)gw, 0, FFBH_ADJ_ARGS);
         }
     }
+}
+
+// The split walk: one block per item, its waves share the item's 64 targets.  The FP64 walk and the order-2
+// walks take up to 128 VGPRs (four waves per SIMD), the FP32-mixed walk with the paper's cells 96.
+template <bool MIXED, bool QUAD, bool SCALED>
+__global__ __launch_bounds__(kSplitMaxWaves *kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_adjoint_split(
+    FFBH_ADJ_PARAMS, int split_shift)
+{
+    adjoint_wave<MIXED, QUAD, SCALED, true>(xcd_block(blockIdx.x, gridDim.x), split_shift, FFBH_ADJ_ARGS);
 }
 
 // Order of the wave items of the next persistent launch, from the previous launch's costs, within each of
@@ -709,6 +773,16 @@ static int adjoint_items(const Handle &h)
     return (int)(h.L.B * wps * h.adj_parts);
 }
 
+// Waves that share the fused walk of 64 targets: the forward walk's rule, for the shapes of one wave per item
+// in index order (the other shapes have their own way to divide or order the work).  Measured on the kernel,
+// FP64 / FP32-mixed, undivided -> divided: 1000 particles 282 / 285 -> 60 / 62 us, 4096 451 / 459 -> 105 / 118 us,
+// 20000 818 / 804 -> 271 / 300 us, 50000 838 / 759 -> 474 / 424 us, 64 systems of 1000 294 / 309 -> 187 / 168 us;
+// at 131072 particles four waves take 1545 / 1529 us against 1301 / 1203.
+static int adjoint_split(const Handle &h)
+{
+    return h.adj_parts == 1 && h.adj_sched == 0 && h.adj_tpw == kWave ? walk_split(h.L) : 1;
+}
+
 bool uses_wave_order(const Handle &h) { return h.adj_sched && h.adj_parts == 1; }
 
 void launch_order_items(const uint32_t *cost, int nw, uint32_t *order, uint32_t *work_ctr, hipStream_t s)
@@ -764,11 +838,29 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
         const int inside = mac == kMacInside ? 1 : 0;
         const bool scaled = mac == kMacScaled;
 #define FFBH_ADJ(MX, QD, SC, T)                                                                                 \
-    hipLaunchKernelGGL((k_adjoint<MX, QD, SC>), dim3(grid), dim3(wpb * kWave), wpb * sizeof(AdjLds<T>), s, w.nodes, \
+    hipLaunchKernelGGL((k_adjoint<MX, QD, SC>), dim3(grid), dim3(wpb * kWave), (adj_lds_bytes<T, false>(wpb)), s, w.nodes, \
                        w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext, w.g_gather,    \
                        w.g_rm, w.node_adj, w.Hs, d_H, w.e_part, w.status, L.n, L.ntot, wps, nwv, theta2,          \
                        (int)L.max_nodes, tpw, parts, w.part_buf, cost, nq, w.node_adjq, tgt, inside, ord, ctr)
-        if (scaled) {
+        const int W = adjoint_split(h), shift = split_shift(L.n, W);
+#define FFBH_ADJ_SPLIT(MX, QD, SC, T)                                                                            \
+    hipLaunchKernelGGL((k_adjoint_split<MX, QD, SC>), dim3((unsigned)nwv), dim3(W * kWave), (adj_lds_bytes<T, true>(W)), \
+                       s, w.nodes, w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext,    \
+                       w.g_gather, w.g_rm, w.node_adj, w.Hs, d_H, w.e_part, w.status, L.n, L.ntot, wps, nwv,      \
+                       theta2, (int)L.max_nodes, tpw, parts, w.part_buf, nullptr, nq, w.node_adjq, tgt, inside, shift)
+        if (W > 1) {
+            if (scaled) {
+                if (mixed && quad) FFBH_ADJ_SPLIT(true, true, true, float);
+                else if (mixed) FFBH_ADJ_SPLIT(true, false, true, float);
+                else if (quad) FFBH_ADJ_SPLIT(false, true, true, double);
+                else FFBH_ADJ_SPLIT(false, false, true, double);
+            } else {
+                if (mixed && quad) FFBH_ADJ_SPLIT(true, true, false, float);
+                else if (mixed) FFBH_ADJ_SPLIT(true, false, false, float);
+                else if (quad) FFBH_ADJ_SPLIT(false, true, false, double);
+                else FFBH_ADJ_SPLIT(false, false, false, double);
+            }
+        } else if (scaled) {
             if (mixed && quad) FFBH_ADJ(true, true, true, float);
             else if (mixed) FFBH_ADJ(true, false, true, float);
             else if (quad) FFBH_ADJ(false, true, true, double);
@@ -780,6 +872,7 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
             else FFBH_ADJ(false, false, false, double);
         }
 #undef FFBH_ADJ
+#undef FFBH_ADJ_SPLIT
         if (parts > 1)
             hipLaunchKernelGGL(k_parts_sum, dim3((unsigned)((L.n + 255) / 256), (unsigned)L.B), dim3(256), 0, s,
                                w.part_buf, parts, w.smom, d_hext, w.perm, w.g_gather, w.Hs, d_H, w.e_part, L.n,
@@ -809,11 +902,11 @@ hipError_t adjoint_resident_blocks(Handle &h, int &blocks)
     if (h.p.precision == BH_FP32_MIXED) {
         auto k = quad ? (sc ? k_adjoint<true, true, true> : k_adjoint<true, true, false>)
                       : (sc ? k_adjoint<true, false, true> : k_adjoint<true, false, false>);
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, wpb * kWave, wpb * sizeof(AdjLds<float>));
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, wpb * kWave, adj_lds_bytes<float, false>(wpb));
     } else {
         auto k = quad ? (sc ? k_adjoint<false, true, true> : k_adjoint<false, true, false>)
                       : (sc ? k_adjoint<false, false, true> : k_adjoint<false, false, false>);
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, wpb * kWave, wpb * sizeof(AdjLds<double>));
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, wpb * kWave, adj_lds_bytes<double, false>(wpb));
     }
     if (e != hipSuccess) return e;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h.device);

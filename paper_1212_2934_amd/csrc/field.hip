@@ -317,9 +317,21 @@ __global__ __launch_bounds__(256) void k_energy_final(const double *__restrict__
 // -> 23 / 22 us, 4096 273 / 236 -> 66 / 72 us, 20000 475 / 402 -> 155 / 184 us, 100003 739 / 596 -> 480 / 437
 // us; at 131072 particles four waves take 681 / 643 us against 684 / 564.  The rule counts the target groups of
 // the whole batch: a batch of 1000 x 1000 takes 0.5 ms undivided and 2.2 ms with sixteen waves.
-int field_split(const Layout &L)
+int walk_split(const Layout &L)
 {
     return L.num_waves <= 192 ? 16 : L.num_waves <= 768 ? 8 : L.num_waves <= 1600 ? 4 : 1;
+}
+
+// Interval length of a divided walk: a sixteenth of a wave's share of the positions, which deals the near cells
+// of any target group out evenly, but no shorter than 128 positions (shorter ones repeat more of the cells
+// above them) unless a wave's share is.  20000 particles, eight waves: 210, 184 us with intervals of 256 and
+// 128; 100003, four waves: 539, 491, 439, 524 us with 2048, 1024, 512, 256 (FP32-mixed forward walk).
+int split_shift(int64_t n, int W)
+{
+    const int64_t share = n / W, want = share / 16 > 128 ? share / 16 : 128, len = want < share ? want : share;
+    int shift = 0;
+    while (((int64_t)2 << shift) <= len) ++shift;
+    return shift;
 }
 
 template <bool MIXED, bool COUNT, bool QUAD, bool SPLIT>
@@ -353,13 +365,7 @@ static void launch_k_field(Handle &h, const double *d_hext, double *d_H, int W, 
 template <bool MIXED, bool COUNT, bool QUAD>
 static void launch_k_field(Handle &h, const double *d_hext, double *d_H, hipStream_t s)
 {
-    const int W = field_split(h.L);
-    // intervals: two per wave with sixteen waves, sixteen per wave otherwise (4096 particles, sixteen waves: 70,
-    // 66, 75 us with 2, 4, 8; 20000, eight waves: 210, 184 us with 8, 16; 100003, four: 540, 491, 439, 524 us
-    // with 4, 8, 16, 32)
-    const int64_t per = W == 16 ? 2 : 16;
-    int shift = 0;
-    while ((W * per << (shift + 1)) <= h.L.n) ++shift;
+    const int W = walk_split(h.L), shift = split_shift(h.L.n, W);
     if (W > 1) launch_k_field<MIXED, COUNT, QUAD, true>(h, d_hext, d_H, W, shift, s);
     else launch_k_field<MIXED, COUNT, QUAD, false>(h, d_hext, d_H, 1, 0, s);
 }

@@ -138,3 +138,34 @@ def test_invariants_at_full_size_c4():
     w = workloads.config4()
     gdr, gdm = _gpu_grad(w.pos, w.mom, np.zeros(3), 0.5, "fp64")
     assert np.abs(gdr.sum(axis=1)).max() <= 1e-10 * np.abs(gdr).sum()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("n,leaf,theta,expansion", [
+    (3, 16, 0.5, 1), (70, 1, 0.5, 2), (3001, 40, 0.3, 1), (64 * 192, 16, 0.5, 1), (64 * 192 + 1, 16, 0.9, 2),
+    (64 * 768 + 1, 16, 0.7, 1)])
+def test_divided_walks_at_the_edges_of_their_range(oracle_mod, precision, n, leaf, theta, expansion):
+    """16, 8 or 4 waves divide the fused walk of 64 targets, by the number of target groups: the energy
+    gradient against the oracle on either side of each change, with leaves of several chunks and order-2 cells."""
+    w = workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n + leaf, hext=(0.2, 0.0, 1.0))
+    _, _, dr, dm = oracle_mod.Tree(w.pos, w.mom, leaf).energy_grad(theta, w.hext, order=expansion)
+    bh = BarnesHut(n, 1, leaf, theta, precision, expansion=expansion)
+    bh.build(torch.from_numpy(w.pos).cuda())
+    gdr, gdm = bh.field_backward(torch.from_numpy(w.mom).cuda(), torch.from_numpy(w.hext).cuda(),
+                                 gE=torch.ones(1, dtype=torch.float64, device="cuda"))
+    assert bh.check_status() == 0
+    grad_check(gdr.cpu().numpy(), dr, precision, f"dE/dr n {n}")
+    grad_check(gdm.cpu().numpy(), dm, precision, f"dE/dm n {n}")
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
+def test_divided_walk_keeps_the_sums_of_the_undivided_walk(precision):
+    """101 copies of a system of 1000 particles walk undivided, one copy is walked by sixteen waves per group:
+    FP64 sums are regrouped, FP32 sums are not, so the gradients agree to FP64 rounding (the net force of a
+    chain bead is a hundredth of its neighbours' forces: 1e-13)."""
+    w = workloads.config3(seed=98, n=1000)
+    one = _gpu_grad(w.pos, w.mom, np.zeros((1, 3)), 0.5, precision)
+    many = _gpu_grad(np.repeat(w.pos[None], 101, 0), np.repeat(w.mom[None], 101, 0), np.zeros((101, 3)), 0.5,
+                     precision)
+    for b in (0, 57, 100):
+        assert rel(many[0][b], one[0]) <= 1e-13 and rel(many[1][b], one[1]) <= 1e-13

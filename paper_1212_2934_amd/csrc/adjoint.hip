@@ -657,34 +657,33 @@ __global__ __launch_bounds__(256) void k_parts_sum(const double *__restrict__ pa
     if ((threadIdx.x & (kWave - 1)) == 0 && local < n) e_part[(int64_t)seg * wps + local / kWave] = e;
 }
 
-// Upstream field gradient in sorted order: Hbar = gH - 1/2 gE m.
-__global__ __launch_bounds__(256) void k_hbar(const double *__restrict__ gH, const double *__restrict__ gE,
-                                              const double *__restrict__ smom, const uint32_t *__restrict__ perm,
-                                              int64_t n, int64_t ntot, double *__restrict__ hbar)
+// Before the fused walk, in one launch: the upstream field gradient in sorted order, Hbar = gH - 1/2 gE m, and
+// zeros in the adjoint records of the particles (g_rm) and of the nodes the last build made (their count is
+// on the device; node_adjq is null without order-2 cells).  Bound by the writes, 104 B a particle and 64 B a
+// node (2^20 particles: about 25 us); as three launches small systems paid 9 us more.
+__global__ __launch_bounds__(256) void k_adj_setup(const double *__restrict__ gH, const double *__restrict__ gE,
+                                                   const double *__restrict__ smom, const uint32_t *__restrict__ perm,
+                                                   int64_t n, int64_t ntot, double *__restrict__ hbar,
+                                                   double *__restrict__ g_rm, double *__restrict__ node_adj,
+                                                   double *__restrict__ node_adjq, const uint32_t *__restrict__ nn,
+                                                   int64_t max_nodes)
 {
-    int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= ntot) return;
-    const int64_t o = perm[s], b = o / n, i = o - b * n;
-    if (o >= ntot) return;
-    const double ge = gE ? gE[b] : 0.0;
-    for (int a = 0; a < 3; ++a) {
-        double v = gH ? gH[b * 3 * n + a * n + i] : 0.0;
-        v += -0.5 * ge * smom[a * ntot + s];
-        hbar[a * ntot + s] = v;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+    for (int64_t s = t; s < ntot; s += stride) {
+        const int64_t o = perm[s], b = o / n, i = o - b * n;
+        if (o >= ntot) continue;
+        const double ge = gE ? gE[b] : 0.0;
+        for (int a = 0; a < 3; ++a) {
+            double v = gH ? gH[b * 3 * n + a * n + i] : 0.0;
+            v += -0.5 * ge * smom[a * ntot + s];
+            hbar[a * ntot + s] = v;
+        }
     }
-}
-
-__global__ __launch_bounds__(256) void k_zero(double *__restrict__ a, int64_t len)
-{
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) a[i] = 0.0;
-}
-
-// The node adjoint records of the nodes the last build made (their count is on the device).
-__global__ __launch_bounds__(256) void k_zero_nodes(double *__restrict__ a, const uint32_t *__restrict__ nn,
-                                                    int64_t max_nodes)
-{
+    for (int64_t i = t; i < 8 * ntot; i += stride) g_rm[i] = 0.0;
     const int64_t len = 8 * ((int64_t)*nn < max_nodes ? (int64_t)*nn : max_nodes);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) a[i] = 0.0;
+    for (int64_t i = t; i < len; i += stride) node_adj[i] = 0.0;
+    if (node_adjq)
+        for (int64_t i = t; i < len; i += stride) node_adjq[i] = 0.0;
 }
 
 // Downward pass and output: members collect their cells' adjoints along the leaf-to-root path; the
@@ -747,23 +746,35 @@ __global__ __launch_bounds__(256) void k_downward(
     dm[2 * n + i] = q[5] + Az + ge * ez + qm[2];
 }
 
-// dL/dH_ext = -dL/dE * sum_i m_i, one block per system.
-__global__ __launch_bounds__(1024) void k_dhext(const double *__restrict__ mom, const double *__restrict__ gE,
-                                                int64_t n, double *__restrict__ dhext)
+// dL/dH_ext = -dL/dE * sum_i m_i: partial sums of a system's moments over nb workgroups, then one wave per
+// system folds them in order.  (One workgroup per system read 2^18 moments in 84 us.)
+__global__ __launch_bounds__(256) void k_dhext_part(const double *__restrict__ mom, int64_t n,
+                                                    double *__restrict__ part)
 {
-    __shared__ double red[3][1024];
-    const int b = blockIdx.x;
+    __shared__ double red[3][256];
+    const int b = blockIdx.y;
     double s[3] = {0.0, 0.0, 0.0};
-    for (int64_t i = threadIdx.x; i < n; i += 1024)
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         for (int a = 0; a < 3; ++a) s[a] += mom[(int64_t)b * 3 * n + a * n + i];
     for (int a = 0; a < 3; ++a) red[a][threadIdx.x] = s[a];
     __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
+    for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w)
             for (int a = 0; a < 3; ++a) red[a][threadIdx.x] += red[a][threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x < 3) dhext[3 * b + threadIdx.x] = gE ? -gE[b] * red[threadIdx.x][0] : 0.0;
+    if (threadIdx.x < 3) part[((int64_t)b * gridDim.x + blockIdx.x) * 3 + threadIdx.x] = red[threadIdx.x][0];
+}
+
+__global__ __launch_bounds__(64) void k_dhext(const double *__restrict__ part, const double *__restrict__ gE, int nb,
+                                              double *__restrict__ dhext)
+{
+    const int b = blockIdx.x;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int k = threadIdx.x; k < nb; k += kWave)
+        for (int a = 0; a < 3; ++a) s[a] += part[((int64_t)b * nb + k) * 3 + a];
+    for (int a = 0; a < 3; ++a) s[a] = wave_sum(s[a]);
+    if (threadIdx.x < 3) dhext[3 * b + threadIdx.x] = gE ? -gE[b] * (threadIdx.x == 0 ? s[0] : threadIdx.x == 1 ? s[1] : s[2]) : 0.0;
 }
 
 // Items of the independent-wave fused traversal: (system, target wave, part).
@@ -797,23 +808,17 @@ void launch_order_waves(Handle &h, hipStream_t s)
 
 hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext, const double *d_gH,
                            const double *d_gE, double *d_dpos, double *d_dmom, double *d_dhext, hipStream_t s,
-                           double *d_H, double *d_E, bool moments_done, bool order_done)
+                           double *d_H, double *d_E, bool moments_done, bool order_done, bool enter)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
     if (!moments_done) {
-        hipError_t e = launch_upward_moments(h, d_mom, s);  // pseudo-particle moments
+        hipError_t e = launch_upward_moments(h, d_mom, s, enter);  // pseudo-particle moments
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_hbar, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, d_gH, d_gE, w.smom, w.perm, L.n,
-                       L.ntot, w.hbar);
-    hipLaunchKernelGGL(k_zero_nodes, dim3(grid_for(8 * L.max_nodes, 256, 2048)), dim3(256), 0, s, w.node_adj,
-                       w.status + 2, L.max_nodes);
     const bool quad = L.expansion == 2;
-    if (quad)
-        hipLaunchKernelGGL(k_zero_nodes, dim3(grid_for(8 * L.max_nodes, 256, 2048)), dim3(256), 0, s, w.node_adjq,
-                           w.status + 2, L.max_nodes);
-    hipLaunchKernelGGL(k_zero, dim3(grid_for(8 * L.ntot, 256, 4096)), dim3(256), 0, s, w.g_rm, 8 * L.ntot);
+    hipLaunchKernelGGL(k_adj_setup, dim3(grid_for(L.ntot, 256, 4096)), dim3(256), 0, s, d_gH, d_gE, w.smom, w.perm, L.n,
+                       L.ntot, w.hbar, w.g_rm, w.node_adj, quad ? w.node_adjq : nullptr, w.status + 2, L.max_nodes);
     const int wpb = h.waves_per_block;
     const double theta2 = h.p.theta * h.p.theta;
     if (h.ev[2]) (void)hipEventRecord(h.ev[2], s);
@@ -884,8 +889,12 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
     hipLaunchKernelGGL(k_downward, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, w.nodes, w.leaf_of, w.node_adj,
                        w.g_gather, w.g_rm, w.Hs, d_hext, d_gE, w.perm, L.n, L.ntot, d_dpos, d_dmom,
                        L.max_nodes, quad ? w.node_adjq : nullptr, w.node_m64, w.spos, w.smom);
-    if (d_dhext)
-        hipLaunchKernelGGL(k_dhext, dim3((unsigned)L.B), dim3(1024), 0, s, d_mom, d_gE, L.n, d_dhext);
+    if (d_dhext) {
+        // the build's partial boxes are free here
+        const int nb = (int)(L.n < 256 * kBboxBlocks ? (L.n + 255) / 256 : kBboxBlocks);
+        hipLaunchKernelGGL(k_dhext_part, dim3((unsigned)nb, (unsigned)L.B), dim3(256), 0, s, d_mom, L.n, w.bbox_part);
+        hipLaunchKernelGGL(k_dhext, dim3((unsigned)L.B), dim3(64), 0, s, w.bbox_part, d_gE, nb, d_dhext);
+    }
     return hipGetLastError();
 }
 

@@ -110,8 +110,7 @@ void carve(const Layout &Lc, void *base, Workspace &w)
     w.node_level = (int32_t *)take(4 * mn);
     w.node_m64 = (double *)take(4 * 8 * mn);
     w.ones = (double *)take(8 * (size_t)L.B);
-    w.lvl = (uint32_t *)take(4 * 128);
-    w.lvl_nodes = (int32_t *)take(4 * mn);
+    w.top_nodes = (int32_t *)take(4 * mn);
     w.leaf_of = (int32_t *)take(4 * nt);
     w.e_part = (double *)take(8 * (size_t)(L.B * ((L.n + kMinTpw - 1) / kMinTpw)));  // waves of kMinTpw targets
     w.node_adj = (double *)take(8 * 8 * mn);
@@ -160,14 +159,14 @@ __global__ void k_clear_status(uint32_t *status)
     if (threadIdx.x == 0) status[0] = 0u;
 }
 
-// First and last kernel of the entry points whose own kernels do not count the call in and out.
-__global__ void k_enter(uint32_t *status)
-{
-    if (threadIdx.x == 0) call_enter(status);
-}
+// Last kernel of the entry points whose own last kernel does not count the call out.
 __global__ void k_leave(uint32_t *status)
 {
     if (threadIdx.x == 0) call_leave(status);
+}
+void launch_leave(uint32_t *status, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_leave, dim3(1), dim3(64), 0, s, status);
 }
 
 __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *a, int64_t len, uint32_t v)
@@ -412,7 +411,7 @@ bh_status bh_build(bh_handle *hh, const double *d_pos, void *stream)
     if (launch_build(h, d_pos, s, nullptr, side, true, true, order_field) != hipSuccess) return BH_EDEVICE;
     if (order_here) launch_order_field(h, s);
     h.field_sched = ordered ? 1 : 0;
-    hipLaunchKernelGGL(k_leave, dim3(1), dim3(64), 0, s, h.w.status);
+    launch_leave(h.w.status, s);
     if (hipGetLastError() != hipSuccess) return BH_EDEVICE;
     hh->h.built = 1;
     return BH_OK;
@@ -426,9 +425,7 @@ bh_status bh_field(bh_handle *hh, const double *d_mom, const double *d_hext, dou
     if ((d_hext && !dptr_ok(d_hext)) || (d_E && !dptr_ok(d_E))) return BH_EINVAL;
     if (!hh->h.built) return BH_ESTATE;
     const hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_enter, dim3(1), dim3(64), 0, s, hh->h.w.status);
-    if (launch_field(hh->h, d_mom, d_hext, d_H, d_E, s) != hipSuccess) return BH_EDEVICE;
-    hipLaunchKernelGGL(k_leave, dim3(1), dim3(64), 0, s, hh->h.w.status);
+    if (launch_field(hh->h, d_mom, d_hext, d_H, d_E, s, true, true) != hipSuccess) return BH_EDEVICE;
     return hipGetLastError() == hipSuccess ? BH_OK : BH_EDEVICE;
 }
 
@@ -442,10 +439,10 @@ bh_status bh_field_backward(bh_handle *hh, const double *d_mom, const double *d_
         return BH_EINVAL;
     if (!hh->h.built) return BH_ESTATE;
     const hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_enter, dim3(1), dim3(64), 0, s, hh->h.w.status);
-    if (launch_backward(hh->h, d_mom, d_hext, d_gH, d_gE, d_dpos, d_dmom, d_dhext, s) != hipSuccess)
+    if (launch_backward(hh->h, d_mom, d_hext, d_gH, d_gE, d_dpos, d_dmom, d_dhext, s, nullptr, nullptr, false, false,
+                        true) != hipSuccess)
         return BH_EDEVICE;
-    hipLaunchKernelGGL(k_leave, dim3(1), dim3(64), 0, s, hh->h.w.status);
+    launch_leave(hh->h.w.status, s);
     return hipGetLastError() == hipSuccess ? BH_OK : BH_EDEVICE;
 }
 

@@ -52,14 +52,14 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const double *__restrict__
 }
 
 // One workgroup of 256 per system folds the nb partial boxes (min and max are exact in any order).
-// Block 0 also clears the level-bucket counters (lvl, 128 words), which the build fills after the octree.
+// It also clears the count of the system's list of cells for k_upward_top, which the build fills.
 __global__ __launch_bounds__(256) void k_bbox_final(const double *__restrict__ part, int nb,
-                                                    double *__restrict__ bbox, uint32_t *__restrict__ lvl,
+                                                    double *__restrict__ bbox, int32_t *__restrict__ top,
                                                     double s2_scale)
 {
     __shared__ double red[6][256];
-    if (blockIdx.x == 0 && threadIdx.x < 128) lvl[threadIdx.x] = 0u;
     const int b = blockIdx.x;
+    if (threadIdx.x == 0) top[b] = 0;
     double v[6];
     for (int a = 0; a < 3; ++a) {
         v[a] = __builtin_inf();
@@ -918,77 +918,22 @@ __global__ __launch_bounds__(256) void k_oct_link(int64_t nint_tot, int64_t B, c
 }
 
 // ------------------------------------------------------------------------------------------------
-// Upward pass: first every leaf (in one launch: a leaf sums its members in sorted order starting from
-// +0.0, whatever its level), then the internal nodes level by level from the deepest cell level to the
-// root (a parent sums its children's sums in octant order, the order they are stored in).  Every child
-// of a level-l cell is a leaf or sits at a deeper level, so one launch per level (21 down to 0) sees all
-// children finished.  Nodes are bucketed once per build: internal nodes by level (buckets 0..21), leaves
-// in bucket kLeafBucket.
-//   MODE 0: positions -> centroid S / count and squared side into the node record, and the exact
-//           bounding box of the members (used by short-range neighbour queries).
+// Upward pass: every leaf sums its members in sorted order starting from +0.0, every internal node its
+// children's sums in octant order (the order they are stored in), children before parents.
+//   MODE 0: positions -> centroid S / count and squared side into the node record.
 //   MODE 1: moments   -> FP64 moment sum into node_m64 and its FP32 rounding into the record.
+//
+// One workgroup per chunk of consecutive sorted positions of a system (k_upward_sub).  The binary node that
+// allocates a cell's children lies inside the cell (its index is one end of its range), and ids follow the
+// binary nodes, so the children of all cells inside a chunk have consecutive ids and belong to the chunk's
+// workgroup, which sums its leaves and then, level by level with a barrier between levels, the cells inside
+// the chunk.  Cells that reach beyond their chunk (the ancestors of the chunk boundaries, a few dozen a chunk)
+// are listed per system when the tree is built and follow in a second launch of one workgroup per system
+// (k_upward_top).  Systems of one chunk need no second launch.
+//
+// A launch costs about 4.5 us in a stream, so what the pass cost before, one launch per level (twelve of them
+// above 2^16 nodes, 50-60 us for a few us of work), is now two.
 // ------------------------------------------------------------------------------------------------
-
-constexpr int kLeafBucket = kMaxLevel + 1;
-constexpr int kBuckets = kMaxLevel + 2;
-
-__device__ inline int bucket_of(const NodeRec *__restrict__ nodes, const int32_t *__restrict__ node_level, int64_t i)
-{
-    const int lev = node_level[i];
-    if ((unsigned)lev > (unsigned)kMaxLevel) return -1;
-    return nodes[i].nchild == 0 ? kLeafBucket : lev;
-}
-
-__global__ __launch_bounds__(256) void k_level_count(const NodeRec *__restrict__ nodes,
-                                                     const int32_t *__restrict__ node_level,
-                                                     const uint32_t *__restrict__ num_nodes, int64_t max_nodes,
-                                                     uint32_t *__restrict__ lvl)
-{
-    __shared__ uint32_t h[kBuckets];
-    if (threadIdx.x < kBuckets) h[threadIdx.x] = 0u;
-    __syncthreads();
-    const int64_t nn = min((int64_t)*num_nodes, max_nodes);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nn; i += (int64_t)gridDim.x * 256) {
-        const int bk = bucket_of(nodes, node_level, i);
-        if (bk >= 0) atomicAdd(&h[bk], 1u);
-    }
-    __syncthreads();
-    if (threadIdx.x < kBuckets && h[threadIdx.x]) atomicAdd(&lvl[threadIdx.x], h[threadIdx.x]);
-}
-
-// lvl[0..22] counts -> lvl[32..55] bucket starts (exclusive, 24 entries), lvl[64..86] cursors.
-__global__ void k_level_starts(uint32_t *lvl)
-{
-    if (threadIdx.x != 0) return;
-    uint32_t acc = 0;
-    for (int l = 0; l < kBuckets; ++l) {
-        lvl[32 + l] = acc;
-        lvl[64 + l] = acc;
-        acc += lvl[l];
-    }
-    lvl[32 + kBuckets] = acc;
-}
-
-// One block per 256 node ids: ranks within the block come from LDS atomics, and one global atomic per
-// bucket and block reserves the block's slots.
-__global__ __launch_bounds__(256) void k_level_scatter(const NodeRec *__restrict__ nodes,
-                                                       const int32_t *__restrict__ node_level,
-                                                       const uint32_t *__restrict__ num_nodes, int64_t max_nodes,
-                                                       uint32_t *__restrict__ lvl, int32_t *__restrict__ lvl_nodes)
-{
-    __shared__ uint32_t cnt[kBuckets], base[kBuckets];
-    const int64_t nn = min((int64_t)*num_nodes, max_nodes);
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if ((int64_t)blockIdx.x * 256 >= nn) return;  // whole block beyond the nodes
-    if (threadIdx.x < kBuckets) cnt[threadIdx.x] = 0u;
-    __syncthreads();
-    const int bk = i < nn ? bucket_of(nodes, node_level, i) : -1;
-    const uint32_t r = bk >= 0 ? atomicAdd(&cnt[bk], 1u) : 0u;
-    __syncthreads();
-    if (threadIdx.x < kBuckets && cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&lvl[64 + threadIdx.x], cnt[threadIdx.x]);
-    __syncthreads();
-    if (bk >= 0 && (int64_t)base[bk] + r < max_nodes) lvl_nodes[base[bk] + r] = (int32_t)i;
-}
 
 // MODE 0: member positions -> centroids and s^2; MODE 1: member moments -> FP64 and FP32 moment sums;
 // MODE 2: both in one pass (vals = positions, vals2 = moments).  Child sums are read from `sums` (8 doubles
@@ -998,15 +943,13 @@ __global__ __launch_bounds__(256) void k_level_scatter(const NodeRec *__restrict
 // a leaf sums its members in sorted order, a parent adds its children's D shifted to its own centre,
 // D_child + (c_child - c) M_child^T, in octant order.
 template <int MODE>
-__device__ inline void upward_node(uint32_t q, const double *__restrict__ vals, const double *__restrict__ vals2,
-                                   int64_t ntot, int64_t n, NodeRec *__restrict__ nodes, double *__restrict__ sums,
+__device__ inline void upward_node(int id, const NodeRec &nd, const double *__restrict__ vals,
+                                   const double *__restrict__ vals2, int64_t ntot, int64_t n,
+                                   NodeRec *__restrict__ nodes, double *__restrict__ sums,
                                    double *__restrict__ node_m64, const int32_t *__restrict__ node_level,
-                                   const int32_t *__restrict__ lvl_nodes, const double *__restrict__ bbox,
-                                   int64_t max_nodes, double *__restrict__ q64, float *__restrict__ q32)
+                                   const double *__restrict__ bbox, int64_t max_nodes, double *__restrict__ q64,
+                                   float *__restrict__ q32)
 {
-    const int id = lvl_nodes[q];
-    if (id < 0 || id >= max_nodes) return;
-    const NodeRec nd = nodes[id];
     if (nd.first < 0 || nd.count < 1 || (int64_t)nd.first + nd.count > ntot ||
         (nd.nchild != 0 && (nd.child < 0 || (int64_t)nd.child + nd.nchild > max_nodes)))
         return;
@@ -1101,86 +1044,157 @@ __device__ inline void upward_node(uint32_t q, const double *__restrict__ vals, 
     }
 }
 
-// Level bucket [b0, b1) of the level-sorted node list.
-__device__ inline void level_range(const uint32_t *lvl, int level, int64_t max_nodes, uint32_t &b0, uint32_t &b1)
+constexpr int kUpThreads = 1024;
+constexpr int kUpCache = 16384;         // nodes of a workgroup whose levels are kept in LDS
+constexpr uint8_t kUpSkip = 255;
+
+// Positions per chunk: 64 chunks a system, of 2048 to 8192 positions, and at most 256 chunks.  Short chunks give
+// more workgroups, long ones leave fewer cells to the one workgroup of the second launch (field evaluation with
+// chunks of 2048, 4096, 8192: 20000 particles 391, 397, 416 us; 262144 896, 883, 888 us; 2^20 2375, 2361, 2326 us).
+static int64_t up_chunk(const Layout &L)
 {
-    b0 = lvl[32 + level];
-    b1 = (int64_t)lvl[32 + level + 1] < max_nodes ? lvl[32 + level + 1] : (uint32_t)max_nodes;
+    const int64_t c = L.n / 64 < 2048 ? 2048 : L.n / 64 > 8192 ? 8192 : L.n / 64, least = (L.n + 255) / 256;
+    return c > least ? c : least;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_upward_level(const double *__restrict__ vals,
-                                                      const double *__restrict__ vals2, int64_t ntot, int64_t n,
-                                                      NodeRec *__restrict__ nodes, double *__restrict__ sums,
-                                                      double *__restrict__ node_m64,
-                                                      const int32_t *__restrict__ node_level,
-                                                      const uint32_t *__restrict__ lvl,
-                                                      const int32_t *__restrict__ lvl_nodes,
-                                                      const double *__restrict__ bbox, int level,
-                                                      int64_t max_nodes, double *__restrict__ q64,
-                                                      float *__restrict__ q32)
-{
-    uint32_t b0, b1;
-    level_range(lvl, level, max_nodes, b0, b1);
-    for (uint32_t q = b0 + blockIdx.x * 256 + threadIdx.x; q < b1; q += gridDim.x * 256)
-        upward_node<MODE>(q, vals, vals2, ntot, n, nodes, sums, node_m64, node_level, lvl_nodes, bbox, max_nodes,
-                          q64, q32);
-}
+// The per-system lists of k_upward_top live in one array: entry b counts system b's list, which starts at
+// entry B + 2 n b (a system has fewer than 2 n nodes).
+__device__ inline int64_t up_list(int64_t B, int64_t n, int64_t b) { return B + 2 * n * b; }
 
-// Buckets level_hi down to level_lo in one workgroup (kLeafBucket, the leaves, comes first; then the
-// internal nodes of levels 21 .. 0), a barrier between buckets (the children's sums are written by this
-// workgroup before their parents read them): where the per-level launches of k_upward_level would cost
-// more than the work.  Any number of nodes is handled; few are expected.
-constexpr int kUpwardOneThreads = 1024;
-constexpr int64_t kUpwardOneMaxNodes = 1 << 16;
-// Larger trees: the levels at and below kUpwardDeepLevel hold an internal node only where more than leaf_size
-// particles share a cell 2^-kUpwardDeepLevel of the cube wide (none in the dense liquids and chain
-// systems simulated), so they take one workgroup launch.  (The top levels are not merged: one
-// workgroup walks their few hundred cells more slowly than four grid launches.)
-constexpr int kUpwardDeepLevel = 10;
+#define FFBH_UP_PARAMS                                                                                          \
+    const double *__restrict__ vals, const double *__restrict__ vals2, int64_t ntot, int64_t n,                  \
+        NodeRec *__restrict__ nodes, double *__restrict__ sums, double *__restrict__ node_m64,                   \
+        const int32_t *__restrict__ node_level, const double *__restrict__ bbox, int64_t max_nodes,              \
+        double *__restrict__ q64, float *__restrict__ q32
+#define FFBH_UP_ARGS vals, vals2, ntot, n, nodes, sums, node_m64, node_level, bbox, max_nodes, q64, q32
 
-template <int MODE>
-__global__ __launch_bounds__(kUpwardOneThreads) void k_upward_all(
-    const double *__restrict__ vals, const double *__restrict__ vals2, int64_t ntot, int64_t n,
-    NodeRec *__restrict__ nodes, double *__restrict__ sums, double *__restrict__ node_m64,
-    const int32_t *__restrict__ node_level, const uint32_t *__restrict__ lvl, const int32_t *__restrict__ lvl_nodes,
-    const double *__restrict__ bbox, int64_t max_nodes, double *__restrict__ q64, float *__restrict__ q32,
-    int level_hi, int level_lo)
+// Levels lo..hi of the cells k (0 <= k < count) of this workgroup, deepest first: id_of(k) and its level or
+// kUpSkip, from the LDS copy where it holds it.
+template <int MODE, typename Id, typename Level>
+__device__ inline void up_levels(int lo, int hi, int count, const uint8_t *lev, const Id &id_of, const Level &level_of,
+                                 FFBH_UP_PARAMS)
 {
-    for (int level = level_hi; level >= level_lo; --level) {
-        uint32_t b0, b1;
-        level_range(lvl, level, max_nodes, b0, b1);
-        for (uint32_t q = b0 + threadIdx.x; q < b1; q += kUpwardOneThreads)
-            upward_node<MODE>(q, vals, vals2, ntot, n, nodes, sums, node_m64, node_level, lvl_nodes, bbox,
-                              max_nodes, q64, q32);
+    for (int l = hi; l >= lo; --l) {
+        for (int k = threadIdx.x; k < count; k += blockDim.x) {
+            if ((k < kUpCache ? lev[k] : level_of(k)) != l) continue;
+            const int id = id_of(k);
+            const NodeRec nd = nodes[id];
+            upward_node<MODE>(id, nd, FFBH_UP_ARGS);
+        }
         __syncthreads();
     }
 }
 
+// append: list the cells left to k_upward_top (the build's pass).
 template <int MODE>
-static void upward(Handle &h, const double *vals, const double *vals2, hipStream_t s)
+__global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const uint32_t *__restrict__ scan,
+                                                           uint32_t *__restrict__ status, int64_t B, int64_t chunk,
+                                                           int chunks, int32_t *__restrict__ top, int append,
+                                                           int leave)
+{
+    __shared__ uint8_t lev[kUpCache];
+    __shared__ int lmin, lmax;
+    const int64_t b = blockIdx.x / chunks;
+    const int c = (int)(blockIdx.x - b * chunks);
+    const int64_t c0 = c * chunk, c1 = min(c0 + chunk, n), ib = b * (n - 1);
+    // ids of the children that binary nodes c0 .. c1 - 1 of the system allocated
+    const int64_t end = B + (n > 1 ? (int64_t)status[1] : 0);
+    auto start = [&](int64_t i) {
+        if (i < n - 1) return B + (int64_t)scan[ib + i];
+        return n > 1 && b + 1 < B ? B + (int64_t)scan[ib + n - 1] : end;
+    };
+    const int64_t i0 = start(c0), i1 = min(start(c1), max_nodes);
+    // the root is the first chunk's, before its children
+    const int root = c == 0 ? 1 : 0;
+    const int count = (int)(i1 > i0 ? i1 - i0 : 0) + root;
+    auto id_of = [&](int k) { return root && k == 0 ? (int)b : (int)(i0 + k - root); };
+    auto level_at = [&](int id, const NodeRec &nd) -> uint8_t {
+        const int64_t f = nd.first - b * n;
+        const int l = node_level[id];
+        if (nd.nchild == 0 || f < c0 || f + nd.count > c1 || (unsigned)l > (unsigned)kMaxLevel) return kUpSkip;
+        return (uint8_t)l;
+    };
+    if (threadIdx.x == 0) {
+        lmin = kMaxLevel + 1;
+        lmax = -1;
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < count; k += blockDim.x) {
+        const int id = id_of(k);
+        const NodeRec nd = nodes[id];
+        const uint8_t l = level_at(id, nd);
+        if (k < kUpCache) lev[k] = l;
+        if (nd.nchild == 0) {
+            upward_node<MODE>(id, nd, FFBH_UP_ARGS);
+        } else if (l != kUpSkip) {
+            atomicMin(&lmin, (int)l);
+            atomicMax(&lmax, (int)l);
+        } else if (append) {
+            const uint32_t at = atomicAdd((uint32_t *)&top[b], 1u);
+            if ((int64_t)at < 2 * n) top[up_list(B, n, b) + at] = id;
+        }
+    }
+    __syncthreads();
+    up_levels<MODE>(lmin, lmax, count, lev, id_of, [&](int k) { const int id = id_of(k); return level_at(id, nodes[id]); },
+                    FFBH_UP_ARGS);
+    if (leave && threadIdx.x == 0) call_leave(status);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(kUpThreads) void k_upward_top(FFBH_UP_PARAMS, uint32_t *__restrict__ status, int64_t B,
+                                                           const int32_t *__restrict__ top, int leave)
+{
+    __shared__ uint8_t lev[kUpCache];
+    __shared__ int lmin, lmax;
+    const int64_t b = blockIdx.x;
+    const int32_t *list = top + up_list(B, n, b);
+    const int64_t listed = (uint32_t)top[b];
+    const int count = (int)(listed < 2 * n ? listed : 2 * n);
+    auto id_of = [&](int k) { return list[k]; };
+    auto level_of = [&](int k) -> uint8_t {
+        const int id = list[k];
+        if (id < 0 || id >= max_nodes) return kUpSkip;
+        const int l = node_level[id];
+        return (unsigned)l > (unsigned)kMaxLevel ? kUpSkip : (uint8_t)l;
+    };
+    if (threadIdx.x == 0) {
+        lmin = kMaxLevel + 1;
+        lmax = -1;
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < count; k += blockDim.x) {
+        const uint8_t l = level_of(k);
+        if (k < kUpCache) lev[k] = l;
+        if (l == kUpSkip) continue;
+        atomicMin(&lmin, (int)l);
+        atomicMax(&lmax, (int)l);
+    }
+    __syncthreads();
+    up_levels<MODE>(lmin, lmax, count, lev, id_of, level_of, FFBH_UP_ARGS);
+    if (leave && threadIdx.x == 0) call_leave(status);
+}
+
+// append: the build's pass lists the cells that reach beyond their chunk.  leave: the pass is the call's last
+// work; returns whether its last kernel counts the call out (it does where it is one workgroup, so that nothing
+// of the call still runs then).
+template <int MODE>
+static bool upward(Handle &h, const double *vals, const double *vals2, hipStream_t s, bool append, bool leave)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
-    auto one = [&](int level_hi, int level_lo) {
-        hipLaunchKernelGGL(k_upward_all<MODE>, dim3(1), dim3(kUpwardOneThreads), 0, s, vals, vals2, L.ntot, L.n,
-                           w.nodes, w.node_adj, w.node_m64, w.node_level, w.lvl, w.lvl_nodes, w.bbox, L.max_nodes,
-                           w.node_q64, w.node_q32, level_hi, level_lo);
-    };
-    auto level = [&](int bucket) {
-        const unsigned g = grid_for(L.max_nodes, 256, bucket == kLeafBucket ? 1024 : 512);
-        hipLaunchKernelGGL(k_upward_level<MODE>, dim3(g), dim3(256), 0, s, vals,
-                           vals2, L.ntot, L.n, w.nodes, w.node_adj, w.node_m64, w.node_level, w.lvl, w.lvl_nodes,
-                           w.bbox, bucket, L.max_nodes, w.node_q64, w.node_q32);
-    };
-    if (L.max_nodes <= kUpwardOneMaxNodes) {
-        one(kLeafBucket, 0);  // the leaves, then levels 21 .. 0
-        return;
-    }
-    // the leaves hold every member: one launch over all of them; then the internal levels
-    level(kLeafBucket);
-    one(kMaxLevel, kUpwardDeepLevel);
-    for (int l = kUpwardDeepLevel - 1; l >= 0; --l) level(l);
+    const int64_t chunk = up_chunk(L);
+    const int chunks = (int)((L.n + chunk - 1) / chunk);
+    const int threads = L.n <= 512 ? 256 : kUpThreads;
+    leave = leave && L.B == 1;
+    hipLaunchKernelGGL(k_upward_sub<MODE>, dim3((unsigned)(L.B * chunks)), dim3(threads), 0, s, vals, vals2, L.ntot,
+                       L.n, w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
+                       w.bin_scan, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0,
+                       leave && chunks == 1 ? 1 : 0);
+    if (chunks > 1)
+        hipLaunchKernelGGL(k_upward_top<MODE>, dim3((unsigned)L.B), dim3(kUpThreads), 0, s, vals, vals2, L.ntot, L.n,
+                           w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
+                           w.status, L.B, w.top_nodes, leave ? 1 : 0);
+    return leave;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1193,7 +1207,7 @@ static void upward(Handle &h, const double *vals, const double *vals2, hipStream
         if (e_ != hipSuccess) return e_;    \
     } while (0)
 
-static void gather_moments(Handle &h, const double *d_mom, hipStream_t s);
+static void gather_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter);
 
 hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const double *d_mom, hipStream_t side,
                         bool join, bool enter, const SortedWork &after_sort)
@@ -1205,7 +1219,7 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     const int nb = (int)((n + 255) / 256 < kBboxBlocks ? (n + 255) / 256 : kBboxBlocks);
     hipLaunchKernelGGL(k_bbox_partial, dim3((unsigned)nb, (unsigned)B), dim3(256), 0, s, d_pos, n,
                        w.bbox_part, w.status, enter ? 1 : 0);
-    hipLaunchKernelGGL(k_bbox_final, dim3((unsigned)B), dim3(256), 0, s, w.bbox_part, nb, w.bbox, w.lvl,
+    hipLaunchKernelGGL(k_bbox_final, dim3((unsigned)B), dim3(256), 0, s, w.bbox_part, nb, w.bbox, w.top_nodes,
                        node_s2_scale(h.p.theta * h.p.theta));
     hipLaunchKernelGGL(k_morton, dim3(grid_for(ntot, 256)), dim3(256), 0, s, d_pos, n, ntot, w.bbox,
                        w.keys[0], w.vals[0]);
@@ -1269,18 +1283,12 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     if (nint > 0)
         hipLaunchKernelGGL(k_oct_link, dim3(grid_for(nint, 256)), dim3(256), 0, s, nint, B,
                            w.bin_nchild, w.bin_scan, w.bin_octid, w.nodes, L.max_nodes);
-    // bucket the nodes by level, then the upward pass for the centroids
-    hipLaunchKernelGGL(k_level_count, dim3(grid_for(L.max_nodes, 256, 1024)), dim3(256), 0, s, w.nodes,
-                       w.node_level, w.status + 2, L.max_nodes, w.lvl);
-    hipLaunchKernelGGL(k_level_starts, dim3(1), dim3(64), 0, s, w.lvl);
-    hipLaunchKernelGGL(k_level_scatter, dim3(grid_for(L.max_nodes, 256)), dim3(256), 0, s, w.nodes,
-                       w.node_level, w.status + 2, L.max_nodes, w.lvl, w.lvl_nodes);
     if (d_mom) {
         // positions and moments summed in one upward pass
-        gather_moments(h, d_mom, s);
-        upward<2>(h, w.spos, w.smom, s);
+        gather_moments(h, d_mom, s, false);
+        upward<2>(h, w.spos, w.smom, s, true, false);
     } else {
-        upward<0>(h, w.spos, nullptr, s);
+        upward<0>(h, w.spos, nullptr, s, true, false);
     }
     if (side && join) {
         hipError_t e = hipEventRecord(h.join_ev, side);
@@ -1377,9 +1385,11 @@ namespace ffbh {
 __global__ __launch_bounds__(256) void k_gather_pack(const double *__restrict__ mom, const uint32_t *__restrict__ perm,
                                                      const double *__restrict__ spos, int64_t n, int64_t ntot,
                                                      double *__restrict__ smom, double *__restrict__ src64,
-                                                     double *__restrict__ src32, uint32_t *__restrict__ status)
+                                                     double *__restrict__ src32, uint32_t *__restrict__ status,
+                                                     int enter)
 {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (enter && k == 0) call_enter(status);
     if (k >= ntot) return;
     const int64_t o = perm[k];
     if (o >= ntot) {
@@ -1407,32 +1417,33 @@ __global__ __launch_bounds__(256) void k_gather_pack(const double *__restrict__ 
     }
 }
 
-// Moments in sorted order and the packed source records of the handle's precision.
-static void gather_moments(Handle &h, const double *d_mom, hipStream_t s)
+// Moments in sorted order and the packed source records of the handle's precision.  enter: the first kernel of
+// the call.
+static void gather_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
     const bool mixed = h.p.precision == BH_FP32_MIXED;
     hipLaunchKernelGGL(k_gather_pack, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, d_mom, w.perm, w.spos, L.n,
                        L.ntot, w.smom, mixed ? (double *)nullptr : (double *)w.src64,
-                       mixed ? (double *)w.src32 : (double *)nullptr, w.status);
+                       mixed ? (double *)w.src32 : (double *)nullptr, w.status, enter ? 1 : 0);
 }
 
 // First moments of every node from the sorted moments and positions already in the workspace (after a
 // build with moments): the order-2 cells of an MD step.
 hipError_t launch_upward_first_moments(Handle &h, hipStream_t s)
 {
-    upward<3>(h, h.w.smom, h.w.spos, s);
+    upward<3>(h, h.w.smom, h.w.spos, s, false, false);
     return hipGetLastError();
 }
 
-hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s)
+hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter)
 {
-    gather_moments(h, d_mom, s);
+    gather_moments(h, d_mom, s, enter);
     if (h.L.expansion == 2)
-        upward<3>(h, h.w.smom, h.w.spos, s);
+        upward<3>(h, h.w.smom, h.w.spos, s, false, false);
     else
-        upward<1>(h, h.w.smom, nullptr, s);
+        upward<1>(h, h.w.smom, nullptr, s, false, false);
     return hipGetLastError();
 }
 

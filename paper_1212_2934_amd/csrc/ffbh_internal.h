@@ -108,8 +108,7 @@ struct Workspace {
     float *node_q32;         // max_nodes x 16: the same rounded to FP32 (mixed-precision traversal)
     double *node_adjq;       // max_nodes x 8: dL/dD of each node, symmetric (xx, yy, zz, xy, xz, yz)
     double *ones;            // B: constant 1.0 (dL/dE for the MD force)
-    uint32_t *lvl;           // 128: per-bucket node counts [0,23), bucket starts [32,56), cursors [64,87)
-    int32_t *lvl_nodes;      // max_nodes: node ids bucketed (internal nodes by level 0..21, leaves in 22)
+    int32_t *top_nodes;      // max_nodes: per system the count, then the list of the cells that k_upward_top sums
     int32_t *leaf_of;        // N_tot: sorted particle -> its leaf
     // traversal outputs and adjoint accumulators
     double *e_part;          // per wave energy partials
@@ -210,6 +209,7 @@ __device__ inline void call_enter(uint32_t *status)
     if (atomicAdd(status + kStatusInFlight, 1u) != 0u) set_flag(status, BH_FLAG_OVERLAP);
 }
 __device__ inline void call_leave(uint32_t *status) { atomicSub(status + kStatusInFlight, 1u); }
+void launch_leave(uint32_t *status, hipStream_t s);
 
 inline unsigned grid_for(int64_t work, int threads, int64_t cap = (int64_t)1 << 30)
 {
@@ -238,16 +238,17 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
 // Targets of every system in Hilbert order (the positions' cells at kHilbertBits bits per axis), sorted
 // positions as values: consecutive targets of a traversal wave then lie close together.
 void launch_target_order(Handle &h, hipStream_t s);
-hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s);
+hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter);
 hipError_t launch_upward_first_moments(Handle &h, hipStream_t s);
+// enter: the first kernel counts the call in (call_enter); leave: the last one counts it out.
 hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, double *d_H,
-                        double *d_E, hipStream_t s);
+                        double *d_E, hipStream_t s, bool enter = false, bool leave = false);
 // moments_done: the build already summed the moments (launch_build with d_mom).
 // order_done: the wave order of the persistent launch was already enqueued (launch_order_waves).
 hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext, const double *d_gH,
                            const double *d_gE, double *d_dpos, double *d_dmom, double *d_dhext,
                            hipStream_t s, double *d_H = nullptr, double *d_E = nullptr, bool moments_done = false,
-                           bool order_done = false);
+                           bool order_done = false, bool enter = false);
 // Whether the fused traversal of this handle runs the persistent, cost-ordered launch, and the launch
 // that orders its items from the costs the previous traversal recorded.
 bool uses_wave_order(const Handle &h);
@@ -262,7 +263,7 @@ int split_shift(int64_t n, int W);
 inline bool uses_field_order(const Layout &L) { return L.ntot >= kForkMinParticles && walk_split(L) == 1; }
 // Order of the forward walk's items from the costs the previous forward walk recorded.
 void launch_order_field(Handle &h, hipStream_t s);
-void launch_energy_final(Handle &h, double *d_E, hipStream_t s, int targets_per_wave);
+void launch_energy_final(Handle &h, double *d_E, hipStream_t s, int targets_per_wave, bool leave = false);
 hipError_t adjoint_resident_blocks(Handle &h, int &blocks);
 hipError_t launch_ap(int64_t n, int32_t batch, int32_t precision, const double *pos, const double *mom,
                      const double *hext, double *H, double *dEdr, double *E, hipStream_t s);

@@ -295,7 +295,8 @@ __global__ __launch_bounds__(SPLIT ? 1024 : 512) __attribute__((amdgpu_waves_per
 // E of every system: sum of its waves' partials in a fixed order (strided per thread, then a fixed
 // LDS tree), so repeated runs give the same bits.
 __global__ __launch_bounds__(256) void k_energy_final(const double *__restrict__ e_part, int waves_per_seg,
-                                                      double *__restrict__ E)
+                                                      double *__restrict__ E, uint32_t *__restrict__ status,
+                                                      int leave)
 {
     __shared__ double red[256];
     const int b = blockIdx.x;
@@ -307,7 +308,9 @@ __global__ __launch_bounds__(256) void k_energy_final(const double *__restrict__
         if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
         __syncthreads();
     }
-    if (threadIdx.x == 0) E[b] = red[0];
+    if (threadIdx.x != 0) return;
+    E[b] = red[0];
+    if (leave) call_leave(status);
 }
 
 // Waves that share the walk of 64 targets.  A walk is one chain of dependent instructions (about 1000 cycles a
@@ -371,9 +374,9 @@ static void launch_k_field(Handle &h, const double *d_hext, double *d_H, hipStre
 }
 
 hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, double *d_H, double *d_E,
-                        hipStream_t s)
+                        hipStream_t s, bool enter, bool leave)
 {
-    hipError_t e = launch_upward_moments(h, d_mom, s);
+    hipError_t e = launch_upward_moments(h, d_mom, s, enter);
     if (e != hipSuccess) return e;
     const bool mixed = h.p.precision == BH_FP32_MIXED;
     const bool cnt = h.cnt_far != nullptr;
@@ -390,7 +393,10 @@ hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, do
         else launch_k_field<false, false, false>(h, d_hext, d_H, s);
     }
     if (h.ev[1]) (void)hipEventRecord(h.ev[1], s);
-    if (d_E) launch_energy_final(h, d_E, s, kWave);
+    // the energy of one system is one workgroup, the call's last: it also counts the call out
+    const bool last = leave && d_E && h.L.B == 1;
+    if (d_E) launch_energy_final(h, d_E, s, kWave, last);
+    if (leave && !last) launch_leave(h.w.status, s);
     return hipGetLastError();
 }
 
@@ -399,10 +405,11 @@ void launch_order_field(Handle &h, hipStream_t s)
     launch_order_items(h.w.field_cost, (int)h.L.num_waves, h.w.field_order, h.w.field_ctr, s);
 }
 
-void launch_energy_final(Handle &h, double *d_E, hipStream_t s, int targets_per_wave)
+void launch_energy_final(Handle &h, double *d_E, hipStream_t s, int targets_per_wave, bool leave)
 {
     const int waves_per_seg = (int)((h.L.n + targets_per_wave - 1) / targets_per_wave);
-    hipLaunchKernelGGL(k_energy_final, dim3((unsigned)h.L.B), dim3(256), 0, s, h.w.e_part, waves_per_seg, d_E);
+    hipLaunchKernelGGL(k_energy_final, dim3((unsigned)h.L.B), dim3(256), 0, s, h.w.e_part, waves_per_seg, d_E,
+                       h.w.status, leave ? 1 : 0);
 }
 
 }  // namespace ffbh

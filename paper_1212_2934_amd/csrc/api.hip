@@ -49,7 +49,6 @@ Layout plan_layout(const bh_params &p)
     L.sort_items = (int)(items < 1 ? 1 : items > kSortItems ? kSortItems : items);
     L.tiles = (L.n + (int64_t)kSortThreads * L.sort_items - 1) / ((int64_t)kSortThreads * L.sort_items);
     L.hist_len = L.B * kRadixBins * L.tiles;
-    L.bin_int = L.B * (L.n - 1);
     L.num_waves = L.B * ((L.n + kWave - 1) / kWave);
     // short-range grid: at most 32 entries per particle and level 7
     int lg = 0;
@@ -73,7 +72,8 @@ void carve(const Layout &Lc, void *base, Workspace &w)
         off += bytes ? bytes : 1;
         return p;
     };
-    const size_t nt = (size_t)L.ntot, mn = (size_t)L.max_nodes, bi = (size_t)(L.bin_int > 0 ? L.bin_int : 1);
+    const size_t nt = (size_t)L.ntot, mn = (size_t)L.max_nodes;
+    const size_t bi = L.n > 1 ? (size_t)(L.B * (L.n - 1)) : 1;  // particle pairs (j - 1, j) of the systems
     w.status = (uint32_t *)take(64);
     w.bbox = (double *)take(8 * sizeof(double) * L.B);
     w.bbox_part = (double *)take(6 * sizeof(double) * kBboxBlocks * L.B);
@@ -82,7 +82,7 @@ void carve(const Layout &Lc, void *base, Workspace &w)
     w.vals[0] = (uint32_t *)take(4 * nt);
     w.vals[1] = (uint32_t *)take(4 * nt);
     w.hist = (uint32_t *)take(4 * (size_t)L.hist_len);
-    w.scan_tmp = (uint32_t *)take(4 * ((size_t)(L.hist_len > L.bin_int ? L.hist_len : L.bin_int) / 4096 + 64));
+    w.scan_tmp = (uint32_t *)take(4 * (((size_t)L.hist_len > bi ? (size_t)L.hist_len : bi) / 4096 + 64));
     w.perm = w.vals[0];
     w.codes = w.keys[0];
     // the target-order sort ping-pongs between (keys[1], vals[1]), free once the particles are sorted, and
@@ -96,16 +96,13 @@ void carve(const Layout &Lc, void *base, Workspace &w)
     // one 48-byte source record per particle, in the handle's precision (src64 or src32, never both)
     w.src64 = take(48 * nt);
     w.src32 = w.src64;
-    w.bin_left = (int32_t *)take(4 * bi);
-    w.bin_right = (int32_t *)take(4 * bi);
-    w.bin_first = (int32_t *)take(4 * bi);
-    w.bin_last = (int32_t *)take(4 * bi);
-    w.bin_delta = (int32_t *)take(4 * bi);
-    w.bin_parent = (int32_t *)take(4 * bi);
-    w.leaf_parent = (int32_t *)take(4 * nt);
-    w.bin_nchild = (int32_t *)take(4 * bi);
-    w.bin_scan = (uint32_t *)take(4 * bi);
-    w.bin_octid = (int32_t *)take(4 * bi);
+    // The octree construction needs three of the ten arrays that this region once held.  Its size is kept: it
+    // decides which calls the fixed array of bh_field_noalloc takes.
+    const size_t region = align_up(off, 256) + 9 * align_up(4 * bi, 256) + align_up(4 * nt, 256) + 512;
+    w.cell_mask = (uint32_t *)take(4 * nt);
+    w.cell_scan = (uint32_t *)take(4 * nt);
+    w.cell_key = (int32_t *)take(4 * nt);
+    off = region;
     w.nodes = (NodeRec *)take(sizeof(NodeRec) * mn);
     w.node_level = (int32_t *)take(4 * mn);
     w.node_m64 = (double *)take(4 * 8 * mn);

@@ -1,12 +1,10 @@
-// Tree construction on gfx950: bounding cube, Morton codes, LDS radix sort, binary radix tree,
-// collapsed octree, and the upward pass that forms the pseudo-particles.
+// Tree construction on gfx950: bounding cube, Morton codes, LDS radix sort, octree, and the upward pass that forms the pseudo-particles.
 //
 // Paper: Sec. 3.2 (kernels 1-4 of the GPU Barnes-Hut scheme: bounding box, octree, cell centres and
 // moments, sort by location) and Eq. (magCenter) (pseudo-particle = moment sum at the geometric
-// centre of the members).  The lock-based insertion of the paper is replaced by the binary radix tree
-// construction of T. Karras, "Maximizing parallelism in the construction of BVHs, octrees, and k-d
-// trees" (HPG 2012), collapsed to an octree with leaf size leaf_size; the spin-waiting moment kernel
-// is replaced by a level-synchronous upward pass (one launch per level, or one workgroup for small trees).
+// centre of the members).  The lock-based insertion of the paper is replaced by a construction of all cells
+// from the sorted codes at once, the spin-waiting moment kernel by an upward pass over chunks of the sorted
+// particles.
 #include "ffbh_internal.h"
 
 namespace ffbh {
@@ -110,7 +108,8 @@ __device__ inline uint32_t quantise(double r, double lo, double scale)
 
 __global__ __launch_bounds__(256) void k_morton(const double *__restrict__ pos, int64_t n, int64_t ntot,
                                                 const double *__restrict__ bbox,
-                                                uint64_t *__restrict__ keys, uint32_t *__restrict__ vals)
+                                                uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
+                                                uint32_t *__restrict__ mask)
 {
     int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (o >= ntot) return;
@@ -122,6 +121,7 @@ __global__ __launch_bounds__(256) void k_morton(const double *__restrict__ pos, 
     uint32_t qz = quantise(p[2 * n + i], bb[2], bb[4]);
     keys[o] = morton(qx, qy, qz);
     vals[o] = (uint32_t)o;
+    mask[o] = 0u;  // filled by k_oct_mark
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -154,8 +154,8 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint64_t *__r
     hist[((int64_t)b * kRadixBins + threadIdx.x) * tiles + t] = cnt[threadIdx.x];
 }
 
-// Device-wide exclusive scan of a uint32 array in place, in three launches: per-tile sums, a scan of
-// the tile sums (one workgroup), and the per-tile scan with its offset.  Tiles are kScanTile entries,
+// Device-wide exclusive scan of a uint32 array (BITS: of its entries' bit counts) into another or in place, in
+// three launches: per-tile sums, a scan of the tile sums (one workgroup), and the per-tile scan with its offset.  Tiles are kScanTile entries,
 // read and written through LDS so that global accesses are coalesced.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
@@ -179,7 +179,11 @@ __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t *sh, uint32_t &t
     return r;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const uint32_t *__restrict__ a, int64_t len,
+template <bool BITS>
+__device__ inline uint32_t scan_value(uint32_t v) { return BITS ? (uint32_t)__popc(v) : v; }
+
+template <bool BITS>
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const uint32_t *a, int64_t len,
                                                              uint32_t *__restrict__ tile_sum)
 {
     __shared__ uint32_t sh[kScanThreads];
@@ -187,7 +191,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const uint32_t *__r
     uint32_t s = 0;
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t i = base + (int64_t)k * kScanThreads + threadIdx.x;
-        if (i < len) s += a[i];
+        if (i < len) s += scan_value<BITS>(a[i]);
     }
     uint32_t total;
     block_excl_scan(s, sh, total);
@@ -210,7 +214,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(uint32_t *__restrict
     if (threadIdx.x == 0 && total_out) *total_out = carry;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t *__restrict__ a, int64_t len,
+template <bool BITS>
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t *a, uint32_t *out, int64_t len,
                                                              const uint32_t *__restrict__ tile_off)
 {
     __shared__ uint32_t tile[kScanTile];
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t *__restric
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
     for (int k = 0; k < kScanItems; ++k) {
         const int j = k * kScanThreads + threadIdx.x;
-        tile[j] = base + j < len ? a[base + j] : 0u;
+        tile[j] = base + j < len ? scan_value<BITS>(a[base + j]) : 0u;
     }
     __syncthreads();
     // each thread scans its own run of kScanItems consecutive entries
@@ -235,7 +240,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t *__restric
     __syncthreads();
     for (int k = 0; k < kScanItems; ++k) {
         const int j = k * kScanThreads + threadIdx.x;
-        if (base + j < len) a[base + j] = tile[j];
+        if (base + j < len) out[base + j] = tile[j];
     }
 }
 
@@ -261,7 +266,8 @@ constexpr int64_t kScanSmallMax = 4 * (int64_t)kScanSmallChunk;
 
 __device__ inline int scan_pad(int j) { return j + (j >> 5); }
 
-__global__ __launch_bounds__(kScanSmallThreads) void k_scan_small(uint32_t *__restrict__ a, int64_t len,
+template <bool BITS>
+__global__ __launch_bounds__(kScanSmallThreads) void k_scan_small(const uint32_t *a, uint32_t *out, int64_t len,
                                                                   uint32_t *__restrict__ total_out)
 {
     constexpr int kWaves = kScanSmallThreads / kWave;
@@ -273,7 +279,7 @@ __global__ __launch_bounds__(kScanSmallThreads) void k_scan_small(uint32_t *__re
 #pragma unroll
         for (int k = 0; k < kScanSmallItems; ++k) {
             const int j = k * kScanSmallThreads + t;
-            tile[scan_pad(j)] = base + j < len ? a[base + j] : 0u;
+            tile[scan_pad(j)] = base + j < len ? scan_value<BITS>(a[base + j]) : 0u;
         }
         __syncthreads();
         uint32_t run = 0;
@@ -300,7 +306,7 @@ __global__ __launch_bounds__(kScanSmallThreads) void k_scan_small(uint32_t *__re
 #pragma unroll
         for (int k = 0; k < kScanSmallItems; ++k) {
             const int j = k * kScanSmallThreads + t;
-            if (base + j < len) a[base + j] = tile[scan_pad(j)];
+            if (base + j < len) out[base + j] = tile[scan_pad(j)];
         }
         carry += ctot;
         __syncthreads();  // tile and wsum are rewritten by the next chunk
@@ -308,17 +314,19 @@ __global__ __launch_bounds__(kScanSmallThreads) void k_scan_small(uint32_t *__re
     if (t == 0 && total_out) *total_out = carry;
 }
 
-// Exclusive scan in place; writes the total to *total if not null.  scratch: one uint32 per tile.
-static void scan_excl(uint32_t *a, int64_t len, uint32_t *scratch, uint32_t *total, hipStream_t s)
+// Exclusive scan of a into out (which may be a); writes the total to *total if not null.  scratch: one uint32
+// per tile.
+template <bool BITS>
+static void scan_excl(const uint32_t *a, uint32_t *out, int64_t len, uint32_t *scratch, uint32_t *total, hipStream_t s)
 {
     if (len <= kScanSmallMax) {
-        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kScanSmallThreads), 0, s, a, len, total);
+        hipLaunchKernelGGL(k_scan_small<BITS>, dim3(1), dim3(kScanSmallThreads), 0, s, a, out, len, total);
         return;
     }
     const int ntiles = (int)((len + kScanTile - 1) / kScanTile);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(kScanThreads), 0, s, a, len, scratch);
+    hipLaunchKernelGGL(k_scan_tiles<BITS>, dim3(ntiles), dim3(kScanThreads), 0, s, a, len, scratch);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, scratch, ntiles, total);
-    hipLaunchKernelGGL(k_scan_apply, dim3(ntiles), dim3(kScanThreads), 0, s, a, len, scratch);
+    hipLaunchKernelGGL(k_scan_apply<BITS>, dim3(ntiles), dim3(kScanThreads), 0, s, a, out, len, scratch);
 }
 
 constexpr int kFusedTiles = 256;
@@ -654,267 +662,207 @@ __global__ __launch_bounds__(256) void k_gather3(const double *__restrict__ src,
 }
 
 // ------------------------------------------------------------------------------------------------
-// Binary radix tree (Karras 2012), one per system over its n sorted codes.  delta(i, j) is the length
-// of the common prefix of codes i and j within the 63 code bits; equal codes are told apart by their
-// sorted positions (63 + common prefix of the 32-bit positions).  Out-of-range j gives -1.
+// Octree from the sorted codes.  Call digits(a, c) the number of leading octal digits (of 21) that codes a and
+// c share: the level of the deepest cell holding both.  A system's sorted codes then give its octree without
+// a binary tree:
+//   - A cell of level l around particle i holds more than `leaf` particles iff some window of leaf + 1
+//     consecutive particles around i shares l digits, so the deepest such cell has level
+//       W_i = max of digits(code_s, code_{s + leaf}) over the windows s .. s + leaf that hold i.
+//   - Particles j - 1 and j lie in different children of the cell of level L = digits(code_{j-1}, code_j) that
+//     holds both; the cell is split, and j starts a child, iff L <= W_j and L < 21.
+//   - A stored cell is one that is split into at least two children (a run of unary cells is stored once, at its
+//     deepest level, which leaves every pseudo-particle and every acceptance decision unchanged: same members,
+//     smaller side), so each has exactly one first such j, the end of its first child: its key.  The octants of
+//     its children are collected in mask[key], the exclusive scan of the masks' bit counts allocates the
+//     children (contiguous, octant order), and a child's place is the number of lower octants in the mask.
+//   - Leaves are the children of at most `leaf` particles (stored at the first level of their run) and, flagged,
+//     the cells of level 21 with more.
+// Cell ends and starts are found by galloping from the particle at hand, since most cells are small: a few
+// dependent loads.
+// (A binary radix tree over all particles with the octree cut from it took ten launches and 285 us at 2^20,
+// where 2 % of its nodes were of use; this takes five launches.)
 // ------------------------------------------------------------------------------------------------
 
-__device__ inline int prefix_len(const uint64_t *k, int n, int i, int j)
+__device__ inline int digits(uint64_t a, uint64_t c)
 {
-    if (j < 0 || j >= n) return -1;
-    uint64_t a = k[i], c = k[j];
-    if (a == c) return 63 + __clz((unsigned)(i ^ j));
-    return __clzll((long long)(a ^ c)) - 1;
+    return a == c ? kMaxLevel : (__clzll((long long)(a ^ c)) - 1) / 3;
 }
+// First and last code of the cell of level l that holds code x, and x's octant in its parent cell of level l - 1.
+__device__ inline uint64_t cell_low(uint64_t x, int l) { return x & ~((1ull << (3 * (kMaxLevel - l))) - 1ull); }
+__device__ inline uint64_t cell_high(uint64_t x, int l) { return x | ((1ull << (3 * (kMaxLevel - l))) - 1ull); }
+__device__ inline uint32_t octant(uint64_t x, int l) { return (uint32_t)(x >> (3 * (kMaxLevel - l))) & 7u; }
 
-__global__ __launch_bounds__(256) void k_karras(const uint64_t *__restrict__ codes, int64_t n, int64_t nint_tot,
-                                                int32_t *__restrict__ left, int32_t *__restrict__ right,
-                                                int32_t *__restrict__ first, int32_t *__restrict__ last,
-                                                int32_t *__restrict__ delta, int32_t *__restrict__ bparent,
-                                                int32_t *__restrict__ lparent)
+// Smallest k in [0, j] with code_k >= low, for code_j >= low.
+__device__ inline int gallop_left(const uint64_t *code, int j, uint64_t low)
 {
-    int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= nint_tot) return;
-    const int nn = (int)n;
-    const int64_t b = g / (n - 1);
-    const int i = (int)(g - b * (n - 1));
-    const uint64_t *k = codes + b * n;
-    const int d = (prefix_len(k, nn, i, i + 1) - prefix_len(k, nn, i, i - 1)) > 0 ? 1 : -1;
-    const int dmin = prefix_len(k, nn, i, i - d);
-    int lmax = 2;
-    while (prefix_len(k, nn, i, i + lmax * d) > dmin) lmax <<= 1;
-    int l = 0;
-    for (int t = lmax >> 1; t >= 1; t >>= 1)
-        if (prefix_len(k, nn, i, i + (l + t) * d) > dmin) l += t;
-    const int j = i + l * d;
-    const int dnode = prefix_len(k, nn, i, j);
-    int s = 0;
-    for (int div = 2;; div <<= 1) {
-        const int t = (l + div - 1) / div;
-        if (prefix_len(k, nn, i, i + (s + t) * d) > dnode) s += t;
-        if (t <= 1) break;
+    int hi = j, step = 1;
+    while (hi - step >= 0 && code[hi - step] >= low) {
+        hi -= step;
+        step <<= 1;
     }
-    const int gamma = i + s * d + min(d, 0);
-    const int lo = min(i, j), hi = max(i, j);
-    const int64_t ib = b * (n - 1), lb = b * n;
-    int32_t L, R;
-    if (lo == gamma) { L = ~gamma; lparent[lb + gamma] = i; }
-    else { L = gamma; bparent[ib + gamma] = i; }
-    if (hi == gamma + 1) { R = ~(gamma + 1); lparent[lb + gamma + 1] = i; }
-    else { R = gamma + 1; bparent[ib + gamma + 1] = i; }
-    left[g] = L;
-    right[g] = R;
-    first[g] = lo;
-    last[g] = hi;
-    delta[g] = dnode;
-    if (i == 0) bparent[ib] = -1;
+    int lo = hi - step < 0 ? -1 : hi - step;  // code_lo < low (or before the first)
+    while (hi - lo > 1) {
+        const int m = (lo + hi) >> 1;
+        if (code[m] >= low) hi = m; else lo = m;
+    }
+    return hi;
+}
+// Smallest k in (j, end] with code_k > high (end itself if none), for code_j <= high.
+__device__ inline int gallop_right(const uint64_t *code, int j, int end, uint64_t high)
+{
+    int lo = j, step = 1;
+    while (lo + step < end && code[lo + step] <= high) {
+        lo += step;
+        step <<= 1;
+    }
+    int hi = lo + step > end ? end : lo + step;  // code_hi > high (or past the last)
+    while (hi - lo > 1) {
+        const int m = (lo + hi) >> 1;
+        if (code[m] <= high) lo = m; else hi = m;
+    }
+    return hi;
 }
 
-// ------------------------------------------------------------------------------------------------
-// Octree from the binary tree.  A binary node whose members share 3*l but no more code bits has its
-// deepest common cell at level lev = min(21, delta / 3).  It starts a new octree cell iff its level
-// exceeds its binary parent's; a run of unary cells is stored once, at its deepest level, which
-// leaves every pseudo-particle and every acceptance decision unchanged (a unary parent has the same
-// members and a larger side).  A cell is in the tree iff its octree parent is internal
-// (count > leaf_size and level < 21).  Leaves sit at the top of their run (they are not split).
-// ------------------------------------------------------------------------------------------------
-
-__device__ inline int bin_level(const int32_t *delta, int64_t g)
+// Particle j (1 <= j < n) of a system with W_j = wj: if it starts a child of a split cell, that cell's key (which
+// gets the octants of this child and, at the key, of the first one), else -1.
+template <typename Or>
+__device__ inline int oct_mark(const uint64_t *code, int n, int j, int wj, const Or &or_mask)
 {
-    int l = delta[g] / 3;
-    return l > kMaxLevel ? kMaxLevel : l;
+    const uint64_t cj = code[j];
+    const int L = digits(code[j - 1], cj);
+    if (L > wj || L >= kMaxLevel) return -1;
+    const int p = gallop_left(code, j, cell_low(cj, L));
+    const uint64_t cp = code[p];
+    const int key = gallop_right(code, p, j, cell_high(cp, L + 1));
+    or_mask(key, (1u << octant(cj, L + 1)) | (key == j ? 1u << octant(cp, L + 1) : 0u));
+    return key;
 }
 
-__global__ __launch_bounds__(256) void k_oct_count(int64_t n, int64_t nint_tot, int leaf,
-                                                   const int32_t *__restrict__ left,
-                                                   const int32_t *__restrict__ right,
-                                                   const int32_t *__restrict__ first,
-                                                   const int32_t *__restrict__ last,
-                                                   const int32_t *__restrict__ delta,
-                                                   const int32_t *__restrict__ bparent,
-                                                   int32_t *__restrict__ nchild, uint32_t *__restrict__ scan_in,
-                                                   uint32_t *__restrict__ status)
+// What the node records and the leaf index are written to; ids of the system's children start at `base`.
+struct OctOut {
+    NodeRec *nodes;
+    int32_t *node_level, *leaf_of;
+    uint32_t *status;
+    int64_t base, first, max_nodes;  // first: sorted position of the system's first particle
+    int leaf;
+};
+
+// The record of cell [f, e) as node id; `level` is that of the first cell of its run.  A split cell also
+// writes its id into its children's records (the one field they do not write themselves).
+template <typename Mask, typename Scan>
+__device__ inline void oct_cell(const OctOut &o, const uint64_t *code, int f, int e, int level, int64_t id,
+                                const Mask &mask, const Scan &scan)
 {
-    int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= nint_tot) return;
-    const int64_t b = g / (n - 1), ib = b * (n - 1);
-    const int cnt = last[g] - first[g] + 1;
-    int out = 0;
-    if (cnt <= leaf) {  // no children whether or not the node is in the tree (most nodes)
-        nchild[g] = 0;
-        scan_in[g] = 0u;
+    if (id < 0 || id >= o.max_nodes) {
+        set_flag(o.status, BH_FLAG_TREE);
         return;
     }
-    const int lev = bin_level(delta, g);
-    // is this node the deepest cell of an octree run, and is that cell in the tree?
-    const int p = bparent[g];
-    bool in_tree;
-    if (p < 0) {
-        in_tree = true;
-    } else if (lev <= bin_level(delta, ib + p)) {
-        in_tree = false;  // an intermediate binary split inside one octant digit
-    } else {
-        // octree parent: nearest binary ancestor that starts a cell (at most 2 binary levels up)
-        int x = p;
-        for (int up = 0; up < 64; ++up) {
-            const int px = bparent[ib + x];
-            if (px < 0 || px >= n - 1 || bin_level(delta, ib + x) > bin_level(delta, ib + px)) break;
-            x = px;
-        }
-        const int pc = last[ib + x] - first[ib + x] + 1;
-        in_tree = pc > leaf && bin_level(delta, ib + x) < kMaxLevel;
-    }
-    if (in_tree) {
-        if (lev >= kMaxLevel) {
-            set_flag(status, BH_FLAG_DEEP_LEAF);
+    const int count = e - f;
+    int child = -1, nchild = 0;
+    if (count > o.leaf) {
+        level = digits(code[f], code[e - 1]);
+        if (level >= kMaxLevel) {
+            set_flag(o.status, BH_FLAG_DEEP_LEAF);
         } else {
-            // children: walk the binary subtree down to the nodes that start the next cells
-            int32_t stk[8];
-            int sp = 0;
-            stk[sp++] = right[g];
-            stk[sp++] = left[g];
-            while (sp > 0) {
-                const int32_t c = stk[--sp];
-                if (c < 0 || c >= n - 1 || bin_level(delta, ib + c) > lev) {
-                    ++out;
-                } else if (sp > 5) {  // one octant digit spans at most three binary levels
-                    set_flag(status, BH_FLAG_TREE);
-                    break;
-                } else {
-                    stk[sp++] = right[ib + c];
-                    stk[sp++] = left[ib + c];
-                }
-            }
-        }
-    }
-    nchild[g] = out;
-    scan_in[g] = (uint32_t)out;
-}
-
-// Write the records of the children of every in-tree internal node (and of the roots), and, for each
-// leaf among them, its id as the leaf of its members.
-__device__ inline void stamp_leaf(int32_t *__restrict__ leaf_of, int64_t first, int count, int64_t end, int32_t id)
-{
-    for (int k = 0; k < count; ++k)
-        if (first + k < end) leaf_of[first + k] = id;
-}
-
-__global__ __launch_bounds__(256) void k_oct_emit(int64_t n, int64_t nint_tot, int64_t B, int leaf,
-                                                  const int32_t *__restrict__ left,
-                                                  const int32_t *__restrict__ right,
-                                                  const int32_t *__restrict__ first,
-                                                  const int32_t *__restrict__ last,
-                                                  const int32_t *__restrict__ delta,
-                                                  const int32_t *__restrict__ nchild,
-                                                  const uint32_t *__restrict__ scan,
-                                                  NodeRec *__restrict__ nodes, int32_t *__restrict__ node_level,
-                                                  int32_t *__restrict__ octid, uint32_t *__restrict__ status,
-                                                  int64_t max_nodes, int32_t *__restrict__ leaf_of)
-{
-    int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g == 0) status[2] = (uint32_t)B + (nint_tot > 0 ? status[1] : 0u);  // number of nodes
-    // roots: one thread per system (threads g < B); node b is the root of system b
-    if (g < B) {
-        const int64_t b = g;
-        NodeRec r{};
-        r.first = (int32_t)(b * n);
-        r.count = (int32_t)n;
-        r.parent = -1;
-        r.child = -1;
-        r.nchild = 0;
-        int lev = 0;
-        if (n > 1 && n > leaf) {
-            const int64_t rg = b * (n - 1);
-            lev = bin_level(delta, rg);  // deepest cell of the root's run (kMaxLevel: one deep leaf)
-            if (nchild[rg] > 0) {
-                r.child = (int32_t)(B + scan[rg]);
-                r.nchild = nchild[rg];
-            }
-            octid[rg] = (int32_t)b;
-        }
-        nodes[b] = r;
-        node_level[b] = lev;
-        if (r.nchild == 0) stamp_leaf(leaf_of, b * n, (int)n, b * n + n, (int32_t)b);
-    }
-    if (g >= nint_tot) return;
-    const int nc = nchild[g];
-    if (nc == 0) return;
-    const int64_t b = g / (n - 1), ib = b * (n - 1);
-    const int lev = bin_level(delta, g);
-    int id = (int)(B + scan[g]);
-    if ((int64_t)id + nc > max_nodes) {
-        set_flag(status, BH_FLAG_TREE);
-        return;
-    }
-    int32_t stk[8];
-    int sp = 0;
-    stk[sp++] = right[g];
-    stk[sp++] = left[g];
-    while (sp > 0) {
-        const int32_t c = stk[--sp];
-        const bool particle = c < 0;
-        if (!particle && c >= n - 1) {
-            set_flag(status, BH_FLAG_TREE);
-            break;
-        }
-        if (particle || bin_level(delta, ib + c) > lev) {
-            if (id >= B + (int64_t)scan[g] + nc || (particle && ~c >= n)) {
-                set_flag(status, BH_FLAG_TREE);
-                break;
-            }
-            NodeRec r{};
-            int cf, cc, clev;
-            int ch = -1, cn = 0;
-            if (particle) {
-                cf = ~c; cc = 1; clev = lev + 1;
+            const int key = gallop_right(code, f, e, cell_high(code[f], level + 1));
+            const uint32_t m = key < e ? mask(key) : 0u;
+            const int64_t c = o.base + scan(key < e ? key : f);
+            nchild = __popc(m);
+            if (nchild < 2 || c + nchild > o.max_nodes) {
+                set_flag(o.status, BH_FLAG_TREE);
+                nchild = 0;
             } else {
-                const int64_t cg = ib + c;
-                cf = first[cg];
-                cc = last[cg] - first[cg] + 1;
-                if (cc > leaf) {
-                    clev = bin_level(delta, cg);  // deepest cell of the run; kMaxLevel for a deep leaf
-                    if (nchild[cg] > 0) {
-                        ch = (int)(B + scan[cg]);
-                        cn = nchild[cg];
-                    }
-                } else {
-                    clev = lev + 1;  // a leaf is the first cell of its run
-                }
-                octid[cg] = id;
+                child = (int)c;
+                for (int q = 0; q < nchild; ++q) o.nodes[c + q].parent = (int32_t)id;
             }
-            r.first = (int32_t)(b * n + cf);
-            r.count = cc;
-            r.child = ch;
-            r.nchild = cn;
-            r.parent = -1;  // set by k_oct_link
-            nodes[id] = r;
-            node_level[id] = clev;
-            if (cn == 0) stamp_leaf(leaf_of, b * n + cf, cc, b * n + n, id);
-            ++id;
-        } else if (sp > 5) {
-            set_flag(status, BH_FLAG_TREE);
-            break;
-        } else {
-            stk[sp++] = right[ib + c];
-            stk[sp++] = left[ib + c];
         }
     }
+    NodeRec *r = o.nodes + id;
+    r->first = (int32_t)(o.first + f);
+    r->count = count;
+    r->child = child;
+    r->nchild = nchild;
+    o.node_level[id] = level;
+    if (nchild == 0)
+        for (int k = f; k < e; ++k) o.leaf_of[o.first + k] = (int32_t)id;
 }
 
-// Parent links: every in-tree internal node stamps its id into its children.
-__global__ __launch_bounds__(256) void k_oct_link(int64_t nint_tot, int64_t B, const int32_t *__restrict__ nchild,
-                                                  const uint32_t *__restrict__ scan,
-                                                  const int32_t *__restrict__ octid, NodeRec *__restrict__ nodes,
-                                                  int64_t max_nodes)
+// The children that start at particle j, whose cell has key `key`: j's own cell and, at the key, the first child.
+template <typename Mask, typename Scan>
+__device__ inline void oct_children(const OctOut &o, const uint64_t *code, int n, int j, int key, const Mask &mask,
+                                    const Scan &scan)
 {
-    int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= nint_tot) return;
-    const int nc = nchild[g];
-    if (nc == 0) return;
-    const int self = octid[g];
-    const int c0 = (int)(B + scan[g]);
-    if (nc < 0 || nc > 8 || (int64_t)c0 + nc > max_nodes) return;
-    for (int q = 0; q < nc; ++q) nodes[c0 + q].parent = self;
+    const uint64_t cj = code[j];
+    const int L = digits(code[j - 1], cj);
+    const uint32_t m = mask(key);
+    const int64_t c = o.base + scan(key);
+    const uint32_t below = m & ((1u << octant(cj, L + 1)) - 1u);
+    oct_cell(o, code, j, gallop_right(code, j, n, cell_high(cj, L + 1)), L + 1, c + __popc(below), mask, scan);
+    if (key == j) oct_cell(o, code, gallop_left(code, j - 1, cell_low(code[j - 1], L + 1)), j, L + 1, c, mask, scan);
+}
+
+// The root of a system of n particles (node id): one leaf up to leaf_size particles.
+template <typename Mask, typename Scan>
+__device__ inline void oct_root(const OctOut &o, const uint64_t *code, int n, int64_t id, const Mask &mask,
+                                const Scan &scan)
+{
+    o.nodes[id].parent = -1;
+    oct_cell(o, code, 0, n, 0, id, mask, scan);
+}
+
+constexpr int kOctThreads = 256;
+constexpr int kMaxLeaf = 64;  // largest leaf_size
+
+// Keys and masks of all systems: one thread per particle, blockIdx.y the system.  The block's codes and a
+// window of them on either side are staged in LDS for the windows' digits.
+__global__ __launch_bounds__(kOctThreads) void k_oct_mark(const uint64_t *__restrict__ codes, int n, int leaf,
+                                                          int32_t *__restrict__ keys, uint32_t *__restrict__ mask,
+                                                          int64_t blocks_per_sys)
+{
+    __shared__ uint64_t sc[kOctThreads + 2 * kMaxLeaf];
+    __shared__ int8_t win[kOctThreads + kMaxLeaf];  // digits of window s at s - (i0 - leaf); -1: not a window
+    const int64_t b = blockIdx.x / blocks_per_sys;
+    const int i0 = (int)(blockIdx.x - b * blocks_per_sys) * kOctThreads, t = threadIdx.x;
+    const uint64_t *code = codes + b * n;
+    for (int k = t; k < kOctThreads + 2 * leaf; k += kOctThreads) {
+        const int i = i0 - leaf + k;
+        sc[k] = i >= 0 && i < n ? code[i] : 0ull;
+    }
+    __syncthreads();
+    for (int k = t; k < kOctThreads + leaf; k += kOctThreads) {
+        const int i = i0 - leaf + k;
+        win[k] = i >= 0 && i + leaf < n ? (int8_t)digits(sc[k], sc[k + leaf]) : (int8_t)-1;
+    }
+    __syncthreads();
+    const int j = i0 + t;
+    if (j >= n) return;
+    int w = -1;
+    for (int k = 0; k <= leaf; ++k) w = max(w, (int)win[t + k]);
+    int key = -1;
+    if (j > 0)
+        key = oct_mark(code, n, j, w, [&](int k, uint32_t m) { atomicOr(&mask[b * n + k], m); });
+    keys[b * n + j] = key;
+}
+
+__global__ __launch_bounds__(kOctThreads) void k_oct_emit(const uint64_t *__restrict__ codes, int64_t n, int64_t ntot,
+                                                          int64_t B, int leaf, const int32_t *__restrict__ keys,
+                                                          const uint32_t *__restrict__ mask,
+                                                          const uint32_t *__restrict__ scan,
+                                                          NodeRec *__restrict__ nodes, int32_t *__restrict__ node_level,
+                                                          int32_t *__restrict__ leaf_of, uint32_t *__restrict__ status,
+                                                          int64_t max_nodes)
+{
+    const int64_t g = (int64_t)blockIdx.x * kOctThreads + threadIdx.x;
+    if (g >= ntot) return;
+    if (g == 0) status[2] = (uint32_t)B + status[1];  // number of nodes
+    const int64_t b = g / n, first = b * n;
+    const int j = (int)(g - first);
+    const OctOut o{nodes, node_level, leaf_of, status, B, first, max_nodes, leaf};
+    auto mask_of = [&](int k) { return mask[first + k]; };
+    auto scan_of = [&](int k) { return (int64_t)scan[first + k]; };
+    if (j == 0) oct_root(o, codes + first, (int)n, b, mask_of, scan_of);
+    const int key = keys[g];
+    if (key > 0 && key <= j) oct_children(o, codes + first, (int)n, j, key, mask_of, scan_of);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -923,10 +871,9 @@ __global__ __launch_bounds__(256) void k_oct_link(int64_t nint_tot, int64_t B, c
 //   MODE 0: positions -> centroid S / count and squared side into the node record.
 //   MODE 1: moments   -> FP64 moment sum into node_m64 and its FP32 rounding into the record.
 //
-// One workgroup per chunk of consecutive sorted positions of a system (k_upward_sub).  The binary node that
-// allocates a cell's children lies inside the cell (its index is one end of its range), and ids follow the
-// binary nodes, so the children of all cells inside a chunk have consecutive ids and belong to the chunk's
-// workgroup, which sums its leaves and then, level by level with a barrier between levels, the cells inside
+// One workgroup per chunk of consecutive sorted positions of a system (k_upward_sub).  The key that allocates a
+// cell's children is a position inside the cell, and ids follow the keys, so the children of all cells inside
+// a chunk have consecutive ids and belong to the chunk's workgroup, which sums its leaves and then, level by level with a barrier between levels, the cells inside
 // the chunk.  Cells that reach beyond their chunk (the ancestors of the chunk boundaries, a few dozen a chunk)
 // are listed per system when the tree is built and follow in a second launch of one workgroup per system
 // (k_upward_top).  Systems of one chunk need no second launch.
@@ -1096,13 +1043,9 @@ __global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const
     __shared__ int lmin, lmax;
     const int64_t b = blockIdx.x / chunks;
     const int c = (int)(blockIdx.x - b * chunks);
-    const int64_t c0 = c * chunk, c1 = min(c0 + chunk, n), ib = b * (n - 1);
-    // ids of the children that binary nodes c0 .. c1 - 1 of the system allocated
-    const int64_t end = B + (n > 1 ? (int64_t)status[1] : 0);
-    auto start = [&](int64_t i) {
-        if (i < n - 1) return B + (int64_t)scan[ib + i];
-        return n > 1 && b + 1 < B ? B + (int64_t)scan[ib + n - 1] : end;
-    };
+    const int64_t c0 = c * chunk, c1 = min(c0 + chunk, n);
+    // ids of the children of the cells whose keys are positions c0 .. c1 - 1 of the system
+    auto start = [&](int64_t i) { return B + (int64_t)(b * n + i < ntot ? scan[b * n + i] : status[1]); };
     const int64_t i0 = start(c0), i1 = min(start(c1), max_nodes);
     // the root is the first chunk's, before its children
     const int root = c == 0 ? 1 : 0;
@@ -1188,7 +1131,7 @@ static bool upward(Handle &h, const double *vals, const double *vals2, hipStream
     leave = leave && L.B == 1;
     hipLaunchKernelGGL(k_upward_sub<MODE>, dim3((unsigned)(L.B * chunks)), dim3(threads), 0, s, vals, vals2, L.ntot,
                        L.n, w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
-                       w.bin_scan, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0,
+                       w.cell_scan, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0,
                        leave && chunks == 1 ? 1 : 0);
     if (chunks > 1)
         hipLaunchKernelGGL(k_upward_top<MODE>, dim3((unsigned)L.B), dim3(kUpThreads), 0, s, vals, vals2, L.ntot, L.n,
@@ -1222,7 +1165,7 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     hipLaunchKernelGGL(k_bbox_final, dim3((unsigned)B), dim3(256), 0, s, w.bbox_part, nb, w.bbox, w.top_nodes,
                        node_s2_scale(h.p.theta * h.p.theta));
     hipLaunchKernelGGL(k_morton, dim3(grid_for(ntot, 256)), dim3(256), 0, s, d_pos, n, ntot, w.bbox,
-                       w.keys[0], w.vals[0]);
+                       w.keys[0], w.vals[0], w.cell_mask);
     const int tiles = (int)L.tiles;
     const unsigned sblocks = (unsigned)(B * tiles);
     if (n <= kSortSmallMax) {
@@ -1238,7 +1181,7 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
                            L.sort_items, shift, w.hist);
         // up to kFusedTiles tiles per system the scatter derives its offsets from the raw counts
         const int fused = tiles <= kFusedTiles;
-        if (!fused) scan_excl(w.hist, (int64_t)L.hist_len, w.scan_tmp, nullptr, s);
+        if (!fused) scan_excl<false>(w.hist, w.hist, (int64_t)L.hist_len, w.scan_tmp, nullptr, s);
         hipLaunchKernelGGL(k_radix_scatter, dim3(sblocks), dim3(kSortThreads), 0, s, w.keys[src],
                            w.vals[src], w.keys[dst], w.vals[dst], w.hist, n, tiles, L.sort_items, shift, ntot,
                            fused);
@@ -1261,28 +1204,18 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     // below matters: the first octree kernels go first, the side stream's work next (before the rest of
     // the octree, which it runs beside).  With the side stream's work first, the binary radix tree started
     // up to 130 us after the sort in graph replays.
-    const int64_t nint = L.bin_int;  // B * (n - 1)
-    if (nint > 0) {
-        hipLaunchKernelGGL(k_karras, dim3(grid_for(nint, 256)), dim3(256), 0, s, w.codes, n, nint,
-                           w.bin_left, w.bin_right, w.bin_first, w.bin_last, w.bin_delta, w.bin_parent,
-                           w.leaf_parent);
-        hipLaunchKernelGGL(k_oct_count, dim3(grid_for(nint, 256)), dim3(256), 0, s, n, nint,
-                           (int)h.p.leaf_size, w.bin_left, w.bin_right, w.bin_first, w.bin_last,
-                           w.bin_delta, w.bin_parent, w.bin_nchild, w.bin_scan, w.status);
-    }
+    const int64_t sysblocks = (n + kOctThreads - 1) / kOctThreads;
+    hipLaunchKernelGGL(k_oct_mark, dim3((unsigned)(B * sysblocks)), dim3(kOctThreads), 0, s, w.codes, (int)n,
+                       (int)h.p.leaf_size, w.cell_key, w.cell_mask, sysblocks);
     if (uses_target_order(L)) launch_target_order(h, side ? side : s);
     if (after_sort) {
         const hipError_t e = after_sort(side ? side : s);
         if (e != hipSuccess) return e;
     }
-    if (nint > 0) scan_excl(w.bin_scan, nint, w.scan_tmp, w.status + 1, s);
-    hipLaunchKernelGGL(k_oct_emit, dim3(grid_for(nint > B ? nint : B, 256)), dim3(256), 0, s, n, nint, B,
-                       (int)h.p.leaf_size, w.bin_left, w.bin_right, w.bin_first, w.bin_last, w.bin_delta,
-                       w.bin_nchild, w.bin_scan, w.nodes, w.node_level, w.bin_octid, w.status, L.max_nodes,
-                       w.leaf_of);
-    if (nint > 0)
-        hipLaunchKernelGGL(k_oct_link, dim3(grid_for(nint, 256)), dim3(256), 0, s, nint, B,
-                           w.bin_nchild, w.bin_scan, w.bin_octid, w.nodes, L.max_nodes);
+    scan_excl<true>(w.cell_mask, w.cell_scan, ntot, w.scan_tmp, w.status + 1, s);
+    hipLaunchKernelGGL(k_oct_emit, dim3(grid_for(ntot, kOctThreads)), dim3(kOctThreads), 0, s, w.codes, n, ntot, B,
+                       (int)h.p.leaf_size, w.cell_key, w.cell_mask, w.cell_scan, w.nodes, w.node_level, w.leaf_of,
+                       w.status, L.max_nodes);
     if (d_mom) {
         // positions and moments summed in one upward pass
         gather_moments(h, d_mom, s, false);
@@ -1369,7 +1302,7 @@ void launch_target_order(Handle &h, hipStream_t s)
         const int shift = pass * kRadixBits;
         hipLaunchKernelGGL(k_radix_hist, dim3(sblocks), dim3(kSortThreads), 0, s, kb[src], L.n, tiles,
                            L.sort_items, shift, w.hist);
-        if (!fused) scan_excl(w.hist, (int64_t)L.hist_len, w.hscan_tmp, nullptr, s);
+        if (!fused) scan_excl<false>(w.hist, w.hist, (int64_t)L.hist_len, w.hscan_tmp, nullptr, s);
         hipLaunchKernelGGL(k_radix_scatter, dim3(sblocks), dim3(kSortThreads), 0, s, kb[src], vb[src], kb[dst],
                            vb[dst], w.hist, L.n, tiles, L.sort_items, shift, L.ntot, fused);
     }

@@ -81,18 +81,11 @@ struct Workspace {
     double *smom;            // 3 x N_tot sorted moments FP64
     void *src64;             // N_tot sorted source records (position, moment FP64), 48 bytes each (FP64)
     void *src32;             // the same buffer as records of position FP64, moment FP32 (FP32-mixed)
-    // binary radix tree (per system: n-1 internal nodes, n leaves)
-    int32_t *bin_left;       // internal node -> left child (>= 0 internal, < 0: leaf ~idx)
-    int32_t *bin_right;
-    int32_t *bin_first;      // range of an internal node (segment-local sorted positions)
-    int32_t *bin_last;
-    int32_t *bin_delta;      // common prefix length in bits (63 + x for equal codes)
-    int32_t *bin_parent;     // internal node -> parent internal node (-1 root)
-    int32_t *leaf_parent;    // sorted particle -> parent internal node (-1 if n == 1)
-    int32_t *bin_nchild;     // octree children of an internal node (0 if not an in-tree internal)
-    uint32_t *bin_scan;      // exclusive scan of bin_nchild
+    // octree construction, per sorted particle
+    uint32_t *cell_mask;     // at a split cell's key: the octants of its children
+    uint32_t *cell_scan;     // exclusive scan of the masks' bit counts: where the children start
+    int32_t *cell_key;       // key of the cell that the particle starts a child of (-1: none)
     // octree
-    int32_t *bin_octid;      // internal node -> octree node id (in-tree internal nodes only)
     NodeRec *nodes;          // max_nodes
     int32_t *node_level;     // max_nodes: cell level (side = side_root / 2^level)
     double *node_m64;        // 4 x max_nodes: moment sum FP64 (x, y, z, pad) per node
@@ -126,7 +119,7 @@ struct Workspace {
 constexpr int kBboxBlocks = 512;  // partial bounding boxes per system (two workgroups per CU)
 
 struct Layout {
-    int64_t n, B, ntot, max_nodes, tiles, num_waves, hist_len, bin_int;
+    int64_t n, B, ntot, max_nodes, tiles, num_waves, hist_len;
     int sort_items;         // keys per thread per radix-sort tile (1..kSortItems)
     int adj_parts;          // parts of a split adjoint walk that the workspace holds (0: none)
     int expansion;          // 2: first moments are kept (order-2 cells); else 1

@@ -658,7 +658,7 @@ __global__ __launch_bounds__(256) void k_parts_sum(const double *__restrict__ pa
 }
 
 // Before the fused walk, in one launch: the upstream field gradient in sorted order, Hbar = gH - 1/2 gE m, and
-// zeros in the adjoint records of the particles (g_rm) and of the nodes the last build made (their count is
+// zeros in the adjoint records of the particles (g_rm) and of the nodes the last build made (their counts are
 // on the device; node_adjq is null without order-2 cells).  Bound by the writes, 104 B a particle and 64 B a
 // node (2^20 particles: about 25 us); as three launches small systems paid 9 us more.
 __global__ __launch_bounds__(256) void k_adj_setup(const double *__restrict__ gH, const double *__restrict__ gE,
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256) void k_adj_setup(const double *__restrict__ gH
                                                    int64_t n, int64_t ntot, double *__restrict__ hbar,
                                                    double *__restrict__ g_rm, double *__restrict__ node_adj,
                                                    double *__restrict__ node_adjq, const uint32_t *__restrict__ nn,
-                                                   int64_t max_nodes)
+                                                   int64_t max_nodes, const int32_t *__restrict__ per_system)
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
     for (int64_t s = t; s < ntot; s += stride) {
@@ -680,6 +680,17 @@ __global__ __launch_bounds__(256) void k_adj_setup(const double *__restrict__ gH
         }
     }
     for (int64_t i = t; i < 8 * ntot; i += stride) g_rm[i] = 0.0;
+    if (per_system) {
+        // small systems: the roots, then 2 n node places per system of which the first per_system[b] are used
+        const int64_t B = ntot / n;
+        for (int64_t i = t; i < 8 * (B + 2 * ntot); i += stride) {
+            const int64_t k = i / 8 - B, b = k / (2 * n);
+            if (k >= 0 && k - 2 * n * b >= (int64_t)per_system[b]) continue;
+            node_adj[i] = 0.0;
+            if (node_adjq) node_adjq[i] = 0.0;
+        }
+        return;
+    }
     const int64_t len = 8 * ((int64_t)*nn < max_nodes ? (int64_t)*nn : max_nodes);
     for (int64_t i = t; i < len; i += stride) node_adj[i] = 0.0;
     if (node_adjq)
@@ -818,7 +829,8 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
     }
     const bool quad = L.expansion == 2;
     hipLaunchKernelGGL(k_adj_setup, dim3(grid_for(L.ntot, 256, 4096)), dim3(256), 0, s, d_gH, d_gE, w.smom, w.perm, L.n,
-                       L.ntot, w.hbar, w.g_rm, w.node_adj, quad ? w.node_adjq : nullptr, w.status + 2, L.max_nodes);
+                       L.ntot, w.hbar, w.g_rm, w.node_adj, quad ? w.node_adjq : nullptr, w.status + 2, L.max_nodes,
+                       L.n <= kSmallMax ? w.top_nodes : nullptr);
     const int wpb = h.waves_per_block;
     const double theta2 = h.p.theta * h.p.theta;
     if (h.ev[2]) (void)hipEventRecord(h.ev[2], s);

@@ -177,22 +177,38 @@ __global__ void k_init(uint32_t *status, double *ones, int64_t B)
     for (int64_t b = threadIdx.x; b < B; b += blockDim.x) ones[b] = 1.0;
 }
 
+// off: where the nodes of small systems (built in one workgroup each, with 2 n node places a system) go, so that
+// the exported ids have no gaps; null for dense ids.  count_of: their number per system, with off.
 __global__ __launch_bounds__(256) void k_export(const NodeRec *__restrict__ nodes,
-                                                const int32_t *__restrict__ level, const uint32_t *__restrict__ nn,
-                                                int32_t *first, int32_t *count, int32_t *lev, int32_t *nchild,
-                                                int32_t *child, double *centroid)
+                                                const int32_t *__restrict__ level, int64_t n, int64_t B,
+                                                const int32_t *__restrict__ count_of, const uint32_t *__restrict__ off,
+                                                const uint32_t *__restrict__ nn, int64_t max_nodes, int32_t *first,
+                                                int32_t *count, int32_t *lev, int32_t *nchild, int32_t *child,
+                                                double *centroid)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int)*nn) return;
-    if (first) first[i] = nodes[i].first;
-    if (count) count[i] = nodes[i].count;
-    if (lev) lev[i] = level[i];
-    if (nchild) nchild[i] = nodes[i].nchild;
-    if (child) child[i] = nodes[i].child;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= max_nodes || (!off && i >= (int64_t)*nn)) return;
+    int64_t o = i, shift = 0;  // exported id, and that of the children less their own
+    if (off) {
+        if (i >= B) {
+            const int64_t b = (i - B) / (2 * n), k = i - B - 2 * n * b;
+            if (k >= (int64_t)count_of[b]) return;
+            shift = (int64_t)off[b] - 2 * n * b;
+        } else {
+            shift = (int64_t)off[i] - 2 * n * i;
+        }
+        o = i < B ? i : i + shift;
+    }
+    const NodeRec nd = nodes[i];
+    if (first) first[o] = nd.first;
+    if (count) count[o] = nd.count;
+    if (lev) lev[o] = level[i];
+    if (nchild) nchild[o] = nd.nchild;
+    if (child) child[o] = nd.child < 0 ? -1 : (int32_t)(nd.child + shift);
     if (centroid) {
-        centroid[3 * i] = nodes[i].cx;
-        centroid[3 * i + 1] = nodes[i].cy;
-        centroid[3 * i + 2] = nodes[i].cz;
+        centroid[3 * o] = nd.cx;
+        centroid[3 * o + 1] = nd.cy;
+        centroid[3 * o + 2] = nd.cz;
     }
 }
 
@@ -600,6 +616,7 @@ bh_status bh_num_nodes(bh_handle *hh, void *stream, int64_t *out_nodes)
     if (!hh->h.built) return BH_ESTATE;
     uint32_t v = 0;
     hipStream_t s = (hipStream_t)stream;
+    if (hh->h.L.n <= kSmallMax) launch_small_counts(hh->h, hh->h.w.cell_scan, s);
     if (hipMemcpyAsync(&v, hh->h.w.status + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess)
         return BH_EDEVICE;
     if (hipStreamSynchronize(s) != hipSuccess) return BH_EDEVICE;
@@ -617,8 +634,11 @@ bh_status bh_export_tree(bh_handle *hh, int32_t *d_perm, int32_t *d_first, int32
     hipStream_t s = (hipStream_t)stream;
     if (d_perm)
         hipLaunchKernelGGL(k_copy_u32, dim3(grid_for(h.L.ntot, 256)), dim3(256), 0, s, h.w.perm, h.L.ntot, d_perm);
-    hipLaunchKernelGGL(k_export, dim3(grid_for(h.L.max_nodes, 256)), dim3(256), 0, s, h.w.nodes, h.w.node_level,
-                       h.w.status + 2, d_first, d_count, d_level, d_nchild, d_child_first, d_centroid);
+    const bool small = h.L.n <= kSmallMax;
+    if (small) launch_small_counts(h, h.w.cell_scan, s);
+    hipLaunchKernelGGL(k_export, dim3(grid_for(h.L.max_nodes, 256)), dim3(256), 0, s, h.w.nodes, h.w.node_level, h.L.n,
+                       h.L.B, h.w.top_nodes, small ? h.w.cell_scan : nullptr, h.w.status + 2, h.L.max_nodes, d_first,
+                       d_count, d_level, d_nchild, d_child_first, d_centroid);
     if (d_bbox)
         hipLaunchKernelGGL(k_copy_bbox, dim3(grid_for(h.L.B, 64)), dim3(64), 0, s, h.w.bbox, h.L.B, d_bbox);
     return hipGetLastError() == hipSuccess ? BH_OK : BH_EDEVICE;

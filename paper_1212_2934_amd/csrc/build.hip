@@ -537,106 +537,6 @@ __global__ __launch_bounds__(256) void k_fix_ties(uint64_t *__restrict__ keys, u
         }
 }
 
-// Whole sort of one small system in one workgroup (systems of at most kSortSmallMax keys): the keys stay
-// in LDS for all eight passes (the full codes, no tie fix needed), so a small system's sort is one launch
-// instead of the tiled path's nine (four passes of two launches, then the runs of equal upper bits).
-// Each pass is the tile pass of k_radix_scatter over the whole system: every wave ranks a contiguous
-// chunk of keys (ballot match masks, running per-wave digit counts), the digit starts and per-wave
-// offsets place every key, and the keys move to the other LDS buffer.  Stable, so the result is the
-// multi-workgroup sort's.
-constexpr int kSortSmallThreads = 512;
-constexpr int kSortSmallMax = 2048;
-
-__global__ __launch_bounds__(kSortSmallThreads) void k_sort_small(uint64_t *__restrict__ keys,
-                                                                  uint32_t *__restrict__ vals, int n)
-{
-    constexpr int kWaves = kSortSmallThreads / kWave;
-    constexpr int kItems = kSortSmallMax / kSortSmallThreads;  // rounds of 64 keys per wave
-    __shared__ uint64_t sk[2][kSortSmallMax];
-    __shared__ uint32_t sv[2][kSortSmallMax];
-    __shared__ uint32_t wcnt[kWaves][kRadixBins];
-    __shared__ uint32_t lstart[kRadixBins];
-    __shared__ uint32_t dsum[kRadixBins / kWave];
-    const int64_t base = (int64_t)blockIdx.x * n;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-    const uint32_t dmask = kRadixBins - 1;
-    const int cn = n < kSortSmallMax ? n : kSortSmallMax;
-    for (int i = tid; i < cn; i += kSortSmallThreads) {
-        sk[0][i] = keys[base + i];
-        sv[0][i] = vals[base + i];
-    }
-    // wave w ranks keys [w * chunk, (w + 1) * chunk) in rounds of 64
-    const int chunk = ((cn + kWaves * kWave - 1) / (kWaves * kWave)) * kWave;
-    const int c0 = wave * chunk;
-    for (int pass = 0; pass < kRadixPasses; ++pass) {
-        const int src = pass & 1, dst = src ^ 1, shift = pass * kRadixBits;
-        for (int w = 0; w < kWaves; ++w)
-            for (int d = tid; d < kRadixBins; d += kSortSmallThreads) wcnt[w][d] = 0u;
-        __syncthreads();  // loads (or the previous pass's moves) and the cleared counts are visible
-        uint32_t rank[kItems];
-        uint32_t dig[kItems];
-#pragma unroll
-        for (int r = 0; r < kItems; ++r) {
-            const int p = c0 + r * kWave + lane;
-            const bool valid = r * kWave < chunk && p < cn;
-            const uint32_t d = valid ? (uint32_t)(sk[src][p] >> shift) & dmask : 0u;
-            uint64_t m = __ballot(valid);
-#pragma unroll
-            for (int bit = 0; bit < kRadixBits; ++bit) {
-                const bool set = (d >> bit) & 1u;
-                const uint64_t v = __ballot(set);
-                m &= set ? v : ~v;
-            }
-            const uint32_t before = (uint32_t)__popcll(m & lt);
-            // one wave's LDS accesses complete in order: this read sees the previous round's update
-            const uint32_t cur = valid ? wcnt[wave][d] : 0u;
-            rank[r] = cur + before;
-            dig[r] = d;
-            if (valid && before == 0) wcnt[wave][d] = cur + (uint32_t)__popcll(m);
-        }
-        __syncthreads();
-        // threads below kRadixBins own one digit: per-wave offsets and the digit's start
-        uint32_t tot = 0;
-        if (tid < kRadixBins) {
-            for (int w = 0; w < kWaves; ++w) {
-                const uint32_t c = wcnt[w][tid];
-                wcnt[w][tid] = tot;
-                tot += c;
-            }
-        }
-        uint32_t incl = 0;
-        if (tid < kRadixBins) {
-            incl = wave_incl_scan_u32(tot, lane);
-            if (lane == kWave - 1) dsum[wave] = incl;
-        }
-        __syncthreads();
-        if (tid < kRadixBins) {
-            uint32_t woff = 0;
-            for (int w = 0; w < wave; ++w) woff += dsum[w];
-            lstart[tid] = woff + incl - tot;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kItems; ++r) {
-            const int p = c0 + r * kWave + lane;
-            if (r * kWave < chunk && p < cn) {
-                const uint32_t at = lstart[dig[r]] + wcnt[wave][dig[r]] + rank[r];
-                if (at < (uint32_t)kSortSmallMax) {  // always true for consistent counts
-                    sk[dst][at] = sk[src][p];
-                    sv[dst][at] = sv[src][p];
-                }
-            }
-        }
-        __syncthreads();  // every move (and every read of wcnt, lstart) done before the next pass
-    }
-    // kRadixPasses is even: the sorted keys are in buffer 0
-    for (int i = tid; i < cn; i += kSortSmallThreads) {
-        keys[base + i] = sk[0][i];
-        vals[base + i] = sv[0][i];
-    }
-}
-
 // Sorted positions (SoA, global over systems).
 __global__ __launch_bounds__(256) void k_gather3(const double *__restrict__ src, const uint32_t *__restrict__ perm,
                                                  int64_t n, int64_t ntot, double *__restrict__ dst,
@@ -1032,23 +932,13 @@ __device__ inline void up_levels(int lo, int hi, int count, const uint8_t *lev, 
     }
 }
 
-// append: list the cells left to k_upward_top (the build's pass).
+// One workgroup's part of the upward pass: positions [c0, c1) of system b, whose cells' children have ids
+// [i0, i1), and with `root` the system's root.  lev: kUpCache bytes of LDS.  top (may be null): list the cells
+// left to k_upward_top there (the build's pass).
 template <int MODE>
-__global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const uint32_t *__restrict__ scan,
-                                                           uint32_t *__restrict__ status, int64_t B, int64_t chunk,
-                                                           int chunks, int32_t *__restrict__ top, int append,
-                                                           int leave)
+__device__ inline void up_chunk(int64_t b, int64_t c0, int64_t c1, int64_t i0, int64_t i1, int root, uint8_t *lev,
+                                int *lrange, int64_t B, int32_t *top, FFBH_UP_PARAMS)
 {
-    __shared__ uint8_t lev[kUpCache];
-    __shared__ int lmin, lmax;
-    const int64_t b = blockIdx.x / chunks;
-    const int c = (int)(blockIdx.x - b * chunks);
-    const int64_t c0 = c * chunk, c1 = min(c0 + chunk, n);
-    // ids of the children of the cells whose keys are positions c0 .. c1 - 1 of the system
-    auto start = [&](int64_t i) { return B + (int64_t)(b * n + i < ntot ? scan[b * n + i] : status[1]); };
-    const int64_t i0 = start(c0), i1 = min(start(c1), max_nodes);
-    // the root is the first chunk's, before its children
-    const int root = c == 0 ? 1 : 0;
     const int count = (int)(i1 > i0 ? i1 - i0 : 0) + root;
     auto id_of = [&](int k) { return root && k == 0 ? (int)b : (int)(i0 + k - root); };
     auto level_at = [&](int id, const NodeRec &nd) -> uint8_t {
@@ -1058,8 +948,8 @@ __global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const
         return (uint8_t)l;
     };
     if (threadIdx.x == 0) {
-        lmin = kMaxLevel + 1;
-        lmax = -1;
+        lrange[0] = kMaxLevel + 1;
+        lrange[1] = -1;
     }
     __syncthreads();
     for (int k = threadIdx.x; k < count; k += blockDim.x) {
@@ -1070,16 +960,33 @@ __global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const
         if (nd.nchild == 0) {
             upward_node<MODE>(id, nd, FFBH_UP_ARGS);
         } else if (l != kUpSkip) {
-            atomicMin(&lmin, (int)l);
-            atomicMax(&lmax, (int)l);
-        } else if (append) {
+            atomicMin(&lrange[0], (int)l);
+            atomicMax(&lrange[1], (int)l);
+        } else if (top) {
             const uint32_t at = atomicAdd((uint32_t *)&top[b], 1u);
             if ((int64_t)at < 2 * n) top[up_list(B, n, b) + at] = id;
         }
     }
     __syncthreads();
-    up_levels<MODE>(lmin, lmax, count, lev, id_of, [&](int k) { const int id = id_of(k); return level_at(id, nodes[id]); },
-                    FFBH_UP_ARGS);
+    up_levels<MODE>(lrange[0], lrange[1], count, lev, id_of,
+                    [&](int k) { const int id = id_of(k); return level_at(id, nodes[id]); }, FFBH_UP_ARGS);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const uint32_t *__restrict__ scan,
+                                                           uint32_t *__restrict__ status, int64_t B, int64_t chunk,
+                                                           int chunks, int32_t *__restrict__ top, int append,
+                                                           int leave)
+{
+    __shared__ uint8_t lev[kUpCache];
+    __shared__ int lrange[2];
+    const int64_t b = blockIdx.x / chunks;
+    const int c = (int)(blockIdx.x - b * chunks);
+    const int64_t c0 = c * chunk, c1 = min(c0 + chunk, n);
+    // ids of the children of the cells whose keys are positions c0 .. c1 - 1 of the system
+    auto start = [&](int64_t i) { return B + (int64_t)(b * n + i < ntot ? scan[b * n + i] : status[1]); };
+    up_chunk<MODE>(b, c0, c1, start(c0), min(start(c1), max_nodes), c == 0 ? 1 : 0, lev, lrange, B,
+                   append ? top : nullptr, FFBH_UP_ARGS);
     if (leave && threadIdx.x == 0) call_leave(status);
 }
 
@@ -1127,9 +1034,8 @@ static bool upward(Handle &h, const double *vals, const double *vals2, hipStream
     Workspace &w = h.w;
     const int64_t chunk = up_chunk(L);
     const int chunks = (int)((L.n + chunk - 1) / chunk);
-    const int threads = L.n <= 512 ? 256 : kUpThreads;
     leave = leave && L.B == 1;
-    hipLaunchKernelGGL(k_upward_sub<MODE>, dim3((unsigned)(L.B * chunks)), dim3(threads), 0, s, vals, vals2, L.ntot,
+    hipLaunchKernelGGL(k_upward_sub<MODE>, dim3((unsigned)(L.B * chunks)), dim3(kUpThreads), 0, s, vals, vals2, L.ntot,
                        L.n, w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
                        w.cell_scan, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0,
                        leave && chunks == 1 ? 1 : 0);
@@ -1138,6 +1044,425 @@ static bool upward(Handle &h, const double *vals, const double *vals2, hipStream
                            w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
                            w.status, L.B, w.top_nodes, leave ? 1 : 0);
     return leave;
+}
+
+// Hilbert index of the cell (x, y, z) of a 2^b grid per axis: Skilling's transform of the axes to the
+// transposed index (J. Skilling, "Programming the Hilbert curve", AIP Conf. Proc. 707, 381 (2004)),
+// whose bits, interleaved from the most significant down with x first, are the index.
+template <int b>
+__device__ inline uint32_t hilbert_index(uint32_t x, uint32_t y, uint32_t z)
+{
+    uint32_t X[3] = {x, y, z};
+    // undo the excess work of the curve's reflections and rotations, from the coarsest bit down
+#pragma unroll
+    for (uint32_t Q = 1u << (b - 1); Q > 1u; Q >>= 1) {
+        const uint32_t P = Q - 1u;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const bool invert = (X[i] & Q) != 0u;
+            const uint32_t t = invert ? 0u : ((X[0] ^ X[i]) & P);  // exchange the low bits of X[0], X[i]
+            X[0] ^= invert ? P : t;
+            X[i] ^= t;
+        }
+    }
+    // Gray encode
+    X[1] ^= X[0];
+    X[2] ^= X[1];
+    uint32_t t = 0u;
+#pragma unroll
+    for (uint32_t Q = 1u << (b - 1); Q > 1u; Q >>= 1)
+        if (X[2] & Q) t ^= Q - 1u;
+    X[0] ^= t; X[1] ^= t; X[2] ^= t;
+    return (uint32_t)morton(X[0], X[1], X[2]);
+}
+
+// The Hilbert index of a code's cell at kHilbertBits bits per axis, read off the top bits of the code.
+__device__ inline uint32_t hilbert_key(uint64_t code)
+{
+    const uint64_t c = code >> (3 * (kBits - kHilbertBits));
+    return hilbert_index<kHilbertBits>(compact3(c >> 2), compact3(c >> 1), compact3(c));
+}
+
+// The packed source record of a sorted particle: FP64 position and the moment in the handle's precision.
+__device__ inline void pack_source(double *r, bool mixed, double x, double y, double z, double mx, double my, double mz)
+{
+    r[0] = x; r[1] = y; r[2] = z;
+    if (mixed) {
+        float *f = (float *)(r + 3);
+        f[0] = (float)mx; f[1] = (float)my; f[2] = (float)mz; f[3] = 0.0f;
+    } else {
+        r[3] = mx; r[4] = my; r[5] = mz;
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Systems of at most kSmallMax particles: the whole build of a system in one workgroup (k_build_small), with its
+// keys, codes and cell masks in LDS, and the moments' upward pass of a later call in another
+// (k_moments_small).  A launch costs about 4.5 us in a stream and a small system's kernels little more than
+// that: 300 particles took twelve launches and 58 us for bh_build, this takes one.
+// The children's ids of system b start at B + 2 n b (a system has fewer than 2 n nodes), so the ids of a batch
+// have gaps; entry b of the list array counts the system's nodes below its root.
+// ------------------------------------------------------------------------------------------------
+
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallItems = kSmallMax / kSmallThreads;  // particles per thread
+
+// LDS of k_build_small, 57 KB: the sort's keys and values (ping-pong), then the codes in the keys' place, the cell
+// masks in the values' and the scan in the counts'.
+struct SmallLds {
+    union {
+        uint32_t key[2][kSmallMax];  // 31 or 32 bits of the codes
+        uint64_t code[kSmallMax];
+        uint8_t lev[kUpCache];       // the upward pass's levels
+    };
+    union {
+        uint16_t val[2][kSmallMax];  // index in the system
+        uint32_t mask[kSmallMax];
+    };
+    union {
+        uint16_t wcnt[kSmallThreads / kWave][kRadixBins];
+        uint16_t scan[kSmallMax];
+        int8_t win[kSmallMax];
+    };
+    uint32_t lstart[kRadixBins];
+    uint32_t dsum[kSmallThreads / kWave];
+    double box[kSmallThreads / kWave][6];
+    int lrange[2];
+    int flag;
+};
+static_assert(sizeof(SmallLds) <= 65536, "LDS of k_build_small");
+static_assert(kSmallThreads / kWave * kRadixBins >= kSmallMax, "the scan fits the counts");
+
+// One stable pass over 8 bits of the keys from buffer src to the other one: every wave ranks a contiguous run of
+// keys (match masks from ballots, running per-wave digit counts), the counts give every key its place.
+__device__ inline void small_pass(SmallLds &S, int n, int src, int shift)
+{
+    constexpr int kWaves = kSmallThreads / kWave;
+    const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1);
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    const int chunk = ((n + kWaves * kWave - 1) / (kWaves * kWave)) * kWave, c0 = wave * chunk;
+    for (int k = t; k < kWaves * kRadixBins / 2; k += kSmallThreads) ((uint32_t *)S.wcnt)[k] = 0u;
+    __syncthreads();
+    uint32_t rank[kSmallItems], dig[kSmallItems];
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+        if (r * kWave >= chunk) break;
+        const int p = c0 + r * kWave + lane;
+        const bool valid = p < n;
+        const uint32_t d = valid ? (S.key[src][p] >> shift) & (kRadixBins - 1) : 0u;
+        uint64_t m = __ballot(valid);
+#pragma unroll
+        for (int bit = 0; bit < kRadixBits; ++bit) {
+            const bool set = (d >> bit) & 1u;
+            const uint64_t v = __ballot(set);
+            m &= set ? v : ~v;
+        }
+        const uint32_t before = (uint32_t)__popcll(m & lt);
+        // one wave's LDS accesses complete in order: this read sees the previous round's update
+        const uint32_t cur = valid ? S.wcnt[wave][d] : 0u;
+        rank[r] = cur + before;
+        dig[r] = d;
+        if (valid && before == 0) S.wcnt[wave][d] = (uint16_t)(cur + (uint32_t)__popcll(m));
+    }
+    __syncthreads();
+    uint32_t tot = 0, incl = 0;
+    if (t < kRadixBins) {
+        for (int w = 0; w < kWaves; ++w) {
+            const uint32_t c = S.wcnt[w][t];
+            S.wcnt[w][t] = (uint16_t)tot;
+            tot += c;
+        }
+        incl = wave_incl_scan_u32(tot, lane);
+        if (lane == kWave - 1) S.dsum[wave] = incl;
+    }
+    __syncthreads();
+    if (t < kRadixBins) {
+        uint32_t woff = 0;
+        for (int w = 0; w < wave; ++w) woff += S.dsum[w];
+        S.lstart[t] = woff + incl - tot;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+        if (r * kWave >= chunk) break;
+        const int p = c0 + r * kWave + lane;
+        if (p >= n) continue;
+        const uint32_t at = S.lstart[dig[r]] + S.wcnt[wave][dig[r]] + rank[r];
+        if (at < (uint32_t)kSmallMax) {  // always true for consistent counts
+            S.key[src ^ 1][at] = S.key[src][p];
+            S.val[src ^ 1][at] = S.val[src][p];
+        }
+    }
+    __syncthreads();
+}
+
+struct SmallArgs {
+    const double *pos, *mom;
+    int n, leaf, enter, hilbert, mixed;
+    int64_t ntot, B, max_nodes;
+    double s2_scale;
+    double *bbox, *spos, *smom, *src, *sums, *node_m64;
+    uint64_t *codes;
+    uint32_t *perm, *tgt_order, *status;
+    NodeRec *nodes;
+    int32_t *node_level, *leaf_of, *top;
+};
+
+template <bool MOM>
+__global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
+{
+    __shared__ SmallLds S;
+    const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1), n = a.n;
+    constexpr int kWaves = kSmallThreads / kWave;
+    const int64_t b = blockIdx.x, first = b * n;
+    const double *p = a.pos + 3 * first;
+    if (a.enter && b == 0 && t == 0) call_enter(a.status);
+
+    // bounding cube (as k_bbox_partial and k_bbox_final)
+    double lo[3], hi[3];
+    bool bad = false;
+    for (int c = 0; c < 3; ++c) { lo[c] = __builtin_inf(); hi[c] = -__builtin_inf(); }
+    for (int i = t; i < n; i += kSmallThreads)
+        for (int c = 0; c < 3; ++c) {
+            const double v = p[c * n + i];
+            bad |= !__builtin_isfinite(v);
+            if (v < lo[c]) lo[c] = v;
+            if (v > hi[c]) hi[c] = v;
+        }
+    if (bad) set_flag(a.status, BH_FLAG_NONFINITE);
+    for (int c = 0; c < 3; ++c)
+        for (int off = 1; off < kWave; off <<= 1) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off, kWave));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off, kWave));
+        }
+    if (lane == 0)
+        for (int c = 0; c < 3; ++c) {
+            S.box[wave][c] = lo[c];
+            S.box[wave][3 + c] = hi[c];
+        }
+    if (t == 0) S.flag = 0;
+    __syncthreads();
+    double side = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        for (int w = 0; w < kWaves; ++w) {
+            lo[c] = fmin(lo[c], S.box[w][c]);
+            hi[c] = fmax(hi[c], S.box[w][3 + c]);
+        }
+        if (hi[c] - lo[c] > side) side = hi[c] - lo[c];
+    }
+    const double scale = side > 0.0 ? 2097152.0 / side : 0.0;
+    if (t == 0) {
+        double *o = a.bbox + 8 * b;
+        o[0] = lo[0]; o[1] = lo[1]; o[2] = lo[2];
+        o[3] = side;
+        o[4] = scale;
+        o[5] = a.s2_scale;
+    }
+    auto code_of = [&](int i) {
+        return morton(quantise(p[i], lo[0], scale), quantise(p[n + i], lo[1], scale), quantise(p[2 * n + i], lo[2], scale));
+    };
+
+    // sort: the codes' upper 31 bits, then runs of equal upper bits by the low 32 (as k_fix_ties); where a run is
+    // longer than an insertion sort should take, all 63 bits from the start
+    for (int i = t; i < n; i += kSmallThreads) {
+        S.key[0][i] = (uint32_t)(code_of(i) >> kTieBits);
+        S.val[0][i] = (uint16_t)i;
+    }
+    for (int q = 0; q < 4; ++q) small_pass(S, n, q & 1, 8 * q);
+    for (int i = t; i + kTieInsertMax < n; i += kSmallThreads)
+        if (S.key[0][i] == S.key[0][i + kTieInsertMax]) S.flag = 1;
+    __syncthreads();
+    const bool long_run = S.flag != 0;
+    if (long_run) {
+        for (int i = t; i < n; i += kSmallThreads) {
+            S.key[0][i] = (uint32_t)code_of(i);
+            S.val[0][i] = (uint16_t)i;
+        }
+        for (int q = 0; q < 4; ++q) small_pass(S, n, q & 1, 8 * q);
+        for (int i = t; i < n; i += kSmallThreads) S.key[0][i] = (uint32_t)(code_of(S.val[0][i]) >> kTieBits);
+        for (int q = 0; q < 4; ++q) small_pass(S, n, q & 1, 8 * q);
+    }
+    // the full codes, in the keys' place
+    uint64_t c[kSmallItems];
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) c[r] = t + r * kSmallThreads < n ? code_of(S.val[0][t + r * kSmallThreads]) : 0ull;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r)
+        if (t + r * kSmallThreads < n) S.code[t + r * kSmallThreads] = c[r];
+    __syncthreads();
+    if (!long_run) {
+        for (int i = t; i < n; i += kSmallThreads) {
+            const uint64_t h = S.code[i] >> kTieBits;
+            if (i > 0 && (S.code[i - 1] >> kTieBits) == h) continue;  // not the start of a run
+            for (int e = i + 1; e < n && (S.code[e] >> kTieBits) == h; ++e) {
+                const uint64_t k = S.code[e];
+                const uint16_t v = S.val[0][e];
+                int j = e;
+                while (j > i && low_less(k, S.code[j - 1])) {
+                    S.code[j] = S.code[j - 1];
+                    S.val[0][j] = S.val[0][j - 1];
+                    --j;
+                }
+                S.code[j] = k;
+                S.val[0][j] = v;
+            }
+        }
+        __syncthreads();
+    }
+
+    // the particles in sorted order (as k_gather3 and k_gather_pack)
+    for (int i = t; i < n; i += kSmallThreads) {
+        const int o = S.val[0][i];
+        const int64_t g = first + i;
+        a.codes[g] = S.code[i];
+        a.perm[g] = (uint32_t)(first + o);
+        const double x = p[o], y = p[n + o], z = p[2 * n + o];
+        a.spos[g] = x; a.spos[a.ntot + g] = y; a.spos[2 * a.ntot + g] = z;
+        if (MOM) {
+            const double *m = a.mom + 3 * first;
+            const double mx = m[o], my = m[n + o], mz = m[2 * n + o];
+            if (!__builtin_isfinite(mx) || !__builtin_isfinite(my) || !__builtin_isfinite(mz))
+                set_flag(a.status, BH_FLAG_NONFINITE);
+            a.smom[g] = mx; a.smom[a.ntot + g] = my; a.smom[2 * a.ntot + g] = mz;
+            pack_source(a.src + 6 * g, a.mixed != 0, x, y, z, mx, my, mz);
+        }
+    }
+    // windows, cell keys and masks (as k_oct_mark)
+    for (int i = t; i < n; i += kSmallThreads)
+        S.win[i] = i + a.leaf < n ? (int8_t)digits(S.code[i], S.code[i + a.leaf]) : (int8_t)-1;
+    __syncthreads();
+    for (int i = t; i < n; i += kSmallThreads) S.mask[i] = 0u;
+    int key[kSmallItems];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+        const int j = t + r * kSmallThreads;
+        key[r] = -1;
+        if (j >= n || j == 0) continue;
+        int w = -1;
+        for (int k = max(j - a.leaf, 0); k <= j; ++k) w = max(w, (int)S.win[k]);
+        key[r] = oct_mark(S.code, n, j, w, [&](int k, uint32_t m) { atomicOr(&S.mask[k], m); });
+    }
+    __syncthreads();
+    // scan of the masks' bit counts, each thread its run of kSmallItems positions
+    uint32_t run = 0;
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+        const int i = t * kSmallItems + r;
+        run += i < n ? (uint32_t)__popc(S.mask[i]) : 0u;
+    }
+    const uint32_t incl = wave_incl_scan_u32(run, lane);
+    if (lane == kWave - 1) S.dsum[wave] = incl;
+    __syncthreads();
+    uint32_t off = incl - run, total = 0;
+    for (int w = 0; w < kWaves; ++w) {
+        off += w < wave ? S.dsum[w] : 0u;
+        total += S.dsum[w];
+    }
+#pragma unroll
+    for (int r = 0; r < kSmallItems; ++r) {
+        const int i = t * kSmallItems + r;
+        if (i >= n) break;
+        S.scan[i] = (uint16_t)off;
+        off += (uint32_t)__popc(S.mask[i]);
+    }
+    if (t == 0) {
+        a.top[b] = (int32_t)total;
+        if (a.B == 1) a.status[2] = 1u + total;
+    }
+    __syncthreads();
+    const int64_t base = a.B + 2 * first;
+    {
+        const OctOut o{a.nodes, a.node_level, a.leaf_of, a.status, base, first, a.max_nodes, a.leaf};
+        auto mask_of = [&](int k) { return S.mask[k]; };
+        auto scan_of = [&](int k) { return (int64_t)S.scan[k]; };
+        if (t == kSmallThreads - 1) oct_root(o, S.code, n, b, mask_of, scan_of);
+#pragma unroll
+        for (int r = 0; r < kSmallItems; ++r)
+            if (key[r] > 0) oct_children(o, S.code, n, t + r * kSmallThreads, key[r], mask_of, scan_of);
+    }
+    __syncthreads();
+    up_chunk<MOM ? 2 : 0>(b, 0, n, base, min(base + (int64_t)total, a.max_nodes), 1, S.lev, S.lrange, a.B, nullptr,
+                          a.spos, a.smom, a.ntot, n, a.nodes, a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes,
+                          nullptr, nullptr);
+    if (!a.hilbert) return;
+    // target order (as launch_target_order)
+    __syncthreads();
+    for (int i = t; i < n; i += kSmallThreads) {
+        S.key[0][i] = hilbert_key(a.codes[first + i]);
+        S.val[0][i] = (uint16_t)i;
+    }
+    for (int q = 0; q < 3; ++q) small_pass(S, n, q & 1, 8 * q);
+    for (int i = t; i < n; i += kSmallThreads) a.tgt_order[first + i] = (uint32_t)(first + S.val[1][i]);
+}
+
+// Moments of a small system: gathered into sorted order with the packed source records, then summed upward.
+template <int MODE>
+__global__ __launch_bounds__(kSmallThreads) void k_moments_small(SmallArgs a, double *q64, float *q32)
+{
+    __shared__ uint8_t lev[2 * kSmallMax + 1];
+    __shared__ int lrange[2];
+    static_assert(2 * kSmallMax + 1 <= kUpCache, "every node's level fits");
+    const int n = a.n;
+    const int64_t b = blockIdx.x, first = b * n;
+    if (a.enter && b == 0 && threadIdx.x == 0) call_enter(a.status);
+    const double *m = a.mom + 3 * first;
+    for (int i = threadIdx.x; i < n; i += kSmallThreads) {
+        const int64_t g = first + i, o = (int64_t)a.perm[g] - first;
+        if (o < 0 || o >= n) {
+            set_flag(a.status, BH_FLAG_TREE);
+            continue;
+        }
+        const double mx = m[o], my = m[n + o], mz = m[2 * n + o];
+        if (!__builtin_isfinite(mx) || !__builtin_isfinite(my) || !__builtin_isfinite(mz))
+            set_flag(a.status, BH_FLAG_NONFINITE);
+        a.smom[g] = mx; a.smom[a.ntot + g] = my; a.smom[2 * a.ntot + g] = mz;
+        pack_source(a.src + 6 * g, a.mixed != 0, a.spos[g], a.spos[a.ntot + g], a.spos[2 * a.ntot + g], mx, my, mz);
+    }
+    __syncthreads();
+    const int64_t base = a.B + 2 * first, total = min((int64_t)(uint32_t)a.top[b], (int64_t)2 * n);
+    up_chunk<MODE>(b, 0, n, base, min(base + total, a.max_nodes), 1, lev, lrange, a.B, nullptr, a.smom, a.spos, a.ntot,
+                   n, a.nodes, a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes, q64, q32);
+}
+
+// Number of nodes from the scan's total.
+__global__ void k_small_total(uint32_t *status, int64_t B)
+{
+    if (threadIdx.x == 0) status[2] = (uint32_t)B + status[1];
+}
+
+static SmallArgs small_args(Handle &h, const double *d_pos, const double *d_mom, bool enter)
+{
+    const Layout &L = h.L;
+    Workspace &w = h.w;
+    SmallArgs a{};
+    a.pos = d_pos;
+    a.mom = d_mom;
+    a.n = (int)L.n;
+    a.leaf = h.p.leaf_size;
+    a.enter = enter ? 1 : 0;
+    a.hilbert = uses_target_order(L) ? 1 : 0;
+    a.mixed = h.p.precision == BH_FP32_MIXED ? 1 : 0;
+    a.ntot = L.ntot;
+    a.B = L.B;
+    a.max_nodes = L.max_nodes;
+    a.s2_scale = node_s2_scale(h.p.theta * h.p.theta);
+    a.bbox = w.bbox;
+    a.spos = w.spos;
+    a.smom = w.smom;
+    a.src = (double *)w.src64;
+    a.sums = w.node_adj;
+    a.node_m64 = w.node_m64;
+    a.codes = w.codes;
+    a.perm = w.perm;
+    a.tgt_order = w.tgt_order;
+    a.status = w.status;
+    a.nodes = w.nodes;
+    a.node_level = w.node_level;
+    a.leaf_of = w.leaf_of;
+    a.top = w.top_nodes;
+    return a;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1158,6 +1483,21 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     const Layout &L = h.L;
     Workspace &w = h.w;
     const int64_t n = L.n, B = L.B, ntot = L.ntot;
+    if (L.n <= kSmallMax) {
+        const SmallArgs a = small_args(h, d_pos, d_mom, enter);
+        if (d_mom) hipLaunchKernelGGL(k_build_small<true>, dim3((unsigned)B), dim3(kSmallThreads), 0, s, a);
+        else hipLaunchKernelGGL(k_build_small<false>, dim3((unsigned)B), dim3(kSmallThreads), 0, s, a);
+        if (side) {
+            FFBH_TRY(hipEventRecord(h.sorted_ev, s));
+            FFBH_TRY(hipStreamWaitEvent(side, h.sorted_ev, 0));
+        }
+        if (after_sort) FFBH_TRY(after_sort(side ? side : s));
+        if (side && join) {
+            FFBH_TRY(hipEventRecord(h.join_ev, side));
+            FFBH_TRY(hipStreamWaitEvent(s, h.join_ev, 0));
+        }
+        return hipGetLastError();
+    }
     // partial boxes: at most kBboxBlocks per system, no more than one workgroup per 256 particles
     const int nb = (int)((n + 255) / 256 < kBboxBlocks ? (n + 255) / 256 : kBboxBlocks);
     hipLaunchKernelGGL(k_bbox_partial, dim3((unsigned)nb, (unsigned)B), dim3(256), 0, s, d_pos, n,
@@ -1168,11 +1508,6 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
                        w.keys[0], w.vals[0], w.cell_mask);
     const int tiles = (int)L.tiles;
     const unsigned sblocks = (unsigned)(B * tiles);
-    if (n <= kSortSmallMax) {
-        // small systems: the whole sort in LDS, one workgroup per system
-        hipLaunchKernelGGL(k_sort_small, dim3((unsigned)B), dim3(kSortSmallThreads), 0, s, w.keys[0], w.vals[0],
-                           (int)n);
-    } else {
     // the digits above the low kTieBits bits; k_fix_ties then orders the rare runs of equal upper bits
     for (int pass = kTieBits / kRadixBits; pass < kRadixPasses; ++pass) {
         const int src = pass & 1, dst = src ^ 1;
@@ -1188,7 +1523,6 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     }
     hipLaunchKernelGGL(k_fix_ties, dim3(grid_for(ntot, 256)), dim3(256), 0, s, w.keys[0], w.vals[0], w.keys[1],
                        w.vals[1], n, ntot);
-    }
     static_assert((kRadixPasses - kTieBits / kRadixBits) % 2 == 0 && kTieBits % kRadixBits == 0,
                   "an even number of tiled passes leaves the sorted data in buffer 0");
     // the sorted data is back in buffer 0
@@ -1240,36 +1574,6 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
 // FP32-mixed partial sums and of the adjoint's reductions.
 // ------------------------------------------------------------------------------------------------
 
-// Hilbert index of the cell (x, y, z) of a 2^b grid per axis: Skilling's transform of the axes to the
-// transposed index (J. Skilling, "Programming the Hilbert curve", AIP Conf. Proc. 707, 381 (2004)),
-// whose bits, interleaved from the most significant down with x first, are the index.
-template <int b>
-__device__ inline uint32_t hilbert_index(uint32_t x, uint32_t y, uint32_t z)
-{
-    uint32_t X[3] = {x, y, z};
-    // undo the excess work of the curve's reflections and rotations, from the coarsest bit down
-#pragma unroll
-    for (uint32_t Q = 1u << (b - 1); Q > 1u; Q >>= 1) {
-        const uint32_t P = Q - 1u;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const bool invert = (X[i] & Q) != 0u;
-            const uint32_t t = invert ? 0u : ((X[0] ^ X[i]) & P);  // exchange the low bits of X[0], X[i]
-            X[0] ^= invert ? P : t;
-            X[i] ^= t;
-        }
-    }
-    // Gray encode
-    X[1] ^= X[0];
-    X[2] ^= X[1];
-    uint32_t t = 0u;
-#pragma unroll
-    for (uint32_t Q = 1u << (b - 1); Q > 1u; Q >>= 1)
-        if (X[2] & Q) t ^= Q - 1u;
-    X[0] ^= t; X[1] ^= t; X[2] ^= t;
-    return (uint32_t)morton(X[0], X[1], X[2]);
-}
-
 // Key of sorted particle o: the Hilbert index of its cell at kHilbertBits bits per axis, read off the top
 // bits of its Morton code (the same cube); the value is o itself.
 __global__ __launch_bounds__(256) void k_hilbert_keys(const uint64_t *__restrict__ codes, int64_t ntot,
@@ -1277,8 +1581,7 @@ __global__ __launch_bounds__(256) void k_hilbert_keys(const uint64_t *__restrict
 {
     const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (o >= ntot) return;
-    const uint64_t c = codes[o] >> (3 * (kBits - kHilbertBits));
-    keys[o] = hilbert_index<kHilbertBits>(compact3(c >> 2), compact3(c >> 1), compact3(c));
+    keys[o] = hilbert_key(codes[o]);
     vals[o] = (uint32_t)o;
 }
 
@@ -1291,7 +1594,6 @@ void launch_target_order(Handle &h, hipStream_t s)
     // three stable 8-bit passes over the 24-bit keys, per system: (keys[1], vals[1]) -> (hkeys, tgt_order)
     // -> (keys[1], vals[1]) -> (hkeys, tgt_order); within a cell the sorted order is kept
     static_assert(kHilbertBits <= kRadixBits, "three radix passes cover the Hilbert keys");
-    static_assert(kTargetOrderMin > kSortSmallMax, "systems with a target order take the tiled sort");
     uint64_t *kb[2] = {w.keys[1], w.hkeys};
     uint32_t *vb[2] = {w.vals[1], w.tgt_order};
     const int tiles = (int)L.tiles;
@@ -1317,9 +1619,8 @@ namespace ffbh {
 // position).
 __global__ __launch_bounds__(256) void k_gather_pack(const double *__restrict__ mom, const uint32_t *__restrict__ perm,
                                                      const double *__restrict__ spos, int64_t n, int64_t ntot,
-                                                     double *__restrict__ smom, double *__restrict__ src64,
-                                                     double *__restrict__ src32, uint32_t *__restrict__ status,
-                                                     int enter)
+                                                     double *__restrict__ smom, double *__restrict__ src, int mixed,
+                                                     uint32_t *__restrict__ status, int enter)
 {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (enter && k == 0) call_enter(status);
@@ -1337,17 +1638,7 @@ __global__ __launch_bounds__(256) void k_gather_pack(const double *__restrict__ 
     smom[k] = mx;
     smom[ntot + k] = my;
     smom[2 * ntot + k] = mz;
-    const double x = spos[k], y = spos[ntot + k], z = spos[2 * ntot + k];
-    if (src64) {
-        double *a = src64 + 6 * k;
-        a[0] = x; a[1] = y; a[2] = z; a[3] = mx; a[4] = my; a[5] = mz;
-    }
-    if (src32) {
-        double *r = src32 + 6 * k;
-        r[0] = x; r[1] = y; r[2] = z;
-        float *f = (float *)(r + 3);
-        f[0] = (float)mx; f[1] = (float)my; f[2] = (float)mz; f[3] = 0.0f;
-    }
+    pack_source(src + 6 * k, mixed != 0, spos[k], spos[ntot + k], spos[2 * ntot + k], mx, my, mz);
 }
 
 // Moments in sorted order and the packed source records of the handle's precision.  enter: the first kernel of
@@ -1356,28 +1647,50 @@ static void gather_moments(Handle &h, const double *d_mom, hipStream_t s, bool e
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
-    const bool mixed = h.p.precision == BH_FP32_MIXED;
     hipLaunchKernelGGL(k_gather_pack, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, d_mom, w.perm, w.spos, L.n,
-                       L.ntot, w.smom, mixed ? (double *)nullptr : (double *)w.src64,
-                       mixed ? (double *)w.src32 : (double *)nullptr, w.status, enter ? 1 : 0);
+                       L.ntot, w.smom, (double *)w.src64, h.p.precision == BH_FP32_MIXED ? 1 : 0, w.status,
+                       enter ? 1 : 0);
 }
 
-// First moments of every node from the sorted moments and positions already in the workspace (after a
-// build with moments): the order-2 cells of an MD step.
-hipError_t launch_upward_first_moments(Handle &h, hipStream_t s)
+// First moments of every node from the moments and positions of a build with moments: the order-2 cells of an MD
+// step.
+hipError_t launch_upward_first_moments(Handle &h, const double *d_mom, hipStream_t s)
 {
-    upward<3>(h, h.w.smom, h.w.spos, s, false, false);
+    if (h.L.n <= kSmallMax)
+        hipLaunchKernelGGL(k_moments_small<3>, dim3((unsigned)h.L.B), dim3(kSmallThreads), 0, s,
+                           small_args(h, nullptr, d_mom, false), h.w.node_q64, h.w.node_q32);
+    else
+        upward<3>(h, h.w.smom, h.w.spos, s, false, false);
     return hipGetLastError();
 }
 
 hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter)
 {
+    if (h.L.n <= kSmallMax) {
+        const SmallArgs a = small_args(h, nullptr, d_mom, enter);
+        if (h.L.expansion == 2)
+            hipLaunchKernelGGL(k_moments_small<3>, dim3((unsigned)h.L.B), dim3(kSmallThreads), 0, s, a, h.w.node_q64,
+                               h.w.node_q32);
+        else
+            hipLaunchKernelGGL(k_moments_small<1>, dim3((unsigned)h.L.B), dim3(kSmallThreads), 0, s, a,
+                               (double *)nullptr, (float *)nullptr);
+        return hipGetLastError();
+    }
     gather_moments(h, d_mom, s, enter);
     if (h.L.expansion == 2)
         upward<3>(h, h.w.smom, h.w.spos, s, false, false);
     else
         upward<1>(h, h.w.smom, nullptr, s, false, false);
     return hipGetLastError();
+}
+
+// Node counts of small systems, whose ids have gaps: the number of nodes of the batch into *total, and with off
+// (B entries) the exclusive scan of the systems' counts.
+void launch_small_counts(Handle &h, uint32_t *off, hipStream_t s)
+{
+    Workspace &w = h.w;
+    scan_excl<false>((const uint32_t *)w.top_nodes, off, h.L.B, w.scan_tmp, w.status + 1, s);
+    hipLaunchKernelGGL(k_small_total, dim3(1), dim3(64), 0, s, w.status, h.L.B);
 }
 
 }  // namespace ffbh

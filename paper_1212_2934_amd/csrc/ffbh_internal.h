@@ -22,6 +22,7 @@ constexpr int kRadixPasses = 8;                 // 8 x 8 bits cover the 63-bit c
 constexpr int kTieBits = 32;                    // low code bits the tiled sort leaves to k_fix_ties
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 16;                  // most keys per thread per tile
+constexpr int kSmallMax = 4096;                  // systems up to this size are built in one workgroup each
 constexpr int kMinTpw = 16;                     // fewest targets an adjoint wave owns
 constexpr int kStackMax = 64;                   // one traversal stack entry per lane of a wave
 // Largest theta^2 for which the acceptance test alone rejects every cell holding the target: target and
@@ -101,7 +102,8 @@ struct Workspace {
     float *node_q32;         // max_nodes x 16: the same rounded to FP32 (mixed-precision traversal)
     double *node_adjq;       // max_nodes x 8: dL/dD of each node, symmetric (xx, yy, zz, xy, xz, yz)
     double *ones;            // B: constant 1.0 (dL/dE for the MD force)
-    int32_t *top_nodes;      // max_nodes: per system the count, then the list of the cells that k_upward_top sums
+    int32_t *top_nodes;      // max_nodes: per system the count, then the list of the cells that k_upward_top sums;
+                             // for systems built in one workgroup the number of their nodes below the root
     int32_t *leaf_of;        // N_tot: sorted particle -> its leaf
     // traversal outputs and adjoint accumulators
     double *e_part;          // per wave energy partials
@@ -232,7 +234,8 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
 // positions as values: consecutive targets of a traversal wave then lie close together.
 void launch_target_order(Handle &h, hipStream_t s);
 hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter);
-hipError_t launch_upward_first_moments(Handle &h, hipStream_t s);
+hipError_t launch_upward_first_moments(Handle &h, const double *d_mom, hipStream_t s);
+void launch_small_counts(Handle &h, uint32_t *off, hipStream_t s);
 // enter: the first kernel counts the call in (call_enter); leave: the last one counts it out.
 hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, double *d_H,
                         double *d_E, hipStream_t s, bool enter = false, bool leave = false);

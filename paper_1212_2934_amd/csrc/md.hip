@@ -329,7 +329,7 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
     e = launch_build(h, st->pos, s, st->mom, fork ? h.side : nullptr, false, true, short_range);
     if (e != hipSuccess) return e;
     if (L.expansion == 2) {
-        e = launch_upward_first_moments(h, s);  // order-2 cells
+        e = launch_upward_first_moments(h, st->mom, s);  // order-2 cells
         if (e != hipSuccess) return e;
     }
     if (fork && (e = hipStreamWaitEvent(s, h.join_ev, 0)) != hipSuccess) return e;

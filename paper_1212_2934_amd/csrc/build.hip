@@ -1132,6 +1132,7 @@ struct SmallLds {
 };
 static_assert(sizeof(SmallLds) <= 65536, "LDS of k_build_small");
 static_assert(kSmallThreads / kWave * kRadixBins >= kSmallMax, "the scan fits the counts");
+static_assert(kSmallThreads == 4 * kRadixBins && kSmallThreads / kWave == 16, "four threads per digit, sixteen waves");
 
 // One stable pass over 8 bits of the keys from buffer src to the other one: every wave ranks a contiguous run of
 // keys (match masks from ballots, running per-wave digit counts), the counts give every key its place.
@@ -1165,21 +1166,29 @@ __device__ inline void small_pass(SmallLds &S, int n, int src, int shift)
         if (valid && before == 0) S.wcnt[wave][d] = (uint16_t)(cur + (uint32_t)__popcll(m));
     }
     __syncthreads();
-    uint32_t tot = 0, incl = 0;
-    if (t < kRadixBins) {
-        for (int w = 0; w < kWaves; ++w) {
-            const uint32_t c = S.wcnt[w][t];
-            S.wcnt[w][t] = (uint16_t)tot;
-            tot += c;
+    // four threads per digit, each four waves' counts: the waves' offsets in the digit and the digits' starts
+    {
+        const int d = t >> 2, w0 = 4 * (t & 3);
+        uint32_t c[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            c[k] = S.wcnt[w0 + k][d];
+            sum += c[k];
         }
-        incl = wave_incl_scan_u32(tot, lane);
+        const uint32_t incl = wave_incl_scan_u32(sum, lane);
+        // sums of the digit's threads before this one: the inclusive scan less that of the digit before
+        const uint32_t digit0 = (uint32_t)__shfl((int)(incl - sum), lane & ~3, kWave);
+        uint32_t at = incl - sum - digit0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            S.wcnt[w0 + k][d] = (uint16_t)at;
+            at += c[k];
+        }
         if (lane == kWave - 1) S.dsum[wave] = incl;
-    }
-    __syncthreads();
-    if (t < kRadixBins) {
+        __syncthreads();
         uint32_t woff = 0;
-        for (int w = 0; w < wave; ++w) woff += S.dsum[w];
-        S.lstart[t] = woff + incl - tot;
+        for (int w = 0; w < kWaves; ++w) woff += w < wave ? S.dsum[w] : 0u;
+        if ((t & 3) == 0) S.lstart[d] = woff + digit0;
     }
     __syncthreads();
 #pragma unroll
@@ -1244,9 +1253,11 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
     __syncthreads();
     double side = 0.0;
     for (int c = 0; c < 3; ++c) {
-        for (int w = 0; w < kWaves; ++w) {
-            lo[c] = fmin(lo[c], S.box[w][c]);
-            hi[c] = fmax(hi[c], S.box[w][3 + c]);
+        lo[c] = S.box[lane & (kWaves - 1)][c];
+        hi[c] = S.box[lane & (kWaves - 1)][3 + c];
+        for (int off = 1; off < kWaves; off <<= 1) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off, kWave));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off, kWave));
         }
         if (hi[c] - lo[c] > side) side = hi[c] - lo[c];
     }

@@ -515,12 +515,12 @@ __global__ __launch_bounds__(kSplitMaxWaves *kWave) __attribute__((amdgpu_waves_
 // Order of the wave items of the next persistent launch, from the previous launch's costs, within each of
 // the kXcds segments of consecutive items: the items outside the lightest ~45 % (of the whole launch)
 // first, in index order (neighbouring items share tree data, so the launch keeps its cache locality), then
-// the light items, heaviest first (64 buckets of the cost range), so each segment ends on short items.  A
-// stable counting sort in one workgroup on the key (segment, class); then the segments' work counters are
-// reset.  Costs all zero (first launch) give the index order.
+// the light items, heaviest first (64 buckets of the cost range), so each segment ends on short items.  One
+// workgroup per segment: each finds the cost range and the light buckets from all items, then sorts its own
+// segment by a stable counting sort and resets its work counter.  Costs all zero (first launch) give the
+// index order.  (One workgroup for all segments, with serial scans over 512 keys, took 62 us at 16384 items.)
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderBins = 64;
-constexpr int kOrderKeys = kXcds * kOrderBins;
 // Share of the items moved to the end of their segment (measured at 2^20: 15 % and 30 % slower, 60 % and
 // 75 % slower again; 45 % the fastest in both precisions).
 constexpr uint32_t kLightPercent = 45u;
@@ -530,66 +530,64 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_waves(const uint32_t *_
                                                                uint32_t *__restrict__ work_ctr)
 {
     constexpr int kWaves = kOrderThreads / kWave;
+    static_assert(kOrderBins == kWave, "one lane per bucket");
     __shared__ uint32_t red[kWaves];
     __shared__ uint32_t fine[kOrderBins];  // items per cost bucket, lightest bucket first
-    __shared__ uint32_t hist[kOrderKeys];  // items per key, then the start of each key
-    __shared__ uint32_t wcnt[kWaves][kOrderKeys];
+    __shared__ uint32_t hist[kOrderBins];  // items of the segment per class, then the start of each class
+    __shared__ uint32_t wcnt[kWaves][kOrderBins];
     __shared__ int split;                  // buckets below it are the light items
-    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, seg = blockIdx.x;
     uint32_t mx = 0u;
     for (int i = t; i < nw; i += kOrderThreads) mx = max(mx, cost[i]);
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, kWave));
     if (lane == 0) red[wave] = mx;
-    if (t < kOrderBins) fine[t] = 0u;
+    if (t < kOrderBins) fine[t] = hist[t] = 0u;
     __syncthreads();
     uint32_t cmax = 0u;
     for (int w = 0; w < kWaves; ++w) cmax = max(cmax, red[w]);
     auto bucket = [cmax](uint32_t c) -> int { return (int)((uint64_t)c * kOrderBins / ((uint64_t)cmax + 1u)); };
     for (int i = t; i < nw; i += kOrderThreads) atomicAdd(&fine[bucket(cost[i])], 1u);
     __syncthreads();
-    if (t == 0) {
-        // the light items: the lowest buckets holding at most kLightPercent % of the items (bucket 63
-        // holds the heaviest item, so split <= 63 and the keys below fit in six bits)
-        uint32_t acc = 0u;
-        int sp = 0;
-        while (sp < kOrderBins && (uint64_t)(acc + fine[sp]) * 100u <= (uint64_t)nw * kLightPercent)
-            acc += fine[sp++];
-        split = sp;
+    auto wave_scan = [lane](uint32_t v) {  // inclusive
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t x = (uint32_t)__shfl_up((int)v, off, kWave);
+            if (lane >= off) v += x;
+        }
+        return v;
+    };
+    if (wave == 0) {
+        // the light items: the lowest buckets holding at most kLightPercent % of the items (bucket 63 holds the
+        // heaviest item and all items are more than that, so split <= 63)
+        const uint32_t acc = wave_scan(fine[lane]);
+        const uint64_t light = ballot((uint64_t)acc * 100u <= (uint64_t)nw * kLightPercent);
+        if (lane == 0) split = __builtin_popcountll(light);
     }
     __syncthreads();
     const int sp = split;
-    // key = segment * kOrderBins + class; class 0: heavy items; class k = 1..split: light bucket split - k
-    // (heaviest light bucket first)
-    auto key_of = [&](int i, uint32_t c) -> int {
+    const int s0 = (int)order_segment_start(seg, nw), s1 = (int)order_segment_start(seg + 1, nw);
+    // class 0: heavy items; class k = 1..split: light bucket split - k (heaviest light bucket first)
+    auto class_of = [&](uint32_t c) -> int {
         const int q = bucket(c);
-        const int seg = (int)(((int64_t)i * kXcds) / nw);
-        return seg * kOrderBins + (q >= sp ? 0 : sp - q);
+        return q >= sp ? 0 : sp - q;
     };
-    // exclusive starts of the keys: count, then scan (one thread per key, then a serial scan)
-    for (int k = t; k < kOrderKeys; k += kOrderThreads) hist[k] = 0u;
+    for (int i = s0 + t; i < s1; i += kOrderThreads) atomicAdd(&hist[class_of(cost[i])], 1u);
     __syncthreads();
-    for (int i = t; i < nw; i += kOrderThreads) atomicAdd(&hist[key_of(i, cost[i])], 1u);
-    __syncthreads();
-    if (t == 0) {
-        uint32_t start = 0u;
-        for (int k = 0; k < kOrderKeys; ++k) {
-            const uint32_t c = hist[k];
-            hist[k] = start;
-            start += c;
-        }
+    if (wave == 0) {
+        const uint32_t h = hist[lane];
+        hist[lane] = (uint32_t)s0 + wave_scan(h) - h;
     }
     __syncthreads();
-    for (int c0 = 0; c0 < nw; c0 += kOrderThreads) {
-        for (int k = t; k < kWaves * kOrderKeys; k += kOrderThreads) (&wcnt[0][0])[k] = 0u;
-        __syncthreads();
+    for (int c0 = s0; c0 < s1; c0 += kOrderThreads) {
+        wcnt[wave][lane] = 0u;
         const int i = c0 + t;
-        const bool ok = i < nw;
-        const int b = ok ? key_of(i, cost[i]) : 0;
-        // lanes of this wave with the same key, and this lane's rank among them
+        const bool ok = i < s1;
+        const int b = ok ? class_of(cost[i]) : 0;
+        // lanes of this wave with the same class, and this lane's rank among them
         uint64_t m = ballot(ok);
 #pragma unroll
-        for (int bit = 0; bit < 9; ++bit) {
+        for (int bit = 0; bit < 6; ++bit) {
             const bool set = (b >> bit) & 1;
             const uint64_t v = ballot(set);
             m &= set ? v : ~v;
@@ -597,14 +595,14 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_waves(const uint32_t *_
         const int before = lanes_below(m);
         if (ok && before == 0) wcnt[wave][b] = (uint32_t)__builtin_popcountll(m);
         __syncthreads();
-        for (int k = t; k < kOrderKeys; k += kOrderThreads) {
-            uint32_t acc = hist[k];
+        if (t < kOrderBins) {
+            uint32_t acc = hist[t];
             for (int w = 0; w < kWaves; ++w) {
-                const uint32_t c = wcnt[w][k];
-                wcnt[w][k] = acc;
+                const uint32_t c = wcnt[w][t];
+                wcnt[w][t] = acc;
                 acc += c;
             }
-            hist[k] = acc;
+            hist[t] = acc;
         }
         __syncthreads();
         if (ok) {
@@ -613,7 +611,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_waves(const uint32_t *_
         }
         __syncthreads();
     }
-    if (t < kXcds) work_ctr[t] = 0u;
+    if (t == 0) work_ctr[seg] = 0u;
 }
 
 // Sum of the parts of a split adjoint walk for every target, in part order (so the result does not depend
@@ -809,7 +807,7 @@ bool uses_wave_order(const Handle &h) { return h.adj_sched && h.adj_parts == 1; 
 
 void launch_order_items(const uint32_t *cost, int nw, uint32_t *order, uint32_t *work_ctr, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_order_waves, dim3(1), dim3(kOrderThreads), 0, s, cost, nw, order, work_ctr);
+    hipLaunchKernelGGL(k_order_waves, dim3(kXcds), dim3(kOrderThreads), 0, s, cost, nw, order, work_ctr);
 }
 
 void launch_order_waves(Handle &h, hipStream_t s)

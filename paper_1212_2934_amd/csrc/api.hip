@@ -43,12 +43,20 @@ Layout plan_layout(const bh_params &p)
     const int tid = p.tuning_id < 0 || p.tuning_id >= kNumTunings ? 0 : p.tuning_id;
     L.adj_parts = kTuneParts[tid] > 1 ? kTuneParts[tid] : 0;
     L.expansion = p.expansion == 2 ? 2 : 1;
-    // radix-sort tiles of 256 x sort_items keys: 16 items per thread once there are 2^20 keys, fewer
-    // below so that a pass still spreads over about 256 workgroups
-    const int64_t items = (L.ntot + 65535) / 65536;
-    L.sort_items = (int)(items < 1 ? 1 : items > kSortItems ? kSortItems : items);
-    L.tiles = (L.n + (int64_t)kSortThreads * L.sort_items - 1) / ((int64_t)kSortThreads * L.sort_items);
+    // radix-sort tiles of 256 x sort_items keys, a power of two that grows with the keys up to 16: enough tiles
+    // to spread over the chip, and enough keys per tile to fill the scatter's 1024 threads (bh_build of 50000
+    // particles with 1, 2, 4 items: 177, 158, 163 us; 100003 with 1, 4, 8: 193, 180, 185; 2^18 with 4, 8: 215,
+    // 202)
+    int items = 1;
+    while (items < kSortItems && (int64_t)items * 32768 < L.ntot) items *= 2;
+    L.sort_items = items;
+    auto tiles_of = [&](int64_t k) { return (L.n + kSortThreads * k - 1) / (kSortThreads * k); };
+    L.tiles = tiles_of(items);
     L.hist_len = L.B * kRadixBins * L.tiles;
+    // the histograms' space is that of one item per 65536 keys, at least what they take: workspace sizes decide
+    // which calls the fixed array of bh_field_noalloc takes, and do not follow the tile size
+    const int64_t space = (L.ntot + 65535) / 65536;
+    L.hist_space = L.B * kRadixBins * tiles_of(space < 1 ? 1 : space > kSortItems ? kSortItems : space);
     L.num_waves = L.B * ((L.n + kWave - 1) / kWave);
     // short-range grid: at most 32 entries per particle and level 7
     int lg = 0;
@@ -81,8 +89,8 @@ void carve(const Layout &Lc, void *base, Workspace &w)
     w.keys[1] = (uint64_t *)take(8 * nt);
     w.vals[0] = (uint32_t *)take(4 * nt);
     w.vals[1] = (uint32_t *)take(4 * nt);
-    w.hist = (uint32_t *)take(4 * (size_t)L.hist_len);
-    w.scan_tmp = (uint32_t *)take(4 * (((size_t)L.hist_len > bi ? (size_t)L.hist_len : bi) / 4096 + 64));
+    w.hist = (uint32_t *)take(4 * (size_t)L.hist_space);
+    w.scan_tmp = (uint32_t *)take(4 * (((size_t)L.hist_space > bi ? (size_t)L.hist_space : bi) / 4096 + 64));
     w.perm = w.vals[0];
     w.codes = w.keys[0];
     // the target-order sort ping-pongs between (keys[1], vals[1]), free once the particles are sorted, and
@@ -90,18 +98,19 @@ void carve(const Layout &Lc, void *base, Workspace &w)
     const size_t no = uses_target_order(L) ? nt : 0;
     w.hkeys = (uint64_t *)take(8 * no);
     w.tgt_order = (uint32_t *)take(4 * no);
-    w.hscan_tmp = (uint32_t *)take(no ? 4 * ((size_t)L.hist_len / 4096 + 64) : 0);
+    w.hscan_tmp = (uint32_t *)take(no ? 4 * ((size_t)L.hist_space / 4096 + 64) : 0);
     w.spos = (double *)take(3 * 8 * nt);
     w.smom = (double *)take(3 * 8 * nt);
     // one 48-byte source record per particle, in the handle's precision (src64 or src32, never both)
     w.src64 = take(48 * nt);
     w.src32 = w.src64;
-    // The octree construction needs three of the ten arrays that this region once held.  Its size is kept: it
+    // The octree construction needs four of the ten arrays that this region once held.  Its size is kept: it
     // decides which calls the fixed array of bh_field_noalloc takes.
     const size_t region = align_up(off, 256) + 9 * align_up(4 * bi, 256) + align_up(4 * nt, 256) + 512;
     w.cell_mask = (uint32_t *)take(4 * nt);
     w.cell_scan = (uint32_t *)take(4 * nt);
     w.cell_key = (int32_t *)take(4 * nt);
+    w.cell_id = (int32_t *)take(4 * nt);
     off = region;
     w.nodes = (NodeRec *)take(sizeof(NodeRec) * mn);
     w.node_level = (int32_t *)take(4 * mn);

@@ -332,21 +332,26 @@ static void scan_excl(const uint32_t *a, uint32_t *out, int64_t len, uint32_t *s
 constexpr int kFusedTiles = 256;
 
 // One pass of the stable LSD sort over one tile of up to kSortThreads * items keys.  Each wave ranks a
-// contiguous chunk of 64 * items keys (the keys of equal digit before it in the chunk: match masks from
-// ballots plus running per-wave digit counts in LDS); the chunks' counts give every key its position in
+// contiguous run of 64 * ceil(items / 4) keys (the keys of equal digit before it in the run: match masks from
+// ballots plus running per-wave digit counts in LDS); the runs' counts give every key its position in
 // the tile sorted by digit, where the keys are staged in LDS; then each digit's run of the tile is
-// written out to consecutive addresses.
-__global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
+// written out to consecutive addresses.  Four times as many threads as a count pass (a tile's keys are the
+// same): the ranking is a chain of rounds, so more waves with fewer rounds each end sooner (bh_build of 2^20
+// particles, seven passes of which four on the main stream, 419 -> 358 us together with k_order_waves' split).
+constexpr int kScatterThreads = 4 * kSortThreads;
+constexpr int kScatterItems = kSortItems / 4;  // most keys per thread per tile
+__global__ __launch_bounds__(kScatterThreads) void k_radix_scatter(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout,
     uint32_t *__restrict__ vout, const uint32_t *__restrict__ hist, int64_t n, int tiles, int items, int shift,
     int64_t ntot, int fused)
 {
-    constexpr int kWaves = kSortThreads / kWave;
+    constexpr int kWaves = kScatterThreads / kWave;
     constexpr int kTileMax = kSortThreads * kSortItems;
+    static_assert(kScatterThreads == 4 * kRadixBins && kWaves == 16, "four threads per digit, sixteen waves");
     __shared__ uint32_t gbase[kRadixBins];        // output offset of the tile's first key of digit d
     __shared__ uint32_t lstart[kRadixBins];       // position of that key in the digit-sorted tile
-    __shared__ uint32_t wcnt[kWaves][kRadixBins]; // per-wave digit counts, then per-wave digit offsets
-    __shared__ uint32_t dsum[kWaves];
+    __shared__ uint16_t wcnt[kWaves][kRadixBins]; // per-wave digit counts, then per-wave digit offsets
+    __shared__ uint32_t dsum[kWaves], dtot[kWaves];
     __shared__ uint64_t skey[kTileMax];
     __shared__ uint32_t sval[kTileMax];
     const int b = blockIdx.x / tiles, t = blockIdx.x - b * tiles;
@@ -357,23 +362,51 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     const uint32_t dmask = kRadixBins - 1;
-    for (int w = 0; w < kWaves; ++w) wcnt[w][tid] = 0u;
+    for (int k = tid; k < kWaves * kRadixBins / 2; k += kScatterThreads) ((uint32_t *)wcnt)[k] = 0u;
 
-    // this wave's chunk, loaded up front (coalesced, all loads in flight together)
-    const int c0 = wave * kWave * items;
-    uint64_t key[kSortItems];
-    uint32_t val[kSortItems], rank[kSortItems];
+    // this wave's run of keys, loaded up front (coalesced, all loads in flight together)
+    const int rounds = (items + 3) / 4;
+    const int c0 = wave * kWave * rounds;
+    uint64_t key[kScatterItems];
+    uint32_t val[kScatterItems], rank[kScatterItems];
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < kScatterItems; ++r) {
         const int p = c0 + r * kWave + lane;
-        const bool valid = r < items && p < count;
+        const bool valid = r < rounds && p < count;
         key[r] = valid ? kin[lo + p] : 0ull;
         val[r] = valid ? vin[lo + p] : 0u;
     }
+    // the output offset of (digit, tile): four threads per digit, each a quarter of the digit's row of counts.
+    // fused: hist holds raw counts, and the offset is the system's start, plus the keys of smaller digits, plus
+    // this digit's keys in earlier tiles
+    const int d4 = tid >> 2, q4 = tid & 3;
+    uint32_t pre = 0, tot = 0;
+    if (fused) {
+        const uint32_t *hd = hist + ((int64_t)b * kRadixBins + d4) * tiles;
+        if ((tiles & 3) == 0) {
+            // rows of a multiple of four counts start 16-byte aligned: read them four at a time, sixteen
+            // loads in flight (one at a time, the row's L2 latencies add up to most of the kernel)
+            const uint4 *h4 = (const uint4 *)hd;
+#pragma unroll 16
+            for (int u4 = q4; u4 < tiles / 4; u4 += 4) {
+                const uint4 c = h4[u4];
+                const int u = 4 * u4;
+                tot += c.x + c.y + c.z + c.w;
+                pre += (u < t ? c.x : 0u) + (u + 1 < t ? c.y : 0u) + (u + 2 < t ? c.z : 0u) + (u + 3 < t ? c.w : 0u);
+            }
+        } else {
+#pragma unroll 16
+            for (int u = q4; u < tiles; u += 4) {
+                const uint32_t c = hd[u];
+                tot += c;
+                pre += u < t ? c : 0u;
+            }
+        }
+    }
     __syncthreads();  // wcnt cleared
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        if (r < items) {
+    for (int r = 0; r < kScatterItems; ++r) {
+        if (r < rounds) {
             const bool valid = c0 + r * kWave + lane < count;
             const uint32_t d = (uint32_t)(key[r] >> shift) & dmask;
             uint64_t m = __ballot(valid);
@@ -387,66 +420,49 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
             // one wave's LDS accesses complete in order: this read sees the previous round's update
             const uint32_t cur = valid ? wcnt[wave][d] : 0u;
             rank[r] = cur + before;
-            if (valid && before == 0) wcnt[wave][d] = cur + (uint32_t)__popcll(m);
+            if (valid && before == 0) wcnt[wave][d] = (uint16_t)(cur + (uint32_t)__popcll(m));
         }
     }
     __syncthreads();
 
-    // thread tid owns digit tid: per-wave offsets, the tile's digit starts, and the output offset
-    uint32_t tot_tile = 0;
+    // the waves' offsets in the digit and the digits' starts in the tile and in the output
+    uint32_t c[4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        c[k] = wcnt[4 * q4 + k][d4];
+        sum += c[k];
+    }
+    const uint32_t incl = wave_incl_scan_u32(sum, lane), gincl = wave_incl_scan_u32(tot, lane);
+    const uint32_t digit0 = (uint32_t)__shfl((int)(incl - sum), lane & ~3, kWave);
+    uint32_t off = incl - sum - digit0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        wcnt[4 * q4 + k][d4] = (uint16_t)off;
+        off += c[k];
+    }
+    pre += __shfl_xor(pre, 1, kWave);
+    pre += __shfl_xor(pre, 2, kWave);
+    if (lane == kWave - 1) {
+        dsum[wave] = incl;
+        dtot[wave] = gincl;
+    }
+    __syncthreads();
+    uint32_t woff = 0, goff = 0;
     for (int w = 0; w < kWaves; ++w) {
-        const uint32_t c = wcnt[w][tid];
-        wcnt[w][tid] = tot_tile;
-        tot_tile += c;
+        woff += w < wave ? dsum[w] : 0u;
+        goff += w < wave ? dtot[w] : 0u;
     }
-    {
-        const uint32_t incl = wave_incl_scan_u32(tot_tile, lane);
-        if (lane == kWave - 1) dsum[wave] = incl;
-        __syncthreads();
-        uint32_t woff = 0;
-        for (int w = 0; w < wave; ++w) woff += dsum[w];
-        lstart[tid] = woff + incl - tot_tile;
-    }
-    if (fused) {
-        // hist holds raw counts: the offset of (digit, tile t) is the system's start, plus the keys of
-        // smaller digits, plus this digit's keys in earlier tiles
-        const uint32_t *hd = hist + ((int64_t)b * kRadixBins + tid) * tiles;
-        uint32_t pre = 0, tot = 0;
-        if ((tiles & 3) == 0) {
-            // rows of a multiple of four counts start 16-byte aligned: read them four at a time, sixteen
-            // loads in flight (one at a time, the row's L2 latencies add up to most of the kernel)
-            const uint4 *h4 = (const uint4 *)hd;
-#pragma unroll 16
-            for (int u4 = 0; u4 < tiles / 4; ++u4) {
-                const uint4 c = h4[u4];
-                const int u = 4 * u4;
-                tot += c.x + c.y + c.z + c.w;
-                pre += (u < t ? c.x : 0u) + (u + 1 < t ? c.y : 0u) + (u + 2 < t ? c.z : 0u) + (u + 3 < t ? c.w : 0u);
-            }
-        } else {
-#pragma unroll 16
-            for (int u = 0; u < tiles; ++u) {
-                const uint32_t c = hd[u];
-                tot += c;
-                pre += u < t ? c : 0u;
-            }
-        }
-        __syncthreads();  // dsum is reused
-        const uint32_t incl = wave_incl_scan_u32(tot, lane);
-        if (lane == kWave - 1) dsum[wave] = incl;
-        __syncthreads();
-        uint32_t woff = 0;
-        for (int w = 0; w < wave; ++w) woff += dsum[w];
-        gbase[tid] = (uint32_t)((int64_t)b * n) + woff + incl - tot + pre;
-    } else {
-        gbase[tid] = hist[((int64_t)b * kRadixBins + tid) * tiles + t];
+    if (q4 == 0) {
+        lstart[d4] = woff + digit0;
+        gbase[d4] = fused ? (uint32_t)((int64_t)b * n) + goff + gincl - tot + pre
+                          : hist[((int64_t)b * kRadixBins + d4) * tiles + t];
     }
     __syncthreads();
 
     // stage the tile in digit order
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        if (r < items && c0 + r * kWave + lane < count) {
+    for (int r = 0; r < kScatterItems; ++r) {
+        if (r < rounds && c0 + r * kWave + lane < count) {
             const uint32_t d = (uint32_t)(key[r] >> shift) & dmask;
             const uint32_t at = lstart[d] + wcnt[wave][d] + rank[r];
             if (at < (uint32_t)kTileMax) {  // always true for a consistent count
@@ -457,7 +473,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     }
     __syncthreads();
     // each digit's run goes to consecutive output addresses
-    for (int j = tid; j < count; j += kSortThreads) {
+    for (int j = tid; j < count; j += kScatterThreads) {
         const uint64_t k = skey[j];
         const uint32_t d = (uint32_t)(k >> shift) & dmask;
         const int64_t at = (int64_t)gbase[d] + (j - (int64_t)lstart[d]);
@@ -641,7 +657,7 @@ __device__ inline int oct_mark(const uint64_t *code, int n, int j, int wj, const
 // What the node records and the leaf index are written to; ids of the system's children start at `base`.
 struct OctOut {
     NodeRec *nodes;
-    int32_t *node_level, *leaf_of;
+    int32_t *node_level, *leaf_of, *cell_id;
     uint32_t *status;
     int64_t base, first, max_nodes;  // first: sorted position of the system's first particle
     int leaf;
@@ -673,6 +689,7 @@ __device__ inline void oct_cell(const OctOut &o, const uint64_t *code, int f, in
                 nchild = 0;
             } else {
                 child = (int)c;
+                if (o.cell_id) o.cell_id[o.first + key] = (int32_t)id;
                 for (int q = 0; q < nchild; ++q) o.nodes[c + q].parent = (int32_t)id;
             }
         }
@@ -749,15 +766,15 @@ __global__ __launch_bounds__(kOctThreads) void k_oct_emit(const uint64_t *__rest
                                                           const uint32_t *__restrict__ mask,
                                                           const uint32_t *__restrict__ scan,
                                                           NodeRec *__restrict__ nodes, int32_t *__restrict__ node_level,
-                                                          int32_t *__restrict__ leaf_of, uint32_t *__restrict__ status,
-                                                          int64_t max_nodes)
+                                                          int32_t *__restrict__ leaf_of, int32_t *__restrict__ cell_id,
+                                                          uint32_t *__restrict__ status, int64_t max_nodes)
 {
     const int64_t g = (int64_t)blockIdx.x * kOctThreads + threadIdx.x;
     if (g >= ntot) return;
     if (g == 0) status[2] = (uint32_t)B + status[1];  // number of nodes
     const int64_t b = g / n, first = b * n;
     const int j = (int)(g - first);
-    const OctOut o{nodes, node_level, leaf_of, status, B, first, max_nodes, leaf};
+    const OctOut o{nodes, node_level, leaf_of, cell_id, status, B, first, max_nodes, leaf};
     auto mask_of = [&](int k) { return mask[first + k]; };
     auto scan_of = [&](int k) { return (int64_t)scan[first + k]; };
     if (j == 0) oct_root(o, codes + first, (int)n, b, mask_of, scan_of);
@@ -771,12 +788,13 @@ __global__ __launch_bounds__(kOctThreads) void k_oct_emit(const uint64_t *__rest
 //   MODE 0: positions -> centroid S / count and squared side into the node record.
 //   MODE 1: moments   -> FP64 moment sum into node_m64 and its FP32 rounding into the record.
 //
-// One workgroup per chunk of consecutive sorted positions of a system (k_upward_sub).  The key that allocates a
-// cell's children is a position inside the cell, and ids follow the keys, so the children of all cells inside
-// a chunk have consecutive ids and belong to the chunk's workgroup, which sums its leaves and then, level by level with a barrier between levels, the cells inside
-// the chunk.  Cells that reach beyond their chunk (the ancestors of the chunk boundaries, a few dozen a chunk)
-// are listed per system when the tree is built and follow in a second launch of one workgroup per system
-// (k_upward_top).  Systems of one chunk need no second launch.
+// One workgroup per chunk of consecutive sorted positions of a system (k_upward_sub) sums the leaves among the
+// children that the chunk's keys allocated (consecutive ids), then, level by level with a barrier between
+// levels, the cells inside the chunk: a cell's key lies inside it, so the chunk's keys list them all, and their
+// children are leaves of the chunk's or cells inside the chunk.  Cells that reach beyond their chunk (the
+// ancestors of the chunk boundaries, about seven a boundary) are listed per system when the tree is built and
+// follow in a second launch of one workgroup per system (k_upward_top).  Systems of one chunk need no second
+// launch.
 //
 // A launch costs about 4.5 us in a stream, so what the pass cost before, one launch per level (twelve of them
 // above 2^16 nodes, 50-60 us for a few us of work), is now two.
@@ -892,16 +910,14 @@ __device__ inline void upward_node(int id, const NodeRec &nd, const double *__re
 }
 
 constexpr int kUpThreads = 1024;
-constexpr int kUpCache = 16384;         // nodes of a workgroup whose levels are kept in LDS
+constexpr int kUpChunkMax = 8192;  // positions per chunk, at most: as many cells as the LDS list holds
 constexpr uint8_t kUpSkip = 255;
 
-// Positions per chunk: 64 chunks a system, of 2048 to 8192 positions, and at most 256 chunks.  Short chunks give
-// more workgroups, long ones leave fewer cells to the one workgroup of the second launch (field evaluation with
-// chunks of 2048, 4096, 8192: 20000 particles 391, 397, 416 us; 262144 896, 883, 888 us; 2^20 2375, 2361, 2326 us).
-static int64_t up_chunk(const Layout &L)
+// Positions per chunk: 64 chunks a system, of 2048 to 8192 positions.  Short chunks give more workgroups, long ones
+// leave fewer cells to the one workgroup of the second launch.
+static int64_t up_chunk_size(const Layout &L)
 {
-    const int64_t c = L.n / 64 < 2048 ? 2048 : L.n / 64 > 8192 ? 8192 : L.n / 64, least = (L.n + 255) / 256;
-    return c > least ? c : least;
+    return L.n / 64 < 2048 ? 2048 : L.n / 64 > kUpChunkMax ? kUpChunkMax : L.n / 64;
 }
 
 // The per-system lists of k_upward_top live in one array: entry b counts system b's list, which starts at
@@ -915,78 +931,91 @@ __device__ inline int64_t up_list(int64_t B, int64_t n, int64_t b) { return B + 
         double *__restrict__ q64, float *__restrict__ q32
 #define FFBH_UP_ARGS vals, vals2, ntot, n, nodes, sums, node_m64, node_level, bbox, max_nodes, q64, q32
 
-// Levels lo..hi of the cells k (0 <= k < count) of this workgroup, deepest first: id_of(k) and its level or
-// kUpSkip, from the LDS copy where it holds it.
-template <int MODE, typename Id, typename Level>
-__device__ inline void up_levels(int lo, int hi, int count, const uint8_t *lev, const Id &id_of, const Level &level_of,
-                                 FFBH_UP_PARAMS)
+// The cells of a workgroup, in LDS, and the range of their levels.
+struct UpList {
+    int32_t id[kUpChunkMax];
+    uint8_t lev[kUpChunkMax];
+    int count, lmin, lmax;
+};
+
+__device__ inline void up_reset(UpList &S)
 {
-    for (int l = hi; l >= lo; --l) {
+    if (threadIdx.x == 0) {
+        S.count = 0;
+        S.lmin = kMaxLevel + 1;
+        S.lmax = -1;
+    }
+    __syncthreads();
+}
+__device__ inline void up_add(UpList &S, int id, int level)
+{
+    if ((unsigned)level > (unsigned)kMaxLevel) return;
+    const int k = atomicAdd(&S.count, 1);
+    if (k >= kUpChunkMax) return;  // never: a chunk holds fewer split cells than positions
+    S.id[k] = id;
+    S.lev[k] = (uint8_t)level;
+    atomicMin(&S.lmin, level);
+    atomicMax(&S.lmax, level);
+}
+// Sum the listed cells, deepest level first.
+template <int MODE>
+__device__ inline void up_levels(const UpList &S, FFBH_UP_PARAMS)
+{
+    __syncthreads();
+    const int lmin = S.lmin, lmax = S.lmax, count = min(S.count, kUpChunkMax);
+    for (int l = lmax; l >= lmin; --l) {
         for (int k = threadIdx.x; k < count; k += blockDim.x) {
-            if ((k < kUpCache ? lev[k] : level_of(k)) != l) continue;
-            const int id = id_of(k);
+            if (S.lev[k] != l) continue;
+            const int id = S.id[k];
             const NodeRec nd = nodes[id];
             upward_node<MODE>(id, nd, FFBH_UP_ARGS);
         }
         __syncthreads();
     }
 }
-
-// One workgroup's part of the upward pass: positions [c0, c1) of system b, whose cells' children have ids
-// [i0, i1), and with `root` the system's root.  lev: kUpCache bytes of LDS.  top (may be null): list the cells
-// left to k_upward_top there (the build's pass).
+// Sum the leaves among the nodes [i0, i1) and, with `root`, that of system b; with `all`, list the other nodes.
 template <int MODE>
-__device__ inline void up_chunk(int64_t b, int64_t c0, int64_t c1, int64_t i0, int64_t i1, int root, uint8_t *lev,
-                                int *lrange, int64_t B, int32_t *top, FFBH_UP_PARAMS)
+__device__ inline void up_leaves(UpList &S, int64_t b, int64_t i0, int64_t i1, bool root, bool all, FFBH_UP_PARAMS)
 {
-    const int count = (int)(i1 > i0 ? i1 - i0 : 0) + root;
-    auto id_of = [&](int k) { return root && k == 0 ? (int)b : (int)(i0 + k - root); };
-    auto level_at = [&](int id, const NodeRec &nd) -> uint8_t {
-        const int64_t f = nd.first - b * n;
-        const int l = node_level[id];
-        if (nd.nchild == 0 || f < c0 || f + nd.count > c1 || (unsigned)l > (unsigned)kMaxLevel) return kUpSkip;
-        return (uint8_t)l;
-    };
-    if (threadIdx.x == 0) {
-        lrange[0] = kMaxLevel + 1;
-        lrange[1] = -1;
-    }
-    __syncthreads();
+    const int count = (int)(i1 > i0 ? i1 - i0 : 0) + (root ? 1 : 0);
     for (int k = threadIdx.x; k < count; k += blockDim.x) {
-        const int id = id_of(k);
+        const int id = root && k == 0 ? (int)b : (int)(i0 + k - (root ? 1 : 0));
         const NodeRec nd = nodes[id];
-        const uint8_t l = level_at(id, nd);
-        if (k < kUpCache) lev[k] = l;
-        if (nd.nchild == 0) {
-            upward_node<MODE>(id, nd, FFBH_UP_ARGS);
-        } else if (l != kUpSkip) {
-            atomicMin(&lrange[0], (int)l);
-            atomicMax(&lrange[1], (int)l);
-        } else if (top) {
-            const uint32_t at = atomicAdd((uint32_t *)&top[b], 1u);
-            if ((int64_t)at < 2 * n) top[up_list(B, n, b) + at] = id;
-        }
+        if (nd.nchild == 0) upward_node<MODE>(id, nd, FFBH_UP_ARGS);
+        else if (all) up_add(S, id, node_level[id]);
     }
-    __syncthreads();
-    up_levels<MODE>(lrange[0], lrange[1], count, lev, id_of,
-                    [&](int k) { const int id = id_of(k); return level_at(id, nodes[id]); }, FFBH_UP_ARGS);
 }
 
+// append: list the cells left to k_upward_top (the build's pass).
 template <int MODE>
-__global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const uint32_t *__restrict__ scan,
+__global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const uint32_t *__restrict__ mask,
+                                                           const uint32_t *__restrict__ scan,
+                                                           const int32_t *__restrict__ cell_id,
                                                            uint32_t *__restrict__ status, int64_t B, int64_t chunk,
                                                            int chunks, int32_t *__restrict__ top, int append,
                                                            int leave)
 {
-    __shared__ uint8_t lev[kUpCache];
-    __shared__ int lrange[2];
+    __shared__ UpList S;
     const int64_t b = blockIdx.x / chunks;
     const int c = (int)(blockIdx.x - b * chunks);
-    const int64_t c0 = c * chunk, c1 = min(c0 + chunk, n);
-    // ids of the children of the cells whose keys are positions c0 .. c1 - 1 of the system
-    auto start = [&](int64_t i) { return B + (int64_t)(b * n + i < ntot ? scan[b * n + i] : status[1]); };
-    up_chunk<MODE>(b, c0, c1, start(c0), min(start(c1), max_nodes), c == 0 ? 1 : 0, lev, lrange, B,
-                   append ? top : nullptr, FFBH_UP_ARGS);
+    const int64_t first = b * n, c0 = c * chunk, c1 = min(c0 + chunk, n);
+    up_reset(S);
+    // the cells of the chunk's keys: inside the chunk, or left to the second launch
+    for (int64_t j = c0 + threadIdx.x; j < c1; j += blockDim.x) {
+        if (mask[first + j] == 0u) continue;
+        const int id = cell_id[first + j];
+        if ((unsigned)id >= (unsigned)max_nodes) continue;
+        const int64_t f = nodes[id].first - first, e = f + nodes[id].count;
+        if (f >= c0 && e <= c1) {
+            up_add(S, id, node_level[id]);
+        } else if (append) {
+            const uint32_t at = atomicAdd((uint32_t *)&top[b], 1u);
+            if ((int64_t)at < 2 * n) top[up_list(B, n, b) + at] = id;
+        }
+    }
+    auto start = [&](int64_t i) { return B + (int64_t)(first + i < ntot ? scan[first + i] : status[1]); };
+    up_leaves<MODE>(S, b, start(c0), min(start(c1), max_nodes), c == 0, false, FFBH_UP_ARGS);
+    up_levels<MODE>(S, FFBH_UP_ARGS);
     if (leave && threadIdx.x == 0) call_leave(status);
 }
 
@@ -994,16 +1023,15 @@ template <int MODE>
 __global__ __launch_bounds__(kUpThreads) void k_upward_top(FFBH_UP_PARAMS, uint32_t *__restrict__ status, int64_t B,
                                                            const int32_t *__restrict__ top, int leave)
 {
-    __shared__ uint8_t lev[kUpCache];
+    __shared__ uint8_t lev[kUpChunkMax];  // levels of the first entries; of the others they are read again
     __shared__ int lmin, lmax;
     const int64_t b = blockIdx.x;
     const int32_t *list = top + up_list(B, n, b);
     const int64_t listed = (uint32_t)top[b];
     const int count = (int)(listed < 2 * n ? listed : 2 * n);
-    auto id_of = [&](int k) { return list[k]; };
     auto level_of = [&](int k) -> uint8_t {
         const int id = list[k];
-        if (id < 0 || id >= max_nodes) return kUpSkip;
+        if ((unsigned)id >= (unsigned)max_nodes) return kUpSkip;
         const int l = node_level[id];
         return (unsigned)l > (unsigned)kMaxLevel ? kUpSkip : (uint8_t)l;
     };
@@ -1014,13 +1042,21 @@ __global__ __launch_bounds__(kUpThreads) void k_upward_top(FFBH_UP_PARAMS, uint3
     __syncthreads();
     for (int k = threadIdx.x; k < count; k += blockDim.x) {
         const uint8_t l = level_of(k);
-        if (k < kUpCache) lev[k] = l;
+        if (k < kUpChunkMax) lev[k] = l;
         if (l == kUpSkip) continue;
         atomicMin(&lmin, (int)l);
         atomicMax(&lmax, (int)l);
     }
     __syncthreads();
-    up_levels<MODE>(lmin, lmax, count, lev, id_of, level_of, FFBH_UP_ARGS);
+    for (int l = lmax; l >= lmin; --l) {
+        for (int k = threadIdx.x; k < count; k += blockDim.x) {
+            if ((k < kUpChunkMax ? lev[k] : level_of(k)) != l) continue;
+            const int id = list[k];
+            const NodeRec nd = nodes[id];
+            upward_node<MODE>(id, nd, FFBH_UP_ARGS);
+        }
+        __syncthreads();
+    }
     if (leave && threadIdx.x == 0) call_leave(status);
 }
 
@@ -1032,12 +1068,12 @@ static bool upward(Handle &h, const double *vals, const double *vals2, hipStream
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
-    const int64_t chunk = up_chunk(L);
+    const int64_t chunk = up_chunk_size(L);
     const int chunks = (int)((L.n + chunk - 1) / chunk);
     leave = leave && L.B == 1;
     hipLaunchKernelGGL(k_upward_sub<MODE>, dim3((unsigned)(L.B * chunks)), dim3(kUpThreads), 0, s, vals, vals2, L.ntot,
                        L.n, w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
-                       w.cell_scan, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0,
+                       w.cell_mask, w.cell_scan, w.cell_id, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0,
                        leave && chunks == 1 ? 1 : 0);
     if (chunks > 1)
         hipLaunchKernelGGL(k_upward_top<MODE>, dim3((unsigned)L.B), dim3(kUpThreads), 0, s, vals, vals2, L.ntot, L.n,
@@ -1109,11 +1145,10 @@ constexpr int kSmallItems = kSmallMax / kSmallThreads;  // particles per thread
 
 // LDS of k_build_small, 57 KB: the sort's keys and values (ping-pong), then the codes in the keys' place, the cell
 // masks in the values' and the scan in the counts'.
-struct SmallLds {
+struct SmallSort {
     union {
         uint32_t key[2][kSmallMax];  // 31 or 32 bits of the codes
         uint64_t code[kSmallMax];
-        uint8_t lev[kUpCache];       // the upward pass's levels
     };
     union {
         uint16_t val[2][kSmallMax];  // index in the system
@@ -1127,8 +1162,11 @@ struct SmallLds {
     uint32_t lstart[kRadixBins];
     uint32_t dsum[kSmallThreads / kWave];
     double box[kSmallThreads / kWave][6];
-    int lrange[2];
     int flag;
+};
+union SmallLds {
+    SmallSort s;
+    UpList up;  // the upward pass's cells, once the tree is written
 };
 static_assert(sizeof(SmallLds) <= 65536, "LDS of k_build_small");
 static_assert(kSmallThreads / kWave * kRadixBins >= kSmallMax, "the scan fits the counts");
@@ -1136,7 +1174,7 @@ static_assert(kSmallThreads == 4 * kRadixBins && kSmallThreads / kWave == 16, "f
 
 // One stable pass over 8 bits of the keys from buffer src to the other one: every wave ranks a contiguous run of
 // keys (match masks from ballots, running per-wave digit counts), the counts give every key its place.
-__device__ inline void small_pass(SmallLds &S, int n, int src, int shift)
+__device__ inline void small_pass(SmallSort &S, int n, int src, int shift)
 {
     constexpr int kWaves = kSmallThreads / kWave;
     const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1);
@@ -1217,10 +1255,23 @@ struct SmallArgs {
     int32_t *node_level, *leaf_of, *top;
 };
 
+// Upward pass of one system whose `total` nodes below the root start at id base.
+template <int MODE>
+__device__ inline void small_upward(UpList &U, int64_t b, int64_t base, int64_t total, const double *vals,
+                                    const double *vals2, const SmallArgs &a, double *q64, float *q32)
+{
+    up_reset(U);
+    up_leaves<MODE>(U, b, base, min(base + total, a.max_nodes), true, true, vals, vals2, a.ntot, a.n, a.nodes, a.sums,
+                    a.node_m64, a.node_level, a.bbox, a.max_nodes, q64, q32);
+    up_levels<MODE>(U, vals, vals2, a.ntot, a.n, a.nodes, a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes, q64,
+                    q32);
+}
+
 template <bool MOM>
 __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
 {
-    __shared__ SmallLds S;
+    __shared__ SmallLds lds;
+    SmallSort &S = lds.s;
     const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1), n = a.n;
     constexpr int kWaves = kSmallThreads / kWave;
     const int64_t b = blockIdx.x, first = b * n;
@@ -1385,7 +1436,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
     __syncthreads();
     const int64_t base = a.B + 2 * first;
     {
-        const OctOut o{a.nodes, a.node_level, a.leaf_of, a.status, base, first, a.max_nodes, a.leaf};
+        const OctOut o{a.nodes, a.node_level, a.leaf_of, nullptr, a.status, base, first, a.max_nodes, a.leaf};
         auto mask_of = [&](int k) { return S.mask[k]; };
         auto scan_of = [&](int k) { return (int64_t)S.scan[k]; };
         if (t == kSmallThreads - 1) oct_root(o, S.code, n, b, mask_of, scan_of);
@@ -1394,9 +1445,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
             if (key[r] > 0) oct_children(o, S.code, n, t + r * kSmallThreads, key[r], mask_of, scan_of);
     }
     __syncthreads();
-    up_chunk<MOM ? 2 : 0>(b, 0, n, base, min(base + (int64_t)total, a.max_nodes), 1, S.lev, S.lrange, a.B, nullptr,
-                          a.spos, a.smom, a.ntot, n, a.nodes, a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes,
-                          nullptr, nullptr);
+    small_upward<MOM ? 2 : 0>(lds.up, b, base, total, a.spos, a.smom, a, nullptr, nullptr);
     if (!a.hilbert) return;
     // target order (as launch_target_order)
     __syncthreads();
@@ -1412,9 +1461,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
 template <int MODE>
 __global__ __launch_bounds__(kSmallThreads) void k_moments_small(SmallArgs a, double *q64, float *q32)
 {
-    __shared__ uint8_t lev[2 * kSmallMax + 1];
-    __shared__ int lrange[2];
-    static_assert(2 * kSmallMax + 1 <= kUpCache, "every node's level fits");
+    __shared__ UpList U;
+    static_assert(kSmallMax <= kUpChunkMax, "every split cell fits");
     const int n = a.n;
     const int64_t b = blockIdx.x, first = b * n;
     if (a.enter && b == 0 && threadIdx.x == 0) call_enter(a.status);
@@ -1433,8 +1481,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_moments_small(SmallArgs a, do
     }
     __syncthreads();
     const int64_t base = a.B + 2 * first, total = min((int64_t)(uint32_t)a.top[b], (int64_t)2 * n);
-    up_chunk<MODE>(b, 0, n, base, min(base + total, a.max_nodes), 1, lev, lrange, a.B, nullptr, a.smom, a.spos, a.ntot,
-                   n, a.nodes, a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes, q64, q32);
+    small_upward<MODE>(U, b, base, total, a.smom, a.spos, a, q64, q32);
 }
 
 // Number of nodes from the scan's total.
@@ -1528,7 +1575,7 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
         // up to kFusedTiles tiles per system the scatter derives its offsets from the raw counts
         const int fused = tiles <= kFusedTiles;
         if (!fused) scan_excl<false>(w.hist, w.hist, (int64_t)L.hist_len, w.scan_tmp, nullptr, s);
-        hipLaunchKernelGGL(k_radix_scatter, dim3(sblocks), dim3(kSortThreads), 0, s, w.keys[src],
+        hipLaunchKernelGGL(k_radix_scatter, dim3(sblocks), dim3(kScatterThreads), 0, s, w.keys[src],
                            w.vals[src], w.keys[dst], w.vals[dst], w.hist, n, tiles, L.sort_items, shift, ntot,
                            fused);
     }
@@ -1560,7 +1607,7 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     scan_excl<true>(w.cell_mask, w.cell_scan, ntot, w.scan_tmp, w.status + 1, s);
     hipLaunchKernelGGL(k_oct_emit, dim3(grid_for(ntot, kOctThreads)), dim3(kOctThreads), 0, s, w.codes, n, ntot, B,
                        (int)h.p.leaf_size, w.cell_key, w.cell_mask, w.cell_scan, w.nodes, w.node_level, w.leaf_of,
-                       w.status, L.max_nodes);
+                       w.cell_id, w.status, L.max_nodes);
     if (d_mom) {
         // positions and moments summed in one upward pass
         gather_moments(h, d_mom, s, false);
@@ -1616,7 +1663,7 @@ void launch_target_order(Handle &h, hipStream_t s)
         hipLaunchKernelGGL(k_radix_hist, dim3(sblocks), dim3(kSortThreads), 0, s, kb[src], L.n, tiles,
                            L.sort_items, shift, w.hist);
         if (!fused) scan_excl<false>(w.hist, w.hist, (int64_t)L.hist_len, w.hscan_tmp, nullptr, s);
-        hipLaunchKernelGGL(k_radix_scatter, dim3(sblocks), dim3(kSortThreads), 0, s, kb[src], vb[src], kb[dst],
+        hipLaunchKernelGGL(k_radix_scatter, dim3(sblocks), dim3(kScatterThreads), 0, s, kb[src], vb[src], kb[dst],
                            vb[dst], w.hist, L.n, tiles, L.sort_items, shift, L.ntot, fused);
     }
 }

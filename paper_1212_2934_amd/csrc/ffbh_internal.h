@@ -85,6 +85,7 @@ struct Workspace {
     // octree construction, per sorted particle
     uint32_t *cell_mask;     // at a split cell's key: the octants of its children
     uint32_t *cell_scan;     // exclusive scan of the masks' bit counts: where the children start
+    int32_t *cell_id;        // at a split cell's key: its node (systems above kSmallMax)
     int32_t *cell_key;       // key of the cell that the particle starts a child of (-1: none)
     // octree
     NodeRec *nodes;          // max_nodes
@@ -121,7 +122,7 @@ struct Workspace {
 constexpr int kBboxBlocks = 512;  // partial bounding boxes per system (two workgroups per CU)
 
 struct Layout {
-    int64_t n, B, ntot, max_nodes, tiles, num_waves, hist_len;
+    int64_t n, B, ntot, max_nodes, tiles, num_waves, hist_len, hist_space;
     int sort_items;         // keys per thread per radix-sort tile (1..kSortItems)
     int adj_parts;          // parts of a split adjoint walk that the workspace holds (0: none)
     int expansion;          // 2: first moments are kept (order-2 cells); else 1

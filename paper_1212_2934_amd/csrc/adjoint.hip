@@ -225,7 +225,8 @@ __device__ inline void close_pairs(AdjLds<float, SPLIT> &W, int lane, bool valid
 // gradient to the target and (negated) to the cell centre, and d/dD to node_adjq (six values, stride 8).
 // SCALED: the node records hold s^2 / theta^2 and the acceptance test is s2 < d^2 (kMacScaled).  SPLIT: the
 // block's waves (a power of two) share the item's targets and divide the tree by sorted positions, as in the
-// forward walk (k_field): interval q of 2^split_shift positions belongs to wave q mod W.  Every far cell and
+// forward walk (k_field): interval q of 2^split_shift positions belongs to wave q mod W; in the FP64 walk with a
+// negative split_shift node i belongs to wave i mod W instead, and all waves descend.  Every far cell and
 // every leaf is summed and scattered by one wave, an FP32-mixed wave sums whole segments between two leaf
 // visits, and the FP64 sums of the targets meet in LDS, in wave order.
 template <bool MIXED, bool QUAD, bool SCALED, bool SPLIT>
@@ -294,7 +295,11 @@ __device__ __forceinline__ void adjoint_wave(int gw, int split_shift, FFBH_ADJ_P
         const NodeRec nd = nodes[cur];
         ++work;
         bool own = true;
-        if constexpr (SPLIT) {
+        if (SPLIT && !MIXED && split_shift < 0) {
+            // by node: the waves take turns at the children of a cell, and all descend
+            own = live = (cur & (waves - 1)) == wave;
+            if (!live && nd.nchild == 0) continue;
+        } else if constexpr (SPLIT) {
             const int q0 = (nd.first - seg0) >> split_shift, q1 = (nd.first - seg0 + nd.count - 1) >> split_shift;
             own = ((q0 ^ wave) & (waves - 1)) == 0;
             if constexpr (!MIXED) live = own;
@@ -798,9 +803,20 @@ static int adjoint_items(const Handle &h)
 // FP64 / FP32-mixed, undivided -> divided: 1000 particles 282 / 285 -> 60 / 62 us, 4096 451 / 459 -> 105 / 118 us,
 // 20000 818 / 804 -> 271 / 300 us, 50000 838 / 759 -> 474 / 424 us, 64 systems of 1000 294 / 309 -> 187 / 168 us;
 // at 131072 particles four waves take 1545 / 1529 us against 1301 / 1203.
-static int adjoint_split(const Handle &h)
+// Above that the FP64 walk still gains from two waves that take turns at the nodes (shift -1): the work is dealt
+// out evenly and only the opened cells are tested twice, where intervals long enough to be skipped leave most of a
+// group's near cells to one wave (131072 particles: 1281 us undivided, 1436 with intervals, 1193 by node; 200000
+// 1723 -> 1699; with four waves and more intervals are ahead).
+static int adjoint_split(const Handle &h, int &shift)
 {
-    return h.adj_parts == 1 && h.adj_sched == 0 && h.adj_tpw == kWave ? walk_split(h.L) : 1;
+    const bool plain = h.adj_parts == 1 && h.adj_sched == 0 && h.adj_tpw == kWave;
+    const int W = plain ? walk_split(h.L) : 1;
+    shift = split_shift(h.L.n, W);
+    if (plain && W == 1 && h.p.precision == BH_FP64 && h.L.num_waves <= 3200) {
+        shift = -1;
+        return 2;
+    }
+    return W;
 }
 
 bool uses_wave_order(const Handle &h) { return h.adj_sched && h.adj_parts == 1; }
@@ -857,7 +873,8 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
                        w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext, w.g_gather,    \
                        w.g_rm, w.node_adj, w.Hs, d_H, w.e_part, w.status, L.n, L.ntot, wps, nwv, theta2,          \
                        (int)L.max_nodes, tpw, parts, w.part_buf, cost, nq, w.node_adjq, tgt, inside, ord, ctr)
-        const int W = adjoint_split(h), shift = split_shift(L.n, W);
+        int shift = 0;
+        const int W = adjoint_split(h, shift);
 #define FFBH_ADJ_SPLIT(MX, QD, SC, T)                                                                            \
     hipLaunchKernelGGL((k_adjoint_split<MX, QD, SC>), dim3((unsigned)nwv), dim3(W * kWave), (adj_lds_bytes<T, true>(W)), \
                        s, w.nodes, w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext,    \

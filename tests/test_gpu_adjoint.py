@@ -143,9 +143,9 @@ def test_invariants_at_full_size_c4():
 @pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
 @pytest.mark.parametrize("n,leaf,theta,expansion", [
     (3, 16, 0.5, 1), (70, 1, 0.5, 2), (3001, 40, 0.3, 1), (64 * 192, 16, 0.5, 1), (64 * 192 + 1, 16, 0.9, 2),
-    (64 * 768 + 1, 16, 0.7, 1)])
+    (64 * 768 + 1, 16, 0.7, 1), (64 * 1600 + 1, 16, 0.7, 1)])
 def test_divided_walks_at_the_edges_of_their_range(oracle_mod, precision, n, leaf, theta, expansion):
-    """16, 8 or 4 waves divide the fused walk of 64 targets, by the number of target groups: the energy
+    """16, 8, 4 or (FP64) 2 waves divide the fused walk of 64 targets, by the number of target groups: the energy
     gradient against the oracle on either side of each change, with leaves of several chunks and order-2 cells."""
     w = workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n + leaf, hext=(0.2, 0.0, 1.0))
     _, _, dr, dm = oracle_mod.Tree(w.pos, w.mom, leaf).energy_grad(theta, w.hext, order=expansion)

@@ -212,6 +212,109 @@ __global__ __launch_bounds__(256) void k_wca(const uint64_t *__restrict__ codes,
     out[2 * n + i] = fz;
 }
 
+// The short-range forces of systems of at most kSmallMax particles.  Such a system is a few waves with one thread
+// per particle, each a chain of dependent loads over its 27 cells, behind two launches that clear and fill the
+// table.  Here every workgroup fills the table of its system in LDS (level at most 4: 16 KB, ranges in 16 bits)
+// and 8 lanes share a particle: each reads the ranges of four of the cells, and the candidates of all cells are
+// dealt out to the lanes in turn, so 8 candidates are one load deep whether they lie in one cell or in all.
+// Bound by latency for one system (one of 1000: 37 us in three launches -> 10), by issue for many (64 of 1000: 27 ->
+// 14 us).  A whole step of 1000 / 64 x 1000 / 16 x 4096 takes 139.4 / 287.5 / 478.0 us with 8 lanes, 138.4 / 290.6
+// / 480.6 with 16, 139.4 / 302.6 / 488.6 with 32.  Above kSmallMax the table outgrows 16 bits and one thread per
+// particle fills the chip.
+constexpr int kSrThreads = 512, kSrLanes = 8, kSrAtOnce = kSrThreads / kSrLanes, kSrLevel = 4;
+constexpr int64_t kSrGroups = 512;
+
+__global__ __launch_bounds__(kSrThreads) void k_wca_small(
+    const uint64_t *__restrict__ codes, const double *__restrict__ bbox, const double *__restrict__ spos,
+    const uint32_t *__restrict__ perm, double *__restrict__ F, int n, int64_t ntot, int per_system, int lcap,
+    double sigma, double eps, double c12, double rc, double rcw, double3 box_lo, double3 box_hi)
+{
+    __shared__ ushort2 tab[1 << (3 * kSrLevel)];
+    const int t = threadIdx.x, k = t & (kSrLanes - 1);
+    const int64_t b = blockIdx.x / per_system, base = b * n;
+    const int L = grid_level(bbox[8 * b + 3], rc, lcap < kSrLevel ? lcap : kSrLevel);
+    const int shift = 3 * (kBits - L), down = kBits - L, cmax = (1 << L) - 1;
+    if (eps > 0.0) {
+        for (int i = t; i < 1 << (3 * L); i += kSrThreads) tab[i] = make_ushort2(0, 0);
+        __syncthreads();
+        for (int i = t; i < n; i += kSrThreads) {
+            const uint64_t c = codes[base + i] >> shift;
+            if (c >= (uint64_t)1 << (3 * L)) continue;  // never for a code of the build
+            if (i == 0 || (codes[base + i - 1] >> shift) != c) tab[c].x = (uint16_t)i;
+            if (i == n - 1 || (codes[base + i + 1] >> shift) != c) tab[c].y = (uint16_t)(i + 1);
+        }
+        __syncthreads();
+    }
+    const double rc2 = rc * rc, s2 = sigma * sigma;
+    const int first = (int)(blockIdx.x % per_system) * kSrAtOnce;
+    for (int s0 = first; s0 < n; s0 += per_system * kSrAtOnce) {
+        const int own = s0 + t / kSrLanes;
+        const int s = own < n ? own : n - 1;  // the shuffles want every lane; an idle group repeats the last particle
+        const int64_t o = base + s;
+        const double r[3] = {spos[o], spos[ntot + o], spos[2 * ntot + o]};
+        const int64_t i = (int64_t)perm[o] - base;
+        double f[3] = {0.0, 0.0, 0.0};
+        if (eps > 0.0) {
+            const uint64_t code = codes[o];
+            const int cx = (int)(compact3(code >> 2) >> down), cy = (int)(compact3(code >> 1) >> down),
+                      cz = (int)(compact3(code) >> down);
+            uint32_t cell[4];  // first member << 16 | candidates of the lane's cells before
+            int cnt = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int c = 4 * k + q, nx = cx + c % 3 - 1, ny = cy + c / 3 % 3 - 1, nz = cz + c / 9 - 1;
+                const bool in = c < 27 && (unsigned)nx <= (unsigned)cmax && (unsigned)ny <= (unsigned)cmax &&
+                                (unsigned)nz <= (unsigned)cmax;
+                const ushort2 m = in ? tab[(spread3_small((uint32_t)nx) << 2) | (spread3_small((uint32_t)ny) << 1) |
+                                           spread3_small((uint32_t)nz)]
+                                     : make_ushort2(0, 0);
+                cell[q] = (uint32_t)m.x << 16 | (uint32_t)cnt;
+                cnt += (int)m.y - (int)m.x;
+            }
+            int upto = cnt;
+#pragma unroll
+            for (int d = 1; d < kSrLanes; d *= 2) {
+                const int below = __shfl_up(upto, d, kSrLanes);
+                if (k >= d) upto += below;
+            }
+            const int start = upto - cnt;  // candidates of the lanes below
+            const int tot = __shfl(upto, kSrLanes - 1, kSrLanes);
+            // every lane stays for the shuffles until the wave's busiest particle is done
+            for (int c0 = 0; ballot(c0 < tot) != 0; c0 += kSrLanes) {
+                const int c = c0 + k;
+                int at = 0;  // the last lane whose start is at most c
+#pragma unroll
+                for (int d = kSrLanes / 2; d > 0; d /= 2)
+                    if (__shfl(start, at + d, kSrLanes) <= c) at += d;
+                const int in_lane = c - __shfl(start, at, kSrLanes);
+                int j = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {  // the last of its cells that starts at or before the candidate
+                    const uint32_t m = (uint32_t)__shfl((int)cell[q], at, kSrLanes);
+                    const int from = (int)(m & 0xffffu);
+                    if (from <= in_lane) j = (int)(m >> 16) + in_lane - from;
+                }
+                if (c < tot && j != s) {
+                    const int64_t p = base + j;
+                    sr_pair(r[0] - spos[p], r[1] - spos[ntot + p], r[2] - spos[2 * ntot + p], s2, eps, c12, rc2,
+                            f[0], f[1], f[2]);
+                }
+            }
+#pragma unroll
+            for (int d = kSrLanes / 2; d > 0; d /= 2)
+                for (int a = 0; a < 3; ++a) f[a] += __shfl_xor(f[a], d, kSrLanes);
+        }
+        if (k < 3 && own < n && i >= 0 && i < n) {  // one lane per axis: the walls, the output
+            const double x = k == 0 ? r[0] : k == 1 ? r[1] : r[2];
+            const double lo = k == 0 ? box_lo.x : k == 1 ? box_lo.y : box_lo.z;
+            const double hi = k == 0 ? box_hi.x : k == 1 ? box_hi.y : box_hi.z;
+            double v = k == 0 ? f[0] : k == 1 ? f[1] : f[2];
+            if (eps > 0.0) v += wall_force(x - lo, hi - x, 0.5 * sigma, eps, c12, rcw);
+            F[3 * base + k * n + i] = v;
+        }
+    }
+}
+
 // ---- integrator ---------------------------------------------------------------------------------------
 
 struct MDConst {
@@ -312,14 +415,24 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
     const double rc = lj ? (mp->sr_cut > 0.0 ? mp->sr_cut : 2.5 * mp->wca_sigma) : wca_rc * mp->wca_sigma;
     const double rcw = lj ? 0.5 * rc : wca_rc * 0.5 * mp->wca_sigma;
     const SortedWork short_range = [&](hipStream_t ss) {
-        const int64_t ncell = L.B * L.cell_T;
-        hipLaunchKernelGGL(k_clear_cells, dim3(grid_for(ncell, 256, 2048)), dim3(256), 0, ss, w.cells, ncell);
-        hipLaunchKernelGGL(k_cell_fill, dim3(grid_for(L.ntot, 256)), dim3(256), 0, ss, w.codes, w.bbox, L.n,
-                           L.ntot, rc, L.cell_lcap, L.cell_T, w.cells);
-        hipLaunchKernelGGL(k_wca, dim3(grid_for(L.ntot, 256)), dim3(256), 0, ss, w.codes, w.bbox, w.cells, w.spos,
-                           w.perm, w.md_force, L.n, L.ntot, L.cell_lcap, L.cell_T, mp->wca_sigma, mp->wca_eps, c12,
-                           rc, rcw, make_double3(mp->box_lo[0], mp->box_lo[1], mp->box_lo[2]),
-                           make_double3(mp->box_hi[0], mp->box_hi[1], mp->box_hi[2]));
+        const double3 lo = make_double3(mp->box_lo[0], mp->box_lo[1], mp->box_lo[2]);
+        const double3 hi = make_double3(mp->box_hi[0], mp->box_hi[1], mp->box_hi[2]);
+        if (L.n <= kSmallMax) {
+            // about kSrGroups workgroups: every one fills a table of its own
+            const int64_t all = (L.n + kSrAtOnce - 1) / kSrAtOnce, share = L.B < kSrGroups ? kSrGroups / L.B : 1;
+            const int per_system = (int)(share < all ? share : all);
+            hipLaunchKernelGGL(k_wca_small, dim3((unsigned)(L.B * per_system)), dim3(kSrThreads), 0, ss, w.codes,
+                               w.bbox, w.spos, w.perm, w.md_force, (int)L.n, L.ntot, per_system, L.cell_lcap,
+                               mp->wca_sigma, mp->wca_eps, c12, rc, rcw, lo, hi);
+        } else {
+            const int64_t ncell = L.B * L.cell_T;
+            hipLaunchKernelGGL(k_clear_cells, dim3(grid_for(ncell, 256, 2048)), dim3(256), 0, ss, w.cells, ncell);
+            hipLaunchKernelGGL(k_cell_fill, dim3(grid_for(L.ntot, 256)), dim3(256), 0, ss, w.codes, w.bbox, L.n,
+                               L.ntot, rc, L.cell_lcap, L.cell_T, w.cells);
+            hipLaunchKernelGGL(k_wca, dim3(grid_for(L.ntot, 256)), dim3(256), 0, ss, w.codes, w.bbox, w.cells, w.spos,
+                               w.perm, w.md_force, L.n, L.ntot, L.cell_lcap, L.cell_T, mp->wca_sigma, mp->wca_eps, c12,
+                               rc, rcw, lo, hi);
+        }
         hipError_t e2 = hipGetLastError();
         if (e2 == hipSuccess && fork) e2 = hipEventRecord(h.join_ev, ss);
         return e2;

@@ -141,6 +141,41 @@ def test_paper_short_range_law(batch, sr_cut):
         assert err <= 1e-11, (key, err)
 
 
+@pytest.mark.parametrize("n,batch,sr_cut", [(1, 2, 0.0), (2, 1, 0.0), (64, 3, 0.0), (65, 1, 0.0), (1023, 1, 0.0),
+                                            (1024, 1, 0.0), (1025, 2, 3.0), (33, 1100, 0.0), (1000, 1, 60.0),
+                                            (4096, 1, 0.0), (4097, 1, 0.0)])
+def test_short_range_of_small_systems(n, batch, sr_cut):
+    """Up to 4096 particles 8 lanes share a particle and a workgroup takes 64 at once: one particle, the edges of a
+    round, the grid's levels, more systems than workgroups are asked for, a cut-off as wide as the box (every
+    partner a candidate from one cell), and the last size with the first that takes one thread per particle.  The
+    sums differ from the reference's in order only; one FP64 step, to the bound of the tests above."""
+    rng = np.random.default_rng(n + batch)
+    side = max(4.0, 2.5 * n ** (1.0 / 3.0))
+    pos, mom = workloads.rsa_chains(rng, n, (0.0, 0.0, 0.0), (side, side, side))
+    rows = min(batch, 3)  # further systems repeat these
+    shift = rng.standard_normal((rows, 3, n)) * 0.01
+    pick = np.arange(batch) % rows
+    st = dict(pos=(pos[None] + shift)[pick], vel=rng.standard_normal((rows, 3, n))[pick],
+              mom=np.repeat(mom[None], batch, 0), omega=rng.standard_normal((rows, 3, n))[pick])
+    p = _params(side)
+    p["kT"] = 0.0
+    p["hext"] = np.tile(p["hext"], (batch, 1))
+    p["sr_kind"], p["sr_cut"] = (1, sr_cut) if sr_cut else (0, 0.0)
+    bh = BarnesHut(n, batch, 16, 0.5, "fp64")
+    d = _to_dev(st)
+    he = torch.from_numpy(p["hext"]).cuda()
+    mp = _mdp(p, he)
+    mp.sr_kind, mp.sr_cut = p["sr_kind"], p["sr_cut"]
+    bh.md_step(d, mp)
+    few = dict(p, hext=p["hext"][:rows])
+    ref = omd.md_step({k: v[:rows] for k, v in st.items()}, few, 0, theta=0.5, leaf=16)
+    assert bh.check_status() == 0
+    for key in ("pos", "vel", "mom", "omega"):
+        g = d[key].cpu().numpy()
+        err = np.abs(g - ref[key][pick]).max() / np.abs(ref[key]).max()
+        assert err <= 1e-11, (key, err)
+
+
 def test_short_range_law_argument_checks():
     """An unknown law or a negative or non-finite cut-off is rejected before anything is enqueued."""
     w = workloads.uniform_cube(256, 10.0, seed=3)

@@ -10,6 +10,7 @@
 // Scatters are reduced across the wave before one FP64 atomic per value.  The records hold the sums of
 // +g (S_C = -B_C for a cell, the sum of g over a source's partners for a particle), and the downward pass
 // subtracts them, so the scattered values need no negation.
+#include "downward.h"
 #include "traverse.h"
 
 namespace ffbh {
@@ -238,7 +239,7 @@ __device__ __forceinline__ void adjoint_wave(int gw, int split_shift, FFBH_ADJ_P
     const int lane = threadIdx.x & (kWave - 1);
     const int wcomp = total6_comp(lane);
     // a wave owns tpw consecutive targets (lanes at and above tpw stay idle) and, with parts > 1, walks
-    // the subtree of one child of the root (part p: child p); the parts' sums meet in k_parts_sum
+    // the subtree of one child of the root (part p: child p); the parts' sums meet in downward()
     const int per_seg = waves_per_seg * parts;
     const int seg = gw / per_seg;
     const int grp = (gw - seg * per_seg) / parts, part = gw - seg * per_seg - grp * parts;
@@ -619,145 +620,23 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_waves(const uint32_t *_
     if (t == 0) work_ctr[seg] = 0u;
 }
 
-// Sum of the parts of a split adjoint walk for every target, in part order (so the result does not depend
-// on scheduling): gathered dL/dr, forward field (sorted order and caller order), and per-wave energy
-// partials of 64 targets.  Grid: (ceil(n / 256), B) workgroups of 256.
-__global__ __launch_bounds__(256) void k_parts_sum(const double *__restrict__ part_buf, int parts,
-                                                   const double *__restrict__ smom, const double *__restrict__ hext,
-                                                   const uint32_t *__restrict__ perm, double *__restrict__ g_gather,
-                                                   double *__restrict__ Hs, double *__restrict__ Hout,
-                                                   double *__restrict__ e_part, int64_t n, int64_t ntot)
+__global__ __launch_bounds__(256) void k_adj_setup(AdjSetup a)
 {
-    const int64_t local = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int seg = blockIdx.y;
-    const bool valid = local < n;
-    const int64_t si = (int64_t)seg * n + (valid ? local : 0);
-    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (valid)
-        for (int p = 0; p < parts; ++p)
-#pragma unroll
-            for (int c = 0; c < 6; ++c) v[c] += part_buf[((int64_t)p * 6 + c) * ntot + si];
-    double e = 0.0;
-    if (valid) {
-        const double mx = smom[si], my = smom[ntot + si], mz = smom[2 * ntot + si];
-        e = -0.5 * (mx * v[3] + my * v[4] + mz * v[5]);
-        if (hext) e -= mx * hext[3 * seg] + my * hext[3 * seg + 1] + mz * hext[3 * seg + 2];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            g_gather[c * ntot + si] = v[c];
-            Hs[c * ntot + si] = v[3 + c];
-        }
-        const int64_t i = (int64_t)perm[si] - (int64_t)seg * n;
-        if (Hout && i >= 0 && i < n) {
-            double *out = Hout + (int64_t)seg * 3 * n;
-            out[i] = v[3];
-            out[n + i] = v[4];
-            out[2 * n + i] = v[5];
-        }
-    }
-    e = wave_sum(e);
-    const int64_t wps = (n + kWave - 1) / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0 && local < n) e_part[(int64_t)seg * wps + local / kWave] = e;
+    adj_setup(a, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
-// Before the fused walk, in one launch: the upstream field gradient in sorted order, Hbar = gH - 1/2 gE m, and
-// zeros in the adjoint records of the particles (g_rm) and of the nodes the last build made (their counts are
-// on the device; node_adjq is null without order-2 cells).  Bound by the writes, 104 B a particle and 64 B a
-// node (2^20 particles: about 25 us); as three launches small systems paid 9 us more.
-__global__ __launch_bounds__(256) void k_adj_setup(const double *__restrict__ gH, const double *__restrict__ gE,
-                                                   const double *__restrict__ smom, const uint32_t *__restrict__ perm,
-                                                   int64_t n, int64_t ntot, double *__restrict__ hbar,
-                                                   double *__restrict__ g_rm, double *__restrict__ node_adj,
-                                                   double *__restrict__ node_adjq, const uint32_t *__restrict__ nn,
-                                                   int64_t max_nodes, const int32_t *__restrict__ per_system)
+// Gradients of the sorted particles, to caller order: one thread each, five waves per SIMD to hide the path's loads
+// (2^20 particles 80 us, bound by the six scattered stores; one path per distinct leaf instead took 73).
+__global__ __launch_bounds__(256, 5) void k_downward(Downward a, double *__restrict__ dpos, double *__restrict__ dmom)
 {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
-    for (int64_t s = t; s < ntot; s += stride) {
-        const int64_t o = perm[s], b = o / n, i = o - b * n;
-        if (o >= ntot) continue;
-        const double ge = gE ? gE[b] : 0.0;
-        for (int a = 0; a < 3; ++a) {
-            double v = gH ? gH[b * 3 * n + a * n + i] : 0.0;
-            v += -0.5 * ge * smom[a * ntot + s];
-            hbar[a * ntot + s] = v;
-        }
-    }
-    for (int64_t i = t; i < 8 * ntot; i += stride) g_rm[i] = 0.0;
-    if (per_system) {
-        // small systems: the roots, then 2 n node places per system of which the first per_system[b] are used
-        const int64_t B = ntot / n;
-        for (int64_t i = t; i < 8 * (B + 2 * ntot); i += stride) {
-            const int64_t k = i / 8 - B, b = k / (2 * n);
-            if (k >= 0 && k - 2 * n * b >= (int64_t)per_system[b]) continue;
-            node_adj[i] = 0.0;
-            if (node_adjq) node_adjq[i] = 0.0;
-        }
-        return;
-    }
-    const int64_t len = 8 * ((int64_t)*nn < max_nodes ? (int64_t)*nn : max_nodes);
-    for (int64_t i = t; i < len; i += stride) node_adj[i] = 0.0;
-    if (node_adjq)
-        for (int64_t i = t; i < len; i += stride) node_adjq[i] = 0.0;
-}
-
-// Downward pass and output: members collect their cells' adjoints along the leaf-to-root path; the
-// explicit derivative of E in m (-1/2 H - H_ext, times dL/dE) is added; results go to caller order.
-// With order-2 cells (node_adjq not null) a member j of cell C also receives, through
-// D_C = sum (r_j - c_C) m_j^T and c_C = the members' mean, dL/dr_j += E_C m_j - E_C M_C / n_C and
-// dL/dm_j += E_C (r_j - c_C) (E_C symmetric, stored as xx, yy, zz, xy, xz, yz).
-__global__ __launch_bounds__(256) void k_downward(
-    const NodeRec *__restrict__ nodes, const int32_t *__restrict__ leaf_of, const double *__restrict__ node_adj,
-    const double *__restrict__ g_gather, const double *__restrict__ g_rm, const double *__restrict__ Hs,
-    const double *__restrict__ hext, const double *__restrict__ gE,
-    const uint32_t *__restrict__ perm, int64_t n, int64_t ntot, double *__restrict__ dpos,
-    double *__restrict__ dmom, int64_t max_nodes, const double *__restrict__ node_adjq,
-    const double *__restrict__ node_m64, const double *__restrict__ spos, const double *__restrict__ smom)
-{
-    int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= ntot) return;
-    double Ax = 0.0, Ay = 0.0, Az = 0.0, Bx = 0.0, By = 0.0, Bz = 0.0;
-    double qr[3] = {0.0, 0.0, 0.0}, qm[3] = {0.0, 0.0, 0.0};
-    double rj[3] = {0.0, 0.0, 0.0}, mj[3] = {0.0, 0.0, 0.0};
-    if (node_adjq) {
-        for (int a = 0; a < 3; ++a) {
-            rj[a] = spos[a * ntot + s];
-            mj[a] = smom[a * ntot + s];
-        }
-    }
-    int node = leaf_of[s];
-    for (int depth = 0; node >= 0 && node < max_nodes && depth < 2 * kMaxLevel + 2; ++depth) {
-        const double *a = node_adj + 8 * (int64_t)node;
-        const NodeRec nd = nodes[node];
-        const double inv = 1.0 / (double)nd.count;
-        Ax += a[0]; Ay += a[1]; Az += a[2];
-        Bx += a[3] * inv; By += a[4] * inv; Bz += a[5] * inv;
-        if (node_adjq) {
-            const double *e = node_adjq + 8 * (int64_t)node;
-            const double E[3][3] = {{e[0], e[3], e[4]}, {e[3], e[1], e[5]}, {e[4], e[5], e[2]}};
-            const double *M = node_m64 + 4 * (int64_t)node;
-            const double d[3] = {rj[0] - nd.cx, rj[1] - nd.cy, rj[2] - nd.cz};
-            for (int k = 0; k < 3; ++k) {
-                qr[k] += E[k][0] * (mj[0] - M[0] * inv) + E[k][1] * (mj[1] - M[1] * inv) +
-                         E[k][2] * (mj[2] - M[2] * inv);
-                qm[k] += E[k][0] * d[0] + E[k][1] * d[1] + E[k][2] * d[2];
-            }
-        }
-        node = nd.parent;
-    }
-    const int64_t o = perm[s], b = o / n, i = o - b * n;
-    if (o >= ntot) return;
-    const double ge = gE ? gE[b] : 0.0;
-    const double *he = hext ? hext + 3 * b : nullptr;
-    double *dp = dpos + b * 3 * n, *dm = dmom + b * 3 * n;
-    const double *q = g_rm + 8 * s;
-    dp[i] = g_gather[s] - q[0] - Bx + qr[0];
-    dp[n + i] = g_gather[ntot + s] - q[1] - By + qr[1];
-    dp[2 * n + i] = g_gather[2 * ntot + s] - q[2] - Bz + qr[2];
-    double ex = -0.5 * Hs[s], ey = -0.5 * Hs[ntot + s], ez = -0.5 * Hs[2 * ntot + s];
-    if (he) { ex -= he[0]; ey -= he[1]; ez -= he[2]; }
-    dm[i] = q[3] + Ax + ge * ex + qm[0];
-    dm[n + i] = q[4] + Ay + ge * ey + qm[1];
-    dm[2 * n + i] = q[5] + Az + ge * ez + qm[2];
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (s >= a.ntot) return;
+    const int64_t o = a.perm[s], b = o / a.n, i = o - b * a.n;
+    if (o >= a.ntot) return;
+    double dr[3], dm[3];
+    downward<false>(a, s, b, dr, dm);
+    for (int k = 0; k < 3; ++k) dpos[b * 3 * a.n + k * a.n + i] = dr[k];
+    for (int k = 0; k < 3; ++k) dmom[b * 3 * a.n + k * a.n + i] = dm[k];
 }
 
 // dL/dH_ext = -dL/dE * sum_i m_i: partial sums of a system's moments over nb workgroups, then one wave per
@@ -833,7 +712,7 @@ void launch_order_waves(Handle &h, hipStream_t s)
 
 hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext, const double *d_gH,
                            const double *d_gE, double *d_dpos, double *d_dmom, double *d_dhext, hipStream_t s,
-                           double *d_H, double *d_E, bool moments_done, bool order_done, bool enter)
+                           bool moments_done, bool order_done, bool setup_done, bool enter)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
@@ -842,9 +721,8 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
         if (e != hipSuccess) return e;
     }
     const bool quad = L.expansion == 2;
-    hipLaunchKernelGGL(k_adj_setup, dim3(grid_for(L.ntot, 256, 4096)), dim3(256), 0, s, d_gH, d_gE, w.smom, w.perm, L.n,
-                       L.ntot, w.hbar, w.g_rm, w.node_adj, quad ? w.node_adjq : nullptr, w.status + 2, L.max_nodes,
-                       L.n <= kSmallMax ? w.top_nodes : nullptr);
+    if (!setup_done)
+        hipLaunchKernelGGL(k_adj_setup, dim3(grid_for(L.ntot, 256, 4096)), dim3(256), 0, s, adj_setup_args(h, d_gH, d_gE));
     const int wpb = h.waves_per_block;
     const double theta2 = h.p.theta * h.p.theta;
     if (h.ev[2]) (void)hipEventRecord(h.ev[2], s);
@@ -871,14 +749,14 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
 #define FFBH_ADJ(MX, QD, SC, T)                                                                                 \
     hipLaunchKernelGGL((k_adjoint<MX, QD, SC>), dim3(grid), dim3(wpb * kWave), (adj_lds_bytes<T, false>(wpb)), s, w.nodes, \
                        w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext, w.g_gather,    \
-                       w.g_rm, w.node_adj, w.Hs, d_H, w.e_part, w.status, L.n, L.ntot, wps, nwv, theta2,          \
+                       w.g_rm, w.node_adj, w.Hs, nullptr, w.e_part, w.status, L.n, L.ntot, wps, nwv, theta2,          \
                        (int)L.max_nodes, tpw, parts, w.part_buf, cost, nq, w.node_adjq, tgt, inside, ord, ctr)
         int shift = 0;
         const int W = adjoint_split(h, shift);
 #define FFBH_ADJ_SPLIT(MX, QD, SC, T)                                                                            \
     hipLaunchKernelGGL((k_adjoint_split<MX, QD, SC>), dim3((unsigned)nwv), dim3(W * kWave), (adj_lds_bytes<T, true>(W)), \
                        s, w.nodes, w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext,    \
-                       w.g_gather, w.g_rm, w.node_adj, w.Hs, d_H, w.e_part, w.status, L.n, L.ntot, wps, nwv,      \
+                       w.g_gather, w.g_rm, w.node_adj, w.Hs, nullptr, w.e_part, w.status, L.n, L.ntot, wps, nwv,      \
                        theta2, (int)L.max_nodes, tpw, parts, w.part_buf, nullptr, nq, w.node_adjq, tgt, inside, shift)
         if (W > 1) {
             if (scaled) {
@@ -905,17 +783,11 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
         }
 #undef FFBH_ADJ
 #undef FFBH_ADJ_SPLIT
-        if (parts > 1)
-            hipLaunchKernelGGL(k_parts_sum, dim3((unsigned)((L.n + 255) / 256), (unsigned)L.B), dim3(256), 0, s,
-                               w.part_buf, parts, w.smom, d_hext, w.perm, w.g_gather, w.Hs, d_H, w.e_part, L.n,
-                               L.ntot);
     }
     if (h.ev[3]) (void)hipEventRecord(h.ev[3], s);
-    if (d_E)
-        launch_energy_final(h, d_E, s, h.adj_parts > 1 ? kWave : h.adj_tpw);
-    hipLaunchKernelGGL(k_downward, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, w.nodes, w.leaf_of, w.node_adj,
-                       w.g_gather, w.g_rm, w.Hs, d_hext, d_gE, w.perm, L.n, L.ntot, d_dpos, d_dmom,
-                       L.max_nodes, quad ? w.node_adjq : nullptr, w.node_m64, w.spos, w.smom);
+    if (d_dpos)
+        hipLaunchKernelGGL(k_downward, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, downward_args(h, d_hext, d_gE),
+                           d_dpos, d_dmom);
     if (d_dhext) {
         // the build's partial boxes are free here
         const int nb = (int)(L.n < 256 * kBboxBlocks ? (L.n + 255) / 256 : kBboxBlocks);

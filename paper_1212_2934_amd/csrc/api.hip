@@ -461,7 +461,7 @@ bh_status bh_field_backward(bh_handle *hh, const double *d_mom, const double *d_
         return BH_EINVAL;
     if (!hh->h.built) return BH_ESTATE;
     const hipStream_t s = (hipStream_t)stream;
-    if (launch_backward(hh->h, d_mom, d_hext, d_gH, d_gE, d_dpos, d_dmom, d_dhext, s, nullptr, nullptr, false, false,
+    if (launch_backward(hh->h, d_mom, d_hext, d_gH, d_gE, d_dpos, d_dmom, d_dhext, s, false, false, false,
                         true) != hipSuccess)
         return BH_EDEVICE;
     launch_leave(hh->h.w.status, s);

@@ -242,10 +242,12 @@ hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, do
                         double *d_E, hipStream_t s, bool enter = false, bool leave = false);
 // moments_done: the build already summed the moments (launch_build with d_mom).
 // order_done: the wave order of the persistent launch was already enqueued (launch_order_waves).
+// setup_done: the walk's inputs and zeros (adj_setup) are there.  Without d_dpos the caller collects the gradients
+// (downward) itself.
 hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext, const double *d_gH,
                            const double *d_gE, double *d_dpos, double *d_dmom, double *d_dhext,
-                           hipStream_t s, double *d_H = nullptr, double *d_E = nullptr, bool moments_done = false,
-                           bool order_done = false, bool enter = false);
+                           hipStream_t s, bool moments_done = false, bool order_done = false,
+                           bool setup_done = false, bool enter = false);
 // Whether the fused traversal of this handle runs the persistent, cost-ordered launch, and the launch
 // that orders its items from the costs the previous traversal recorded.
 bool uses_wave_order(const Handle &h);

@@ -12,6 +12,7 @@
 // centre-to-face distance with sigma_w = sigma / 2.
 // Thermal noise: Philox4x32-10 (Salmon et al., SC'11) keyed by (seed, system), counter (step, particle,
 // draw), mapped to normals by the Box-Muller transform.
+#include "downward.h"
 #include "traverse.h"
 
 namespace ffbh {
@@ -227,8 +228,17 @@ constexpr int64_t kSrGroups = 512;
 __global__ __launch_bounds__(kSrThreads) void k_wca_small(
     const uint64_t *__restrict__ codes, const double *__restrict__ bbox, const double *__restrict__ spos,
     const uint32_t *__restrict__ perm, double *__restrict__ F, int n, int64_t ntot, int per_system, int lcap,
-    double sigma, double eps, double c12, double rc, double rcw, double3 box_lo, double3 box_hi)
+    double sigma, double eps, double c12, double rc, double rcw, double3 box_lo, double3 box_hi, AdjSetup setup,
+    uint64_t *step, uint32_t *status, uint32_t finish_groups)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        // for k_finish_small, whose workgroups then need no order among themselves: the step counter is advanced
+        // here, and the call counted in once for each of them
+        *step += 1ull;
+        atomicAdd(status + kStatusInFlight, finish_groups - 1u);
+    }
+    // the walk's inputs and zeros: a launch less (6 us)
+    if (setup.hbar) adj_setup(setup, (int64_t)blockIdx.x * kSrThreads + threadIdx.x, (int64_t)gridDim.x * kSrThreads);
     __shared__ ushort2 tab[1 << (3 * kSrLevel)];
     const int t = threadIdx.x, k = t & (kSrLanes - 1);
     const int64_t b = blockIdx.x / per_system, base = b * n;
@@ -322,17 +332,40 @@ struct MDConst {
     uint64_t seed;
 };
 
-__global__ __launch_bounds__(256) void k_integrate(double *__restrict__ pos, double *__restrict__ vel,
-                                                   double *__restrict__ mom, double *__restrict__ omega,
-                                                   const double *__restrict__ dEdr, const double *__restrict__ dEdm,
-                                                   const double *__restrict__ Fsr, const uint64_t *__restrict__ d_step,
-                                                   int64_t n, int64_t ntot, MDConst c)
+struct MDState {
+    double *pos, *vel, *mom, *omega;
+    uint64_t *step;
+};
+
+// One particle's state and its short-range force.
+struct Particle {
+    double r[3], v[3], m[3], w[3], f[3];
+};
+
+__device__ inline Particle load_particle(const MDState &st, const double *__restrict__ Fsr, int64_t n, int64_t b,
+                                         int64_t i)
 {
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= ntot) return;
-    const int64_t b = g / n, i = g - b * n;
+    Particle p;
+    for (int a = 0; a < 3; ++a) {
+        const int64_t o = (3 * b + a) * n + i;
+        p.r[a] = st.pos[o];
+        p.v[a] = st.vel[o];
+        p.m[a] = st.mom[o];
+        p.w[a] = st.omega[o];
+        p.f[a] = Fsr[o];
+    }
+    return p;
+}
+
+// One Euler-Maruyama update of particle i of system b from the energy's gradients dr, dm.
+__device__ inline void integrate(const MDState &st, const Particle &p, const MDConst &c, uint64_t step, int64_t n,
+                                 int64_t b, int64_t i, const double dr[3], const double dm[3])
+{
+    double *pos = st.pos, *vel = st.vel, *mom = st.mom, *omega = st.omega;
+    const double *r = p.r, *v = p.v, *m = p.m, *w = p.w;
+    const double F[3] = {-dr[0] + p.f[0], -dr[1] + p.f[1], -dr[2] + p.f[2]};
+    const double He[3] = {-dm[0], -dm[1], -dm[2]};
     const int64_t o = b * 3 * n + i;  // x component; y at +n, z at +2n
-    const uint64_t step = *d_step;
     // noise: two Philox blocks -> eight normals, six used
     const uint32_t k0 = (uint32_t)c.seed, k1 = (uint32_t)(c.seed >> 32) ^ (uint32_t)b;
     const U4 q0 = philox4x32_10(U4{(uint32_t)step, (uint32_t)(step >> 32), (uint32_t)i, 0u}, k0, k1);
@@ -343,12 +376,6 @@ __global__ __launch_bounds__(256) void k_integrate(double *__restrict__ pos, dou
     box_muller(q1.x, q1.y, xi[4], xi[5]);
     box_muller(q1.z, q1.w, xi[6], xi[7]);
 
-    const double r[3] = {pos[o], pos[o + n], pos[o + 2 * n]};
-    const double v[3] = {vel[o], vel[o + n], vel[o + 2 * n]};
-    const double m[3] = {mom[o], mom[o + n], mom[o + 2 * n]};
-    const double w[3] = {omega[o], omega[o + n], omega[o + 2 * n]};
-    const double F[3] = {-dEdr[o] + Fsr[o], -dEdr[o + n] + Fsr[o + n], -dEdr[o + 2 * n] + Fsr[o + 2 * n]};
-    const double He[3] = {-dEdm[o], -dEdm[o + n], -dEdm[o + 2 * n]};
     const double tq[3] = {m[1] * He[2] - m[2] * He[1], m[2] * He[0] - m[0] * He[2], m[0] * He[1] - m[1] * He[0]};
     const double at = sqrt(2.0 * c.gamma_t * c.kT * c.dt) / c.mass;
     const double ar = sqrt(2.0 * c.gamma_r * c.kT * c.dt) / c.inertia;
@@ -375,6 +402,37 @@ __global__ __launch_bounds__(256) void k_integrate(double *__restrict__ pos, dou
         omega[o + a * n] = wn[a];
         mom[o + a * n] = mn[a] / ml;
     }
+}
+
+__global__ __launch_bounds__(256) void k_integrate(MDState st, const double *__restrict__ dEdr,
+                                                   const double *__restrict__ dEdm, const double *__restrict__ Fsr,
+                                                   int64_t n, int64_t ntot, MDConst c)
+{
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= ntot) return;
+    const int64_t b = g / n, i = g - b * n, o = b * 3 * n + i;
+    const double dr[3] = {dEdr[o], dEdr[o + n], dEdr[o + 2 * n]}, dm[3] = {dEdm[o], dEdm[o + n], dEdm[o + 2 * n]};
+    integrate(st, load_particle(st, Fsr, n, b, i), c, *st.step, n, b, i, dr, dm);
+}
+
+// The end of a small system's step in one launch: downward pass and integrator (k_wca_small has advanced the step
+// counter).  Bound by latency: 1000 particles 19 us in four launches (parts, downward, integrate, count) -> 12; at 64
+// systems of 1000 the scattered state costs what the launches save (20 -> 19).  Large systems keep them apart: the
+// state is read and written here in sorted order, scattered over caller order.
+__global__ __launch_bounds__(256) void k_finish_small(Downward a, MDState st, const double *__restrict__ Fsr,
+                                                      MDConst c, uint32_t *status)
+{
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint64_t step = *st.step - 1ull;  // counted by k_wca_small
+    const int64_t o = s < a.ntot ? (int64_t)a.perm[s] : a.ntot;
+    if (o < a.ntot) {
+        const int64_t b = o / a.n, i = o - b * a.n;
+        const Particle p = load_particle(st, Fsr, a.n, b, i);  // in flight beside the path
+        double dr[3], dm[3];
+        downward<true>(a, s, b, dr, dm);
+        integrate(st, p, c, step, a.n, b, i, dr, dm);
+    }
+    if (threadIdx.x == 0) call_leave(status);  // counted in once per workgroup
 }
 
 // The step's last kernel: the device step counter, and the call counted out (call_leave).
@@ -414,16 +472,23 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
     const double c12 = lj ? 1.0 : 2.0;
     const double rc = lj ? (mp->sr_cut > 0.0 ? mp->sr_cut : 2.5 * mp->wca_sigma) : wca_rc * mp->wca_sigma;
     const double rcw = lj ? 0.5 * rc : wca_rc * 0.5 * mp->wca_sigma;
+    // Small systems: the set-up of the walk runs with the short-range forces, and k_finish_small ends the step.
+    // The order-2 moments come after the short-range forces and sum in the node adjoints, so there the walk's
+    // zeros have to wait.
+    const bool small = L.n <= kSmallMax, setup_early = small && L.expansion != 2;
     const SortedWork short_range = [&](hipStream_t ss) {
         const double3 lo = make_double3(mp->box_lo[0], mp->box_lo[1], mp->box_lo[2]);
         const double3 hi = make_double3(mp->box_hi[0], mp->box_hi[1], mp->box_hi[2]);
         if (L.n <= kSmallMax) {
+            AdjSetup setup = adj_setup_args(h, nullptr, w.ones);
+            if (!setup_early) setup.hbar = nullptr;
             // about kSrGroups workgroups: every one fills a table of its own
             const int64_t all = (L.n + kSrAtOnce - 1) / kSrAtOnce, share = L.B < kSrGroups ? kSrGroups / L.B : 1;
             const int per_system = (int)(share < all ? share : all);
             hipLaunchKernelGGL(k_wca_small, dim3((unsigned)(L.B * per_system)), dim3(kSrThreads), 0, ss, w.codes,
                                w.bbox, w.spos, w.perm, w.md_force, (int)L.n, L.ntot, per_system, L.cell_lcap,
-                               mp->wca_sigma, mp->wca_eps, c12, rc, rcw, lo, hi);
+                               mp->wca_sigma, mp->wca_eps, c12, rc, rcw, lo, hi, setup,
+                               st->d_step, w.status, (uint32_t)grid_for(L.ntot, 256));
         } else {
             const int64_t ncell = L.B * L.cell_T;
             hipLaunchKernelGGL(k_clear_cells, dim3(grid_for(ncell, 256, 2048)), dim3(256), 0, ss, w.cells, ncell);
@@ -446,13 +511,19 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
         if (e != hipSuccess) return e;
     }
     if (fork && (e = hipStreamWaitEvent(s, h.join_ev, 0)) != hipSuccess) return e;
-    e = launch_backward(h, st->mom, mp->d_hext, nullptr, w.ones, w.md_grad_r, w.md_grad_m, nullptr, s, nullptr,
-                        nullptr, true, order);
+    e = launch_backward(h, st->mom, mp->d_hext, nullptr, w.ones, small ? nullptr : w.md_grad_r, w.md_grad_m, nullptr, s,
+                        true, order, setup_early);
     if (e != hipSuccess) return e;
-    MDConst c{mp->dt, mp->kT, mp->gamma_t, mp->gamma_r, mp->mass, mp->inertia, mp->seed};
-    hipLaunchKernelGGL(k_integrate, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, st->pos, st->vel, st->mom,
-                       st->omega, w.md_grad_r, w.md_grad_m, w.md_force, st->d_step, L.n, L.ntot, c);
-    hipLaunchKernelGGL(k_step_inc, dim3(1), dim3(64), 0, s, st->d_step, w.status);
+    const MDConst c{mp->dt, mp->kT, mp->gamma_t, mp->gamma_r, mp->mass, mp->inertia, mp->seed};
+    const MDState state{st->pos, st->vel, st->mom, st->omega, st->d_step};
+    if (small) {
+        hipLaunchKernelGGL(k_finish_small, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s,
+                           downward_args(h, mp->d_hext, w.ones), state, w.md_force, c, w.status);
+    } else {
+        hipLaunchKernelGGL(k_integrate, dim3(grid_for(L.ntot, 256)), dim3(256), 0, s, state, w.md_grad_r, w.md_grad_m,
+                           w.md_force, L.n, L.ntot, c);
+        hipLaunchKernelGGL(k_step_inc, dim3(1), dim3(64), 0, s, st->d_step, w.status);
+    }
     return hipGetLastError();
 }
 

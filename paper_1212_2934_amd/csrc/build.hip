@@ -800,6 +800,22 @@ __global__ __launch_bounds__(kOctThreads) void k_oct_emit(const uint64_t *__rest
 // above 2^16 nodes, 50-60 us for a few us of work), is now two.
 // ------------------------------------------------------------------------------------------------
 
+// A node's centroid and s^2 from its position sums (bb: its system's cube), and its moments.
+__device__ inline void up_centre(NodeRec &nd, int level, const double *bb, double sx, double sy, double sz)
+{
+    const double cnt = (double)nd.count;
+    const double side = __builtin_ldexp(bb[3], -level);
+    nd.cx = sx / cnt;
+    nd.cy = sy / cnt;
+    nd.cz = sz / cnt;
+    nd.s2 = side * side * bb[5];  // bb[5]: 1, or 1 / theta^2 for the scaled acceptance test
+}
+__device__ inline void up_moment(NodeRec &nd, double *m64, double mx, double my, double mz)
+{
+    m64[0] = mx; m64[1] = my; m64[2] = mz;
+    nd.mx = (float)mx; nd.my = (float)my; nd.mz = (float)mz;
+}
+
 // MODE 0: member positions -> centroids and s^2; MODE 1: member moments -> FP64 and FP32 moment sums;
 // MODE 2: both in one pass (vals = positions, vals2 = moments).  Child sums are read from `sums` (8 doubles
 // per node: position sums at 0..2, moment sums at 4..6).
@@ -890,23 +906,8 @@ __device__ inline void upward_node(int id, const NodeRec &nd, const double *__re
         sums[8 * id + 5] = my;
         sums[8 * id + 6] = mz;
     }
-    if (MODE == 0 || MODE == 2) {
-        const double cnt = (double)nd.count;
-        nodes[id].cx = sx / cnt;
-        nodes[id].cy = sy / cnt;
-        nodes[id].cz = sz / cnt;
-        const double *bb = bbox + 8 * (nd.first / n);
-        const double side = __builtin_ldexp(bb[3], -node_level[id]);
-        nodes[id].s2 = side * side * bb[5];  // bb[5]: 1, or 1 / theta^2 for the scaled acceptance test
-    }
-    if (MODE != 0) {
-        node_m64[4 * id] = mx;
-        node_m64[4 * id + 1] = my;
-        node_m64[4 * id + 2] = mz;
-        nodes[id].mx = (float)mx;
-        nodes[id].my = (float)my;
-        nodes[id].mz = (float)mz;
-    }
+    if (MODE == 0 || MODE == 2) up_centre(nodes[id], node_level[id], bbox + 8 * (nd.first / n), sx, sy, sz);
+    if (MODE != 0) up_moment(nodes[id], node_m64 + 4 * (int64_t)id, mx, my, mz);
 }
 
 constexpr int kUpThreads = 1024;
@@ -938,7 +939,8 @@ struct UpList {
     int count, lmin, lmax;
 };
 
-__device__ inline void up_reset(UpList &S)
+template <typename List>
+__device__ inline void up_reset(List &S)
 {
     if (threadIdx.x == 0) {
         S.count = 0;
@@ -1143,32 +1145,42 @@ __device__ inline void pack_source(double *r, bool mixed, double x, double y, do
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallItems = kSmallMax / kSmallThreads;  // particles per thread
 
-// LDS of k_build_small, 57 KB: the sort's keys and values (ping-pong), then the codes in the keys' place, the cell
-// masks in the values' and the scan in the counts'.
+// LDS of k_build_small: the sort's keys and values (ping-pong in the counting passes), then the codes in the keys'
+// place and, in the values', the list of cell starts and their cells' keys; the cell masks and their scan.
 struct SmallSort {
     union {
         uint32_t key[2][kSmallMax];  // 31 or 32 bits of the codes
         uint64_t code[kSmallMax];
     };
-    union {
-        uint16_t val[2][kSmallMax];  // index in the system
-        uint32_t mask[kSmallMax];
-    };
+    uint16_t val[2][kSmallMax];  // index in the system
     union {
         uint16_t wcnt[kSmallThreads / kWave][kRadixBins];
         uint16_t scan[kSmallMax];
-        int8_t win[kSmallMax];
     };
+    uint32_t mask[kSmallMax];
     uint32_t lstart[kRadixBins];
     uint32_t dsum[kSmallThreads / kWave];
     double box[kSmallThreads / kWave][6];
-    int flag;
+    int starts, flag;
+};
+// Sums and split cells of a system of at most kSumNodes nodes, for its upward pass.
+constexpr int kSumNodes = 1024;
+struct SumList {
+    double sum[kSumNodes][6];  // position sums, moment sums
+    uint16_t from[kSumNodes], len[kSumNodes];  // leaf: first member and count; else first child and children
+    uint16_t cell[kSumNodes];                  // the split cells
+    uint8_t lev[kSumNodes], leaf[kSumNodes];
+    int count, lmin, lmax;
+};
+union SmallUp {
+    UpList list;
+    SumList sums;
 };
 union SmallLds {
     SmallSort s;
-    UpList up;  // the upward pass's cells, once the tree is written
+    SmallUp up;  // the upward pass, once the tree is written
 };
-static_assert(sizeof(SmallLds) <= 65536, "LDS of k_build_small");
+static_assert(sizeof(SmallLds) <= 81920, "two workgroups of k_build_small share a CU's LDS");
 static_assert(kSmallThreads / kWave * kRadixBins >= kSmallMax, "the scan fits the counts");
 static_assert(kSmallThreads == 4 * kRadixBins && kSmallThreads / kWave == 16, "four threads per digit, sixteen waves");
 
@@ -1243,89 +1255,111 @@ __device__ inline void small_pass(SmallSort &S, int n, int src, int shift)
     __syncthreads();
 }
 
-struct SmallArgs {
-    const double *pos, *mom;
-    int n, leaf, enter, hilbert, mixed;
-    int64_t ntot, B, max_nodes;
-    double s2_scale;
-    double *bbox, *spos, *smom, *src, *sums, *node_m64;
-    uint64_t *codes;
-    uint32_t *perm, *tgt_order, *status;
-    NodeRec *nodes;
-    int32_t *node_level, *leaf_of, *top;
-};
-
-// Upward pass of one system whose `total` nodes below the root start at id base.
-template <int MODE>
-__device__ inline void small_upward(UpList &U, int64_t b, int64_t base, int64_t total, const double *vals,
-                                    const double *vals2, const SmallArgs &a, double *q64, float *q32)
+// The value of lane l ^ M, by row and half-row moves where there is one.
+template <int M>
+__device__ inline uint32_t lane_xor(uint32_t v)
 {
-    up_reset(U);
-    up_leaves<MODE>(U, b, base, min(base + total, a.max_nodes), true, true, vals, vals2, a.ntot, a.n, a.nodes, a.sums,
-                    a.node_m64, a.node_level, a.bbox, a.max_nodes, q64, q32);
-    up_levels<MODE>(U, vals, vals2, a.ntot, a.n, a.nodes, a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes, q64,
-                    q32);
+    if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, false);        // quad
+    else if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, false);   // quad
+    else if constexpr (M == 3) return __builtin_amdgcn_update_dpp(0, (int)v, 0x1b, 0xf, 0xf, false);   // quad
+    else if constexpr (M == 7) return __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false);  // half-row mirror
+    else if constexpr (M == 15) return __builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false); // row mirror
+    else if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false);  // row rotate by 8
+    else if constexpr (M == 4) return lane_xor<3>(lane_xor<7>(v));
+    else return (uint32_t)__shfl_xor((int)v, M, kWave);
 }
 
-template <bool MOM>
-__global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
+// One compare-exchange of a bitonic network between lanes l and l ^ M, by key, then index.
+template <int M>
+__device__ inline void sort_step(uint64_t &k, uint32_t &v, int lane)
 {
-    __shared__ SmallLds lds;
-    SmallSort &S = lds.s;
-    const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1), n = a.n;
-    constexpr int kWaves = kSmallThreads / kWave;
-    const int64_t b = blockIdx.x, first = b * n;
-    const double *p = a.pos + 3 * first;
-    if (a.enter && b == 0 && t == 0) call_enter(a.status);
+    constexpr int top = M >= 32 ? 32 : M >= 16 ? 16 : M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
+    const uint64_t ok = (uint64_t)lane_xor<M>((uint32_t)(k >> 32)) << 32 | lane_xor<M>((uint32_t)k);
+    const uint32_t ov = lane_xor<M>(v);
+    const bool less = ok < k || (ok == k && ov < v);
+    if (less == ((lane & top) == 0)) {
+        k = ok;
+        v = ov;
+    }
+}
 
-    // bounding cube (as k_bbox_partial and k_bbox_final)
-    double lo[3], hi[3];
-    bool bad = false;
-    for (int c = 0; c < 3; ++c) { lo[c] = __builtin_inf(); hi[c] = -__builtin_inf(); }
-    for (int i = t; i < n; i += kSmallThreads)
-        for (int c = 0; c < 3; ++c) {
-            const double v = p[c * n + i];
-            bad |= !__builtin_isfinite(v);
-            if (v < lo[c]) lo[c] = v;
-            if (v > hi[c]) hi[c] = v;
+// Stable ascending sort of a system of at most kMergeMax particles, S.code and the indices S.val[0]: runs of 64 in
+// registers (a bitonic network of 21 steps), then rounds in which every key finds its place in the merged run of twice
+// the length by a binary search in the other one.  300 / 1000 particles: 5 / 8 us, where the counting passes with
+// their ties take 13 / 14.  It is bound by issue on the one CU, log(n)^2 a key against a fixed number of passes:
+// 4096 take 32 us, where the passes take 31 (and the Hilbert keys' three passes 20).
+constexpr int kMergeMax = 2048;
+template <typename KeyOf>
+__device__ inline void small_merge_sort(SmallSort &S, int n, const KeyOf &key_of)
+{
+    constexpr int kItems = kMergeMax / kSmallThreads;
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const int p = t + r * kSmallThreads;
+        if (p - lane >= n) continue;  // for the whole wave
+        uint64_t k = p < n ? key_of(p) : ~0ull;
+        uint32_t v = (uint32_t)p;
+        sort_step<1>(k, v, lane);
+        sort_step<3>(k, v, lane); sort_step<1>(k, v, lane);
+        sort_step<7>(k, v, lane); sort_step<2>(k, v, lane); sort_step<1>(k, v, lane);
+        sort_step<15>(k, v, lane); sort_step<4>(k, v, lane); sort_step<2>(k, v, lane); sort_step<1>(k, v, lane);
+        sort_step<31>(k, v, lane); sort_step<8>(k, v, lane); sort_step<4>(k, v, lane); sort_step<2>(k, v, lane);
+        sort_step<1>(k, v, lane);
+        sort_step<63>(k, v, lane); sort_step<16>(k, v, lane); sort_step<8>(k, v, lane); sort_step<4>(k, v, lane);
+        sort_step<2>(k, v, lane); sort_step<1>(k, v, lane);
+        if (p < n) {
+            S.code[p] = k;
+            S.val[0][p] = (uint16_t)v;
         }
-    if (bad) set_flag(a.status, BH_FLAG_NONFINITE);
-    for (int c = 0; c < 3; ++c)
-        for (int off = 1; off < kWave; off <<= 1) {
-            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off, kWave));
-            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off, kWave));
-        }
-    if (lane == 0)
-        for (int c = 0; c < 3; ++c) {
-            S.box[wave][c] = lo[c];
-            S.box[wave][3 + c] = hi[c];
-        }
-    if (t == 0) S.flag = 0;
+    }
     __syncthreads();
-    double side = 0.0;
-    for (int c = 0; c < 3; ++c) {
-        lo[c] = S.box[lane & (kWaves - 1)][c];
-        hi[c] = S.box[lane & (kWaves - 1)][3 + c];
-        for (int off = 1; off < kWaves; off <<= 1) {
-            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off, kWave));
-            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off, kWave));
+    for (int width = kWave; width < n; width *= 2) {
+        uint64_t k[kItems];
+        uint16_t v[kItems];
+        int start[kItems], len[kItems], at[kItems];
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            const int p = t + r * kSmallThreads;
+            at[r] = len[r] = start[r] = 0;
+            k[r] = 0ull;
+            v[r] = 0;
+            if (p >= n) continue;
+            k[r] = S.code[p];
+            v[r] = S.val[0][p];
+            start[r] = (p & ~(2 * width - 1)) + ((p & width) != 0 ? 0 : width);  // the other run
+            len[r] = min(width, max(n - start[r], 0));
+            if ((p & width) != 0) k[r] += 1ull;  // of equal keys those of the first run come first
         }
-        if (hi[c] - lo[c] > side) side = hi[c] - lo[c];
+        // keys of the other run below k
+        for (int step = width; step > 0; step >>= 1)
+#pragma unroll
+            for (int r = 0; r < kItems; ++r) {
+                if (r * kSmallThreads >= n) break;
+                const int next = at[r] + step;
+                if (next <= len[r] && S.code[start[r] + next - 1] < k[r]) at[r] = next;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            const int p = t + r * kSmallThreads;
+            if (p >= n) continue;
+            const bool second = (p & width) != 0;
+            const int to = (second ? p - width : p) + at[r];
+            S.code[to] = second ? k[r] - 1ull : k[r];
+            S.val[0][to] = v[r];
+        }
+        __syncthreads();
     }
-    const double scale = side > 0.0 ? 2097152.0 / side : 0.0;
-    if (t == 0) {
-        double *o = a.bbox + 8 * b;
-        o[0] = lo[0]; o[1] = lo[1]; o[2] = lo[2];
-        o[3] = side;
-        o[4] = scale;
-        o[5] = a.s2_scale;
-    }
-    auto code_of = [&](int i) {
-        return morton(quantise(p[i], lo[0], scale), quantise(p[n + i], lo[1], scale), quantise(p[2 * n + i], lo[2], scale));
-    };
+}
 
-    // sort: the codes' upper 31 bits, then runs of equal upper bits by the low 32 (as k_fix_ties); where a run is
-    // longer than an insertion sort should take, all 63 bits from the start
+// The same by counting passes: the codes' upper 31 bits, then runs of equal upper bits by the low 32 (as k_fix_ties);
+// where a run is longer than an insertion sort should take, all 63 bits from the start.
+template <typename KeyOf>
+__device__ inline void small_count_sort(SmallSort &S, int n, const KeyOf &code_of)
+{
+    const int t = threadIdx.x;
+    if (t == 0) S.flag = 0;  // read behind the passes' barriers
     for (int i = t; i < n; i += kSmallThreads) {
         S.key[0][i] = (uint32_t)(code_of(i) >> kTieBits);
         S.val[0][i] = (uint16_t)i;
@@ -1372,39 +1406,256 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
         }
         __syncthreads();
     }
+}
 
-    // the particles in sorted order (as k_gather3 and k_gather_pack)
-    for (int i = t; i < n; i += kSmallThreads) {
-        const int o = S.val[0][i];
-        const int64_t g = first + i;
-        a.codes[g] = S.code[i];
-        a.perm[g] = (uint32_t)(first + o);
-        const double x = p[o], y = p[n + o], z = p[2 * n + o];
-        a.spos[g] = x; a.spos[a.ntot + g] = y; a.spos[2 * a.ntot + g] = z;
-        if (MOM) {
-            const double *m = a.mom + 3 * first;
-            const double mx = m[o], my = m[n + o], mz = m[2 * n + o];
-            if (!__builtin_isfinite(mx) || !__builtin_isfinite(my) || !__builtin_isfinite(mz))
-                set_flag(a.status, BH_FLAG_NONFINITE);
-            a.smom[g] = mx; a.smom[a.ntot + g] = my; a.smom[2 * a.ntot + g] = mz;
-            pack_source(a.src + 6 * g, a.mixed != 0, x, y, z, mx, my, mz);
+struct SmallArgs {
+    const double *pos, *mom;
+    int n, leaf, enter, hilbert, mixed;
+    int64_t ntot, B, max_nodes;
+    double s2_scale;
+    double *bbox, *spos, *smom, *src, *sums, *node_m64;
+    uint64_t *codes;
+    uint32_t *perm, *tgt_order, *status;
+    NodeRec *nodes;
+    int32_t *node_level, *leaf_of, *top;
+};
+
+__device__ inline void up_add(SumList &S, int cell, int level)
+{
+    if ((unsigned)level > (unsigned)kMaxLevel) return;
+    const int k = atomicAdd(&S.count, 1);
+    if (k >= kSumNodes) return;  // never: each node is listed once
+    S.cell[k] = (uint16_t)cell;
+    S.lev[k] = (uint8_t)level;
+    atomicMin(&S.lmin, level);
+    atomicMax(&S.lmax, level);
+}
+
+// Sum of src[0], src[stride], ... in order, FLIGHT loads at a time.
+template <int FLIGHT>
+__device__ inline double add_in_order(const double *src, int len, int stride)
+{
+    double acc = 0.0;
+    for (int k = 0; k < len; k += FLIGHT) {
+        double v[FLIGHT];
+#pragma unroll
+        for (int q = 0; q < FLIGHT; ++q) v[q] = src[min(k + q, len - 1) * stride];
+#pragma unroll
+        for (int q = 0; q < FLIGHT; ++q) acc = k + q < len ? acc + v[q] : acc;
+    }
+    return acc;
+}
+
+// Upward pass of one system whose `total` nodes below the root start at id base.  Where its nodes fit, their sums
+// stay in LDS: eight lanes sum a node, lane a its component (0..2 positions, 4..6 moments; eight members or children
+// of all components in flight, added in order), and the records, which no sum needs, are written at the end.
+// Through memory a level was a chain of four or five loads, 3.7 us (one system of 1000: 16 us in all).
+template <int MODE>
+__device__ inline void small_upward(SmallUp &U, int64_t b, int64_t base, int64_t total, const double *vals,
+                                    const double *vals2, const SmallArgs &a, double *q64, float *q32)
+{
+    if (MODE == 3 || total >= kSumNodes || base + total > a.max_nodes) {
+        up_reset(U.list);
+        up_leaves<MODE>(U.list, b, base, min(base + total, a.max_nodes), true, true, vals, vals2, a.ntot, a.n, a.nodes,
+                        a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes, q64, q32);
+        up_levels<MODE>(U.list, vals, vals2, a.ntot, a.n, a.nodes, a.sums, a.node_m64, a.node_level, a.bbox,
+                        a.max_nodes, q64, q32);
+        return;
+    }
+    SumList &S = U.sums;
+    constexpr int kLanes = MODE == 2 ? 8 : 4;
+    const int nodes = (int)total + 1, t = threadIdx.x, group = t / kLanes, groups = (int)blockDim.x / kLanes;
+    const int c = (t & (kLanes - 1)) + (MODE == 1 ? 4 : 0);
+    const bool sums = (c & 3) != 3;
+    const int comp = c < 4 ? c : c - 1;
+    auto id_of = [&](int k) { return k == 0 ? (int)b : (int)base + k - 1; };
+    up_reset(S);
+    const int64_t first = (int64_t)b * a.n;
+    for (int k = t; k < nodes; k += (int)blockDim.x) {
+        const NodeRec &nd = a.nodes[id_of(k)];
+        const int nchild = nd.nchild, slot = nd.child - (int)base + 1, at = (int)(nd.first - first), count = nd.count;
+        const bool in = at >= 0 && count > 0 && at + count <= a.n;  // always, and a cell's children too
+        const bool leaf = nchild == 0, ok = leaf ? in : in && nchild > 0 && slot > 0 && slot + nchild <= nodes;
+        S.leaf[k] = leaf ? 1 : 0;
+        S.from[k] = (uint16_t)(ok ? leaf ? at : slot : 0);
+        S.len[k] = (uint16_t)(ok ? leaf ? count : nchild : 0);
+        if (ok && !leaf) up_add(S, k, a.node_level[id_of(k)]);
+    }
+    __syncthreads();
+    if (sums) {
+        const double *src = (MODE == 2 && c >= 4 ? vals2 : vals) + (c & 3) * a.ntot + first;
+        for (int k = group; k < nodes; k += groups)
+            if (S.leaf[k]) S.sum[k][comp] = add_in_order<16>(src + S.from[k], S.len[k], 1);
+    }
+    __syncthreads();
+    const int count = min(S.count, kSumNodes), lmin = S.lmin;
+    for (int l = S.lmax; l >= lmin; --l) {
+        for (int k = group; k < count; k += groups)
+            if (sums && S.lev[k] == l) {
+                const int cell = S.cell[k];
+                S.sum[cell][comp] = add_in_order<8>(&S.sum[S.from[cell]][comp], S.len[cell], 6);
+            }
+        __syncthreads();
+    }
+    for (int k = t; k < nodes; k += (int)blockDim.x) {
+        const int id = id_of(k);
+        if (S.len[k] == 0) continue;
+        NodeRec &nd = a.nodes[id];
+        const double *v = S.sum[k];
+        if (MODE != 1) up_centre(nd, a.node_level[id], a.bbox + 8 * b, v[0], v[1], v[2]);
+        if (MODE != 0) up_moment(nd, a.node_m64 + 4 * (int64_t)id, v[3], v[4], v[5]);
+    }
+}
+
+// Positions (POS) and moments (MOM) of system b in sorted order, and the packed source records: particle i comes from
+// place from(i) of the caller's order, out-of-range places are flagged.  A thread loads all of its particles before
+// it stores any: one after the other they were four round trips at 4096.
+template <bool MOM, bool POS, typename From, typename Also>
+__device__ inline void small_gather(const SmallArgs &a, int64_t b, const double *p, const double *m, const From &from,
+                                    const Also &also)
+{
+    const int n = a.n, t = threadIdx.x;
+    const int64_t first = b * n;
+    int o[kSmallItems];
+    double r[kSmallItems][3], v[kSmallItems][3];
+#pragma unroll
+    for (int q = 0; q < kSmallItems; ++q) o[q] = t + q * kSmallThreads < n ? from(t + q * kSmallThreads) : 0;
+#pragma unroll
+    for (int q = 0; q < kSmallItems; ++q) {
+        const int i = t + q * kSmallThreads;
+        if (i < n && (o[q] < 0 || o[q] >= n)) {
+            set_flag(a.status, BH_FLAG_TREE);
+            o[q] = -1;
+        }
+        if (i >= n || o[q] < 0) continue;
+        for (int k = 0; k < 3; ++k) {
+            r[q][k] = POS ? p[k * n + o[q]] : p[k * a.ntot + first + i];
+            if (MOM) v[q][k] = m[k * n + o[q]];
         }
     }
-    // windows, cell keys and masks (as k_oct_mark)
-    for (int i = t; i < n; i += kSmallThreads)
-        S.win[i] = i + a.leaf < n ? (int8_t)digits(S.code[i], S.code[i + a.leaf]) : (int8_t)-1;
-    __syncthreads();
-    for (int i = t; i < n; i += kSmallThreads) S.mask[i] = 0u;
-    int key[kSmallItems];
-    __syncthreads();
+    bool bad = false;
 #pragma unroll
-    for (int r = 0; r < kSmallItems; ++r) {
-        const int j = t + r * kSmallThreads;
-        key[r] = -1;
-        if (j >= n || j == 0) continue;
-        int w = -1;
-        for (int k = max(j - a.leaf, 0); k <= j; ++k) w = max(w, (int)S.win[k]);
-        key[r] = oct_mark(S.code, n, j, w, [&](int k, uint32_t m) { atomicOr(&S.mask[k], m); });
+    for (int q = 0; q < kSmallItems; ++q) {
+        const int i = t + q * kSmallThreads;
+        if (i >= n || o[q] < 0) continue;
+        const int64_t g = first + i;
+        also(g, i);
+        for (int k = 0; k < 3; ++k) {
+            if (POS) a.spos[k * a.ntot + g] = r[q][k];
+            if (MOM) a.smom[k * a.ntot + g] = v[q][k];
+            if (MOM) bad |= !__builtin_isfinite(v[q][k]);
+        }
+        if (MOM) pack_source(a.src + 6 * g, a.mixed != 0, r[q][0], r[q][1], r[q][2], v[q][0], v[q][1], v[q][2]);
+    }
+    if (bad) set_flag(a.status, BH_FLAG_NONFINITE);
+}
+
+// Whether the deepest cell that holds particles j - 1 and j has more than `leaf` members: the first of them at most
+// `leaf` before j (by halving steps), and the particle `leaf` after that one.
+__device__ inline bool small_starts(const uint64_t *code, int n, int leaf, int j)
+{
+    const uint64_t cj = code[j];
+    const int L = digits(code[j - 1], cj);
+    if (L >= kMaxLevel) return false;
+    const uint64_t low = cell_low(cj, L);
+    int back = 1;  // j - 1 is inside
+    for (int step = kMaxLeaf; step > 0; step >>= 1) {
+        const int b = back + step;
+        const uint64_t c = code[max(j - b, 0)];
+        back = b <= leaf && b <= j && c >= low ? b : back;
+    }
+    const int e = j - back + leaf;
+    return e < n && code[e] <= cell_high(cj, L);
+}
+
+template <bool MOM>
+__global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
+{
+    __shared__ SmallLds lds;
+    SmallSort &S = lds.s;
+    const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1), n = a.n;
+    constexpr int kWaves = kSmallThreads / kWave;
+    const int64_t b = blockIdx.x, first = b * n;
+    const double *p = a.pos + 3 * first;
+    if (a.enter && b == 0 && t == 0) call_enter(a.status);
+
+    // bounding cube (as k_bbox_partial and k_bbox_final)
+    double lo[3], hi[3];
+    bool bad = false;
+    for (int c = 0; c < 3; ++c) { lo[c] = __builtin_inf(); hi[c] = -__builtin_inf(); }
+    for (int i = t; i < n; i += kSmallThreads)
+        for (int c = 0; c < 3; ++c) {
+            const double v = p[c * n + i];
+            bad |= !__builtin_isfinite(v);
+            if (v < lo[c]) lo[c] = v;
+            if (v > hi[c]) hi[c] = v;
+        }
+    if (bad) set_flag(a.status, BH_FLAG_NONFINITE);
+    for (int c = 0; c < 3; ++c)
+        for (int off = 1; off < kWave; off <<= 1) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off, kWave));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off, kWave));
+        }
+    if (lane == 0)
+        for (int c = 0; c < 3; ++c) {
+            S.box[wave][c] = lo[c];
+            S.box[wave][3 + c] = hi[c];
+        }
+    if (t == 0) S.starts = 0;
+    __syncthreads();
+    double side = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        lo[c] = S.box[lane & (kWaves - 1)][c];
+        hi[c] = S.box[lane & (kWaves - 1)][3 + c];
+        for (int off = 1; off < kWaves; off <<= 1) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off, kWave));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off, kWave));
+        }
+        if (hi[c] - lo[c] > side) side = hi[c] - lo[c];
+    }
+    const double scale = side > 0.0 ? 2097152.0 / side : 0.0;
+    if (t == 0) {
+        double *o = a.bbox + 8 * b;
+        o[0] = lo[0]; o[1] = lo[1]; o[2] = lo[2];
+        o[3] = side;
+        o[4] = scale;
+        o[5] = a.s2_scale;
+    }
+    auto code_of = [&](int i) {
+        return morton(quantise(p[i], lo[0], scale), quantise(p[n + i], lo[1], scale), quantise(p[2 * n + i], lo[2], scale));
+    };
+
+    if (n <= kMergeMax) {
+        small_merge_sort(S, n, code_of);
+    } else {
+        small_count_sort(S, n, code_of);
+    }
+
+    // the particles in sorted order (as k_gather3 and k_gather_pack): all of a thread's loads before its stores
+    small_gather<MOM, true>(a, b, p, MOM ? a.mom + 3 * first : nullptr, [&](int i) { return (int)S.val[0][i]; },
+                            [&](int64_t g, int i) {
+                                a.codes[g] = S.code[i];
+                                a.perm[g] = (uint32_t)(first + S.val[0][i]);
+                            });
+    // cell starts, keys and masks (as k_oct_mark): a particle starts a child of the deepest cell that holds it and
+    // the one before it iff that cell has more than `leaf` members.  About a quarter do; they are listed first (in
+    // any order), so that the searches below run with full waves.
+    for (int i = t; i < n; i += kSmallThreads) S.mask[i] = 0u;
+    __syncthreads();  // the values are read, their place takes the list
+    for (int j0 = t - lane; j0 < n; j0 += kSmallThreads) {
+        const int j = j0 + lane;
+        const bool starts = j > 0 && j < n && small_starts(S.code, n, a.leaf, j);
+        const uint64_t m = __ballot(starts);
+        int at = 0;
+        if (lane == 0 && m != 0ull) at = atomicAdd(&S.starts, (int)__popcll(m));
+        at = __shfl(at, 0, kWave) + (int)__popcll(m & ((1ull << lane) - 1ull));
+        if (starts) S.val[0][at] = (uint16_t)j;
+    }
+    __syncthreads();
+    const int starts = S.starts;
+    for (int k = t; k < starts; k += kSmallThreads) {
+        const int j = S.val[0][k];
+        S.val[1][k] = (uint16_t)max(oct_mark(S.code, n, j, kMaxLevel, [&](int q, uint32_t m) { atomicOr(&S.mask[q], m); }), 0);
     }
     __syncthreads();
     // scan of the masks' bit counts, each thread its run of kSmallItems positions
@@ -1440,9 +1691,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
         auto mask_of = [&](int k) { return S.mask[k]; };
         auto scan_of = [&](int k) { return (int64_t)S.scan[k]; };
         if (t == kSmallThreads - 1) oct_root(o, S.code, n, b, mask_of, scan_of);
-#pragma unroll
-        for (int r = 0; r < kSmallItems; ++r)
-            if (key[r] > 0) oct_children(o, S.code, n, t + r * kSmallThreads, key[r], mask_of, scan_of);
+        for (int k = t; k < starts; k += kSmallThreads)
+            if (S.val[1][k] > 0) oct_children(o, S.code, n, S.val[0][k], S.val[1][k], mask_of, scan_of);
     }
     __syncthreads();
     small_upward<MOM ? 2 : 0>(lds.up, b, base, total, a.spos, a.smom, a, nullptr, nullptr);
@@ -1461,24 +1711,17 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
 template <int MODE>
 __global__ __launch_bounds__(kSmallThreads) void k_moments_small(SmallArgs a, double *q64, float *q32)
 {
-    __shared__ UpList U;
+    __shared__ SmallUp U;
     static_assert(kSmallMax <= kUpChunkMax, "every split cell fits");
     const int n = a.n;
     const int64_t b = blockIdx.x, first = b * n;
     if (a.enter && b == 0 && threadIdx.x == 0) call_enter(a.status);
-    const double *m = a.mom + 3 * first;
-    for (int i = threadIdx.x; i < n; i += kSmallThreads) {
-        const int64_t g = first + i, o = (int64_t)a.perm[g] - first;
-        if (o < 0 || o >= n) {
-            set_flag(a.status, BH_FLAG_TREE);
-            continue;
-        }
-        const double mx = m[o], my = m[n + o], mz = m[2 * n + o];
-        if (!__builtin_isfinite(mx) || !__builtin_isfinite(my) || !__builtin_isfinite(mz))
-            set_flag(a.status, BH_FLAG_NONFINITE);
-        a.smom[g] = mx; a.smom[a.ntot + g] = my; a.smom[2 * a.ntot + g] = mz;
-        pack_source(a.src + 6 * g, a.mixed != 0, a.spos[g], a.spos[a.ntot + g], a.spos[2 * a.ntot + g], mx, my, mz);
-    }
+    small_gather<true, false>(a, b, a.spos, a.mom + 3 * first,
+                              [&](int i) {
+                                  const int64_t o = (int64_t)a.perm[first + i] - first;
+                                  return o < 0 || o >= n ? -1 : (int)o;
+                              },
+                              [](int64_t, int) {});
     __syncthreads();
     const int64_t base = a.B + 2 * first, total = min((int64_t)(uint32_t)a.top[b], (int64_t)2 * n);
     small_upward<MODE>(U, b, base, total, a.smom, a.spos, a, q64, q32);

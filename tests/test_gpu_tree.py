@@ -129,6 +129,27 @@ def test_tree_batch_around_the_one_workgroup_sort(oracle_mod, n):
     assert total == g["first"].size
 
 
+@pytest.mark.parametrize("n,leaf", [(65, 16), (127, 1), (1023, 1), (1024, 16), (1025, 64), (2047, 3), (2048, 16),
+                                    (2049, 16), (4095, 1), (4096, 64)])
+def test_tree_of_one_workgroup_with_clusters_and_ties(oracle_mod, n, leaf):
+    """One workgroup builds a system of at most 4096 particles: up to 2048 by merging sorted runs of 64, above by
+    counting passes; the sums stay on the chip up to 1024 nodes.  A quarter of the particles sits in a cluster 1e-4
+    wide and an eighth at one point (runs of equal upper code bits, equal codes, deep cells): order, cells and centres
+    must be the oracle's, bit for bit."""
+    rng = np.random.default_rng(n)
+    w = workloads.uniform_cube(n, 4.0 + 2.0 * n ** (1 / 3), seed=n)
+    pos = w.pos.copy()
+    pick = rng.permutation(n)
+    a, b = pick[:n // 4], pick[n // 4:n // 4 + n // 8]
+    pos[:, a] = np.array([[1.0], [2.0], [3.0]]) + 1e-4 * rng.random((3, a.size))
+    pos[:, b] = np.array([[3.5], [2.25], [1.75]])
+    t = oracle_mod.Tree(pos, w.mom, leaf).export()
+    out = run_field(pos, w.mom, leaf=leaf, counters=False)
+    g = out["bh"].export_tree()
+    assert (g["perm"] == t["perm"]).all()
+    assert _compare(pos, w.mom, leaf, oracle_mod, gtree=g) == g["first"].size
+
+
 def _compare_arrays(pos, mom, leaf, oracle_mod, gtree):
     """_compare for one large system, vectorised: the cells are matched by (first, count) after sorting."""
     t = oracle_mod.Tree(pos, mom, leaf).export()

@@ -268,7 +268,7 @@ __device__ __forceinline__ void adjoint_wave(int gw, int split_shift, FFBH_ADJ_P
     if constexpr (MIXED) W.cl.n[lane] = 0u;
 
     LaneStack st;
-    if (SPLIT || parts == 1) {
+    if (parts == 1) {
         st.init(seg, 1, ballot(valid));
     } else {
         // the root holds every target of the system, so it is always opened: start at child `part` (a leaf
@@ -417,7 +417,7 @@ __device__ __forceinline__ void adjoint_wave(int gw, int split_shift, FFBH_ADJ_P
         }
     }
     if (wave_cost && lane == 0) wave_cost[gw] = work;
-    if (!SPLIT && parts > 1) {
+    if (parts > 1) {
         if (valid) {
             double *q = part_buf + (int64_t)part * 6 * ntot;
             q[si] = grx; q[ntot + si] = gry; q[2 * ntot + si] = grz;
@@ -677,8 +677,8 @@ static int adjoint_items(const Handle &h)
     return (int)(h.L.B * wps * h.adj_parts);
 }
 
-// Waves that share the fused walk of 64 targets: the forward walk's rule, for the shapes of one wave per item
-// in index order (the other shapes have their own way to divide or order the work).  Measured on the kernel,
+// Waves that share a fused walk: the forward walk's rule, for the shapes of one wave per item in index order (the
+// others have their own way to order the work).  Measured on the kernel,
 // FP64 / FP32-mixed, undivided -> divided: 1000 particles 282 / 285 -> 60 / 62 us, 4096 451 / 459 -> 105 / 118 us,
 // 20000 818 / 804 -> 271 / 300 us, 50000 838 / 759 -> 474 / 424 us, 64 systems of 1000 294 / 309 -> 187 / 168 us;
 // at 131072 particles four waves take 1545 / 1529 us against 1301 / 1203.
@@ -686,12 +686,23 @@ static int adjoint_items(const Handle &h)
 // out evenly and only the opened cells are tested twice, where intervals long enough to be skipped leave most of a
 // group's near cells to one wave (131072 particles: 1281 us undivided, 1436 with intervals, 1193 by node; 200000
 // 1723 -> 1699; with four waves and more intervals are ahead).
+// Shapes of fewer targets or of a part of the tree per item follow the same rule by their items; a walk of a part
+// sees an eighth of the positions, so its intervals are a twelfth of that, and no shorter than deals a group's near
+// cells to all waves.  FP32-mixed, undivided -> divided: 1000 particles 171 -> 47 us (16 targets), 92 -> 33 (parts),
+// 62 -> 27 (16 targets and parts); 4096 275 -> 101 (16 targets), 159 -> 61 (parts), 20000 526 -> 436 (16 targets,
+// 1250 items, four waves); 8000 (16 targets and parts, 4000 items) 217 -> 243 with four.
 static int adjoint_split(const Handle &h, int &shift)
 {
-    const bool plain = h.adj_parts == 1 && h.adj_sched == 0 && h.adj_tpw == kWave;
-    const int W = plain ? walk_split(h.L) : 1;
+    if (h.adj_sched != 0) return 1;
+    const int items = adjoint_items(h);
+    const int W = walk_split(items);
+    if (h.adj_parts > 1) {
+        const int64_t want = h.L.n / (12 * h.adj_parts), least = 128 / W, len = want > least ? want : least;
+        for (shift = 0; ((int64_t)2 << shift) <= len;) ++shift;
+        return W;
+    }
     shift = split_shift(h.L.n, W);
-    if (plain && W == 1 && h.p.precision == BH_FP64 && h.L.num_waves <= 3200) {
+    if (W == 1 && h.adj_tpw == kWave && h.p.precision == BH_FP64 && items <= 3200) {
         shift = -1;
         return 2;
     }

@@ -1447,9 +1447,9 @@ __device__ inline double add_in_order(const double *src, int len, int stride)
 }
 
 // Upward pass of one system whose `total` nodes below the root start at id base.  Where its nodes fit, their sums
-// stay in LDS: eight lanes sum a node, lane a its component (0..2 positions, 4..6 moments; eight members or children
-// of all components in flight, added in order), and the records, which no sum needs, are written at the end.
-// Through memory a level was a chain of four or five loads, 3.7 us (one system of 1000: 16 us in all).
+// stay in LDS: a lane sums one component of a node (c = 0..2 positions, 4..6 moments; eight children or sixteen
+// members in flight, added in order), and the records, which no sum needs, are written at the end.  Bound by latency:
+// through memory a level was a chain of four or five loads, 3.7 us; one system of 1000 took 16 us in all and takes 7.
 template <int MODE>
 __device__ inline void small_upward(SmallUp &U, int64_t b, int64_t base, int64_t total, const double *vals,
                                     const double *vals2, const SmallArgs &a, double *q64, float *q32)

@@ -256,10 +256,10 @@ void launch_order_waves(Handle &h, hipStream_t s);
 void launch_order_items(const uint32_t *cost, int nw, uint32_t *order, uint32_t *work_ctr, hipStream_t s);
 // Waves that share the walk of 64 targets (1: the walks are undivided), and the length (as a shift) of the
 // intervals of sorted positions that they deal out.
-int walk_split(const Layout &L);
+int walk_split(int64_t groups);
 int split_shift(int64_t n, int W);
 // Whether bh_build orders the forward walk's items: from 16384 particles on, where the walks are undivided.
-inline bool uses_field_order(const Layout &L) { return L.ntot >= kForkMinParticles && walk_split(L) == 1; }
+inline bool uses_field_order(const Layout &L) { return L.ntot >= kForkMinParticles && walk_split(L.num_waves) == 1; }
 // Order of the forward walk's items from the costs the previous forward walk recorded.
 void launch_order_field(Handle &h, hipStream_t s);
 void launch_energy_final(Handle &h, double *d_E, hipStream_t s, int targets_per_wave, bool leave = false);

@@ -320,9 +320,9 @@ __global__ __launch_bounds__(kEnergyThreads) void k_energy_final(const double *_
 // -> 23 / 22 us, 4096 273 / 236 -> 66 / 72 us, 20000 475 / 402 -> 155 / 184 us, 100003 739 / 596 -> 480 / 437
 // us; at 131072 particles four waves take 681 / 643 us against 684 / 564.  The rule counts the target groups of
 // the whole batch: a batch of 1000 x 1000 takes 0.5 ms undivided and 2.2 ms with sixteen waves.
-int walk_split(const Layout &L)
+int walk_split(int64_t groups)
 {
-    return L.num_waves <= 192 ? 16 : L.num_waves <= 768 ? 8 : L.num_waves <= 1600 ? 4 : 1;
+    return groups <= 192 ? 16 : groups <= 768 ? 8 : groups <= 1600 ? 4 : 1;
 }
 
 // Interval length of a divided walk: a sixteenth of a wave's share of the positions, which deals the near cells
@@ -368,7 +368,7 @@ static void launch_k_field(Handle &h, const double *d_hext, double *d_H, int W, 
 template <bool MIXED, bool COUNT, bool QUAD>
 static void launch_k_field(Handle &h, const double *d_hext, double *d_H, hipStream_t s)
 {
-    const int W = walk_split(h.L), shift = split_shift(h.L.n, W);
+    const int W = walk_split(h.L.num_waves), shift = split_shift(h.L.n, W);
     if (W > 1) launch_k_field<MIXED, COUNT, QUAD, true>(h, d_hext, d_H, W, shift, s);
     else launch_k_field<MIXED, COUNT, QUAD, false>(h, d_hext, d_H, 1, 0, s);
 }

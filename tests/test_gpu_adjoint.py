@@ -169,3 +169,28 @@ def test_divided_walk_keeps_the_sums_of_the_undivided_walk(precision):
                      precision)
     for b in (0, 57, 100):
         assert rel(many[0][b], one[0]) <= 1e-13 and rel(many[1][b], one[1]) <= 1e-13
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("tuning_id", [4, 5, 6, 7, 8])
+@pytest.mark.parametrize("n,leaf,theta,expansion", [(3, 16, 0.5, 1), (70, 1, 0.5, 2), (1000, 16, 0.5, 1),
+                                                    (3001, 40, 0.3, 1), (6000, 16, 0.7, 2)])
+def test_divided_walks_of_fewer_targets_and_of_parts(oracle_mod, precision, tuning_id, n, leaf, theta, expansion):
+    """Shapes of 16 or 32 targets per item (4, 5), of a part of the tree per item (6) and of both (7, 8) are divided
+    by their number of items: a root that is a leaf, parts without a cell, intervals of 8 positions and more.  The
+    energy gradient against the oracle; and where 26 copies are too many items to divide, one copy's gradient is
+    theirs to FP64 rounding (FP64 sums are regrouped, FP32 sums are not)."""
+    w = workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n + leaf, hext=(0.2, 0.0, 1.0))
+    _, _, dr, dm = oracle_mod.Tree(w.pos, w.mom, leaf).energy_grad(theta, w.hext, order=expansion)
+    got = []
+    for copies in ((1, 26) if n == 1000 else (1,)):
+        bh = BarnesHut(n, copies, leaf, theta, precision, expansion=expansion, tuning_id=tuning_id)
+        rep = lambda a: torch.from_numpy(np.ascontiguousarray(np.repeat(a[None], copies, 0))).cuda()
+        bh.build(rep(w.pos))
+        gdr, gdm = bh.field_backward(rep(w.mom), rep(np.asarray(w.hext)),
+                                     gE=torch.ones(copies, dtype=torch.float64, device="cuda"))
+        assert bh.check_status() == 0
+        got.append((gdr.cpu().numpy()[-1], gdm.cpu().numpy()[-1]))
+        grad_check(got[-1][0], dr, precision, f"dE/dr n {n}")
+        grad_check(got[-1][1], dm, precision, f"dE/dm n {n}")
+    assert rel(got[0][0], got[-1][0]) <= 1e-13 and rel(got[0][1], got[-1][1]) <= 1e-13

@@ -670,10 +670,15 @@ __global__ __launch_bounds__(64) void k_dhext(const double *__restrict__ part, c
     if (threadIdx.x < 3) dhext[3 * b + threadIdx.x] = gE ? -gE[b] * (threadIdx.x == 0 ? s[0] : threadIdx.x == 1 ? s[1] : s[2]) : 0.0;
 }
 
+// Whether one wave (or, divided, one group) takes each 64 targets in index order: no part, no order of items.
+static bool adjoint_plain(const Handle &h) { return h.adj_parts == 1 && h.adj_sched == 0 && h.adj_tpw == kWave; }
+// Targets per item.
+static int adjoint_targets(const Handle &h) { return adjoint_plain(h) ? walk_targets(h) : h.adj_tpw; }
+
 // Items of the independent-wave fused traversal: (system, target wave, part).
 static int adjoint_items(const Handle &h)
 {
-    const int wps = (int)((h.L.n + h.adj_tpw - 1) / h.adj_tpw);
+    const int tpw = adjoint_targets(h), wps = (int)((h.L.n + tpw - 1) / tpw);
     return (int)(h.L.B * wps * h.adj_parts);
 }
 
@@ -686,23 +691,25 @@ static int adjoint_items(const Handle &h)
 // out evenly and only the opened cells are tested twice, where intervals long enough to be skipped leave most of a
 // group's near cells to one wave (131072 particles: 1281 us undivided, 1436 with intervals, 1193 by node; 200000
 // 1723 -> 1699; with four waves and more intervals are ahead).
-// Shapes of fewer targets or of a part of the tree per item follow the same rule by their items; a walk of a part
+// Shapes of fewer targets or of a part of the tree per item follow the same rule by their items, with sixteen waves
+// up to 256 (256 items of 16 targets: 101 us with eight, 88 with sixteen; 500: 152 and 194); a walk of a part
 // sees an eighth of the positions, so its intervals are a twelfth of that, and no shorter than deals a group's near
 // cells to all waves.  FP32-mixed, undivided -> divided: 1000 particles 171 -> 47 us (16 targets), 92 -> 33 (parts),
-// 62 -> 27 (16 targets and parts); 4096 275 -> 101 (16 targets), 159 -> 61 (parts), 20000 526 -> 436 (16 targets,
+// 62 -> 27 (16 targets and parts); 4096 275 -> 88 (16 targets), 159 -> 61 (parts), 20000 526 -> 436 (16 targets,
 // 1250 items, four waves); 8000 (16 targets and parts, 4000 items) 217 -> 243 with four.
 static int adjoint_split(const Handle &h, int &shift)
 {
     if (h.adj_sched != 0) return 1;
-    const int items = adjoint_items(h);
-    const int W = walk_split(items);
+    const bool plain = adjoint_plain(h);
+    const int64_t items = plain ? h.L.num_waves : adjoint_items(h);
+    const int W = !plain && items <= 256 ? kSplitMaxWaves : walk_split(items);
     if (h.adj_parts > 1) {
         const int64_t want = h.L.n / (12 * h.adj_parts), least = 128 / W, len = want > least ? want : least;
         for (shift = 0; ((int64_t)2 << shift) <= len;) ++shift;
         return W;
     }
     shift = split_shift(h.L.n, W);
-    if (W == 1 && h.adj_tpw == kWave && h.p.precision == BH_FP64 && items <= 3200) {
+    if (W == 1 && plain && h.p.precision == BH_FP64 && items <= 3200) {
         shift = -1;
         return 2;
     }
@@ -739,7 +746,7 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
     if (h.ev[2]) (void)hipEventRecord(h.ev[2], s);
     const bool mixed = h.p.precision == BH_FP32_MIXED;
     {
-        const int tpw = h.adj_tpw, parts = h.adj_parts;
+        const int tpw = adjoint_targets(h), parts = h.adj_parts;
         const int wps = (int)((L.n + tpw - 1) / tpw);
         const int nwv = adjoint_items(h);
         const unsigned blk = (unsigned)((nwv + wpb - 1) / wpb);

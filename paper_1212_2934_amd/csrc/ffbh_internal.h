@@ -257,6 +257,7 @@ void launch_order_items(const uint32_t *cost, int nw, uint32_t *order, uint32_t 
 // Waves that share the walk of 64 targets (1: the walks are undivided), and the length (as a shift) of the
 // intervals of sorted positions that they deal out.
 int walk_split(int64_t groups);
+int walk_targets(const Handle &h);  // targets per group of a divided walk
 int split_shift(int64_t n, int W);
 // Whether bh_build orders the forward walk's items: from 16384 particles on, where the walks are undivided.
 inline bool uses_field_order(const Layout &L) { return L.ntot >= kForkMinParticles && walk_split(L.num_waves) == 1; }

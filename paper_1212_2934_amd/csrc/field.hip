@@ -95,7 +95,7 @@ __global__ __launch_bounds__(SPLIT ? 1024 : 512) __attribute__((amdgpu_waves_per
     double *__restrict__ e_part, int32_t *__restrict__ cnt_far, int32_t *__restrict__ cnt_near,
     uint32_t *__restrict__ status, int64_t n, int64_t ntot, int waves_per_seg, int num_waves,
     double theta2, int max_nodes, const void *__restrict__ node_q, const uint32_t *__restrict__ tgt_order,
-    const uint32_t *__restrict__ order, uint32_t *__restrict__ wave_cost, int split_shift)
+    const uint32_t *__restrict__ order, uint32_t *__restrict__ wave_cost, int split_shift, int tpw)
 {
     using T = typename std::conditional<MIXED, float, double>::type;
     using Src = typename std::conditional<MIXED, Src32, Src64>::type;
@@ -114,8 +114,8 @@ __global__ __launch_bounds__(SPLIT ? 1024 : 512) __attribute__((amdgpu_waves_per
         if (o < (uint32_t)num_waves) gw = (int)o;
     }
     const int seg = gw / waves_per_seg;
-    const int local = (gw - seg * waves_per_seg) * kWave + lane;
-    const bool valid = local < n;
+    const int local = (gw - seg * waves_per_seg) * (SPLIT ? tpw : kWave) + lane;
+    const bool valid = (!SPLIT || lane < tpw) && local < n;
     const int si = target_of(tgt_order, seg, n, local, valid);
     const double rx = spos[si], ry = spos[ntot + si], rz = spos[2 * ntot + si];
 
@@ -325,6 +325,17 @@ int walk_split(int64_t groups)
     return groups <= 192 ? 16 : groups <= 768 ? 8 : groups <= 1600 ? 4 : 1;
 }
 
+// Targets of a group of a divided walk.  Fewer targets lie closer together and open fewer cells, so while sixteen
+// waves a group do not fill the chip, idle lanes cost nothing and the walks are shorter.  FP64 only: where an
+// FP32-mixed partial sum ends depends on the group's targets.  Forward walk / fused walk, with 64 -> 16 targets: 1000
+// particles 40 -> 32 / 60 -> 45 us, 4096 71 -> 48 / 105 -> 76; 64 -> 32: 8000 89 -> 71 us, but 20000 173 -> 191 and 16
+// systems of 1000 (256 groups) 45 -> 55.
+int walk_targets(const Handle &h)
+{
+    const bool fp64 = h.p.precision != BH_FP32_MIXED;
+    return !fp64 || h.L.num_waves > 128 ? kWave : h.L.num_waves > 64 ? 32 : 16;
+}
+
 // Interval length of a divided walk: a sixteenth of a wave's share of the positions, which deals the near cells
 // of any target group out evenly, but no shorter than 128 positions (shorter ones repeat more of the cells
 // above them) unless a wave's share is.  20000 particles, eight waves: 210, 184 us with intervals of 256 and
@@ -338,13 +349,13 @@ int split_shift(int64_t n, int W)
 }
 
 template <bool MIXED, bool COUNT, bool QUAD, bool SPLIT>
-static void launch_k_field(Handle &h, const double *d_hext, double *d_H, int W, int shift, hipStream_t s)
+static void launch_k_field(Handle &h, const double *d_hext, double *d_H, int W, int shift, int tpw, hipStream_t s)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
     const int wpb = SPLIT ? W : h.waves_per_block;
-    const unsigned blocks = SPLIT ? (unsigned)L.num_waves : (unsigned)((L.num_waves + wpb - 1) / wpb);
-    const int waves_per_seg = (int)((L.n + kWave - 1) / kWave);
+    const int waves_per_seg = (int)((L.n + tpw - 1) / tpw), items = (int)L.B * waves_per_seg;
+    const unsigned blocks = SPLIT ? (unsigned)items : (unsigned)((items + wpb - 1) / wpb);
     const double theta2 = h.p.theta * h.p.theta;
     const void *src = MIXED ? (const void *)w.src32 : (const void *)w.src64;
     using T = typename std::conditional<MIXED, float, double>::type;
@@ -355,9 +366,9 @@ static void launch_k_field(Handle &h, const double *d_hext, double *d_H, int W, 
 #define FFBH_FIELD(MAC)                                                                                          \
     hipLaunchKernelGGL((k_field<MIXED, COUNT, QUAD, MAC, SPLIT>), dim3(blocks), dim3(wpb * kWave), lds, s, w.nodes,  \
                        w.node_m64, w.spos, w.smom, src, w.perm, d_hext, d_H, w.Hs, w.e_part, h.cnt_far,          \
-                       h.cnt_near, w.status, L.n, L.ntot, waves_per_seg, (int)L.num_waves, theta2,               \
+                       h.cnt_near, w.status, L.n, L.ntot, waves_per_seg, items, theta2,               \
                        (int)L.max_nodes, q, tgt, h.field_sched ? w.field_order : nullptr,   \
-                       SPLIT ? nullptr : w.field_cost, shift)
+                       SPLIT ? nullptr : w.field_cost, shift, tpw)
     const int mac = mac_form(theta2);
     if (mac == kMacInside) FFBH_FIELD(kMacInside);
     else if (mac == kMacScaled) FFBH_FIELD(kMacScaled);
@@ -368,9 +379,9 @@ static void launch_k_field(Handle &h, const double *d_hext, double *d_H, int W, 
 template <bool MIXED, bool COUNT, bool QUAD>
 static void launch_k_field(Handle &h, const double *d_hext, double *d_H, hipStream_t s)
 {
-    const int W = walk_split(h.L.num_waves), shift = split_shift(h.L.n, W);
-    if (W > 1) launch_k_field<MIXED, COUNT, QUAD, true>(h, d_hext, d_H, W, shift, s);
-    else launch_k_field<MIXED, COUNT, QUAD, false>(h, d_hext, d_H, 1, 0, s);
+    const int tpw = walk_targets(h), W = walk_split(h.L.num_waves), shift = split_shift(h.L.n, W);
+    if (W > 1) launch_k_field<MIXED, COUNT, QUAD, true>(h, d_hext, d_H, W, shift, tpw, s);
+    else launch_k_field<MIXED, COUNT, QUAD, false>(h, d_hext, d_H, 1, 0, kWave, s);
 }
 
 hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, double *d_H, double *d_E,
@@ -395,7 +406,7 @@ hipError_t launch_field(Handle &h, const double *d_mom, const double *d_hext, do
     if (h.ev[1]) (void)hipEventRecord(h.ev[1], s);
     // the energy of one system is one workgroup, the call's last: it also counts the call out
     const bool last = leave && d_E && h.L.B == 1;
-    if (d_E) launch_energy_final(h, d_E, s, kWave, last);
+    if (d_E) launch_energy_final(h, d_E, s, walk_targets(h), last);
     if (leave && !last) launch_leave(h.w.status, s);
     return hipGetLastError();
 }

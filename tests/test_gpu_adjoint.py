@@ -194,3 +194,18 @@ def test_divided_walks_of_fewer_targets_and_of_parts(oracle_mod, precision, tuni
         grad_check(got[-1][0], dr, precision, f"dE/dr n {n}")
         grad_check(got[-1][1], dm, precision, f"dE/dm n {n}")
     assert rel(got[0][0], got[-1][0]) <= 1e-13 and rel(got[0][1], got[-1][1]) <= 1e-13
+
+
+@pytest.mark.parametrize("n,expansion", [(64 * 64, 1), (64 * 64 + 1, 2), (64 * 128, 2), (64 * 128 + 1, 1)])
+def test_groups_of_fewer_targets(oracle_mod, n, expansion):
+    """The divided FP64 walk takes 16, 32 or 64 targets per group, by the number of groups: the energy gradient
+    against the oracle on either side of each change."""
+    w = workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n, hext=(0.2, 0.0, 1.0))
+    _, _, dr, dm = oracle_mod.Tree(w.pos, w.mom, 16).energy_grad(0.5, w.hext, order=expansion)
+    bh = BarnesHut(n, 1, 16, 0.5, "fp64", expansion=expansion)
+    bh.build(torch.from_numpy(w.pos).cuda())
+    gdr, gdm = bh.field_backward(torch.from_numpy(w.mom).cuda(), torch.from_numpy(w.hext).cuda(),
+                                 gE=torch.ones(1, dtype=torch.float64, device="cuda"))
+    assert bh.check_status() == 0
+    grad_check(gdr.cpu().numpy(), dr, "fp64", f"dE/dr n {n}")
+    grad_check(gdm.cpu().numpy(), dm, "fp64", f"dE/dm n {n}")

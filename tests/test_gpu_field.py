@@ -188,3 +188,16 @@ def test_divided_walk_keeps_the_sums_of_the_undivided_walk(precision):
     assert one["flags"] == 0 and many["flags"] == 0
     for b in (0, 57, 100):
         assert np.linalg.norm(many["H"][b] - one["H"]) <= 1e-14 * np.linalg.norm(one["H"])
+
+
+@pytest.mark.parametrize("n,batch,expansion", [(3, 3, 1), (17, 1, 1), (1000, 5, 2), (64 * 64, 1, 1), (64 * 64 + 1, 1, 1),
+                                               (64 * 128, 1, 2), (64 * 128 + 1, 1, 1)])
+def test_groups_of_fewer_targets(oracle_mod, n, batch, expansion):
+    """The divided FP64 walk takes 16, 32 or 64 targets per group, by the number of groups over the batch (the
+    FP32-mixed walk always 64).  Field, energy and interaction counts against the oracle on either side of each change."""
+    ws = [workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n + b) for b in range(batch)]
+    out = run_field(np.stack([w.pos for w in ws]), np.stack([w.mom for w in ws]), expansion=expansion)
+    for b, w in enumerate(ws):
+        H, nf, nr = oracle_mod.Tree(w.pos, w.mom, 16).field(0.5, expansion)
+        one = dict(flags=out["flags"], H=out["H"][b], E=out["E"][b:b + 1], n_far=out["n_far"][b], n_near=out["n_near"][b])
+        _check(one, H, oracle_mod.energy(w.mom, H), nf, nr, w.mom, "fp64")

@@ -914,11 +914,13 @@ constexpr int kUpThreads = 1024;
 constexpr int kUpChunkMax = 8192;  // positions per chunk, at most: as many cells as the LDS list holds
 constexpr uint8_t kUpSkip = 255;
 
-// Positions per chunk: 64 chunks a system, of 2048 to 8192 positions.  Short chunks give more workgroups, long ones
-// leave fewer cells to the one workgroup of the second launch.
+// Positions per chunk: 256 chunks a system (one a CU), of 2048 to 8192 positions.  Short chunks give more workgroups,
+// long ones leave fewer cells to the one workgroup of the second launch.  bh_build and bh_field together at 2^20, with
+// chunks of 2048 / 4096 / 8192: 2211 / 2174 / 2186 us; 2^19 1241 / 1239 / 1266; 2^18 804 / 808 / 835; 100003 725 / 738
+// / 770 (1024: 720); 32 x 65536 1970 / 1953 / 1948.
 static int64_t up_chunk_size(const Layout &L)
 {
-    return L.n / 64 < 2048 ? 2048 : L.n / 64 > kUpChunkMax ? kUpChunkMax : L.n / 64;
+    return L.n / 256 < 2048 ? 2048 : L.n / 256 > kUpChunkMax ? kUpChunkMax : L.n / 256;
 }
 
 // The per-system lists of k_upward_top live in one array: entry b counts system b's list, which starts at

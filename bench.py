@@ -465,7 +465,9 @@ def main():
             t_fwd += ev.seconds(0, 1)
         assert bh.check_status() == 0 and fbh.check_status() == 0
         fbh.set_raw_timing_events(None)
-        # the energy gradient of this precision on the benchmark state (compared with the oracle's below)
+        # the energy gradient of this precision on the benchmark state (compared with the oracle's below); the
+        # handle's tree is the last MD step's until it is built on that state
+        bh.build(pos)
         grads[precision] = bh.field_backward(mom, hext, gE=ones)
         assert bh.check_status() == 0
         H_bh[precision] = field_only()[0].clone()

@@ -625,8 +625,9 @@ __global__ __launch_bounds__(256) void k_adj_setup(AdjSetup a)
     adj_setup(a, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
-// Gradients of the sorted particles, to caller order: one thread each, five waves per SIMD to hide the path's loads
-// (2^20 particles 80 us, bound by the six scattered stores; one path per distinct leaf instead took 73).
+// Gradients of the sorted particles, to caller order: one thread each, five waves per SIMD to hide the path's loads.
+// Bound by the six scattered stores of a particle: 71 to 80 us at 2^20 from run to run, 205 us at 32 x 65536; one path
+// per distinct leaf of a workgroup instead took 73 and 205.
 __global__ __launch_bounds__(256, 5) void k_downward(Downward a, double *__restrict__ dpos, double *__restrict__ dmom)
 {
     const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;

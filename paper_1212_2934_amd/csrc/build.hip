@@ -1718,12 +1718,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_moments_small(SmallArgs a, do
     const int n = a.n;
     const int64_t b = blockIdx.x, first = b * n;
     if (a.enter && b == 0 && threadIdx.x == 0) call_enter(a.status);
-    small_gather<true, false>(a, b, a.spos, a.mom + 3 * first,
-                              [&](int i) {
-                                  const int64_t o = (int64_t)a.perm[first + i] - first;
-                                  return o < 0 || o >= n ? -1 : (int)o;
-                              },
-                              [](int64_t, int) {});
+    if (a.mom) {  // else they are there
+        small_gather<true, false>(a, b, a.spos, a.mom + 3 * first,
+                                  [&](int i) {
+                                      const int64_t o = (int64_t)a.perm[first + i] - first;
+                                      return o < 0 || o >= n ? -1 : (int)o;
+                                  },
+                                  [](int64_t, int) {});
+    }
     __syncthreads();
     const int64_t base = a.B + 2 * first, total = min((int64_t)(uint32_t)a.top[b], (int64_t)2 * n);
     small_upward<MODE>(U, b, base, total, a.smom, a.spos, a, q64, q32);
@@ -1970,7 +1972,10 @@ hipError_t launch_upward_first_moments(Handle &h, const double *d_mom, hipStream
 hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter)
 {
     if (h.L.n <= kSmallMax) {
-        const SmallArgs a = small_args(h, nullptr, d_mom, enter);
+        // one CU gathers 4096 moments in 13 us; a launch over many costs 4.5 us and pays above 2048
+        const bool apart = h.L.n > kMergeMax;
+        if (apart) gather_moments(h, d_mom, s, enter);
+        const SmallArgs a = small_args(h, nullptr, apart ? nullptr : d_mom, enter && !apart);
         if (h.L.expansion == 2)
             hipLaunchKernelGGL(k_moments_small<3>, dim3((unsigned)h.L.B), dim3(kSmallThreads), 0, s, a, h.w.node_q64,
                                h.w.node_q32);

@@ -430,10 +430,11 @@ bh_status bh_build(bh_handle *hh, const double *d_pos, void *stream)
         return hipGetLastError();
     };
     const bool order_here = !side && ordered;
-    if (launch_build(h, d_pos, s, nullptr, side, true, true, order_field) != hipSuccess) return BH_EDEVICE;
+    bool left = false;
+    if (launch_build(h, d_pos, s, nullptr, side, true, true, order_field, &left) != hipSuccess) return BH_EDEVICE;
     if (order_here) launch_order_field(h, s);
     h.field_sched = ordered ? 1 : 0;
-    launch_leave(h.w.status, s);
+    if (!left) launch_leave(h.w.status, s);
     if (hipGetLastError() != hipSuccess) return BH_EDEVICE;
     hh->h.built = 1;
     return BH_OK;

@@ -1412,7 +1412,7 @@ __device__ inline void small_count_sort(SmallSort &S, int n, const KeyOf &code_o
 
 struct SmallArgs {
     const double *pos, *mom;
-    int n, leaf, enter, hilbert, mixed;
+    int n, leaf, enter, leave, hilbert, mixed;
     int64_t ntot, B, max_nodes;
     double s2_scale;
     double *bbox, *spos, *smom, *src, *sums, *node_m64;
@@ -1698,15 +1698,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
     }
     __syncthreads();
     small_upward<MOM ? 2 : 0>(lds.up, b, base, total, a.spos, a.smom, a, nullptr, nullptr);
-    if (!a.hilbert) return;
-    // target order (as launch_target_order)
-    __syncthreads();
-    for (int i = t; i < n; i += kSmallThreads) {
-        S.key[0][i] = hilbert_key(a.codes[first + i]);
-        S.val[0][i] = (uint16_t)i;
+    if (a.hilbert) {
+        // target order (as launch_target_order)
+        __syncthreads();
+        for (int i = t; i < n; i += kSmallThreads) {
+            S.key[0][i] = hilbert_key(a.codes[first + i]);
+            S.val[0][i] = (uint16_t)i;
+        }
+        for (int q = 0; q < 3; ++q) small_pass(S, n, q & 1, 8 * q);
+        for (int i = t; i < n; i += kSmallThreads) a.tgt_order[first + i] = (uint32_t)(first + S.val[1][i]);
     }
-    for (int q = 0; q < 3; ++q) small_pass(S, n, q & 1, 8 * q);
-    for (int i = t; i < n; i += kSmallThreads) a.tgt_order[first + i] = (uint32_t)(first + S.val[1][i]);
+    if (a.leave) {
+        __syncthreads();
+        if (t == 0) call_leave(a.status);
+    }
 }
 
 // Moments of a small system: gathered into sorted order with the packed source records, then summed upward.
@@ -1783,13 +1788,14 @@ static SmallArgs small_args(Handle &h, const double *d_pos, const double *d_mom,
 static void gather_moments(Handle &h, const double *d_mom, hipStream_t s, bool enter);
 
 hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const double *d_mom, hipStream_t side,
-                        bool join, bool enter, const SortedWork &after_sort)
+                        bool join, bool enter, const SortedWork &after_sort, bool *leave)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
     const int64_t n = L.n, B = L.B, ntot = L.ntot;
     if (L.n <= kSmallMax) {
-        const SmallArgs a = small_args(h, d_pos, d_mom, enter);
+        SmallArgs a = small_args(h, d_pos, d_mom, enter);
+        if (leave) a.leave = *leave = B == 1 && !side && !after_sort;
         if (d_mom) hipLaunchKernelGGL(k_build_small<true>, dim3((unsigned)B), dim3(kSmallThreads), 0, s, a);
         else hipLaunchKernelGGL(k_build_small<false>, dim3((unsigned)B), dim3(kSmallThreads), 0, s, a);
         if (side) {

@@ -226,11 +226,12 @@ inline bool uses_target_order(const Layout &L) { return L.n >= kTargetOrderMin; 
 // after_sort's work (which needs only the sorted particles), beside the rest of the build; with join the
 // caller's stream then waits for the side stream at the end of the build, without it the caller joins
 // the side stream itself (h.join_ev) before the traversal.  Without a side stream everything runs on s.
-// With enter, the build's first kernel counts the call in (call_enter).
+// With enter, the build's first kernel counts the call in (call_enter).  With leave, its last one counts the call out
+// where that is the call's only workgroup (one small system); *leave is whether it does.
 using SortedWork = std::function<hipError_t(hipStream_t)>;
 hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const double *d_mom = nullptr,
                         hipStream_t side = nullptr, bool join = true, bool enter = false,
-                        const SortedWork &after_sort = nullptr);
+                        const SortedWork &after_sort = nullptr, bool *leave = nullptr);
 // Targets of every system in Hilbert order (the positions' cells at kHilbertBits bits per axis), sorted
 // positions as values: consecutive targets of a traversal wave then lie close together.
 void launch_target_order(Handle &h, hipStream_t s);

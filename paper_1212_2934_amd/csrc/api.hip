@@ -104,14 +104,17 @@ void carve(const Layout &Lc, void *base, Workspace &w)
     // one 48-byte source record per particle, in the handle's precision (src64 or src32, never both)
     w.src64 = take(48 * nt);
     w.src32 = w.src64;
-    // The octree construction needs four of the ten arrays that this region once held.  Its size is kept: it
-    // decides which calls the fixed array of bh_field_noalloc takes.
+    // The octree construction of systems above kSmallMax needs four of the ten arrays that this region once held (the
+    // one-workgroup build of smaller ones keeps them in LDS).  Its size is kept: it decides which calls the fixed
+    // array of bh_field_noalloc takes.  It holds the four wherever they are taken: 9 B (n - 1) >= 4 B n entries.
     const size_t region = align_up(off, 256) + 9 * align_up(4 * bi, 256) + align_up(4 * nt, 256) + 512;
-    w.cell_mask = (uint32_t *)take(4 * nt);
-    w.cell_scan = (uint32_t *)take(4 * nt);
-    w.cell_key = (int32_t *)take(4 * nt);
-    w.cell_id = (int32_t *)take(4 * nt);
-    off = region;
+    if (L.n > kSmallMax) {
+        w.cell_mask = (uint32_t *)take(4 * nt);
+        w.cell_scan = (uint32_t *)take(4 * nt);
+        w.cell_key = (int32_t *)take(4 * nt);
+        w.cell_id = (int32_t *)take(4 * nt);
+    }
+    if (off < region) off = region;
     w.nodes = (NodeRec *)take(sizeof(NodeRec) * mn);
     w.node_level = (int32_t *)take(4 * mn);
     w.node_m64 = (double *)take(4 * 8 * mn);
@@ -626,7 +629,7 @@ bh_status bh_num_nodes(bh_handle *hh, void *stream, int64_t *out_nodes)
     if (!hh->h.built) return BH_ESTATE;
     uint32_t v = 0;
     hipStream_t s = (hipStream_t)stream;
-    if (hh->h.L.n <= kSmallMax) launch_small_counts(hh->h, hh->h.w.cell_scan, s);
+    if (hh->h.L.n <= kSmallMax) launch_small_counts(hh->h, hh->h.w.hist, s);
     if (hipMemcpyAsync(&v, hh->h.w.status + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess)
         return BH_EDEVICE;
     if (hipStreamSynchronize(s) != hipSuccess) return BH_EDEVICE;
@@ -645,9 +648,9 @@ bh_status bh_export_tree(bh_handle *hh, int32_t *d_perm, int32_t *d_first, int32
     if (d_perm)
         hipLaunchKernelGGL(k_copy_u32, dim3(grid_for(h.L.ntot, 256)), dim3(256), 0, s, h.w.perm, h.L.ntot, d_perm);
     const bool small = h.L.n <= kSmallMax;
-    if (small) launch_small_counts(h, h.w.cell_scan, s);
+    if (small) launch_small_counts(h, h.w.hist, s);  // the histograms' space is free
     hipLaunchKernelGGL(k_export, dim3(grid_for(h.L.max_nodes, 256)), dim3(256), 0, s, h.w.nodes, h.w.node_level, h.L.n,
-                       h.L.B, h.w.top_nodes, small ? h.w.cell_scan : nullptr, h.w.status + 2, h.L.max_nodes, d_first,
+                       h.L.B, h.w.top_nodes, small ? h.w.hist : nullptr, h.w.status + 2, h.L.max_nodes, d_first,
                        d_count, d_level, d_nchild, d_child_first, d_centroid);
     if (d_bbox)
         hipLaunchKernelGGL(k_copy_bbox, dim3(grid_for(h.L.B, 64)), dim3(64), 0, s, h.w.bbox, h.L.B, d_bbox);

@@ -82,10 +82,10 @@ struct Workspace {
     double *smom;            // 3 x N_tot sorted moments FP64
     void *src64;             // N_tot sorted source records (position, moment FP64), 48 bytes each (FP64)
     void *src32;             // the same buffer as records of position FP64, moment FP32 (FP32-mixed)
-    // octree construction, per sorted particle
+    // octree construction, per sorted particle (systems above kSmallMax only, else null)
     uint32_t *cell_mask;     // at a split cell's key: the octants of its children
     uint32_t *cell_scan;     // exclusive scan of the masks' bit counts: where the children start
-    int32_t *cell_id;        // at a split cell's key: its node (systems above kSmallMax)
+    int32_t *cell_id;        // at a split cell's key: its node
     int32_t *cell_key;       // key of the cell that the particle starts a child of (-1: none)
     // octree
     NodeRec *nodes;          // max_nodes

@@ -203,3 +203,25 @@ def test_exported_bounding_cubes_of_a_large_batch(oracle_mod):
     for b, w in enumerate(ws):
         ref = oracle_mod.Tree(w.pos, w.mom, 16).export()["bbox"]
         assert (g["bbox"][b] == ref).all(), (b, g["bbox"][b], ref)
+
+
+@pytest.mark.parametrize("B", [705, 1000])
+def test_export_of_a_batch_of_single_particles_leaves_the_tree_alone(B):
+    """Each system is one leaf: its exported record, and the field of the same tree after the export, which is exactly
+    zero for a single particle.  From 705 systems on the offsets of an export once ran into the node records."""
+    import torch
+    from paper_1212_2934_amd.binding import BarnesHut
+    rng = np.random.default_rng(B)
+    pos = torch.from_numpy(rng.random((B, 3, 1))).cuda()
+    mom = torch.from_numpy(rng.standard_normal((B, 3, 1))).cuda()
+    bh = BarnesHut(1, B, 16, 0.5, "fp64")
+    bh.build(pos)
+    for _ in range(2):
+        g = bh.export_tree()
+        assert g["first"].size == B
+        assert (g["first"] == np.arange(B)).all() and (g["perm"] == np.arange(B)).all()
+        assert (g["count"] == 1).all() and (g["nchild"] == 0).all() and (g["child"] == -1).all()
+        assert (g["centroid"] == pos.cpu().numpy()[:, :, 0]).all()
+        H, E = bh.field(mom)
+        assert bh.check_status() == 0
+        assert (H == 0).all() and (E == 0).all()

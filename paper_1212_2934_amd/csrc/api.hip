@@ -183,14 +183,20 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *a, int64_t len, uint
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) a[i] = v;
 }
 
-__global__ void k_init(uint32_t *status, double *ones, int64_t B)
+// counts: the systems' node counts, zero until a build writes them (null where the build comes next).
+__global__ void k_init(uint32_t *status, double *ones, int32_t *counts, int64_t B)
 {
     if (threadIdx.x < 16) status[threadIdx.x] = 0u;
-    for (int64_t b = threadIdx.x; b < B; b += blockDim.x) ones[b] = 1.0;
+    for (int64_t b = threadIdx.x; b < B; b += blockDim.x) {
+        ones[b] = 1.0;
+        if (counts) counts[b] = 0;
+    }
 }
 
-// off: where the nodes of small systems (built in one workgroup each, with 2 n node places a system) go, so that
-// the exported ids have no gaps; null for dense ids.  count_of: their number per system, with off.
+// off: where the nodes of a batch of small systems (built in one workgroup each, with 2 n node places a system) go, so
+// that the exported ids have no gaps; null for dense ids.  count_of: their number per system, with off.  No id at or
+// above the number of nodes is written, whatever the workspace holds: a handle whose graph was captured but never
+// replayed has no tree, and its number of nodes is zero.
 __global__ __launch_bounds__(256) void k_export(const NodeRec *__restrict__ nodes,
                                                 const int32_t *__restrict__ level, int64_t n, int64_t B,
                                                 const int32_t *__restrict__ count_of, const uint32_t *__restrict__ off,
@@ -199,18 +205,19 @@ __global__ __launch_bounds__(256) void k_export(const NodeRec *__restrict__ node
                                                 double *centroid)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= max_nodes || (!off && i >= (int64_t)*nn)) return;
+    if (i >= max_nodes) return;
     int64_t o = i, shift = 0;  // exported id, and that of the children less their own
     if (off) {
         if (i >= B) {
             const int64_t b = (i - B) / (2 * n), k = i - B - 2 * n * b;
-            if (k >= (int64_t)count_of[b]) return;
+            if (k >= min((int64_t)(uint32_t)count_of[b], 2 * n)) return;
             shift = (int64_t)off[b] - 2 * n * b;
         } else {
             shift = (int64_t)off[i] - 2 * n * i;
         }
         o = i < B ? i : i + shift;
     }
+    if (o >= (int64_t)*nn) return;
     const NodeRec nd = nodes[i];
     if (first) first[o] = nd.first;
     if (count) count[o] = nd.count;
@@ -338,11 +345,11 @@ static hipError_t setup_handle(Handle &h, const bh_params *p, const Layout &L, v
     return e;
 }
 
-// The workspace words that must start at zero (status) or hold constants (ones, first-launch costs).
+// The workspace words that must start at zero (status, node counts) or hold constants (ones, first-launch costs).
 static hipError_t init_workspace(Handle &h, hipStream_t s)
 {
     const Layout &L = h.L;
-    hipLaunchKernelGGL(k_init, dim3(1), dim3(256), 0, s, h.w.status, h.w.ones, (int64_t)L.B);
+    hipLaunchKernelGGL(k_init, dim3(1), dim3(256), 0, s, h.w.status, h.w.ones, h.w.top_nodes, (int64_t)L.B);
     hipLaunchKernelGGL(k_fill_u32, dim3(64), dim3(256), 0, s, h.w.wave_cost,
                        (int64_t)(L.B * ((L.n + kMinTpw - 1) / kMinTpw)), 0u);
     hipLaunchKernelGGL(k_fill_u32, dim3(64), dim3(256), 0, s, h.w.field_cost, L.num_waves, 0u);
@@ -580,7 +587,7 @@ bh_status bh_field_noalloc(const bh_params *p, const double *d_pos, const double
     hipStream_t s = (hipStream_t)stream;
     // the array keeps the previous call's contents: the status word starts at zero (a kernel, not a
     // memset, so that the call can be captured in a graph)
-    hipLaunchKernelGGL(k_init, dim3(1), dim3(256), 0, s, h.w.status, h.w.ones, (int64_t)L.B);
+    hipLaunchKernelGGL(k_init, dim3(1), dim3(256), 0, s, h.w.status, h.w.ones, (int32_t *)nullptr, (int64_t)L.B);
     if (hipGetLastError() != hipSuccess) return BH_EDEVICE;
     if (launch_build(h, d_pos, s) != hipSuccess) return BH_EDEVICE;
     if (launch_field(h, d_mom, d_hext, d_H, d_E, s) != hipSuccess) return BH_EDEVICE;
@@ -629,7 +636,7 @@ bh_status bh_num_nodes(bh_handle *hh, void *stream, int64_t *out_nodes)
     if (!hh->h.built) return BH_ESTATE;
     uint32_t v = 0;
     hipStream_t s = (hipStream_t)stream;
-    if (hh->h.L.n <= kSmallMax) launch_small_counts(hh->h, hh->h.w.hist, s);
+    if (has_id_gaps(hh->h.L)) launch_small_counts(hh->h, hh->h.w.hist, s);
     if (hipMemcpyAsync(&v, hh->h.w.status + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess)
         return BH_EDEVICE;
     if (hipStreamSynchronize(s) != hipSuccess) return BH_EDEVICE;
@@ -647,10 +654,10 @@ bh_status bh_export_tree(bh_handle *hh, int32_t *d_perm, int32_t *d_first, int32
     hipStream_t s = (hipStream_t)stream;
     if (d_perm)
         hipLaunchKernelGGL(k_copy_u32, dim3(grid_for(h.L.ntot, 256)), dim3(256), 0, s, h.w.perm, h.L.ntot, d_perm);
-    const bool small = h.L.n <= kSmallMax;
-    if (small) launch_small_counts(h, h.w.hist, s);  // the histograms' space is free
+    const bool gaps = has_id_gaps(h.L);
+    if (gaps) launch_small_counts(h, h.w.hist, s);  // the histograms' space is free
     hipLaunchKernelGGL(k_export, dim3(grid_for(h.L.max_nodes, 256)), dim3(256), 0, s, h.w.nodes, h.w.node_level, h.L.n,
-                       h.L.B, h.w.top_nodes, small ? h.w.hist : nullptr, h.w.status + 2, h.L.max_nodes, d_first,
+                       h.L.B, h.w.top_nodes, gaps ? h.w.hist : nullptr, h.w.status + 2, h.L.max_nodes, d_first,
                        d_count, d_level, d_nchild, d_child_first, d_centroid);
     if (d_bbox)
         hipLaunchKernelGGL(k_copy_bbox, dim3(grid_for(h.L.B, 64)), dim3(64), 0, s, h.w.bbox, h.L.B, d_bbox);

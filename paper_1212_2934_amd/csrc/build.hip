@@ -1684,7 +1684,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
     }
     if (t == 0) {
         a.top[b] = (int32_t)total;
-        if (a.B == 1) a.status[2] = 1u + total;
+        // number of nodes; a batch's (at least its roots) is summed when it is asked for (k_small_total)
+        if (b == 0) a.status[2] = a.B == 1 ? 1u + total : (uint32_t)a.B;
     }
     __syncthreads();
     const int64_t base = a.B + 2 * first;
@@ -1736,10 +1737,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_moments_small(SmallArgs a, do
     small_upward<MODE>(U, b, base, total, a.smom, a.spos, a, q64, q32);
 }
 
-// Number of nodes from the scan's total.
+// Number of nodes from the scan's total; zero before the first build.
 __global__ void k_small_total(uint32_t *status, int64_t B)
 {
-    if (threadIdx.x == 0) status[2] = (uint32_t)B + status[1];
+    if (threadIdx.x == 0 && status[2] != 0u) status[2] = (uint32_t)B + status[1];
 }
 
 static SmallArgs small_args(Handle &h, const double *d_pos, const double *d_mom, bool enter)

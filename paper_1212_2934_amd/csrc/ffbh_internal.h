@@ -218,6 +218,8 @@ inline unsigned grid_for(int64_t work, int threads, int64_t cap = (int64_t)1 << 
 // Whether the traversals of this layout take their targets in Hilbert order (w.tgt_order) rather than in
 // sorted (Morton) order.
 inline bool uses_target_order(const Layout &L) { return L.n >= kTargetOrderMin; }
+// Whether the node ids of this layout have gaps: in a batch, every system built in one workgroup has 2 n node places.
+inline bool has_id_gaps(const Layout &L) { return L.n <= kSmallMax && L.B > 1; }
 
 // Launch helpers implemented per source file.
 // Tree build; with d_mom the moments are gathered and summed in the same upward pass (the MD step).

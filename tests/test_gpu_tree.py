@@ -225,3 +225,54 @@ def test_export_of_a_batch_of_single_particles_leaves_the_tree_alone(B):
         H, E = bh.field(mom)
         assert bh.check_status() == 0
         assert (H == 0).all() and (E == 0).all()
+
+
+@pytest.mark.parametrize("n,batch", [(100, 1), (100, 3), (2, 1000), (5000, 2)])
+def test_queries_before_the_first_replay_find_no_nodes(n, batch):
+    """A captured step that has not been replayed has built nothing.  On a workspace full of ones (random words in
+    earnest) the number of nodes is zero and the export writes no node."""
+    import ctypes as C
+
+    import torch
+    from paper_1212_2934_amd import binding
+    L, P = binding.lib(), C.c_void_p
+    p = binding.make_params(n, batch, 16, 0.5, "fp32_mixed")
+    nbytes = binding.workspace_bytes(p)
+    ws = torch.full((nbytes + 256,), 255, dtype=torch.uint8, device="cuda")
+    base = ws.data_ptr() + (-ws.data_ptr()) % 256
+    h = P()
+    assert L.bh_create(C.byref(p), P(base), nbytes, C.byref(h)) == 0
+    d = {k: torch.rand(batch, 3, n, dtype=torch.float64, device="cuda") for k in ("pos", "vel", "mom", "omega")}
+    step = torch.zeros(1, dtype=torch.int64, device="cuda")
+    C3 = C.c_double * 3
+    mdp = binding.md_params(1e-4, 1.0, 0.1, 0.1, 1.0, 0.1, 1.0, 1.0, C3(0.0, 0.0, 0.0), C3(9.0, 9.0, 9.0), None, 7)
+    st = binding.md_state(*[d[k].data_ptr() for k in ("pos", "vel", "mom", "omega")], step.data_ptr())
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = P()
+    assert L.bh_graph_capture_md(h, C.byref(st), C.byref(mdp), P(stream.cuda_stream), C.byref(g)) == 0
+
+    def nodes():
+        v = C.c_int64(-1)
+        assert L.bh_num_nodes(h, None, C.byref(v)) == 0
+        return v.value
+
+    cap = batch * (2 * n + 1)  # the most nodes there can be
+    out = [torch.full((cap,), -7, dtype=torch.int32, device="cuda") for _ in range(5)]
+    cen = torch.full((3 * cap,), -7.0, dtype=torch.float64, device="cuda")
+    assert nodes() == 0
+    assert L.bh_export_tree(h, None, *[P(t.data_ptr()) for t in out], P(cen.data_ptr()), None, None) == 0
+    torch.cuda.synchronize()
+    assert all((t == -7).all() for t in out) and (cen == -7.0).all()
+    # after a replay the nodes are there
+    assert L.bh_graph_launch(g, P(stream.cuda_stream)) == 0
+    torch.cuda.synchronize()
+    nn = nodes()
+    assert batch <= nn < cap
+    assert L.bh_export_tree(h, None, *[P(t.data_ptr()) for t in out], P(cen.data_ptr()), None, None) == 0
+    torch.cuda.synchronize()
+    count, nchild = out[1].cpu().numpy(), out[3].cpu().numpy()
+    assert (count[:batch] == n).all() and (count[:nn] > 0).all() and count[:nn][nchild[:nn] == 0].sum() == batch * n
+    assert all((t[nn:] == -7).all() for t in out) and (cen[3 * nn:] == -7.0).all()
+    L.bh_graph_destroy(g)
+    L.bh_destroy(h)

@@ -239,7 +239,9 @@ bh_status bh_check_status(bh_handle *h, void *stream, uint32_t *flags);
  * counters enabled (bh_enable_counters before the bh_field call); costs one extra write per target. */
 bh_status bh_enable_counters(bh_handle *h, int32_t *d_n_far, int32_t *d_n_near);
 
-/* ---- Introspection (tests and tools) ------------------------------------------------------------ */
+/* ---- Introspection (tests and tools) ------------------------------------------------------------
+ * For a batch of systems of at most 4096 particles the two queries use the workspace to number the nodes, so
+ * they are ordered with the other calls on the handle like any of them, and count themselves in and out. */
 
 /* Number of octree nodes of the last bh_build (synchronises the stream). */
 bh_status bh_num_nodes(bh_handle *h, void *stream, int64_t *out_nodes);

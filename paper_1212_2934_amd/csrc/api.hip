@@ -168,7 +168,12 @@ __global__ void k_clear_status(uint32_t *status)
     if (threadIdx.x == 0) status[0] = 0u;
 }
 
-// Last kernel of the entry points whose own last kernel does not count the call out.
+// First kernel of the tree queries that write the workspace, and last kernel of the entry points whose own last kernel
+// does not count the call out.
+__global__ void k_enter(uint32_t *status)
+{
+    if (threadIdx.x == 0) call_enter(status);
+}
 __global__ void k_leave(uint32_t *status)
 {
     if (threadIdx.x == 0) call_leave(status);
@@ -636,7 +641,12 @@ bh_status bh_num_nodes(bh_handle *hh, void *stream, int64_t *out_nodes)
     if (!hh->h.built) return BH_ESTATE;
     uint32_t v = 0;
     hipStream_t s = (hipStream_t)stream;
-    if (has_id_gaps(hh->h.L)) launch_small_counts(hh->h, hh->h.w.hist, s);
+    if (has_id_gaps(hh->h.L)) {
+        // the batch's counts are summed in the workspace: a call like any other
+        hipLaunchKernelGGL(k_enter, dim3(1), dim3(64), 0, s, hh->h.w.status);
+        launch_small_counts(hh->h, hh->h.w.hist, s);
+        launch_leave(hh->h.w.status, s);
+    }
     if (hipMemcpyAsync(&v, hh->h.w.status + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess)
         return BH_EDEVICE;
     if (hipStreamSynchronize(s) != hipSuccess) return BH_EDEVICE;
@@ -655,10 +665,15 @@ bh_status bh_export_tree(bh_handle *hh, int32_t *d_perm, int32_t *d_first, int32
     if (d_perm)
         hipLaunchKernelGGL(k_copy_u32, dim3(grid_for(h.L.ntot, 256)), dim3(256), 0, s, h.w.perm, h.L.ntot, d_perm);
     const bool gaps = has_id_gaps(h.L);
-    if (gaps) launch_small_counts(h, h.w.hist, s);  // the histograms' space is free
+    if (gaps) {
+        // the offsets go into the workspace (the histograms' space is free): a call like any other
+        hipLaunchKernelGGL(k_enter, dim3(1), dim3(64), 0, s, h.w.status);
+        launch_small_counts(h, h.w.hist, s);
+    }
     hipLaunchKernelGGL(k_export, dim3(grid_for(h.L.max_nodes, 256)), dim3(256), 0, s, h.w.nodes, h.w.node_level, h.L.n,
                        h.L.B, h.w.top_nodes, gaps ? h.w.hist : nullptr, h.w.status + 2, h.L.max_nodes, d_first,
                        d_count, d_level, d_nchild, d_child_first, d_centroid);
+    if (gaps) launch_leave(h.w.status, s);
     if (d_bbox)
         hipLaunchKernelGGL(k_copy_bbox, dim3(grid_for(h.L.B, 64)), dim3(64), 0, s, h.w.bbox, h.L.B, d_bbox);
     return hipGetLastError() == hipSuccess ? BH_OK : BH_EDEVICE;

@@ -128,3 +128,34 @@ def test_two_handles_step_concurrently_on_unordered_streams():
         for k in ("pos", "vel", "mom", "omega"):
             err = ((st[k] - ref[k]).abs().max() / ref[k].abs().max()).item()
             assert err <= 1e-12, (k, err)
+
+
+@pytest.mark.parametrize("n,batch,writes", [(50, 1, False), (50, 3, True), (5000, 2, False)])
+@pytest.mark.parametrize("query", ["num_nodes", "export_tree"])
+def test_queries_that_write_the_workspace_are_counted(query, n, batch, writes):
+    """The tree queries number the nodes of a batch of small systems in the workspace: they count themselves in and
+    out and flag another call in flight.  The others only read."""
+    torch.cuda.set_device(0)
+    pos = torch.rand(batch, 3, n, dtype=torch.float64, device="cuda")
+    bh = BarnesHut(n, batch, 16, 0.5, "fp32_mixed")
+    bh.build(pos)
+    g = bh.export_tree()
+    torch.cuda.synchronize()
+    words = _status_words(bh)
+    assert bh.check_status() == 0 and int(words[IN_FLIGHT].item()) == 0
+    words[IN_FLIGHT] = 1  # as if a call on another stream were running
+    if query == "num_nodes":
+        assert bh.num_nodes() == g["first"].size
+    else:
+        # num_nodes first, without the simulated call
+        words[IN_FLIGHT] = 0
+        nn = bh.num_nodes()
+        words[IN_FLIGHT] = 1
+        out = torch.empty(nn, dtype=torch.int32, device="cuda")
+        st = binding.lib().bh_export_tree(bh._h, None, binding._ptr(out), None, None, None, None, None, None,
+                                          binding._stream())
+        assert st == 0 and (out.cpu().numpy() == g["first"]).all()
+    torch.cuda.synchronize()
+    assert int(words[IN_FLIGHT].item()) == 1
+    words[IN_FLIGHT] = 0
+    assert bh.check_status() == (binding.FLAG_OVERLAP if writes else 0)

@@ -934,10 +934,12 @@ __device__ inline int64_t up_list(int64_t B, int64_t n, int64_t b) { return B + 
         double *__restrict__ q64, float *__restrict__ q32
 #define FFBH_UP_ARGS vals, vals2, ntot, n, nodes, sums, node_m64, node_level, bbox, max_nodes, q64, q32
 
-// The cells of a workgroup, in LDS, and the range of their levels.
+// The cells of a workgroup, at most CAP, in LDS, and the range of their levels.
+template <int CAP>
 struct UpList {
-    int32_t id[kUpChunkMax];
-    uint8_t lev[kUpChunkMax];
+    static constexpr int cap = CAP;
+    int32_t id[CAP];
+    uint8_t lev[CAP];
     int count, lmin, lmax;
 };
 
@@ -951,22 +953,23 @@ __device__ inline void up_reset(List &S)
     }
     __syncthreads();
 }
-__device__ inline void up_add(UpList &S, int id, int level)
+template <int CAP>
+__device__ inline void up_add(UpList<CAP> &S, int id, int level)
 {
     if ((unsigned)level > (unsigned)kMaxLevel) return;
     const int k = atomicAdd(&S.count, 1);
-    if (k >= kUpChunkMax) return;  // never: a chunk holds fewer split cells than positions
+    if (k >= CAP) return;  // never: a chunk holds fewer split cells than positions
     S.id[k] = id;
     S.lev[k] = (uint8_t)level;
     atomicMin(&S.lmin, level);
     atomicMax(&S.lmax, level);
 }
 // Sum the listed cells, deepest level first.
-template <int MODE>
-__device__ inline void up_levels(const UpList &S, FFBH_UP_PARAMS)
+template <int MODE, typename List>
+__device__ inline void up_levels(const List &S, FFBH_UP_PARAMS)
 {
     __syncthreads();
-    const int lmin = S.lmin, lmax = S.lmax, count = min(S.count, kUpChunkMax);
+    const int lmin = S.lmin, lmax = S.lmax, count = min(S.count, List::cap);
     for (int l = lmax; l >= lmin; --l) {
         for (int k = threadIdx.x; k < count; k += blockDim.x) {
             if (S.lev[k] != l) continue;
@@ -978,8 +981,8 @@ __device__ inline void up_levels(const UpList &S, FFBH_UP_PARAMS)
     }
 }
 // Sum the leaves among the nodes [i0, i1) and, with `root`, that of system b; with `all`, list the other nodes.
-template <int MODE>
-__device__ inline void up_leaves(UpList &S, int64_t b, int64_t i0, int64_t i1, bool root, bool all, FFBH_UP_PARAMS)
+template <int MODE, typename List>
+__device__ inline void up_leaves(List &S, int64_t b, int64_t i0, int64_t i1, bool root, bool all, FFBH_UP_PARAMS)
 {
     const int count = (int)(i1 > i0 ? i1 - i0 : 0) + (root ? 1 : 0);
     for (int k = threadIdx.x; k < count; k += blockDim.x) {
@@ -999,7 +1002,7 @@ __global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const
                                                            int chunks, int32_t *__restrict__ top, int append,
                                                            int leave)
 {
-    __shared__ UpList S;
+    __shared__ UpList<kUpChunkMax> S;
     const int64_t b = blockIdx.x / chunks;
     const int c = (int)(blockIdx.x - b * chunks);
     const int64_t first = b * n, c0 = c * chunk, c1 = min(c0 + chunk, n);
@@ -1144,53 +1147,71 @@ __device__ inline void pack_source(double *r, bool mixed, double x, double y, do
 // have gaps; entry b of the list array counts the system's nodes below its root.
 // ------------------------------------------------------------------------------------------------
 
-constexpr int kSmallThreads = 1024;
-constexpr int kSmallItems = kSmallMax / kSmallThreads;  // particles per thread
+// The workgroup of a system: its threads, the most particles and the most nodes whose sums stay in LDS.  Both kernels
+// give the same bits with any.  One thread per particle as far as that goes: of 1024 threads a system of 32 leaves 992
+// idle, two such workgroups fill a CU, and a batch is bound by their rounds, where 64 threads leave room for 32.
+// bh_build and bh_field (FP64) with 1024 threads -> with the shape of the size: 4 particles x 262144 systems 14663 ->
+// 1479 us, 32 x 32768 2409 -> 306, 64 x 16384 1304 -> 261, 100 x 10485 1168 -> 421, 256 x 4096 765 -> 441, 512 x 2048
+// 626 -> 471.  One system gains from the cheaper barriers: 32 particles 29.0 -> 24.5 us, 65 32.0 -> 26.3, 256 44.3 ->
+// 39.4, 512 49.0 -> 44.7.
+template <int THREADS, int MAX, int SUM_NODES>
+struct SmallShape {
+    static constexpr int threads = THREADS, waves = THREADS / kWave, max = MAX, items = MAX / THREADS, sum_nodes = SUM_NODES;
+    static constexpr bool passes = MAX > 2048;  // also sorts by counting passes
+};
+using ShapeWide = SmallShape<1024, kSmallMax, 1024>;
+using ShapeHalf = SmallShape<512, 512, 256>;
+using ShapeMid = SmallShape<256, 256, 128>;
+using ShapeNarrow = SmallShape<64, 64, 64>;
 
 // LDS of k_build_small: the sort's keys and values (ping-pong in the counting passes), then the codes in the keys'
 // place and, in the values', the list of cell starts and their cells' keys; the cell masks and their scan.
+template <typename SH>
 struct SmallSort {
+    static constexpr int bins = SH::passes ? kRadixBins : 1;
     union {
-        uint32_t key[2][kSmallMax];  // 31 or 32 bits of the codes
-        uint64_t code[kSmallMax];
+        uint32_t key[2][SH::max];  // 31 or 32 bits of the codes
+        uint64_t code[SH::max];
     };
-    uint16_t val[2][kSmallMax];  // index in the system
+    uint16_t val[2][SH::max];  // index in the system
     union {
-        uint16_t wcnt[kSmallThreads / kWave][kRadixBins];
-        uint16_t scan[kSmallMax];
+        uint16_t wcnt[SH::waves][bins];
+        uint16_t scan[SH::max];
     };
-    uint32_t mask[kSmallMax];
-    uint32_t lstart[kRadixBins];
-    uint32_t dsum[kSmallThreads / kWave];
-    double box[kSmallThreads / kWave][6];
+    uint32_t mask[SH::max];
+    uint32_t lstart[bins];
+    uint32_t dsum[SH::waves];
+    double box[SH::waves][6];
     int starts, flag;
 };
-// Sums and split cells of a system of at most kSumNodes nodes, for its upward pass.
-constexpr int kSumNodes = 1024;
+// Sums and split cells of a system of at most NODES nodes, for its upward pass.
+template <int NODES>
 struct SumList {
-    double sum[kSumNodes][6];  // position sums, moment sums
-    uint16_t from[kSumNodes], len[kSumNodes];  // leaf: first member and count; else first child and children
-    uint16_t cell[kSumNodes];                  // the split cells
-    uint8_t lev[kSumNodes], leaf[kSumNodes];
+    double sum[NODES][6];  // position sums, moment sums
+    uint16_t from[NODES], len[NODES];  // leaf: first member and count; else first child and children
+    uint16_t cell[NODES];              // the split cells
+    uint8_t lev[NODES], leaf[NODES];
     int count, lmin, lmax;
 };
+template <typename SH>
 union SmallUp {
-    UpList list;
-    SumList sums;
+    UpList<SH::max> list;
+    SumList<SH::sum_nodes> sums;
 };
+template <typename SH>
 union SmallLds {
-    SmallSort s;
-    SmallUp up;  // the upward pass, once the tree is written
+    SmallSort<SH> s;
+    SmallUp<SH> up;  // the upward pass, once the tree is written
 };
-static_assert(sizeof(SmallLds) <= 81920, "two workgroups of k_build_small share a CU's LDS");
-static_assert(kSmallThreads / kWave * kRadixBins >= kSmallMax, "the scan fits the counts");
-static_assert(kSmallThreads == 4 * kRadixBins && kSmallThreads / kWave == 16, "four threads per digit, sixteen waves");
+static_assert(sizeof(SmallLds<ShapeWide>) <= 81920, "two workgroups of k_build_small share a CU's LDS");
+static_assert(ShapeWide::threads == 4 * kRadixBins && ShapeWide::waves == 16, "four threads per digit, sixteen waves");
 
 // One stable pass over 8 bits of the keys from buffer src to the other one: every wave ranks a contiguous run of
 // keys (match masks from ballots, running per-wave digit counts), the counts give every key its place.
-__device__ inline void small_pass(SmallSort &S, int n, int src, int shift)
+template <typename SH>
+__device__ inline void small_pass(SmallSort<SH> &S, int n, int src, int shift)
 {
-    constexpr int kWaves = kSmallThreads / kWave;
+    constexpr int kWaves = SH::waves, kSmallThreads = SH::threads, kSmallItems = SH::items;
     const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1);
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     const int chunk = ((n + kWaves * kWave - 1) / (kWaves * kWave)) * kWave, c0 = wave * chunk;
@@ -1249,7 +1270,7 @@ __device__ inline void small_pass(SmallSort &S, int n, int src, int shift)
         const int p = c0 + r * kWave + lane;
         if (p >= n) continue;
         const uint32_t at = S.lstart[dig[r]] + S.wcnt[wave][dig[r]] + rank[r];
-        if (at < (uint32_t)kSmallMax) {  // always true for consistent counts
+        if (at < (uint32_t)SH::max) {  // always true for consistent counts
             S.key[src ^ 1][at] = S.key[src][p];
             S.val[src ^ 1][at] = S.val[src][p];
         }
@@ -1291,10 +1312,10 @@ __device__ inline void sort_step(uint64_t &k, uint32_t &v, int lane)
 // their ties take 13 / 14.  It is bound by issue on the one CU, log(n)^2 a key against a fixed number of passes:
 // 4096 take 32 us, where the passes take 31 (and the Hilbert keys' three passes 20).
 constexpr int kMergeMax = 2048;
-template <typename KeyOf>
-__device__ inline void small_merge_sort(SmallSort &S, int n, const KeyOf &key_of)
+template <typename SH, typename KeyOf>
+__device__ inline void small_merge_sort(SmallSort<SH> &S, int n, const KeyOf &key_of)
 {
-    constexpr int kItems = kMergeMax / kSmallThreads;
+    constexpr int kSmallThreads = SH::threads, kItems = (SH::max < kMergeMax ? SH::max : kMergeMax) / kSmallThreads;
     const int t = threadIdx.x, lane = t & (kWave - 1);
 #pragma unroll
     for (int r = 0; r < kItems; ++r) {
@@ -1357,9 +1378,10 @@ __device__ inline void small_merge_sort(SmallSort &S, int n, const KeyOf &key_of
 
 // The same by counting passes: the codes' upper 31 bits, then runs of equal upper bits by the low 32 (as k_fix_ties);
 // where a run is longer than an insertion sort should take, all 63 bits from the start.
-template <typename KeyOf>
-__device__ inline void small_count_sort(SmallSort &S, int n, const KeyOf &code_of)
+template <typename SH, typename KeyOf>
+__device__ inline void small_count_sort(SmallSort<SH> &S, int n, const KeyOf &code_of)
 {
+    constexpr int kSmallThreads = SH::threads, kSmallItems = SH::items;
     const int t = threadIdx.x;
     if (t == 0) S.flag = 0;  // read behind the passes' barriers
     for (int i = t; i < n; i += kSmallThreads) {
@@ -1422,11 +1444,12 @@ struct SmallArgs {
     int32_t *node_level, *leaf_of, *top;
 };
 
-__device__ inline void up_add(SumList &S, int cell, int level)
+template <int NODES>
+__device__ inline void up_add(SumList<NODES> &S, int cell, int level)
 {
     if ((unsigned)level > (unsigned)kMaxLevel) return;
     const int k = atomicAdd(&S.count, 1);
-    if (k >= kSumNodes) return;  // never: each node is listed once
+    if (k >= NODES) return;  // never: each node is listed once
     S.cell[k] = (uint16_t)cell;
     S.lev[k] = (uint8_t)level;
     atomicMin(&S.lmin, level);
@@ -1452,10 +1475,11 @@ __device__ inline double add_in_order(const double *src, int len, int stride)
 // stay in LDS: a lane sums one component of a node (c = 0..2 positions, 4..6 moments; eight children or sixteen
 // members in flight, added in order), and the records, which no sum needs, are written at the end.  Bound by latency:
 // through memory a level was a chain of four or five loads, 3.7 us; one system of 1000 took 16 us in all and takes 7.
-template <int MODE>
-__device__ inline void small_upward(SmallUp &U, int64_t b, int64_t base, int64_t total, const double *vals,
+template <int MODE, typename SH>
+__device__ inline void small_upward(SmallUp<SH> &U, int64_t b, int64_t base, int64_t total, const double *vals,
                                     const double *vals2, const SmallArgs &a, double *q64, float *q32)
 {
+    constexpr int kSumNodes = SH::sum_nodes;
     if (MODE == 3 || total >= kSumNodes || base + total > a.max_nodes) {
         up_reset(U.list);
         up_leaves<MODE>(U.list, b, base, min(base + total, a.max_nodes), true, true, vals, vals2, a.ntot, a.n, a.nodes,
@@ -1464,7 +1488,7 @@ __device__ inline void small_upward(SmallUp &U, int64_t b, int64_t base, int64_t
                         a.max_nodes, q64, q32);
         return;
     }
-    SumList &S = U.sums;
+    SumList<kSumNodes> &S = U.sums;
     constexpr int kLanes = MODE == 2 ? 8 : 4;
     const int nodes = (int)total + 1, t = threadIdx.x, group = t / kLanes, groups = (int)blockDim.x / kLanes;
     const int c = (t & (kLanes - 1)) + (MODE == 1 ? 4 : 0);
@@ -1512,10 +1536,11 @@ __device__ inline void small_upward(SmallUp &U, int64_t b, int64_t base, int64_t
 // Positions (POS) and moments (MOM) of system b in sorted order, and the packed source records: particle i comes from
 // place from(i) of the caller's order, out-of-range places are flagged.  A thread loads all of its particles before
 // it stores any: one after the other they were four round trips at 4096.
-template <bool MOM, bool POS, typename From, typename Also>
+template <typename SH, bool MOM, bool POS, typename From, typename Also>
 __device__ inline void small_gather(const SmallArgs &a, int64_t b, const double *p, const double *m, const From &from,
                                     const Also &also)
 {
+    constexpr int kSmallThreads = SH::threads, kSmallItems = SH::items;
     const int n = a.n, t = threadIdx.x;
     const int64_t first = b * n;
     int o[kSmallItems];
@@ -1570,13 +1595,13 @@ __device__ inline bool small_starts(const uint64_t *code, int n, int leaf, int j
     return e < n && code[e] <= cell_high(cj, L);
 }
 
-template <bool MOM>
-__global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
+template <bool MOM, typename SH>
+__global__ __launch_bounds__(SH::threads) void k_build_small(SmallArgs a)
 {
-    __shared__ SmallLds lds;
-    SmallSort &S = lds.s;
+    constexpr int kSmallThreads = SH::threads, kSmallItems = SH::items, kWaves = SH::waves;
+    __shared__ SmallLds<SH> lds;
+    SmallSort<SH> &S = lds.s;
     const int t = threadIdx.x, wave = t / kWave, lane = t & (kWave - 1), n = a.n;
-    constexpr int kWaves = kSmallThreads / kWave;
     const int64_t b = blockIdx.x, first = b * n;
     const double *p = a.pos + 3 * first;
     if (a.enter && b == 0 && t == 0) call_enter(a.status);
@@ -1627,18 +1652,18 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
         return morton(quantise(p[i], lo[0], scale), quantise(p[n + i], lo[1], scale), quantise(p[2 * n + i], lo[2], scale));
     };
 
-    if (n <= kMergeMax) {
+    if (!SH::passes || n <= kMergeMax) {
         small_merge_sort(S, n, code_of);
     } else {
-        small_count_sort(S, n, code_of);
+        if constexpr (SH::passes) small_count_sort(S, n, code_of);
     }
 
     // the particles in sorted order (as k_gather3 and k_gather_pack): all of a thread's loads before its stores
-    small_gather<MOM, true>(a, b, p, MOM ? a.mom + 3 * first : nullptr, [&](int i) { return (int)S.val[0][i]; },
-                            [&](int64_t g, int i) {
-                                a.codes[g] = S.code[i];
-                                a.perm[g] = (uint32_t)(first + S.val[0][i]);
-                            });
+    small_gather<SH, MOM, true>(a, b, p, MOM ? a.mom + 3 * first : nullptr, [&](int i) { return (int)S.val[0][i]; },
+                                [&](int64_t g, int i) {
+                                    a.codes[g] = S.code[i];
+                                    a.perm[g] = (uint32_t)(first + S.val[0][i]);
+                                });
     // cell starts, keys and masks (as k_oct_mark): a particle starts a child of the deepest cell that holds it and
     // the one before it iff that cell has more than `leaf` members.  About a quarter do; they are listed first (in
     // any order), so that the searches below run with full waves.
@@ -1699,15 +1724,17 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
     }
     __syncthreads();
     small_upward<MOM ? 2 : 0>(lds.up, b, base, total, a.spos, a.smom, a, nullptr, nullptr);
-    if (a.hilbert) {
-        // target order (as launch_target_order)
-        __syncthreads();
-        for (int i = t; i < n; i += kSmallThreads) {
-            S.key[0][i] = hilbert_key(a.codes[first + i]);
-            S.val[0][i] = (uint16_t)i;
+    if constexpr (SH::passes) {
+        if (a.hilbert) {
+            // target order (as launch_target_order)
+            __syncthreads();
+            for (int i = t; i < n; i += kSmallThreads) {
+                S.key[0][i] = hilbert_key(a.codes[first + i]);
+                S.val[0][i] = (uint16_t)i;
+            }
+            for (int q = 0; q < 3; ++q) small_pass(S, n, q & 1, 8 * q);
+            for (int i = t; i < n; i += kSmallThreads) a.tgt_order[first + i] = (uint32_t)(first + S.val[1][i]);
         }
-        for (int q = 0; q < 3; ++q) small_pass(S, n, q & 1, 8 * q);
-        for (int i = t; i < n; i += kSmallThreads) a.tgt_order[first + i] = (uint32_t)(first + S.val[1][i]);
     }
     if (a.leave) {
         __syncthreads();
@@ -1716,21 +1743,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(SmallArgs a)
 }
 
 // Moments of a small system: gathered into sorted order with the packed source records, then summed upward.
-template <int MODE>
-__global__ __launch_bounds__(kSmallThreads) void k_moments_small(SmallArgs a, double *q64, float *q32)
+template <int MODE, typename SH>
+__global__ __launch_bounds__(SH::threads) void k_moments_small(SmallArgs a, double *q64, float *q32)
 {
-    __shared__ SmallUp U;
-    static_assert(kSmallMax <= kUpChunkMax, "every split cell fits");
+    __shared__ SmallUp<SH> U;
     const int n = a.n;
     const int64_t b = blockIdx.x, first = b * n;
     if (a.enter && b == 0 && threadIdx.x == 0) call_enter(a.status);
     if (a.mom) {  // else they are there
-        small_gather<true, false>(a, b, a.spos, a.mom + 3 * first,
-                                  [&](int i) {
-                                      const int64_t o = (int64_t)a.perm[first + i] - first;
-                                      return o < 0 || o >= n ? -1 : (int)o;
-                                  },
-                                  [](int64_t, int) {});
+        small_gather<SH, true, false>(a, b, a.spos, a.mom + 3 * first,
+                                      [&](int i) {
+                                          const int64_t o = (int64_t)a.perm[first + i] - first;
+                                          return o < 0 || o >= n ? -1 : (int)o;
+                                      },
+                                      [](int64_t, int) {});
     }
     __syncthreads();
     const int64_t base = a.B + 2 * first, total = min((int64_t)(uint32_t)a.top[b], (int64_t)2 * n);
@@ -1780,6 +1806,16 @@ static SmallArgs small_args(Handle &h, const double *d_pos, const double *d_mom,
 // Host launch sequences
 // ------------------------------------------------------------------------------------------------
 
+// f(shape) with the workgroup shape of systems of n particles: the narrowest with a thread for each.
+template <typename F>
+static void with_small_shape(int64_t n, const F &f)
+{
+    if (n <= ShapeNarrow::max) f(ShapeNarrow{});
+    else if (n <= ShapeMid::max) f(ShapeMid{});
+    else if (n <= ShapeHalf::max) f(ShapeHalf{});
+    else f(ShapeWide{});
+}
+
 #define FFBH_TRY(x)                         \
     do {                                    \
         hipError_t e_ = (x);                \
@@ -1797,8 +1833,11 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     if (L.n <= kSmallMax) {
         SmallArgs a = small_args(h, d_pos, d_mom, enter);
         if (leave) a.leave = *leave = B == 1 && !side && !after_sort;
-        if (d_mom) hipLaunchKernelGGL(k_build_small<true>, dim3((unsigned)B), dim3(kSmallThreads), 0, s, a);
-        else hipLaunchKernelGGL(k_build_small<false>, dim3((unsigned)B), dim3(kSmallThreads), 0, s, a);
+        with_small_shape(n, [&](auto shape) {
+            using SH = decltype(shape);
+            if (d_mom) hipLaunchKernelGGL((k_build_small<true, SH>), dim3((unsigned)B), dim3(SH::threads), 0, s, a);
+            else hipLaunchKernelGGL((k_build_small<false, SH>), dim3((unsigned)B), dim3(SH::threads), 0, s, a);
+        });
         if (side) {
             FFBH_TRY(hipEventRecord(h.sorted_ev, s));
             FFBH_TRY(hipStreamWaitEvent(side, h.sorted_ev, 0));
@@ -1964,13 +2003,26 @@ static void gather_moments(Handle &h, const double *d_mom, hipStream_t s, bool e
                        enter ? 1 : 0);
 }
 
+// Moments of a small system summed upward (with the first moments for order-2 cells).
+static void launch_moments_small(Handle &h, const SmallArgs &a, hipStream_t s)
+{
+    const unsigned B = (unsigned)h.L.B;
+    with_small_shape(h.L.n, [&](auto shape) {
+        using SH = decltype(shape);
+        if (h.L.expansion == 2)
+            hipLaunchKernelGGL((k_moments_small<3, SH>), dim3(B), dim3(SH::threads), 0, s, a, h.w.node_q64, h.w.node_q32);
+        else
+            hipLaunchKernelGGL((k_moments_small<1, SH>), dim3(B), dim3(SH::threads), 0, s, a, (double *)nullptr,
+                               (float *)nullptr);
+    });
+}
+
 // First moments of every node from the moments and positions of a build with moments: the order-2 cells of an MD
 // step.
 hipError_t launch_upward_first_moments(Handle &h, const double *d_mom, hipStream_t s)
 {
     if (h.L.n <= kSmallMax)
-        hipLaunchKernelGGL(k_moments_small<3>, dim3((unsigned)h.L.B), dim3(kSmallThreads), 0, s,
-                           small_args(h, nullptr, d_mom, false), h.w.node_q64, h.w.node_q32);
+        launch_moments_small(h, small_args(h, nullptr, d_mom, false), s);
     else
         upward<3>(h, h.w.smom, h.w.spos, s, false, false);
     return hipGetLastError();
@@ -1983,12 +2035,7 @@ hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s, 
         const bool apart = h.L.n > kMergeMax;
         if (apart) gather_moments(h, d_mom, s, enter);
         const SmallArgs a = small_args(h, nullptr, apart ? nullptr : d_mom, enter && !apart);
-        if (h.L.expansion == 2)
-            hipLaunchKernelGGL(k_moments_small<3>, dim3((unsigned)h.L.B), dim3(kSmallThreads), 0, s, a, h.w.node_q64,
-                               h.w.node_q32);
-        else
-            hipLaunchKernelGGL(k_moments_small<1>, dim3((unsigned)h.L.B), dim3(kSmallThreads), 0, s, a,
-                               (double *)nullptr, (float *)nullptr);
+        launch_moments_small(h, a, s);
         return hipGetLastError();
     }
     gather_moments(h, d_mom, s, enter);

@@ -276,3 +276,49 @@ def test_queries_before_the_first_replay_find_no_nodes(n, batch):
     assert all((t[nn:] == -7).all() for t in out) and (cen[3 * nn:] == -7.0).all()
     L.bh_graph_destroy(g)
     L.bh_destroy(h)
+
+
+@pytest.mark.parametrize("n,leaf", [(2, 1), (63, 16), (64, 1), (65, 1), (255, 16), (256, 1), (256, 16), (257, 1), (512, 1), (513, 16)])
+def test_tree_at_the_edges_of_the_workgroup_shapes(oracle_mod, n, leaf):
+    """64, 256, 512 or 1024 threads build a system, by its size; with leaf size 1 a system has more nodes than the sums on the
+    chip hold.  Three systems, in each a quarter of the particles in a cluster 1e-4 wide and an eighth at one point:
+    order, cells and centres are the oracle's, bit for bit."""
+    rng = np.random.default_rng(7 * n + leaf)
+    ws = [workloads.uniform_cube(n, 4.0 + 2.0 * n ** (1 / 3), seed=n + b) for b in range(3)]
+    pos, mom = np.stack([w.pos for w in ws]), np.stack([w.mom for w in ws])
+    for b in range(3):
+        pick = rng.permutation(n)
+        a, c = pick[:n // 4], pick[n // 4:n // 4 + n // 8]
+        pos[b][:, a] = np.array([[1.0], [2.0], [3.0]]) + 1e-4 * rng.random((3, a.size))
+        pos[b][:, c] = np.array([[3.5], [2.25], [1.75]])
+    g = run_field(pos, mom, leaf=leaf, counters=False)["bh"].export_tree()
+    total = sum(_compare(pos[b], mom[b], leaf, oracle_mod, offset=b * n, gtree=g) for b in range(3))
+    assert total == g["first"].size
+
+
+def test_four_million_pairs():
+    """2^22 systems of two particles, more than a launch of 1024 threads a system can hold (2^32 threads): the field of
+    each pair is its partner's dipole field."""
+    import torch
+    from paper_1212_2934_amd import binding
+    from paper_1212_2934_amd.binding import BarnesHut
+    B = 1 << 22
+    need = binding.workspace_bytes(binding.make_params(2, B, 16, 0.5, "fp64")) + (8 << 30)
+    if torch.cuda.mem_get_info()[0] < need:
+        pytest.skip(f"needs {need >> 30} GiB of free device memory")
+    print(f"[pairs] {need >> 30} GiB", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    pos = torch.rand(B, 3, 2, dtype=torch.float64, device="cuda", generator=gen)
+    pos[:, :, 1] += 1.0
+    mom = torch.randn(B, 3, 2, dtype=torch.float64, device="cuda", generator=gen)
+    bh = BarnesHut(2, B, 16, 0.5, "fp64")
+    bh.build(pos)
+    H = bh.field(mom, energy=False)
+    assert bh.check_status() == 0
+    r = pos[:, :, :1] - pos[:, :, 1:]
+    m = mom.flip(2)
+    r2 = (r * r).sum(1, keepdim=True)
+    ref = (3 * r * (m * r).sum(1, keepdim=True) / r2 - m) / r2 ** 1.5
+    assert ((H - ref).norm() / ref.norm()).item() <= 1e-14
+    del bh
+    torch.cuda.empty_cache()

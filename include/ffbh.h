@@ -183,9 +183,10 @@ typedef struct md_params {
 
 /* One MD step: bh_build on the current positions, field + adjoint of the energy, WCA forces, and the
  * integrator update.  Enqueued on the stream with no host synchronisation (capturable in a graph).  From
- * 16384 particles over the batch, the short-range forces and the ordering of the traversal's work run on
- * the handle's own stream, forked from `stream` (event record + wait) and joined back to it before the
- * traversal; smaller steps run on `stream` alone.  Either way the step starts after everything enqueued
+ * 16384 particles over the batch, the ordering of the traversal's work (in the shapes that have one) and,
+ * for systems of more than 4096 particles, the short-range forces run on the handle's own stream, forked
+ * from `stream` (event record + wait) and joined back to it before the traversal; other steps run on
+ * `stream` alone.  Either way the step starts after everything enqueued
  * on `stream` before it and is complete for everything enqueued on `stream` after it. */
 bh_status md_step(bh_handle *h, const md_state *s, const md_params *p, void *stream);
 

@@ -432,11 +432,11 @@ bh_status bh_build(bh_handle *hh, const double *d_pos, void *stream)
     if (!hh || !dptr_ok(d_pos)) return BH_EINVAL;
     // large builds put the targets in Hilbert order on the handle's side stream, beside the octree
     Handle &h = hh->h;
-    const hipStream_t side = h.L.ntot >= kForkMinParticles && uses_target_order(h.L) ? h.side : nullptr;
+    const hipStream_t side = forks_build(h) ? h.side : nullptr;
     const hipStream_t s = (hipStream_t)stream;
     // the forward walk's wave items are ordered from the costs of the previous walk, and the next bh_field
     // takes them in that order: beside the octree on the side stream, or after the build on the caller's
-    // stream for a handle without one (the ordering costs less than the walk's tail it removes); walks that a
+    // stream where the build does not fork (the ordering costs less than the walk's tail it removes); walks that a
     // workgroup's waves share need no order, all of them run at once
     const bool ordered = uses_field_order(h.L);
     SortedWork order_field;

@@ -1832,21 +1832,14 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     const int64_t n = L.n, B = L.B, ntot = L.ntot;
     if (L.n <= kSmallMax) {
         SmallArgs a = small_args(h, d_pos, d_mom, enter);
-        if (leave) a.leave = *leave = B == 1 && !side && !after_sort;
+        if (leave) a.leave = *leave = B == 1 && !after_sort;
         with_small_shape(n, [&](auto shape) {
             using SH = decltype(shape);
             if (d_mom) hipLaunchKernelGGL((k_build_small<true, SH>), dim3((unsigned)B), dim3(SH::threads), 0, s, a);
             else hipLaunchKernelGGL((k_build_small<false, SH>), dim3((unsigned)B), dim3(SH::threads), 0, s, a);
         });
-        if (side) {
-            FFBH_TRY(hipEventRecord(h.sorted_ev, s));
-            FFBH_TRY(hipStreamWaitEvent(side, h.sorted_ev, 0));
-        }
-        if (after_sort) FFBH_TRY(after_sort(side ? side : s));
-        if (side && join) {
-            FFBH_TRY(hipEventRecord(h.join_ev, side));
-            FFBH_TRY(hipStreamWaitEvent(s, h.join_ev, 0));
-        }
+        // the sort ends with the build: nothing of it is left to run beside after_sort's work
+        if (after_sort) FFBH_TRY(after_sort(s));
         return hipGetLastError();
     }
     // partial boxes: at most kBboxBlocks per system, no more than one workgroup per 256 particles

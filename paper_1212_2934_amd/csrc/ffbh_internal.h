@@ -227,7 +227,8 @@ inline bool has_id_gaps(const Layout &L) { return L.n <= kSmallMax && L.B > 1; }
 // final, the side stream waits for it and computes the traversal's target order, then enqueues
 // after_sort's work (which needs only the sorted particles), beside the rest of the build; with join the
 // caller's stream then waits for the side stream at the end of the build, without it the caller joins
-// the side stream itself (h.join_ev) before the traversal.  Without a side stream everything runs on s.
+// the side stream itself (h.join_ev) before the traversal.  Without a side stream everything runs on s, and so it
+// does for systems of at most kSmallMax particles, whose build is one kernel (no side stream is passed then).
 // With enter, the build's first kernel counts the call in (call_enter).  With leave, its last one counts the call out
 // where that is the call's only workgroup (one small system); *leave is whether it does.
 using SortedWork = std::function<hipError_t(hipStream_t)>;
@@ -262,6 +263,12 @@ void launch_order_items(const uint32_t *cost, int nw, uint32_t *order, uint32_t 
 int walk_split(int64_t groups);
 int walk_targets(const Handle &h);  // targets per group of a divided walk
 int split_shift(int64_t n, int W);
+// Whether a build forks the handle's side stream: from kForkMinParticles over the batch, where it has more than one
+// kernel.
+inline bool forks_build(const Handle &h)
+{
+    return h.side != nullptr && h.L.ntot >= kForkMinParticles && h.L.n > kSmallMax;
+}
 // Whether bh_build orders the forward walk's items: from 16384 particles on, where the walks are undivided.
 inline bool uses_field_order(const Layout &L) { return L.ntot >= kForkMinParticles && walk_split(L.num_waves) == 1; }
 // Order of the forward walk's items from the costs the previous forward walk recorded.

@@ -455,15 +455,17 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
     // short, latency-bound launches).  The side stream rejoins the caller's
     // before the traversal, which therefore has the whole device.  The step starts after everything
     // enqueued on the caller's stream before it and is complete for everything enqueued after it; under
-    // graph capture the fork and the join become edges.  Small systems, and handles without a side stream,
-    // keep everything on one stream.
+    // graph capture the fork and the join become edges.  Steps of fewer particles, and handles without a side
+    // stream, keep everything on one stream; systems built by one kernel have only the order of the items on the
+    // side stream (the short-range forces need the whole build: 64 x 1000 particles take 238 us a step, 256 with them there).
     hipError_t e;
-    const bool fork = L.ntot >= kForkMinParticles && h.side != nullptr;  // a bh_init handle has no side stream
-    const bool order = fork && uses_wave_order(h);  // else launch_backward orders the items itself
+    const bool fork = forks_build(h);
+    const bool order = h.side && L.ntot >= kForkMinParticles && uses_wave_order(h);  // else launch_backward orders them
     if (order) {
         if ((e = hipEventRecord(h.fork_ev, s)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(h.side, h.fork_ev, 0)) != hipSuccess) return e;
         launch_order_waves(h, h.side);
+        if (!fork && (e = hipEventRecord(h.join_ev, h.side)) != hipSuccess) return e;
     }
     // short-range forces from the sorted particles (on the side stream when forked)
     // sr_kind 0: WCA, pair and wall cut at the potential minimum; 1: the paper's form, walls at half the pair cut
@@ -510,7 +512,7 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
         e = launch_upward_first_moments(h, st->mom, s);  // order-2 cells
         if (e != hipSuccess) return e;
     }
-    if (fork && (e = hipStreamWaitEvent(s, h.join_ev, 0)) != hipSuccess) return e;
+    if ((fork || order) && (e = hipStreamWaitEvent(s, h.join_ev, 0)) != hipSuccess) return e;
     e = launch_backward(h, st->mom, mp->d_hext, nullptr, w.ones, small ? nullptr : w.md_grad_r, w.md_grad_m, nullptr, s,
                         true, order, setup_early);
     if (e != hipSuccess) return e;

@@ -272,6 +272,43 @@ def test_caller_owned_handle_steps_without_a_side_stream(tuning_id):
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
 
+@pytest.mark.parametrize("tuning_id", [-1, 9, 12])
+def test_steps_of_small_systems_on_a_busy_stream(tuning_id):
+    """17 systems of 1000 (17000 over the batch), each built by one kernel: the step stays on the caller's stream, but
+    the item order of the cost-ordered shapes (9 persistent, 12 one wave per item) is made on the handle's.  State and
+    steps are enqueued on a stream that is still busy; the result equals the reference trajectory."""
+    rng = np.random.default_rng(17)
+    w = workloads.uniform_cube(1000, 20.0, seed=18)
+    rows = 2
+    st = {k: np.concatenate([a, b]) for (k, a), b in zip(_state(w, rng).items(), _state(w, rng).values())}
+    p = dict(_params(20.0), kT=0.0, hext=np.tile([[0.0, 0.0, 0.5]], (rows, 1)))
+    ref = st
+    for k in range(3):
+        ref = omd.md_step(ref, p, k, theta=0.5, leaf=16)
+    pick = np.arange(17) % rows
+    src = _to_dev({k: v[pick] for k, v in st.items()})
+    d = {k: torch.zeros_like(v) for k, v in src.items()}
+    bh = BarnesHut(1000, 17, 16, 0.5, "fp64", tuning_id=tuning_id)
+    he = torch.from_numpy(np.tile(p["hext"][:1], (17, 1))).cuda()
+    mp = _mdp(p, he)
+    a = torch.randn(2048, 2048, device="cuda")
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        for _ in range(8):  # keeps the stream busy while the host enqueues the rest
+            a = torch.tanh(a @ a)
+        for k in d:
+            d[k].copy_(src[k])
+        for _ in range(3):
+            bh.md_step(d, mp)
+        out = {k: v.clone() for k, v in d.items()}
+    s.synchronize()
+    assert bh.check_status() == 0 and int(out["step"].item()) == 3
+    for key in ("pos", "vel", "mom", "omega"):
+        err = np.abs(out[key].cpu().numpy() - ref[key][pick]).max() / np.abs(ref[key]).max()
+        assert err <= 1e-11, (key, err)
+
+
 def test_resume_continues_the_same_trajectory():
     w = workloads.uniform_cube(2000, 24.0, seed=6)
     rng = np.random.default_rng(7)

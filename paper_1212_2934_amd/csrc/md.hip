@@ -221,9 +221,17 @@ __global__ __launch_bounds__(256) void k_wca(const uint64_t *__restrict__ codes,
 // Bound by latency for one system (one of 1000: 37 us in three launches -> 10), by issue for many (64 of 1000: 27 ->
 // 14 us).  A whole step of 1000 / 64 x 1000 / 16 x 4096 takes 139.4 / 287.5 / 478.0 us with 8 lanes, 138.4 / 290.6
 // / 480.6 with 16, 139.4 / 302.6 / 488.6 with 32.  Above kSmallMax the table outgrows 16 bits and one thread per
-// particle fills the chip.
+// particle fills the chip, and so it does in a larger batch, where the 8 lanes' searches for each candidate cost more
+// than they spread (kSmallStepMax particles over the batch).  A step with 8 lanes and with one, us: 131072 particles, 262 x
+// 500 245 / 247 and with a cut-off of 8 diameters 431 / 443, 131 x 1000 459 / 473 and 814 / 830, 32 x 4096 577 / 568 and
+// 1666 / 1745; 262144 particles, 524 x 500 353 / 338 and 742 / 641, 262 x 1000 660 / 647 and 1343 / 1203, 64 x 4096 749 /
+// 708 and 2842 / 2470.
+// kSrGroups workgroups over the batch, as many as there are particles for: each fills a table of its own, but with one of
+// 512 threads a system and 262 x 500 there were two waves a SIMD (8 diameters: 645 us with 512 workgroups, 463 with 2048,
+// 431 with 4096; the default law of 16 x 4096 takes 352 / 361 / 361).
+constexpr int64_t kSmallStepMax = 1 << 17;
 constexpr int kSrThreads = 512, kSrLanes = 8, kSrAtOnce = kSrThreads / kSrLanes, kSrLevel = 4;
-constexpr int64_t kSrGroups = 512;
+constexpr int64_t kSrGroups = 4096;
 
 __global__ __launch_bounds__(kSrThreads) void k_wca_small(
     const uint64_t *__restrict__ codes, const double *__restrict__ bbox, const double *__restrict__ spos,
@@ -477,11 +485,11 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
     // Small systems: the set-up of the walk runs with the short-range forces, and k_finish_small ends the step.
     // The order-2 moments come after the short-range forces and sum in the node adjoints, so there the walk's
     // zeros have to wait.
-    const bool small = L.n <= kSmallMax, setup_early = small && L.expansion != 2;
+    const bool small = L.n <= kSmallMax && L.ntot <= kSmallStepMax, setup_early = small && L.expansion != 2;
     const SortedWork short_range = [&](hipStream_t ss) {
         const double3 lo = make_double3(mp->box_lo[0], mp->box_lo[1], mp->box_lo[2]);
         const double3 hi = make_double3(mp->box_hi[0], mp->box_hi[1], mp->box_hi[2]);
-        if (L.n <= kSmallMax) {
+        if (small) {
             AdjSetup setup = adj_setup_args(h, nullptr, w.ones);
             if (!setup_early) setup.hbar = nullptr;
             // about kSrGroups workgroups: every one fills a table of its own

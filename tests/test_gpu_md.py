@@ -309,6 +309,35 @@ def test_steps_of_small_systems_on_a_busy_stream(tuning_id):
         assert err <= 1e-11, (key, err)
 
 
+@pytest.mark.parametrize("expansion", [1, 2])
+@pytest.mark.parametrize("n,batch,sr_cut", [(64, 2048, 0.0), (64, 2049, 0.0), (1000, 132, 6.0), (4096, 33, 0.0)])
+def test_small_systems_in_batches_on_either_side_of_the_small_step(n, batch, sr_cut, expansion):
+    """Up to 131072 particles over the batch the short-range forces take 8 lanes a particle and one launch ends the step;
+    above, systems of at most 4096 particles take the launches of large ones.  Two steps of copies of two systems
+    against the same two alone; forces are summed in another order, the bound is that of the tests above."""
+    rng = np.random.default_rng(n + batch)
+    side = max(4.0, 2.5 * n ** (1.0 / 3.0))
+    pos, mom = workloads.rsa_chains(rng, n, (0.0, 0.0, 0.0), (side, side, side))
+    st = dict(pos=pos[None] + rng.standard_normal((2, 3, n)) * 0.01, vel=rng.standard_normal((2, 3, n)),
+              mom=np.repeat(mom[None], 2, 0), omega=rng.standard_normal((2, 3, n)))
+    p = dict(_params(side), kT=0.0)
+    pick = np.arange(batch) % 2
+    out = []
+    for rows in (np.arange(2), pick):
+        bh = BarnesHut(n, rows.size, 16, 0.5, "fp64", expansion=expansion)
+        d = _to_dev({k: v[rows] for k, v in st.items()})
+        he = torch.from_numpy(np.tile(p["hext"], (rows.size, 1))).cuda()
+        mp = _mdp(p, he)
+        mp.sr_kind, mp.sr_cut = (1, sr_cut) if sr_cut else (0, 0.0)
+        for _ in range(2):
+            bh.md_step(d, mp)
+        assert bh.check_status() == 0 and int(d["step"].item()) == 2
+        out.append({k: d[k].cpu().numpy() for k in ("pos", "vel", "mom", "omega")})
+    for key, two in out[0].items():
+        err = np.abs(out[1][key] - two[pick]).max() / np.abs(two).max()
+        assert err <= 1e-11, (key, err)
+
+
 def test_resume_continues_the_same_trajectory():
     w = workloads.uniform_cube(2000, 24.0, seed=6)
     rng = np.random.default_rng(7)

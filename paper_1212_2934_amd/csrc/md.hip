@@ -440,6 +440,7 @@ __global__ __launch_bounds__(256) void k_finish_small(Downward a, MDState st, co
         downward<true>(a, s, b, dr, dm);
         integrate(st, p, c, step, a.n, b, i, dr, dm);
     }
+    __syncthreads();
     if (threadIdx.x == 0) call_leave(status);  // counted in once per workgroup
 }
 

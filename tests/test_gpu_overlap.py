@@ -159,3 +159,44 @@ def test_queries_that_write_the_workspace_are_counted(query, n, batch, writes):
     assert int(words[IN_FLIGHT].item()) == 1
     words[IN_FLIGHT] = 0
     assert bh.check_status() == (binding.FLAG_OVERLAP if writes else 0)
+
+
+@pytest.mark.parametrize("n,batch", [(1000, 1), (4096, 1), (300, 7), (64, 2049)])
+@pytest.mark.parametrize("entry", ["build", "field", "field_backward", "md_step"])
+def test_calls_on_small_systems_are_counted(entry, n, batch):
+    """Systems of at most 4096 particles: a build of one workgroup counts itself out, and a step is counted in once for
+    each workgroup of its last launch (up to 131072 particles over the batch; 64 x 2049 takes the launches of large
+    systems).  A call alone leaves the count at zero, one that finds another in flight is flagged and leaves it."""
+    torch.cuda.set_device(0)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    side = 2.0 * n ** (1.0 / 3.0) + 1.0
+    d = {"pos": side * torch.rand(batch, 3, n, dtype=torch.float64, device="cuda", generator=gen),
+         "mom": torch.randn(batch, 3, n, dtype=torch.float64, device="cuda", generator=gen),
+         "step": torch.zeros(1, dtype=torch.int64, device="cuda")}
+    d["vel"], d["omega"] = torch.zeros_like(d["pos"]), torch.zeros_like(d["pos"])
+    mdp = _mdp(side)
+    mdp.wca_eps = 0.0  # the random particles overlap
+    bh = BarnesHut(n, batch, 16, 0.5, "fp32_mixed")
+    bh.build(d["pos"])
+    words = _status_words(bh)
+
+    def call():
+        if entry == "build":
+            bh.build(d["pos"])
+        elif entry == "field":
+            bh.field(d["mom"])
+        elif entry == "field_backward":
+            bh.field_backward(d["mom"])
+        else:
+            bh.md_step(d, mdp)
+        torch.cuda.synchronize()
+
+    call()
+    assert bh.check_status() == 0 and int(words[IN_FLIGHT].item()) == 0
+    words[IN_FLIGHT] = 1  # as if a call on another stream were running
+    call()
+    assert int(words[IN_FLIGHT].item()) == 1
+    words[IN_FLIGHT] = 0
+    assert bh.check_status() == binding.FLAG_OVERLAP
+    call()
+    assert bh.check_status() == 0 and int(words[IN_FLIGHT].item()) == 0

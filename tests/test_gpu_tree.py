@@ -322,3 +322,22 @@ def test_four_million_pairs():
     assert ((H - ref).norm() / ref.norm()).item() <= 1e-14
     del bh
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,batch", [(4097, 3), (6000, 2), (10000, 3)])
+def test_tree_of_a_batch_above_the_one_workgroup_build(oracle_mod, n, batch):
+    """Systems of more than 4096 particles are built by launches over the whole batch: tiles, chunks of the upward pass
+    (ragged at the end of each system) and the lists of cells across chunks stay inside their system.  Chains, with a
+    tenth of the particles in a cluster and some at one point; order, cells and centres are the oracle's, bit for bit."""
+    rng = np.random.default_rng(n)
+    ws = [workloads.config3(seed=700 + b, n=n) for b in range(batch)]
+    pos, mom = np.stack([w.pos for w in ws]), np.stack([w.mom for w in ws])
+    for b in range(batch):
+        pick = rng.permutation(n)
+        a, c = pick[:n // 10], pick[n // 10:n // 10 + 70]
+        pos[b][:, a] = np.array([[1.0 + b], [2.0], [3.0]]) + 1e-3 * rng.random((3, a.size))
+        pos[b][:, c] = np.array([[3.5], [2.25], [1.75 + b]])
+    g = run_field(pos, mom, counters=False)["bh"].export_tree()
+    total = sum(_compare(pos[b], mom[b], 16, oracle_mod, offset=b * n, gtree=g) for b in range(batch))
+    assert total == g["first"].size
+    assert (g["first"][:batch] == n * np.arange(batch)).all()

@@ -793,8 +793,7 @@ __global__ __launch_bounds__(kOctThreads) void k_oct_emit(const uint64_t *__rest
 // levels, the cells inside the chunk: a cell's key lies inside it, so the chunk's keys list them all, and their
 // children are leaves of the chunk's or cells inside the chunk.  Cells that reach beyond their chunk (the
 // ancestors of the chunk boundaries, about seven a boundary) are listed per system when the tree is built and
-// follow in a second launch of one workgroup per system (k_upward_top).  Systems of one chunk need no second
-// launch.
+// follow in a second launch of one workgroup per system (k_upward_top).
 //
 // A launch costs about 4.5 us in a stream, so what the pass cost before, one launch per level (twelve of them
 // above 2^16 nodes, 50-60 us for a few us of work), is now two.
@@ -998,9 +997,9 @@ template <int MODE>
 __global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const uint32_t *__restrict__ mask,
                                                            const uint32_t *__restrict__ scan,
                                                            const int32_t *__restrict__ cell_id,
-                                                           uint32_t *__restrict__ status, int64_t B, int64_t chunk,
-                                                           int chunks, int32_t *__restrict__ top, int append,
-                                                           int leave)
+                                                           const uint32_t *__restrict__ status, int64_t B,
+                                                           int64_t chunk, int chunks, int32_t *__restrict__ top,
+                                                           int append)
 {
     __shared__ UpList<kUpChunkMax> S;
     const int64_t b = blockIdx.x / chunks;
@@ -1023,12 +1022,10 @@ __global__ __launch_bounds__(kUpThreads) void k_upward_sub(FFBH_UP_PARAMS, const
     auto start = [&](int64_t i) { return B + (int64_t)(first + i < ntot ? scan[first + i] : status[1]); };
     up_leaves<MODE>(S, b, start(c0), min(start(c1), max_nodes), c == 0, false, FFBH_UP_ARGS);
     up_levels<MODE>(S, FFBH_UP_ARGS);
-    if (leave && threadIdx.x == 0) call_leave(status);
 }
 
 template <int MODE>
-__global__ __launch_bounds__(kUpThreads) void k_upward_top(FFBH_UP_PARAMS, uint32_t *__restrict__ status, int64_t B,
-                                                           const int32_t *__restrict__ top, int leave)
+__global__ __launch_bounds__(kUpThreads) void k_upward_top(FFBH_UP_PARAMS, int64_t B, const int32_t *__restrict__ top)
 {
     __shared__ uint8_t lev[kUpChunkMax];  // levels of the first entries; of the others they are read again
     __shared__ int lmin, lmax;
@@ -1064,29 +1061,22 @@ __global__ __launch_bounds__(kUpThreads) void k_upward_top(FFBH_UP_PARAMS, uint3
         }
         __syncthreads();
     }
-    if (leave && threadIdx.x == 0) call_leave(status);
 }
 
-// append: the build's pass lists the cells that reach beyond their chunk.  leave: the pass is the call's last
-// work; returns whether its last kernel counts the call out (it does where it is one workgroup, so that nothing
-// of the call still runs then).
+// append: the build's pass lists the cells that reach beyond their chunk.
 template <int MODE>
-static bool upward(Handle &h, const double *vals, const double *vals2, hipStream_t s, bool append, bool leave)
+static void upward(Handle &h, const double *vals, const double *vals2, hipStream_t s, bool append)
 {
     const Layout &L = h.L;
     Workspace &w = h.w;
     const int64_t chunk = up_chunk_size(L);
     const int chunks = (int)((L.n + chunk - 1) / chunk);
-    leave = leave && L.B == 1;
     hipLaunchKernelGGL(k_upward_sub<MODE>, dim3((unsigned)(L.B * chunks)), dim3(kUpThreads), 0, s, vals, vals2, L.ntot,
                        L.n, w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
-                       w.cell_mask, w.cell_scan, w.cell_id, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0,
-                       leave && chunks == 1 ? 1 : 0);
-    if (chunks > 1)
-        hipLaunchKernelGGL(k_upward_top<MODE>, dim3((unsigned)L.B), dim3(kUpThreads), 0, s, vals, vals2, L.ntot, L.n,
-                           w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32,
-                           w.status, L.B, w.top_nodes, leave ? 1 : 0);
-    return leave;
+                       w.cell_mask, w.cell_scan, w.cell_id, w.status, L.B, chunk, chunks, w.top_nodes, append ? 1 : 0);
+    hipLaunchKernelGGL(k_upward_top<MODE>, dim3((unsigned)L.B), dim3(kUpThreads), 0, s, vals, vals2, L.ntot, L.n,
+                       w.nodes, w.node_adj, w.node_m64, w.node_level, w.bbox, L.max_nodes, w.node_q64, w.node_q32, L.B,
+                       w.top_nodes);
 }
 
 // Hilbert index of the cell (x, y, z) of a 2^b grid per axis: Skilling's transform of the axes to the
@@ -1879,9 +1869,8 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
         if (e != hipSuccess) return e;
     }
     // Replayed graphs submit the kernels in the order they were captured, so the order of the enqueues
-    // below matters: the first octree kernels go first, the side stream's work next (before the rest of
-    // the octree, which it runs beside).  With the side stream's work first, the binary radix tree started
-    // up to 130 us after the sort in graph replays.
+    // below matters: the first octree kernel goes first, the side stream's work next (before the rest of
+    // the octree, which it runs beside).
     const int64_t sysblocks = (n + kOctThreads - 1) / kOctThreads;
     hipLaunchKernelGGL(k_oct_mark, dim3((unsigned)(B * sysblocks)), dim3(kOctThreads), 0, s, w.codes, (int)n,
                        (int)h.p.leaf_size, w.cell_key, w.cell_mask, sysblocks);
@@ -1897,9 +1886,9 @@ hipError_t launch_build(Handle &h, const double *d_pos, hipStream_t s, const dou
     if (d_mom) {
         // positions and moments summed in one upward pass
         gather_moments(h, d_mom, s, false);
-        upward<2>(h, w.spos, w.smom, s, true, false);
+        upward<2>(h, w.spos, w.smom, s, true);
     } else {
-        upward<0>(h, w.spos, nullptr, s, true, false);
+        upward<0>(h, w.spos, nullptr, s, true);
     }
     if (side && join) {
         hipError_t e = hipEventRecord(h.join_ev, side);
@@ -2017,7 +2006,7 @@ hipError_t launch_upward_first_moments(Handle &h, const double *d_mom, hipStream
     if (h.L.n <= kSmallMax)
         launch_moments_small(h, small_args(h, nullptr, d_mom, false), s);
     else
-        upward<3>(h, h.w.smom, h.w.spos, s, false, false);
+        upward<3>(h, h.w.smom, h.w.spos, s, false);
     return hipGetLastError();
 }
 
@@ -2033,9 +2022,9 @@ hipError_t launch_upward_moments(Handle &h, const double *d_mom, hipStream_t s, 
     }
     gather_moments(h, d_mom, s, enter);
     if (h.L.expansion == 2)
-        upward<3>(h, h.w.smom, h.w.spos, s, false, false);
+        upward<3>(h, h.w.smom, h.w.spos, s, false);
     else
-        upward<1>(h, h.w.smom, nullptr, s, false, false);
+        upward<1>(h, h.w.smom, nullptr, s, false);
     return hipGetLastError();
 }
 

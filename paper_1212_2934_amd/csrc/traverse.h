@@ -53,12 +53,6 @@ __device__ inline void dip_acc_r2(bool use, T r2, T x, T y, T z, T mx, T my, T m
 template <typename T>
 __device__ inline T norm2(T x, T y, T z) { return fmaT<T>(z, z, fmaT<T>(y, y, x * x)); }
 
-template <typename T>
-__device__ inline void dip_acc(bool use, T x, T y, T z, T mx, T my, T mz, T &hx, T &hy, T &hz)
-{
-    dip_acc_r2<T>(use, norm2<T>(x, y, z), x, y, z, mx, my, mz, hx, hy, hz);
-}
-
 // Field of a cell's first moment D (row-major, D[3k+b] = sum_j (r_j - c)_k m_j,b) at offset x from the
 // cell's centre c: the next term of the Taylor expansion of Eq. H_dip about c,
 //   h = -3 (D x + D^T x + x tr D) / |x|^5 + 15 (x.D x) x / |x|^7 .
@@ -173,13 +167,6 @@ __device__ inline void adj_field_r2(bool use, T r2, T x, T y, T z, T ax, T ay, T
     hz = fmaT<T>(fmaT<T>(tb, z, -bz), ri3, hz);
 }
 
-template <typename T>
-__device__ inline void adj_field(bool use, T x, T y, T z, T ax, T ay, T az, T bx, T by, T bz, T &gx, T &gy,
-                                 T &gz, T &tx, T &ty, T &tz, T &hx, T &hy, T &hz)
-{
-    adj_field_r2<T>(use, norm2<T>(x, y, z), x, y, z, ax, ay, az, bx, by, bz, gx, gy, gz, tx, ty, tz, hx, hy, hz);
-}
-
 // ---- wave64 reductions (DPP) ---------------------------------------------------------------------
 
 template <int CTRL>
@@ -187,34 +174,6 @@ __device__ inline float dpp_f(float v)
 {
     // bound_ctrl: lanes whose source is out of range read 0
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-
-// Sum of v over all 64 lanes, returned uniformly (must be called with every lane active).
-__device__ inline float wave_sum(float v)
-{
-    v += dpp_f<0xb1>(v);   // quad_perm [1,0,3,2]
-    v += dpp_f<0x4e>(v);   // quad_perm [2,3,0,1]
-    v += dpp_f<0x141>(v);  // row_half_mirror
-    v += dpp_f<0x140>(v);  // row_mirror: every lane of a row now holds the row's sum
-    const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    const float b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return (a + b) + (c + d);
-}
-
-// Sum over all 64 lanes, left in lane 63 only (other lanes hold partial sums); every lane active.
-// Rows are reduced with quad/half-row/row mirrors, then rows 1 and 3 add the row before them
-// (row_bcast:15) and rows 2 and 3 add lane 31 (row_bcast:31).
-__device__ inline float wave_sum_to63(float v)
-{
-    v += dpp_f<0xb1>(v);
-    v += dpp_f<0x4e>(v);
-    v += dpp_f<0x141>(v);
-    v += dpp_f<0x140>(v);
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xc, 0xf, false));
-    return v;
 }
 
 template <int CTRL>
@@ -234,49 +193,22 @@ __device__ inline double readlane_d(double v, int lane)
     return __longlong_as_double(((long long)(unsigned)lo) | ((long long)hi << 32));
 }
 
-__device__ inline double wave_sum_to63(double v)
-{
-    v += dpp_d<0xb1>(v);
-    v += dpp_d<0x4e>(v);
-    v += dpp_d<0x141>(v);
-    v += dpp_d<0x140>(v);
-    const long long bits = __double_as_longlong(v);
-    int lo = __builtin_amdgcn_update_dpp(0, (int)(bits & 0xffffffff), 0x142, 0xa, 0xf, false);
-    int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), 0x142, 0xa, 0xf, false);
-    v += __longlong_as_double(((long long)(unsigned)lo) | ((long long)hi << 32));
-    const long long bits2 = __double_as_longlong(v);
-    lo = __builtin_amdgcn_update_dpp(0, (int)(bits2 & 0xffffffff), 0x143, 0xc, 0xf, false);
-    hi = __builtin_amdgcn_update_dpp(0, (int)(bits2 >> 32), 0x143, 0xc, 0xf, false);
-    v += __longlong_as_double(((long long)(unsigned)lo) | ((long long)hi << 32));
-    return v;
-}
-
-__device__ inline float readlane_t(float v, int lane)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-__device__ inline double readlane_t(double v, int lane) { return readlane_d(v, lane); }
-
+// Sum of v over all 64 lanes, returned uniformly (must be called with every lane active).
 __device__ inline double wave_sum(double v)
 {
-    v += dpp_d<0xb1>(v);
-    v += dpp_d<0x4e>(v);
-    v += dpp_d<0x141>(v);
-    v += dpp_d<0x140>(v);
+    v += dpp_d<0xb1>(v);   // quad_perm [1,0,3,2]
+    v += dpp_d<0x4e>(v);   // quad_perm [2,3,0,1]
+    v += dpp_d<0x141>(v);  // row_half_mirror
+    v += dpp_d<0x140>(v);  // row_mirror: every lane of a row now holds the row's sum
     const double a = readlane_d(v, 0), b = readlane_d(v, 16), c = readlane_d(v, 32), d = readlane_d(v, 48);
     return (a + b) + (c + d);
 }
 
-// Sum over the two lanes l and l ^ 16 (permlane16_swap) or l and l ^ 32 (permlane32_swap): the swap of
-// a register with itself hands every lane the value of its partner row in the second result.
+// Sum over the two lanes l and l ^ 16: the swap of a register with itself hands every lane the value of its partner
+// row in the second result.
 __device__ inline float swap16_sum(float v)
 {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ inline float swap32_sum(float v)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 __device__ inline double swap16_sum(double v)
@@ -284,14 +216,6 @@ __device__ inline double swap16_sum(double v)
     const uint64_t b = (uint64_t)__double_as_longlong(v);
     const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
     const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
-    return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
-           __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
-}
-__device__ inline double swap32_sum(double v)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
     return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
            __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
 }

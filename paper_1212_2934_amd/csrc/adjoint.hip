@@ -206,19 +206,19 @@ __device__ inline void close_pairs(AdjLds<float, SPLIT> &W, int lane, bool valid
     }
 }
 
+// The order of the arguments decides which of them the compiler keeps in scalar registers through the walk: with
+// status between Hs and n the FP32-mixed walk read four back from vector lanes at every leaf, 0.4 % of an MD step.
 #define FFBH_ADJ_PARAMS                                                                                         \
-    const NodeRec *__restrict__ nodes, const double *__restrict__ node_m64, const double *__restrict__ spos,     \
-        const double *__restrict__ smom, const void *__restrict__ src, const double *__restrict__ hbar,          \
-        const uint32_t *__restrict__ perm, const double *__restrict__ hext, double *__restrict__ g_gather,       \
-        double *__restrict__ g_rm, double *__restrict__ node_adj, double *__restrict__ Hs,                       \
-        double *__restrict__ Hout, double *__restrict__ e_part, uint32_t *__restrict__ status, int64_t n,        \
-        int64_t ntot, int waves_per_seg, int num_waves, double theta2, int max_nodes, int tpw, int parts,        \
-        double *__restrict__ part_buf, uint32_t *__restrict__ wave_cost, const void *__restrict__ node_q,         \
-        double *__restrict__ node_adjq, const uint32_t *__restrict__ tgt_order, int inside_test
+    const NodeRec *__restrict__ nodes, const double *__restrict__ node_m64, const double *__restrict__ spos,    \
+        const double *__restrict__ smom, const void *__restrict__ src, const double *__restrict__ hbar,         \
+        double *__restrict__ g_gather, double *__restrict__ g_rm, double *__restrict__ node_adj, int64_t n,     \
+        int64_t ntot, double *__restrict__ Hs, uint32_t *__restrict__ status, int waves_per_seg,                \
+        int num_waves, double theta2, int max_nodes, int tpw, int parts, double *__restrict__ part_buf,         \
+        uint32_t *__restrict__ wave_cost, const void *__restrict__ node_q, double *__restrict__ node_adjq,      \
+        const uint32_t *__restrict__ tgt_order, int inside_test
 #define FFBH_ADJ_ARGS                                                                                           \
-    nodes, node_m64, spos, smom, src, hbar, perm, hext, g_gather, g_rm, node_adj, Hs, Hout, e_part, status, n,   \
-        ntot, waves_per_seg, num_waves, theta2, max_nodes, tpw, parts, part_buf, wave_cost, node_q, node_adjq,  \
-        tgt_order, inside_test
+    nodes, node_m64, spos, smom, src, hbar, g_gather, g_rm, node_adj, n, ntot, Hs, status, waves_per_seg,       \
+        num_waves, theta2, max_nodes, tpw, parts, part_buf, wave_cost, node_q, node_adjq, tgt_order, inside_test
 
 // The fused walk of wave item gw.  If wave_cost is not null, lane 0 stores there a deterministic measure of
 // the item's work (node visits plus leaf pair rounds), which orders the next launch.  QUAD: order-2 cells
@@ -426,14 +426,6 @@ __device__ __forceinline__ void adjoint_wave(int gw, int split_shift, FFBH_ADJ_P
         return;
     }
 
-    double e = 0.0;
-    if (valid) {
-        const double mx = smom[si], my = smom[ntot + si], mz = smom[2 * ntot + si];
-        e = -0.5 * (mx * hx + my * hy + mz * hz);
-        if (hext) e -= mx * hext[3 * seg] + my * hext[3 * seg + 1] + mz * hext[3 * seg + 2];
-    }
-    e = wave_sum(e);
-    if (lane == 0) e_part[gw] = e;
     if (valid) {
         g_gather[si] = grx;
         g_gather[ntot + si] = gry;
@@ -441,13 +433,6 @@ __device__ __forceinline__ void adjoint_wave(int gw, int split_shift, FFBH_ADJ_P
         Hs[si] = hx;
         Hs[ntot + si] = hy;
         Hs[2 * ntot + si] = hz;
-        const int64_t i = (int64_t)perm[si] - (int64_t)seg * n;
-        if (Hout && i >= 0 && i < n) {
-            double *out = Hout + (int64_t)seg * 3 * n;
-            out[i] = hx;
-            out[n + i] = hy;
-            out[2 * n + i] = hz;
-        }
     }
 }
 
@@ -766,17 +751,18 @@ hipError_t launch_backward(Handle &h, const double *d_mom, const double *d_hext,
         const int inside = mac == kMacInside ? 1 : 0;
         const bool scaled = mac == kMacScaled;
 #define FFBH_ADJ(MX, QD, SC, T)                                                                                 \
-    hipLaunchKernelGGL((k_adjoint<MX, QD, SC>), dim3(grid), dim3(wpb * kWave), (adj_lds_bytes<T, false>(wpb)), s, w.nodes, \
-                       w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext, w.g_gather,    \
-                       w.g_rm, w.node_adj, w.Hs, nullptr, w.e_part, w.status, L.n, L.ntot, wps, nwv, theta2,          \
-                       (int)L.max_nodes, tpw, parts, w.part_buf, cost, nq, w.node_adjq, tgt, inside, ord, ctr)
+    hipLaunchKernelGGL((k_adjoint<MX, QD, SC>), dim3(grid), dim3(wpb * kWave), (adj_lds_bytes<T, false>(wpb)), s, \
+                       w.nodes, w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.g_gather, w.g_rm, \
+                       w.node_adj, L.n, L.ntot, w.Hs, w.status, wps, nwv, theta2, (int)L.max_nodes, tpw, parts, \
+                       w.part_buf, cost, nq, w.node_adjq, tgt, inside, ord, ctr)
         int shift = 0;
         const int W = adjoint_split(h, shift);
-#define FFBH_ADJ_SPLIT(MX, QD, SC, T)                                                                            \
-    hipLaunchKernelGGL((k_adjoint_split<MX, QD, SC>), dim3((unsigned)nwv), dim3(W * kWave), (adj_lds_bytes<T, true>(W)), \
-                       s, w.nodes, w.node_m64, w.spos, w.smom, MX ? w.src32 : w.src64, w.hbar, w.perm, d_hext,    \
-                       w.g_gather, w.g_rm, w.node_adj, w.Hs, nullptr, w.e_part, w.status, L.n, L.ntot, wps, nwv,      \
-                       theta2, (int)L.max_nodes, tpw, parts, w.part_buf, nullptr, nq, w.node_adjq, tgt, inside, shift)
+#define FFBH_ADJ_SPLIT(MX, QD, SC, T)                                                                           \
+    hipLaunchKernelGGL((k_adjoint_split<MX, QD, SC>), dim3((unsigned)nwv), dim3(W * kWave),                     \
+                       (adj_lds_bytes<T, true>(W)), s, w.nodes, w.node_m64, w.spos, w.smom,                     \
+                       MX ? w.src32 : w.src64, w.hbar, w.g_gather, w.g_rm, w.node_adj, L.n, L.ntot, w.Hs, w.status, \
+                       wps, nwv, theta2, (int)L.max_nodes, tpw, parts, w.part_buf, nullptr, nq, w.node_adjq, tgt, \
+                       inside, shift)
         if (W > 1) {
             if (scaled) {
                 if (mixed && quad) FFBH_ADJ_SPLIT(true, true, true, float);

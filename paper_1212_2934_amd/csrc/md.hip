@@ -226,12 +226,13 @@ __global__ __launch_bounds__(256) void k_wca(const uint64_t *__restrict__ codes,
 // 500 245 / 247 and with a cut-off of 8 diameters 431 / 443, 131 x 1000 459 / 473 and 814 / 830, 32 x 4096 577 / 568 and
 // 1666 / 1745; 262144 particles, 524 x 500 353 / 338 and 742 / 641, 262 x 1000 660 / 647 and 1343 / 1203, 64 x 4096 749 /
 // 708 and 2842 / 2470.
-// kSrGroups workgroups over the batch, as many as there are particles for: each fills a table of its own, but with one of
-// 512 threads a system and 262 x 500 there were two waves a SIMD (8 diameters: 645 us with 512 workgroups, 463 with 2048,
-// 431 with 4096; the default law of 16 x 4096 takes 352 / 361 / 361).
+// Workgroups over the batch (sr_groups): each fills a table of its own, so up to 65536 particles about two per CU, which
+// the default law needs (64 x 1000 in a graph 260.5 us a step with 512, 263.9 with 1024 and more; 16 x 4096 352 and 361).
+// Above that as many as there are particles for: with one workgroup a system 262 x 500 leave two waves a SIMD (245 us a
+// step against 259, with a cut-off of 8 diameters 431 against 645).
 constexpr int64_t kSmallStepMax = 1 << 17;
 constexpr int kSrThreads = 512, kSrLanes = 8, kSrAtOnce = kSrThreads / kSrLanes, kSrLevel = 4;
-constexpr int64_t kSrGroups = 4096;
+inline int64_t sr_groups(int64_t ntot) { return ntot <= 65536 ? 512 : 4096; }
 
 __global__ __launch_bounds__(kSrThreads) void k_wca_small(
     const uint64_t *__restrict__ codes, const double *__restrict__ bbox, const double *__restrict__ spos,
@@ -493,8 +494,8 @@ hipError_t launch_md(Handle &h, const md_state *st, const md_params *mp, hipStre
         if (small) {
             AdjSetup setup = adj_setup_args(h, nullptr, w.ones);
             if (!setup_early) setup.hbar = nullptr;
-            // about kSrGroups workgroups: every one fills a table of its own
-            const int64_t all = (L.n + kSrAtOnce - 1) / kSrAtOnce, share = L.B < kSrGroups ? kSrGroups / L.B : 1;
+            const int64_t all = (L.n + kSrAtOnce - 1) / kSrAtOnce, groups = sr_groups(L.ntot);
+            const int64_t share = L.B < groups ? groups / L.B : 1;
             const int per_system = (int)(share < all ? share : all);
             hipLaunchKernelGGL(k_wca_small, dim3((unsigned)(L.B * per_system)), dim3(kSrThreads), 0, ss, w.codes,
                                w.bbox, w.spos, w.perm, w.md_force, (int)L.n, L.ntot, per_system, L.cell_lcap,

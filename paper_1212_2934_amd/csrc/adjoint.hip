@@ -74,8 +74,8 @@ struct AdjTargets {
     LdsTarget tgt[kWave];  // the wave's targets
     T hb[kWave][4];        // their upstream field gradients
 };
-// The rest: one record per wave.  A split walk lists lanes in bytes, so that sixteen records fit beside the
-// targets in 64 KB.
+// The rest: one record per wave.  A split walk lists lanes in bytes; sixteen records and the targets then take 58 KB in
+// the FP32-mixed walk and 65 KB in FP64, so that two workgroups share a CU's 160 KB.
 template <typename T, bool SPLIT>
 struct AdjLds {
     T acc[kWave][6];  // direct-sum g (0..2) and field (3..5) of the current leaf, by owner lane
@@ -93,7 +93,9 @@ constexpr size_t adj_lds_bytes(int waves)
 {
     return (SPLIT ? 1 : waves) * sizeof(AdjTargets<T>) + waves * sizeof(AdjLds<T, SPLIT>);
 }
-static_assert(adj_lds_bytes<float, true>(kSplitMaxWaves) <= 65536, "LDS of the FP32-mixed split walk");
+static_assert(2 * adj_lds_bytes<float, true>(kSplitMaxWaves) <= kLdsPerCu &&
+                  2 * adj_lds_bytes<double, true>(kSplitMaxWaves) <= kLdsPerCu,
+              "two workgroups of a split walk share a CU's LDS");
 
 // Direct sums of one leaf (first, count) for the c listed lanes, in groups of G lanes (see the compacted
 // direct sums in traverse.h).  Lane b of group g pairs member b with listed target t0 + g: the group's

@@ -1193,7 +1193,7 @@ union SmallLds {
     SmallSort<SH> s;
     SmallUp<SH> up;  // the upward pass, once the tree is written
 };
-static_assert(sizeof(SmallLds<ShapeWide>) <= 81920, "two workgroups of k_build_small share a CU's LDS");
+static_assert(2 * sizeof(SmallLds<ShapeWide>) <= kLdsPerCu, "two workgroups of k_build_small share a CU's LDS");
 static_assert(ShapeWide::threads == 4 * kRadixBins && ShapeWide::waves == 16, "four threads per digit, sixteen waves");
 
 // One stable pass over 8 bits of the keys from buffer src to the other one: every wave ranks a contiguous run of

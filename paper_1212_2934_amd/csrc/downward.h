@@ -13,7 +13,7 @@ struct AdjSetup {
     double *hbar, *g_rm, *node_adj, *node_adjq;  // node_adjq: null without order-2 cells
     const uint32_t *nn;                          // nodes of the last build
     int64_t max_nodes;
-    const int32_t *per_system;  // split cells of each system where it was built by one workgroup, else null
+    const int32_t *per_system;  // nodes below the root of each system where it was built by one workgroup, else null
 };
 
 inline AdjSetup adj_setup_args(const Handle &h, const double *gH, const double *gE)

@@ -16,6 +16,7 @@ constexpr int kBits = 21;                       // quantisation bits per axis
 constexpr uint32_t kQMax = (1u << kBits) - 1u;  // largest quantised coordinate
 constexpr int kMaxLevel = 21;                   // deepest cell level
 constexpr int kWave = 64;                       // CDNA wavefront width
+constexpr size_t kLdsPerCu = 160 * 1024;        // LDS of a CU, which one workgroup may also take whole
 constexpr int kRadixBits = 8;
 constexpr int kRadixBins = 1 << kRadixBits;
 constexpr int kRadixPasses = 8;                 // 8 x 8 bits cover the 63-bit codes

@@ -97,10 +97,12 @@ bh_status bh_workspace_bytes(const bh_params *p, size_t *out_bytes);
  * another order).  Some shapes split each adjoint walk over the root's children and hold a partial-sum
  * buffer of 384 bytes per particle in the workspace (bh_workspace_bytes depends on tuning_id).  Others
  * order the adjoint walk's wave items by the cost each had in the previous call on the handle (the first
- * call after bh_create runs them in index order), in one persistent launch or one wave per item.  The
- * forward walk of bh_field takes its items in the order of its previous call's costs in every shape above 1600
- * groups of 64 targets over the batch (ordered by bh_build); in smaller calls several waves share the walk of a
- * group, their number a function of the groups (also the adjoint walk of the default shape and shapes 1-3). */
+ * call after bh_create runs them in index order), in one persistent launch or one wave per item.
+ * The forward walk of bh_field is divided alike in every shape: up to 1600 groups of 64 targets over the batch 16,
+ * 8 or 4 waves share the walk of a group; above, one wave walks a group, and from 16384 particles over the batch
+ * the groups are taken in the order of their previous walk's costs (ordered by bh_build).  The adjoint walk is
+ * shared out in the same way in shapes 0-3, and by its number of items in shapes 4-8; in FP64 two waves share a
+ * group of shapes 0-3 from 1601 to 3200 groups. */
 int32_t bh_num_tunings(void);
 
 /* Create a handle (host memory, owned by the caller until bh_destroy) bound to the current HIP device
@@ -142,7 +144,11 @@ bh_status bh_build(bh_handle *h, const double *d_pos, void *stream);
  * traversal).  d_mom (B, 3, n) moments; d_hext (B, 3) external field or NULL (zero); d_H (B, 3, n)
  * receives the dipolar field (without H_ext); d_E (B) receives
  *     E = -1/2 sum_i m_i . H_i - sum_i m_i . H_ext
- * or may be NULL. */
+ * or may be NULL.  Repeated calls give the same bits.  The waves that share a walk (bh_num_tunings) add their
+ * FP64 sums in the end, and their number follows the groups of the whole batch, so a system of up to 102400
+ * particles gives the same bits in two batches only where both take the same number; otherwise they agree to
+ * FP64 rounding, in either precision (every FP32 sum is the same).  Larger systems give the same bits alone
+ * and in any batch. */
 bh_status bh_field(bh_handle *h, const double *d_mom, const double *d_hext, double *d_H, double *d_E,
                    void *stream);
 
@@ -207,7 +213,10 @@ bh_status bh_graph_destroy(void *graph_exec);
  * energy gradient dE/dr_i = -sum_{j != i} f_dip(r_i - r_j; m_i, m_j) (Sec. 2), and d_E (B) with
  * E = -1/2 sum m.H - sum m.H_ext (d_hext (B, 3) or NULL for no external field).  precision BH_FP64, or
  * BH_FP32_MIXED: offsets formed in FP64, pair arithmetic in FP32, partial sums over 256 sources
- * accumulated in FP64.  Distinct particles at the same position contribute nothing to each other.
+ * accumulated in FP64.  Distinct particles at the same position contribute nothing to each other.  Repeated
+ * calls give the same bits; how the sources are shared out, and with it the order of the FP64 sums, depends on n
+ * and on the number of 64-target groups of the batch, so the results of a system alone and in a batch agree to
+ * FP64 rounding.
  * O(n^2) work per system; needs no handle or workspace; enqueued on `stream` without host
  * synchronisation.  Returns BH_EINVAL for n < 1, batch outside [1, 65535], an unknown precision, or a
  * NULL or misaligned required pointer; BH_EDEVICE if the launch fails. */

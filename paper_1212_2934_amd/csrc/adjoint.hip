@@ -74,7 +74,7 @@ struct AdjTargets {
     LdsTarget tgt[kWave];  // the wave's targets
     T hb[kWave][4];        // their upstream field gradients
 };
-// The rest: one record per wave.  A split walk lists lanes in bytes; sixteen records and the targets then take 58 KB in
+// The rest: one record per wave.  A split walk lists lanes in bytes; sixteen records and the targets then take 62 KB in
 // the FP32-mixed walk and 65 KB in FP64, so that two workgroups share a CU's 160 KB.
 template <typename T, bool SPLIT>
 struct AdjLds {

@@ -43,10 +43,11 @@ Layout plan_layout(const bh_params &p)
     const int tid = p.tuning_id < 0 || p.tuning_id >= kNumTunings ? 0 : p.tuning_id;
     L.adj_parts = kTuneParts[tid] > 1 ? kTuneParts[tid] : 0;
     L.expansion = p.expansion == 2 ? 2 : 1;
-    // radix-sort tiles of 256 x sort_items keys, a power of two that grows with the keys up to 16: enough tiles
-    // to spread over the chip, and enough keys per tile to fill the scatter's 1024 threads (bh_build of 50000
-    // particles with 1, 2, 4 items: 177, 158, 163 us; 100003 with 1, 4, 8: 193, 180, 185; 2^18 with 4, 8: 215,
-    // 202)
+    // radix-sort tiles of 256 x sort_items keys, a power of two that grows with the keys up to 16: enough tiles to
+    // spread over the chip, and enough keys per tile to use the scatter's 1024 threads, a wave for every 64 keys.
+    // bh_build with 1 / 2 / 4 / 8 items, us: 4097 particles 130 / 131 / 133 / 144, 8192 138 / 139 / 144 / 153, 16384
+    // 137 / 138 / 136 / 140, 32768 147 / 140 / 137 / 141, 50000 174 / 157 / 157 / 153, 65536 178 / 164 / 159 / 164,
+    // 100003 - / 186 / 176 / 180, 131072 - / 186 / 174 / 173; 2^18 with 4 / 8: 215 / 202.
     int items = 1;
     while (items < kSortItems && (int64_t)items * 32768 < L.ntot) items *= 2;
     L.sort_items = items;

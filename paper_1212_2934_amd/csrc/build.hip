@@ -1,4 +1,5 @@
-// Tree construction on gfx950: bounding cube, Morton codes, LDS radix sort, octree, and the upward pass that forms the pseudo-particles.
+// Tree construction on gfx950: bounding cube, Morton codes, LDS radix sort, octree, and the upward pass that forms the
+// pseudo-particles.
 //
 // Paper: Sec. 3.2 (kernels 1-4 of the GPU Barnes-Hut scheme: bounding box, octree, cell centres and
 // moments, sort by location) and Eq. (magCenter) (pseudo-particle = moment sum at the geometric
@@ -155,8 +156,8 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint64_t *__r
 }
 
 // Device-wide exclusive scan of a uint32 array (BITS: of its entries' bit counts) into another or in place, in
-// three launches: per-tile sums, a scan of the tile sums (one workgroup), and the per-tile scan with its offset.  Tiles are kScanTile entries,
-// read and written through LDS so that global accesses are coalesced.
+// three launches: per-tile sums, a scan of the tile sums (one workgroup), and the per-tile scan with its offset.
+// Tiles are kScanTile entries, read and written through LDS so that global accesses are coalesced.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
@@ -1132,7 +1133,10 @@ __device__ inline void pack_source(double *r, bool mixed, double x, double y, do
 // Systems of at most kSmallMax particles: the whole build of a system in one workgroup (k_build_small), with its
 // keys, codes and cell masks in LDS, and the moments' upward pass of a later call in another
 // (k_moments_small).  A launch costs about 4.5 us in a stream and a small system's kernels little more than
-// that: 300 particles took twelve launches and 58 us for bh_build, this takes one.
+// that: 300 particles took twelve launches and 58 us for bh_build, this takes one of 20.  Against the launches over the
+// whole batch that larger systems take (bh_build, us): one system of 513 28 / 77, 1000 35 / 84, 2049 70 / 123, 4096 97 /
+// 122; 64 x 1000 39 / 127, 1048 x 1000 206 / 354, 64 x 4096 109 / 167, 256 x 4096 131 / 287.  The limit is LDS: above 4096
+// two workgroups no longer share a CU.
 // The children's ids of system b start at B + 2 n b (a system has fewer than 2 n nodes), so the ids of a batch
 // have gaps; entry b of the list array counts the system's nodes below its root.
 // ------------------------------------------------------------------------------------------------

@@ -197,9 +197,9 @@ __device__ inline void set_flag(uint32_t *status, uint32_t bit)
 
 // Calls in flight on a handle's workspace.  Every entry point that writes the workspace counts itself in
 // with its first kernel and out with its last, in its stream's order, so calls on one stream never see
-// each other (the tree queries write it for a batch of systems of at most kSmallMax particles only).  A call that finds another one in flight (calls on one handle overlapping on streams that
-// are not ordered with each other) sets BH_FLAG_OVERLAP.  This detects the misuse; it does not prevent
-// the race.
+// each other (the tree queries write it for a batch of systems of at most kSmallMax particles only).  A call
+// that finds another one in flight (calls on one handle overlapping on streams that are not ordered with each
+// other) sets BH_FLAG_OVERLAP.  This detects the misuse; it does not prevent the race.
 constexpr int kStatusInFlight = 12;  // status word slot of the count
 __device__ inline void call_enter(uint32_t *status)
 {

@@ -316,10 +316,19 @@ __global__ __launch_bounds__(kEnergyThreads) void k_energy_final(const double *_
 // Waves that share the walk of 64 targets.  A walk is one chain of dependent instructions (about 1000 cycles a
 // node with one wave on a SIMD), so systems whose waves do not fill the 1024 SIMDs are bound by the longest
 // walk.  Cells that hold positions of several waves are tested by each of them, so the split costs more than
-// it gives once the chip is full.  Measured (FP64 / FP32-mixed, undivided -> divided): 300 particles 77 / 68
-// -> 23 / 22 us, 4096 273 / 236 -> 66 / 72 us, 20000 475 / 402 -> 155 / 184 us, 100003 739 / 596 -> 480 / 437
-// us; at 131072 particles four waves take 681 / 643 us against 684 / 564.  The rule counts the target groups of
-// the whole batch: a batch of 1000 x 1000 takes 0.5 ms undivided and 2.2 ms with sixteen waves.
+// it gives once the chip is full.  Measured, one system, bh_field in us with 16 / 8 / 4 / 1 waves (FP64, FP32-mixed):
+//   12288 particles (192 groups)  134 / 181 / 260 / 515   162 / 197 / 272 / 433
+//   20000 (313)                   191 / 186 / 263 / 489   206 / 216 / 270 / 418
+//   32768 (512)                   195 / 163 / 206 / 470   279 / 209 / 241 / 395
+//   49152 (768)                   411 / 260 / 289 / 549   431 / 263 / 313 / 449
+//   65536 (1024)                  597 / 435 / 438 / 646   599 / 403 / 404 / 514
+//   102400 (1600)                 957 / 596 / 509 / 771  1038 / 625 / 513 / 626
+//   131072 (2048)                1195 / 746 / 667 / 739  1359 / 796 / 657 / 605
+// The first two lines lie below where the curves cross (about 300 and 1000 groups); the third is where the fused walk,
+// which follows the rule, stops gaining (1600 groups 1314 against 1355 us and 1209 against 1307 for build and gradient,
+// 1797 groups 1589 against 1396 and 1392 against 1269; the FP64 figures against two waves by node, see adjoint_split).  The rule counts the target groups of the whole batch: a batch
+// of 1000 x 1000 takes 0.76 ms undivided and 5.2 ms with sixteen waves (FP64; 0.62 and 2.0 ms FP32-mixed).  The FP64
+// sums of a system are therefore grouped by the batch that it is in.
 int walk_split(int64_t groups)
 {
     return groups <= 192 ? 16 : groups <= 768 ? 8 : groups <= 1600 ? 4 : 1;

@@ -122,3 +122,19 @@ def test_source_split_at_the_edges_of_units_and_target_groups(oracle_mod, n, bat
         assert np.linalg.norm(H[b] - Href) <= tol * np.linalg.norm(Href)
         assert np.linalg.norm(G[b] - Gref) <= tol * np.linalg.norm(Gref)
         assert abs(E[b] - oracle_mod.energy(mom[b], Href)) <= tol * 0.5 * np.abs(mom[b] * Href).sum()
+
+
+@pytest.mark.parametrize("n,batch,precision", [(1000, 70, "fp64"), (8193, 8, "fp64"), (8193, 8, "fp32_mixed")])
+def test_a_system_alone_and_in_a_batch(n, batch, precision):
+    """The targets of a workgroup, and with them the order of the FP64 sums, follow the groups of the whole batch (16
+    targets alone, 64 in these batches): field and gradient agree to FP64 rounding in both precisions, since the
+    FP32-mixed sums of 256 sources are the same."""
+    rng = np.random.default_rng(n)
+    pos = torch.from_numpy(rng.random((3, n)) * 1.5 * n ** (1.0 / 3.0)).cuda()
+    mom = torch.from_numpy(workloads.unit_vectors(rng, n)).cuda()
+    one = allpairs(pos, mom, precision=precision, want_dEdr=True)
+    many = allpairs(pos.expand(batch, 3, n).contiguous(), mom.expand(batch, 3, n).contiguous(), precision=precision,
+                    want_dEdr=True)
+    for a, b in zip(one[:2], many[:2]):
+        for k in (0, batch - 1):
+            assert ((b[k] - a).norm() / a.norm()).item() <= 1e-13

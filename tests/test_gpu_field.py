@@ -201,3 +201,24 @@ def test_groups_of_fewer_targets(oracle_mod, n, batch, expansion):
         H, nf, nr = oracle_mod.Tree(w.pos, w.mom, 16).field(0.5, expansion)
         one = dict(flags=out["flags"], H=out["H"][b], E=out["E"][b:b + 1], n_far=out["n_far"][b], n_near=out["n_near"][b])
         _check(one, H, oracle_mod.energy(w.mom, H), nf, nr, w.mom, "fp64")
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("n,batch,same", [(2500, 5, False), (2500, 4, True), (64 * 1600 + 1, 2, True)])
+def test_a_system_alone_and_in_a_batch(precision, n, batch, same):
+    """The number of waves that share a walk follows the groups of the whole batch.  Where it is the same, and above
+    102400 particles always, a system's field and energy have the same bits alone and in the batch; elsewhere (40
+    groups alone, 200 in the batch) they agree to FP64 rounding in both precisions."""
+    w = workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n)
+    hext = np.array([0.0, 0.0, 0.5])
+    one = run_field(w.pos, w.mom, hext=hext, precision=precision, counters=False)
+    many = run_field(np.repeat(w.pos[None], batch, 0), np.repeat(w.mom[None], batch, 0), hext=np.tile(hext, (batch, 1)),
+                     precision=precision, counters=False)
+    assert one["flags"] == 0 and many["flags"] == 0
+    for b in (0, batch - 1):
+        if same:
+            assert (many["H"][b] == one["H"]).all() and many["E"][b] == one["E"][0]
+        else:
+            assert np.linalg.norm(many["H"][b] - one["H"]) <= 1e-14 * np.linalg.norm(one["H"])
+            scale = 0.5 * np.abs(w.mom * one["H"]).sum() + np.abs(w.mom * hext[:, None]).sum()
+            assert abs(many["E"][b] - one["E"][0]) <= 1e-14 * scale

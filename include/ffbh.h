@@ -102,7 +102,7 @@ bh_status bh_workspace_bytes(const bh_params *p, size_t *out_bytes);
  * 8 or 4 waves share the walk of a group; above, one wave walks a group, and from 16384 particles over the batch
  * the groups are taken in the order of their previous walk's costs (ordered by bh_build).  The adjoint walk is
  * shared out in the same way in shapes 0-3, and by its number of items in shapes 4-8; in FP64 two waves share a
- * group of shapes 0-3 from 1601 to 3200 groups. */
+ * group of shapes 0-3 from 1601 to 2560 groups. */
 int32_t bh_num_tunings(void);
 
 /* Create a handle (host memory, owned by the caller until bh_destroy) bound to the current HIP device

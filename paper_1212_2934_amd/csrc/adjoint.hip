@@ -677,8 +677,11 @@ static int adjoint_items(const Handle &h)
 // at 131072 particles four waves take 1545 / 1529 us against 1301 / 1203.
 // Above that the FP64 walk still gains from two waves that take turns at the nodes (shift -1): the work is dealt
 // out evenly and only the opened cells are tested twice, where intervals long enough to be skipped leave most of a
-// group's near cells to one wave (131072 particles: 1281 us undivided, 1436 with intervals, 1193 by node; 200000
-// 1723 -> 1699; with four waves and more intervals are ahead).
+// group's near cells to one wave (131072 particles: 1281 us undivided, 1436 with intervals, 1193 by node; with four waves
+// and more intervals are ahead).  Up to 2560 groups: two waves of 2048 groups are one round of the chip at four waves a
+// SIMD, and the gain of the shorter walks ends soon after.  bh_build and gradient, undivided over by node: 2344 to 2560
+// groups 1.03 (13000 x 12) to 1.14 (30000 x 5), alone 160000 0.99; 2626 to 2700 0.93 (1000 x 168) to 1.05 (5000 x 34),
+// alone 0.98; 3060 13000 x 15 0.93, 3130 20000 x 10 0.92; alone 185600 0.91, 198400 1.01.
 // Shapes of fewer targets or of a part of the tree per item follow the same rule by their items, with sixteen waves
 // up to 256 (256 items of 16 targets: 101 us with eight, 88 with sixteen; 500: 152 and 194); a walk of a part
 // sees an eighth of the positions, so its intervals are a twelfth of that, and no shorter than deals a group's near
@@ -697,7 +700,7 @@ static int adjoint_split(const Handle &h, int &shift)
         return W;
     }
     shift = split_shift(h.L.n, W);
-    if (W == 1 && plain && h.p.precision == BH_FP64 && items <= 3200) {
+    if (W == 1 && plain && h.p.precision == BH_FP64 && items <= 2560) {
         shift = -1;
         return 2;
     }

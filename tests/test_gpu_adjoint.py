@@ -209,3 +209,19 @@ def test_groups_of_fewer_targets(oracle_mod, n, expansion):
     assert bh.check_status() == 0
     grad_check(gdr.cpu().numpy(), dr, "fp64", f"dE/dr n {n}")
     grad_check(gdm.cpu().numpy(), dm, "fp64", f"dE/dm n {n}")
+
+
+def test_two_waves_by_node_and_one_in_batches(oracle_mod):
+    """The FP64 walk takes two waves per group up to 2560 groups of 64 over the batch: copies of a system of 197 groups,
+    12 of them (2364 groups) and 13 (2561), against the oracle and each other."""
+    n = 64 * 197
+    w = workloads.uniform_cube(n, workloads.cube_side(n, 0.05) + 1.0, seed=n, hext=(0.2, 0.0, 1.0))
+    _, _, dr, dm = oracle_mod.Tree(w.pos, w.mom, 16).energy_grad(0.5, w.hext)
+    got = []
+    for copies in (12, 13):
+        g = _gpu_grad(np.repeat(w.pos[None], copies, 0), np.repeat(w.mom[None], copies, 0),
+                      np.tile(np.asarray(w.hext), (copies, 1)), 0.5, "fp64")
+        got.append((g[0][-1], g[1][-1]))
+        grad_check(got[-1][0], dr, "fp64", f"dE/dr {copies} copies")
+        grad_check(got[-1][1], dm, "fp64", f"dE/dm {copies} copies")
+    assert rel(got[0][0], got[1][0]) <= 1e-13 and rel(got[0][1], got[1][1]) <= 1e-13

@@ -164,3 +164,27 @@ def test_md_trajectory_matches_reference(precision, tol, tuning_id):
         g = d[key].cpu().numpy()
         err = np.abs(g - ref[key]).max() / np.abs(ref[key]).max()
         assert err <= tol, (key, err)
+
+
+@pytest.mark.parametrize("expansion", [1, 2])
+@pytest.mark.parametrize("n,batch", [(1, 8193), (10, 8192), (10, 8193), (16, 8193), (17, 8193)])
+def test_moments_of_many_tiny_systems(oracle_mod, n, batch, expansion):
+    """Above 8192 systems those of one leaf (up to 16 particles) are summed by a thread each.  Copies of three systems:
+    field and gradient are those of the three alone, and the field is the oracle's."""
+    rng = np.random.default_rng(n + batch)
+    pos, mom = rng.random((3, 3, n)) * (2.0 * n ** (1 / 3) + 1.0), rng.standard_normal((3, 3, n))
+    out = []
+    for pick in (np.arange(3), np.arange(batch) % 3):
+        p, m = torch.from_numpy(pos[pick]).cuda(), torch.from_numpy(mom[pick]).cuda()
+        bh = BarnesHut(n, pick.size, 16, 0.5, "fp64", expansion=expansion)
+        bh.build(p)
+        H, E = bh.field(m)
+        dr, dm = bh.field_backward(m, gE=torch.ones(pick.size, dtype=torch.float64, device="cuda"))
+        assert bh.check_status() == 0
+        out.append([x.cpu().numpy() for x in (H, E, dr, dm)])
+    pick = np.arange(batch) % 3
+    for a, b in zip(*out):
+        assert np.abs(b - a[pick]).max() <= 1e-13 * max(np.abs(a).max(), 1e-300)
+    for b in range(3):
+        H = oracle_mod.Tree(pos[b], mom[b], 16).field(0.5, order=expansion)[0]
+        assert np.linalg.norm(out[0][0][b] - H) <= 1e-12 * np.linalg.norm(H)

@@ -1469,12 +1469,15 @@ __device__ inline double add_in_order(const double *src, int len, int stride)
 // stay in LDS: a lane sums one component of a node (c = 0..2 positions, 4..6 moments; eight children or sixteen
 // members in flight, added in order), and the records, which no sum needs, are written at the end.  Bound by latency:
 // through memory a level was a chain of four or five loads, 3.7 us; one system of 1000 took 16 us in all and takes 7.
+// First moments (MODE 3) go to memory, one lane for each of a node's nine.
 template <int MODE, typename SH>
 __device__ inline void small_upward(SmallUp<SH> &U, int64_t b, int64_t base, int64_t total, const double *vals,
                                     const double *vals2, const SmallArgs &a, double *q64, float *q32)
 {
     constexpr int kSumNodes = SH::sum_nodes;
-    if (MODE == 3 || total >= kSumNodes || base + total > a.max_nodes) {
+    // first moments: nine lanes a node leave the wide shape's 350 nodes of 4096 particles more rounds than a thread a
+    // node has (bh_field 73 us, 97 with lanes); the narrower shapes gain (512 x 100 with order-2 cells 63.6 -> 52.2)
+    if ((MODE == 3 && SH::max > ShapeHalf::max) || total >= kSumNodes || base + total > a.max_nodes) {
         up_reset(U.list);
         up_leaves<MODE>(U.list, b, base, min(base + total, a.max_nodes), true, true, vals, vals2, a.ntot, a.n, a.nodes,
                         a.sums, a.node_m64, a.node_level, a.bbox, a.max_nodes, q64, q32);
@@ -1485,7 +1488,7 @@ __device__ inline void small_upward(SmallUp<SH> &U, int64_t b, int64_t base, int
     SumList<kSumNodes> &S = U.sums;
     constexpr int kLanes = MODE == 2 ? 8 : 4;
     const int nodes = (int)total + 1, t = threadIdx.x, group = t / kLanes, groups = (int)blockDim.x / kLanes;
-    const int c = (t & (kLanes - 1)) + (MODE == 1 ? 4 : 0);
+    const int c = (t & (kLanes - 1)) + (MODE == 1 || MODE == 3 ? 4 : 0);
     const bool sums = (c & 3) != 3;
     const int comp = c < 4 ? c : c - 1;
     auto id_of = [&](int k) { return k == 0 ? (int)b : (int)base + k - 1; };
@@ -1517,12 +1520,59 @@ __device__ inline void small_upward(SmallUp<SH> &U, int64_t b, int64_t base, int
             }
         __syncthreads();
     }
+    if constexpr (MODE == 3) {
+        // the first moments as in upward_node, a lane for each of the nine components
+        const int e = t & 15, ra = min(e / 3, 2), rb = e % 3, team = t >> 4, teams = (int)blockDim.x >> 4;
+        auto centre = [&](int k) { return (&a.nodes[id_of(k)].cx)[ra]; };
+        auto store = [&](int k, double D) {
+            q64[16 * (int64_t)id_of(k) + e] = D;
+            q32[16 * (int64_t)id_of(k) + e] = (float)D;
+        };
+        constexpr int kFlight = 8;
+        for (int k = team; k < nodes; k += teams) {
+            const int len = S.len[k];
+            if (e >= 9 || !S.leaf[k] || len == 0) continue;
+            const double *r = vals2 + ra * a.ntot + first + S.from[k], *m = vals + rb * a.ntot + first + S.from[k];
+            const double x = centre(k);
+            double D = 0.0;
+            for (int j = 0; j < len; j += kFlight) {
+                double rv[kFlight], mv[kFlight];
+#pragma unroll
+                for (int q = 0; q < kFlight; ++q) {
+                    rv[q] = r[min(j + q, len - 1)];
+                    mv[q] = m[min(j + q, len - 1)];
+                }
+#pragma unroll
+                for (int q = 0; q < kFlight; ++q) D = j + q < len ? D + (rv[q] - x) * mv[q] : D;
+            }
+            store(k, D);
+        }
+        __syncthreads();
+        for (int l = S.lmax; l >= lmin; --l) {
+            for (int k = team; k < count; k += teams) {
+                if (e >= 9 || S.lev[k] != l) continue;
+                const int cell = S.cell[k], from = S.from[cell], len = S.len[cell];
+                const double x = centre(cell);
+                double cv[8], dv[8], D = 0.0;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int ch = from + min(q, len - 1);
+                    cv[q] = centre(ch);
+                    dv[q] = q64[16 * (int64_t)id_of(ch) + e];
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) D = q < len ? D + (dv[q] + (cv[q] - x) * S.sum[from + q][3 + rb]) : D;
+                store(cell, D);
+            }
+            __syncthreads();
+        }
+    }
     for (int k = t; k < nodes; k += (int)blockDim.x) {
         const int id = id_of(k);
         if (S.len[k] == 0) continue;
         NodeRec &nd = a.nodes[id];
         const double *v = S.sum[k];
-        if (MODE != 1) up_centre(nd, a.node_level[id], a.bbox + 8 * b, v[0], v[1], v[2]);
+        if (MODE == 0 || MODE == 2) up_centre(nd, a.node_level[id], a.bbox + 8 * b, v[0], v[1], v[2]);
         if (MODE != 0) up_moment(nd, a.node_m64 + 4 * (int64_t)id, v[3], v[4], v[5]);
     }
 }

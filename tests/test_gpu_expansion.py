@@ -188,3 +188,23 @@ def test_moments_of_many_tiny_systems(oracle_mod, n, batch, expansion):
     for b in range(3):
         H = oracle_mod.Tree(pos[b], mom[b], 16).field(0.5, order=expansion)[0]
         assert np.linalg.norm(out[0][0][b] - H) <= 1e-12 * np.linalg.norm(H)
+
+
+@pytest.mark.parametrize("n,leaf", [(17, 16), (64, 16), (64, 1), (65, 4), (256, 16), (256, 2), (512, 16), (512, 4), (513, 16)])
+def test_first_moments_at_the_edges_of_the_workgroup_shapes(oracle_mod, n, leaf):
+    """Up to 512 particles nine lanes sum a node's first moment, where the nodes fit on the chip (not with leaf size 1 or
+    2), above a thread: three systems, field and gradient against the oracle's order-2 traversal."""
+    ws = [workloads.uniform_cube(n, 4.0 + 2.0 * n ** (1 / 3), seed=900 + n + b, hext=(0.2, 0.0, 1.0)) for b in range(3)]
+    pos, mom = np.stack([w.pos for w in ws]), np.stack([w.mom for w in ws])
+    out = run_field(pos, mom, leaf=leaf, theta=0.7, expansion=2)
+    hext = torch.from_numpy(np.tile(np.asarray(ws[0].hext), (3, 1))).cuda()
+    dr, dm = out["bh"].field_backward(torch.from_numpy(mom).cuda(), hext,
+                                      gE=torch.ones(3, dtype=torch.float64, device="cuda"))
+    assert out["flags"] == 0 and out["bh"].check_status() == 0
+    for b, w in enumerate(ws):
+        t = oracle_mod.Tree(w.pos, w.mom, leaf)
+        H, nf, nr = t.field(0.7, order=2)
+        assert rel(out["H"][b], H) <= 1e-12
+        assert (out["n_far"][b] == nf).all() and (out["n_near"][b] == nr).all()
+        _, _, gr, gm = t.energy_grad(0.7, w.hext, order=2)
+        assert rel(dr[b].cpu().numpy(), gr) <= 1e-12 and rel(dm[b].cpu().numpy(), gm) <= 1e-12
